@@ -1,7 +1,8 @@
-"""ctypes binding of ``libatom.so``: argument marshalling only.
+"""Python binding of ``libatom.so``: argument marshalling only.
 
-torch is used for device memory and the current HIP stream; no arithmetic of
-the method happens in Python.
+The run-time entry points go through ``_native.so`` (``csrc/atom_torch.cpp``), which reads the tensors
+and calls the library in native code; offline helpers and size queries go through ctypes.  torch is
+used for device memory and the current HIP stream; no arithmetic of the method happens in Python.
 """
 from __future__ import annotations
 
@@ -14,6 +15,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libatom.so")
 _lib = None
+_native = None
 
 EXPORTS = (
     "atom_quantize_act",
@@ -166,6 +168,21 @@ def load_library():
     return L
 
 
+def _run():
+    """The native entry points (built in-tree beside ``libatom.so``; there is no fallback)."""
+    global _native
+    if _native is None:
+        load_library()
+        try:
+            from . import _native as mod
+        except ImportError as e:
+            raise ImportError(f"{_HERE}/_native.so is missing or does not load ({e}): build it with "
+                              "`python -m paper_2310_19102_amd.build`") from e
+        mod.set_error(AtomError)
+        _native = mod
+    return _native
+
+
 def _desc(K: int, group_size: int, n_outlier: int, bits: int = 4) -> _Desc:
     return _Desc(K, group_size, n_outlier, bits, 8)
 
@@ -221,23 +238,7 @@ def atom_quantize_act(x: torch.Tensor, gamma: Optional[torch.Tensor], eps: float
     """Fused RMSNorm -> reorder -> dynamic group quantisation of ``x`` [M, K]
     (fp16, last dim contiguous).  Returns ``(q4, q8, scale)`` device tensors.  ``bits``: width
     of the normal channels, 4 or 3 (same layouts: one code per nibble)."""
-    L = load_library()
-    _dev(x, torch.float16, "x")
-    if reorder_idx is not None:        # None: x already is in reordered order
-        _dev(reorder_idx, torch.int32, "reorder_idx")
-    if gamma is not None:
-        _dev(gamma, torch.float16, "gamma")
-    if x.dim() != 2 or x.stride(1) != 1:
-        raise ValueError("x must be [M, K] with a contiguous last dimension")
-    M, K = x.shape
-    q4, q8, sc = out if out is not None else _quant_outputs(M, K, group_size, n_outlier, x.device)
-    d = _desc(K, group_size, n_outlier, bits)
-    st = L.atom_quantize_act(_ptr(x), M, x.stride(0) if M > 1 else max(K, x.stride(0)), _ptr(gamma),
-                             eps, _ptr(reorder_idx), ctypes.byref(d), clip, _ptr(q4), _ptr(q8),
-                             _ptr(sc), _stream())
-    if st != 0:
-        raise AtomError(st, "atom_quantize_act")
-    return q4, q8, sc
+    return _run().quantize_act(x, gamma, eps, reorder_idx, group_size, n_outlier, clip, out, bits)
 
 
 def atom_tile_weight_decode(w_q4: torch.Tensor, w_q8: torch.Tensor, group_size: int = 128):
@@ -262,18 +263,7 @@ def atom_tile_weight_decode(w_q4: torch.Tensor, w_q8: torch.Tensor, group_size: 
 def atom_w4a4_gemm_decode_tiled(a_q4, a_q8, a_scale, w_q4_tiled, w_q8_tiled, w_scale, group_size: int = 128,
                                 out: Optional[torch.Tensor] = None):
     """Decode-sized group GEMM (M <= 256) on re-tiled weight codes; ``w_scale`` [N, G] canonical."""
-    L = load_library()
-    M, O = a_q8.shape
-    N, G = w_scale.shape
-    K = G * group_size
-    y = out if out is not None else torch.empty((M, N), dtype=torch.float16, device=a_q4.device)
-    d = _desc(K, group_size, O, 4)
-    st = L.atom_w4a4_gemm_decode_tiled(_ptr(a_q4), _ptr(a_q8), _ptr(a_scale), M, _ptr(w_q4_tiled), _ptr(w_q8_tiled),
-                                       _ptr(w_scale), N, ctypes.byref(d), _ptr(y),
-                                       y.stride(0) if M > 1 else max(N, y.stride(0)), _stream())
-    if st != 0:
-        raise AtomError(st, "atom_w4a4_gemm_decode_tiled")
-    return y
+    return _run().w4a4_gemm_decode_tiled(a_q4, a_q8, a_scale, w_q4_tiled, w_q8_tiled, w_scale, group_size, out)
 
 
 def atom_permute_rows(mat: torch.Tensor, row_idx: torch.Tensor, out: Optional[torch.Tensor] = None):
@@ -302,29 +292,7 @@ def atom_decode_linear(x: torch.Tensor, gamma: Optional[torch.Tensor], eps: floa
     """One launch for ``Y = linear(x)`` at M <= 16 rows: front end (RMSNorm when ``gamma`` is given,
     reorder, group quantisation) and weight-streaming group GEMM.  Returns ``Y`` [M, N] fp16, or
     ``(Y, (q4, q8, scale))`` with ``debug`` (the activation codes the kernel computed)."""
-    L = load_library()
-    _dev(x, torch.float16, "x")
-    if reorder_idx is not None:        # None: x already is in reordered order
-        _dev(reorder_idx, torch.int32, "reorder_idx")
-    if gamma is not None:
-        _dev(gamma, torch.float16, "gamma")
-    _dev(w_q4, torch.uint8, "w_q4")
-    _dev(w_q8, torch.int8, "w_q8")
-    _dev(w_scale, torch.float16, "w_scale")
-    if x.dim() != 2 or x.stride(1) != 1:
-        raise ValueError("x must be [M, K] with a contiguous last dimension")
-    M, K = x.shape
-    N, O = w_q8.shape
-    y = out if out is not None else torch.empty((M, N), dtype=torch.float16, device=x.device)
-    dbg = _quant_outputs(M, K, group_size, O, x.device) if debug else (None, None, None)
-    d = _desc(K, group_size, O, bits)
-    st = L.atom_decode_linear(_ptr(x), M, x.stride(0) if M > 1 else max(K, x.stride(0)), _ptr(gamma), eps,
-                              _ptr(reorder_idx), ctypes.byref(d), clip, _ptr(w_q4), _ptr(w_q8), _ptr(w_scale), N,
-                              _ptr(y), y.stride(0) if M > 1 else max(N, y.stride(0)), _ptr(dbg[0]), _ptr(dbg[1]),
-                              _ptr(dbg[2]), _stream())
-    if st != 0:
-        raise AtomError(st, "atom_decode_linear")
-    return (y, dbg) if debug else y
+    return _run().decode_linear(x, gamma, eps, reorder_idx, w_q4, w_q8, w_scale, group_size, clip, out, debug, bits)
 
 
 def atom_decode_linear_coop_sync(device="cuda") -> torch.Tensor:
@@ -342,32 +310,8 @@ def atom_decode_linear_coop(x: torch.Tensor, gamma: Optional[torch.Tensor], eps:
     workgroups quantise the rows, the others stream the weights meanwhile.  ``sync_words``:
     ``atom_decode_linear_coop_sync()`` (int32 zeros on the device), zero before the first call, left
     zero by every call (word 1 set = a wait ran out).  Returns ``(Y, (q4, q8, scale))``: the codes are outputs as in atom_quantize_act."""
-    L = load_library()
-    _dev(x, torch.float16, "x")
-    if reorder_idx is not None:        # None: x already is in reordered order
-        _dev(reorder_idx, torch.int32, "reorder_idx")
-    if gamma is not None:
-        _dev(gamma, torch.float16, "gamma")
-    _dev(w_q4, torch.uint8, "w_q4")
-    _dev(w_q8, torch.int8, "w_q8")
-    _dev(w_scale, torch.float16, "w_scale")
-    _dev(sync_words, torch.int32, "sync_words")
-    if 4 * sync_words.numel() < int(L.atom_decode_linear_coop_sync_bytes()) or not sync_words.is_contiguous():
-        raise ValueError("sync_words is too small: take atom_decode_linear_coop_sync()")
-    if x.dim() != 2 or x.stride(1) != 1:
-        raise ValueError("x must be [M, K] with a contiguous last dimension")
-    M, K = x.shape
-    N, O = w_q8.shape
-    y = out if out is not None else torch.empty((M, N), dtype=torch.float16, device=x.device)
-    q = codes if codes is not None else _quant_outputs(M, K, group_size, O, x.device)
-    d = _desc(K, group_size, O, bits)
-    st = L.atom_decode_linear_coop(_ptr(x), M, x.stride(0) if M > 1 else max(K, x.stride(0)), _ptr(gamma), eps,
-                                   _ptr(reorder_idx), ctypes.byref(d), clip, _ptr(w_q4), _ptr(w_q8), _ptr(w_scale),
-                                   N, _ptr(y), y.stride(0) if M > 1 else max(N, y.stride(0)), _ptr(q[0]), _ptr(q[1]),
-                                   _ptr(q[2]), _ptr(sync_words), _stream())
-    if st != 0:
-        raise AtomError(st, "atom_decode_linear_coop")
-    return y, q
+    return _run().decode_linear_coop(x, gamma, eps, reorder_idx, w_q4, w_q8, w_scale, sync_words, group_size, clip,
+                out, codes, bits)
 
 
 def atom_decode_linear_lds_bytes(M: int, K: int, n_outlier: int = 128, norm: bool = True, group_size: int = 128,
@@ -384,30 +328,8 @@ def atom_add_quantize_act(x: torch.Tensor, residual: torch.Tensor, gamma: Option
     """``h = fp16(x + residual)`` followed by the front end on ``h``.  ``sum_out`` may be
     ``x`` or ``residual`` (in place) or a separate [M, K] tensor; a new one by default.
     Returns ``(h, q4, q8, scale)``."""
-    L = load_library()
-    _dev(x, torch.float16, "x")
-    _dev(residual, torch.float16, "residual")
-    if reorder_idx is not None:        # None: x already is in reordered order
-        _dev(reorder_idx, torch.int32, "reorder_idx")
-    if gamma is not None:
-        _dev(gamma, torch.float16, "gamma")
-    if x.dim() != 2 or x.stride(1) != 1 or residual.shape != x.shape or residual.stride(1) != 1:
-        raise ValueError("x and residual must be [M, K] with a contiguous last dimension")
-    M, K = x.shape
-    if sum_out is None:
-        sum_out = torch.empty((M, K), dtype=torch.float16, device=x.device)
-    _dev(sum_out, torch.float16, "sum_out")
-    if sum_out.shape != x.shape or sum_out.stride(1) != 1:
-        raise ValueError("sum_out must be [M, K] with a contiguous last dimension")
-    d = _desc(K, group_size, n_outlier, bits)
-    q4, q8, sc = out if out is not None else _quant_outputs(M, K, group_size, n_outlier, x.device)
-    ld = lambda t: t.stride(0) if M > 1 else max(K, t.stride(0))
-    st = L.atom_add_quantize_act(_ptr(x), _ptr(residual), M, ld(x), ld(residual), _ptr(sum_out),
-                                 ld(sum_out), _ptr(gamma), eps, _ptr(reorder_idx), ctypes.byref(d),
-                                 clip, _ptr(q4), _ptr(q8), _ptr(sc), _stream())
-    if st != 0:
-        raise AtomError(st, "atom_add_quantize_act")
-    return sum_out, q4, q8, sc
+    return _run().add_quantize_act(x, residual, gamma, eps, reorder_idx, group_size, n_outlier, clip, sum_out, out,
+                bits)
 
 
 def atom_swiglu_quantize_act(gate: torch.Tensor, up: torch.Tensor, reorder_idx: Optional[torch.Tensor],
@@ -416,22 +338,7 @@ def atom_swiglu_quantize_act(gate: torch.Tensor, up: torch.Tensor, reorder_idx: 
     """``silu(gate) * up`` (fp32, never stored) followed by reorder and group quantisation.
     ``gate`` and ``up`` are [M, K] fp16 with a contiguous last dimension, e.g. the two halves
     of the fused gate/up projection's output.  Returns ``(q4, q8, scale)``."""
-    L = load_library()
-    _dev(gate, torch.float16, "gate")
-    _dev(up, torch.float16, "up")
-    if reorder_idx is not None:        # None: x already is in reordered order
-        _dev(reorder_idx, torch.int32, "reorder_idx")
-    if gate.dim() != 2 or gate.stride(1) != 1 or up.shape != gate.shape or up.stride(1) != 1:
-        raise ValueError("gate and up must be [M, K] with a contiguous last dimension")
-    M, K = gate.shape
-    q4, q8, sc = out if out is not None else _quant_outputs(M, K, group_size, n_outlier, gate.device)
-    d = _desc(K, group_size, n_outlier, bits)
-    ld = lambda t: t.stride(0) if M > 1 else max(K, t.stride(0))
-    st = L.atom_swiglu_quantize_act(_ptr(gate), _ptr(up), M, ld(gate), ld(up), _ptr(reorder_idx),
-                                    ctypes.byref(d), clip, _ptr(q4), _ptr(q8), _ptr(sc), _stream())
-    if st != 0:
-        raise AtomError(st, "atom_swiglu_quantize_act")
-    return q4, q8, sc
+    return _run().swiglu_quantize_act(gate, up, reorder_idx, group_size, n_outlier, clip, out, bits)
 
 
 def atom_quantize_weight(w: torch.Tensor, reorder_idx: Optional[torch.Tensor], group_size: int = 128,
@@ -467,37 +374,7 @@ def atom_w4a4_gemm(a_q4, a_q8, a_scale, w_q4, w_q8, w_scale, group_size: int = 1
     """Y[M, N] fp16 = group-dequantised product of quantised activations and
     weights.  ``partials`` (int32 [M, N, G]) also receives every per-group
     integer sum."""
-    L = load_library()
-    for t, dt, nm in ((a_q4, torch.uint8, "a_q4"), (a_q8, torch.int8, "a_q8"),
-                      (a_scale, torch.float16, "a_scale"), (w_q4, torch.uint8, "w_q4"),
-                      (w_q8, torch.int8, "w_q8"), (w_scale, torch.float16, "w_scale")):
-        _dev(t, dt, nm)
-        if not t.is_contiguous():
-            raise ValueError(f"{nm} must be contiguous")
-    M, O = a_q8.shape
-    N = w_q8.shape[0]
-    K = a_q4.shape[1] * 2 + O
-    if w_q4.shape[1] != a_q4.shape[1] or w_q8.shape[1] != O:
-        raise ValueError("activation and weight code shapes disagree")
-    if out is None:
-        out = torch.empty((M, N), dtype=torch.float16, device=a_q4.device)
-    _dev(out, torch.float16, "out")
-    if partials is not None:
-        _dev(partials, torch.int32, "partials")
-        if tuple(partials.shape) != (M, N, K // group_size) or not partials.is_contiguous():
-            raise ValueError("partials must be contiguous int32 [M, N, G]")
-    d = _desc(K, group_size, n_outlier=O)
-    need = int(L.atom_w4a4_gemm_workspace_bytes(M, N, ctypes.byref(d)))
-    if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
-        workspace = torch.empty(need, dtype=torch.uint8, device=a_q4.device)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = L.atom_w4a4_gemm(_ptr(a_q4), _ptr(a_q8), _ptr(a_scale), M, _ptr(w_q4), _ptr(w_q8),
-                          _ptr(w_scale), N, ctypes.byref(d), _ptr(out),
-                          out.stride(0) if M > 1 else max(N, out.stride(0)),
-                          _ptr(partials), _ptr(workspace), ws_bytes, _stream())
-    if st != 0:
-        raise AtomError(st, "atom_w4a4_gemm")
-    return out
+    return _run().w4a4_gemm(a_q4, a_q8, a_scale, w_q4, w_q8, w_scale, group_size, out, partials, workspace)
 
 
 def atom_pack_weight(w_q4, w_q8, w_scale, group_size: int = 128, out: Optional[torch.Tensor] = None):
@@ -524,30 +401,7 @@ def atom_pack_weight(w_q4, w_q8, w_scale, group_size: int = 128, out: Optional[t
 
 def atom_pack_act(a_q4, a_q8, a_scale, group_size: int = 128, out: Optional[torch.Tensor] = None):
     """Canonical activation codes and scales -> the tiled layout (``atom_w4a4_gemm_prepacked``)."""
-    L = load_library()
-    for t, dt, nm in ((a_q4, torch.uint8, "a_q4"), (a_q8, torch.int8, "a_q8"), (a_scale, torch.float16, "a_scale")):
-        _dev(t, dt, nm)
-        if not t.is_contiguous():
-            raise ValueError(f"{nm} must be contiguous")
-    M, O = a_q8.shape
-    K = a_q4.shape[1] * 2 + O
-    d = _desc(K, group_size, n_outlier=O)
-    need = int(L.atom_pack_weight_bytes(M, ctypes.byref(d)))
-    if out is None:
-        out = torch.empty(max(need, 1), dtype=torch.uint8, device=a_q4.device)
-    _dev(out, torch.uint8, "out")
-    st = L.atom_pack_act(_ptr(a_q4), _ptr(a_q8), _ptr(a_scale), M, ctypes.byref(d), _ptr(out), out.numel(), _stream())
-    if st != 0:
-        raise AtomError(st, "atom_pack_act")
-    return out
-
-
-def _packed_out(L, M, d, out, device):
-    need = int(L.atom_pack_weight_bytes(M, ctypes.byref(d)))
-    if out is None:
-        out = torch.empty(max(need, 1), dtype=torch.uint8, device=device)
-    _dev(out, torch.uint8, "out")
-    return out
+    return _run().pack_act(a_q4, a_q8, a_scale, group_size, out)
 
 
 def atom_quantize_act_packed(x: torch.Tensor, gamma: Optional[torch.Tensor], eps: float,
@@ -555,18 +409,7 @@ def atom_quantize_act_packed(x: torch.Tensor, gamma: Optional[torch.Tensor], eps
                              clip: float = 0.9, out: Optional[torch.Tensor] = None, bits: int = 4):
     """``atom_quantize_act`` writing the tiled activations of ``atom_w4a4_gemm_prepacked`` directly
     (the bytes ``atom_pack_act`` would make of its result)."""
-    L = load_library()
-    _dev(x, torch.float16, "x")
-    if x.dim() != 2 or x.stride(1) != 1:
-        raise ValueError("x must be [M, K] with a contiguous last dimension")
-    M, K = x.shape
-    d = _desc(K, group_size, n_outlier, bits)
-    out = _packed_out(L, M, d, out, x.device)
-    st = L.atom_quantize_act_packed(_ptr(x), M, x.stride(0) if M > 1 else max(K, x.stride(0)), _ptr(gamma), eps,
-                                    _ptr(reorder_idx), ctypes.byref(d), clip, _ptr(out), out.numel(), _stream())
-    if st != 0:
-        raise AtomError(st, "atom_quantize_act_packed")
-    return out
+    return _run().quantize_act_packed(x, gamma, eps, reorder_idx, group_size, n_outlier, clip, out, bits)
 
 
 def atom_add_quantize_act_packed(x: torch.Tensor, residual: torch.Tensor, gamma: Optional[torch.Tensor], eps: float,
@@ -574,62 +417,22 @@ def atom_add_quantize_act_packed(x: torch.Tensor, residual: torch.Tensor, gamma:
                                  clip: float = 0.9, sum_out: Optional[torch.Tensor] = None,
                                  out: Optional[torch.Tensor] = None, bits: int = 4):
     """``atom_add_quantize_act`` writing the tiled activations directly.  Returns ``(h, a_packed)``."""
-    L = load_library()
-    _dev(x, torch.float16, "x")
-    _dev(residual, torch.float16, "residual")
-    M, K = x.shape
-    h = sum_out if sum_out is not None else torch.empty((M, K), dtype=torch.float16, device=x.device)
-    d = _desc(K, group_size, n_outlier, bits)
-    out = _packed_out(L, M, d, out, x.device)
-    ld = lambda t: t.stride(0) if M > 1 else max(K, t.stride(0))
-    st = L.atom_add_quantize_act_packed(_ptr(x), _ptr(residual), M, ld(x), ld(residual), _ptr(h), ld(h), _ptr(gamma),
-                                        eps, _ptr(reorder_idx), ctypes.byref(d), clip, _ptr(out), out.numel(), _stream())
-    if st != 0:
-        raise AtomError(st, "atom_add_quantize_act_packed")
-    return h, out
+    return _run().add_quantize_act_packed(x, residual, gamma, eps, reorder_idx, group_size, n_outlier, clip,
+                sum_out, out, bits)
 
 
 def atom_swiglu_quantize_act_packed(gate: torch.Tensor, up: torch.Tensor, reorder_idx: Optional[torch.Tensor],
                                     group_size: int = 128, n_outlier: int = 128, clip: float = 0.9,
                                     out: Optional[torch.Tensor] = None, bits: int = 4):
     """``atom_swiglu_quantize_act`` writing the tiled activations directly."""
-    L = load_library()
-    _dev(gate, torch.float16, "gate")
-    _dev(up, torch.float16, "up")
-    M, K = gate.shape
-    d = _desc(K, group_size, n_outlier, bits)
-    out = _packed_out(L, M, d, out, gate.device)
-    ld = lambda t: t.stride(0) if M > 1 else max(K, t.stride(0))
-    st = L.atom_swiglu_quantize_act_packed(_ptr(gate), _ptr(up), M, ld(gate), ld(up), _ptr(reorder_idx),
-                                           ctypes.byref(d), clip, _ptr(out), out.numel(), _stream())
-    if st != 0:
-        raise AtomError(st, "atom_swiglu_quantize_act_packed")
-    return out
+    return _run().swiglu_quantize_act_packed(gate, up, reorder_idx, group_size, n_outlier, clip, out, bits)
 
 
 def atom_w4a4_gemm_prepacked(a_packed, M: int, w_packed, N: int, K: int, group_size: int = 128,
                              n_outlier: int = 128, out: Optional[torch.Tensor] = None,
                              partials: Optional[torch.Tensor] = None):
     """The GEMM on two tiled operands (``atom_pack_act`` / ``atom_pack_weight``)."""
-    L = load_library()
-    _dev(a_packed, torch.uint8, "a_packed")
-    _dev(w_packed, torch.uint8, "w_packed")
-    d = _desc(K, group_size, n_outlier)
-    if (a_packed.numel() < int(L.atom_pack_weight_bytes(M, ctypes.byref(d))) or
-            w_packed.numel() < int(L.atom_pack_weight_bytes(N, ctypes.byref(d)))):
-        raise ValueError("a packed operand is smaller than atom_pack_weight_bytes of its rows")
-    if out is None:
-        out = torch.empty((M, N), dtype=torch.float16, device=a_packed.device)
-    _dev(out, torch.float16, "out")
-    if partials is not None:
-        _dev(partials, torch.int32, "partials")
-        if tuple(partials.shape) != (M, N, K // group_size) or not partials.is_contiguous():
-            raise ValueError("partials must be contiguous int32 [M, N, G]")
-    st = L.atom_w4a4_gemm_prepacked(_ptr(a_packed), M, _ptr(w_packed), N, ctypes.byref(d), _ptr(out),
-                                    out.stride(0) if M > 1 else max(N, out.stride(0)), _ptr(partials), _stream())
-    if st != 0:
-        raise AtomError(st, "atom_w4a4_gemm_prepacked")
-    return out
+    return _run().w4a4_gemm_prepacked(a_packed, M, w_packed, N, K, group_size, n_outlier, out, partials)
 
 
 def atom_w4a4_gemm_packed_workspace_bytes(M: int, N: int, K: int, group_size: int = 128,
@@ -642,34 +445,7 @@ def atom_w4a4_gemm_packed(a_q4, a_q8, a_scale, w_packed, N: int, group_size: int
                           out: Optional[torch.Tensor] = None, partials: Optional[torch.Tensor] = None,
                           workspace: Optional[torch.Tensor] = None):
     """``atom_w4a4_gemm`` against weights packed by ``atom_pack_weight``."""
-    L = load_library()
-    for t, dt, nm in ((a_q4, torch.uint8, "a_q4"), (a_q8, torch.int8, "a_q8"),
-                      (a_scale, torch.float16, "a_scale"), (w_packed, torch.uint8, "w_packed")):
-        _dev(t, dt, nm)
-        if not t.is_contiguous():
-            raise ValueError(f"{nm} must be contiguous")
-    M, O = a_q8.shape
-    K = a_q4.shape[1] * 2 + O
-    d = _desc(K, group_size, n_outlier=O)
-    if w_packed.numel() < int(L.atom_pack_weight_bytes(N, ctypes.byref(d))):
-        raise ValueError("w_packed is smaller than atom_pack_weight_bytes(N)")
-    if out is None:
-        out = torch.empty((M, N), dtype=torch.float16, device=a_q4.device)
-    _dev(out, torch.float16, "out")
-    if partials is not None:
-        _dev(partials, torch.int32, "partials")
-        if tuple(partials.shape) != (M, N, K // group_size) or not partials.is_contiguous():
-            raise ValueError("partials must be contiguous int32 [M, N, G]")
-    need = int(L.atom_w4a4_gemm_packed_workspace_bytes(M, N, ctypes.byref(d)))
-    if workspace is None or workspace.numel() * workspace.element_size() < need:
-        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=a_q4.device)
-    st = L.atom_w4a4_gemm_packed(_ptr(a_q4), _ptr(a_q8), _ptr(a_scale), M, _ptr(w_packed), N,
-                                 ctypes.byref(d), _ptr(out), out.stride(0) if M > 1 else max(N, out.stride(0)),
-                                 _ptr(partials), _ptr(workspace), workspace.numel() * workspace.element_size(),
-                                 _stream())
-    if st != 0:
-        raise AtomError(st, "atom_w4a4_gemm_packed")
-    return out
+    return _run().w4a4_gemm_packed(a_q4, a_q8, a_scale, w_packed, N, group_size, out, partials, workspace)
 
 
 def atom_decode_attention_kv4_workspace_bytes(B: int, H: int, Hkv: int, D: int, Tmax: int) -> int:
@@ -686,42 +462,7 @@ def atom_kv_quantize(x: torch.Tensor, clip: float = 1.0,
     With ``cache = (codes [B, Hkv, Tmax, D/2], scale [B, Hkv, Tmax], zero [B, Hkv, Tmax])``
     and ``pos`` (device int32 [B]): ``x`` is [B, Hkv, D], the new token of every sequence,
     written in place at position ``pos[b]``; returns ``cache``."""
-    L = load_library()
-    _dev(x, torch.float16, "x")
-    if x.dim() < 1 or not x.is_contiguous():
-        raise ValueError("x must be contiguous [..., D]")
-    D = x.shape[-1]
-    R = x.numel() // D if D else 0
-    if cache is None:
-        if pos is not None:
-            raise ValueError("pos needs a cache to append to")
-        lead = tuple(x.shape[:-1])
-        codes = torch.empty(lead + (D // 2,), dtype=torch.uint8, device=x.device)
-        scale = torch.empty(lead, dtype=torch.float16, device=x.device)
-        zero = torch.empty(lead, dtype=torch.int16, device=x.device)
-        st = L.atom_kv_quantize(_ptr(x), R, D, D, clip, None, 0, 0, _ptr(codes), _ptr(scale),
-                                _ptr(zero), _stream())
-    else:
-        codes, scale, zero = cache
-        _dev(codes, torch.uint8, "cache codes")
-        _dev(scale, torch.float16, "cache scale")
-        _dev(zero, torch.int16, "cache zero")
-        if pos is None:
-            raise ValueError("appending to a cache needs pos")
-        _dev(pos, torch.int32, "pos")
-        if x.dim() != 3 or codes.dim() != 4 or not (codes.is_contiguous() and scale.is_contiguous()
-                                                    and zero.is_contiguous()):
-            raise ValueError("x must be [B, Hkv, D] and the cache contiguous [B, Hkv, Tmax, ...]")
-        B, Hkv, Tmax = codes.shape[:3]
-        if (tuple(x.shape) != (B, Hkv, D) or codes.shape[3] * 2 != D or tuple(scale.shape) != (B, Hkv, Tmax)
-                or tuple(zero.shape) != (B, Hkv, Tmax) or tuple(pos.shape) != (B,)
-                or not pos.is_contiguous()):
-            raise ValueError("cache, x and pos shapes disagree")
-        st = L.atom_kv_quantize(_ptr(x), R, D, D, clip, _ptr(pos), Hkv, Tmax, _ptr(codes),
-                                _ptr(scale), _ptr(zero), _stream())
-    if st != 0:
-        raise AtomError(st, "atom_kv_quantize")
-    return codes, scale, zero
+    return _run().kv_quantize(x, clip, cache, pos)
 
 
 def atom_kv_quantize_pair(k: torch.Tensor, v: torch.Tensor, k_cache: Tuple[torch.Tensor, ...],
@@ -729,60 +470,7 @@ def atom_kv_quantize_pair(k: torch.Tensor, v: torch.Tensor, k_cache: Tuple[torch
     """The new K and V rows of every sequence ([B, Hkv, D] fp16 each) appended in place to
     their caches at position ``pos[b]`` in one launch; the same results as two
     ``atom_kv_quantize`` calls.  Returns ``(k_cache, v_cache)``."""
-    L = load_library()
-    _dev(pos, torch.int32, "pos")
-    for x, cache, nm in ((k, k_cache, "k"), (v, v_cache, "v")):
-        _dev(x, torch.float16, nm)
-        codes, scale, zero = cache
-        _dev(codes, torch.uint8, nm + " cache codes")
-        _dev(scale, torch.float16, nm + " cache scale")
-        _dev(zero, torch.int16, nm + " cache zero")
-        if x.dim() != 3 or codes.dim() != 4 or not (x.is_contiguous() and codes.is_contiguous()
-                                                    and scale.is_contiguous() and zero.is_contiguous()):
-            raise ValueError(nm + " must be contiguous [B, Hkv, D] and its cache contiguous [B, Hkv, Tmax, ...]")
-    B, Hkv, Tmax = k_cache[0].shape[:3]
-    D = k.shape[-1]
-    for x, (codes, scale, zero) in ((k, k_cache), (v, v_cache)):
-        if (tuple(x.shape) != (B, Hkv, D) or tuple(codes.shape) != (B, Hkv, Tmax, D // 2)
-                or tuple(scale.shape) != (B, Hkv, Tmax) or tuple(zero.shape) != (B, Hkv, Tmax)):
-            raise ValueError("cache and row shapes disagree")
-    if tuple(pos.shape) != (B,) or not pos.is_contiguous():
-        raise ValueError("pos must be contiguous int32 [B]")
-    st = L.atom_kv_quantize_pair(_ptr(k), _ptr(v), B * Hkv, D, D, clip, _ptr(pos), Hkv, Tmax,
-                                 _ptr(k_cache[0]), _ptr(k_cache[1]), _ptr(k_cache[2]),
-                                 _ptr(v_cache[0]), _ptr(v_cache[1]), _ptr(v_cache[2]), _stream())
-    if st != 0:
-        raise AtomError(st, "atom_kv_quantize_pair")
-    return k_cache, v_cache
-
-
-def _attention_args(q, k_cache, v_cache, seq_len, out):
-    _dev(q, torch.float16, "q")
-    _dev(seq_len, torch.int32, "seq_len")
-    if q.dim() != 3 or not q.is_contiguous():
-        raise ValueError("q must be contiguous [B, H, D]")
-    B, H, D = q.shape
-    kq, ks, kz = k_cache
-    vq, vs, vz = v_cache
-    for t, dt, nm in ((kq, torch.uint8, "k codes"), (vq, torch.uint8, "v codes"),
-                      (ks, torch.float16, "k scale"), (vs, torch.float16, "v scale"),
-                      (kz, torch.int16, "k zero"), (vz, torch.int16, "v zero")):
-        _dev(t, dt, nm)
-        if not t.is_contiguous():
-            raise ValueError(f"{nm} must be contiguous")
-    if kq.dim() != 4 or kq.shape[0] != B or kq.shape[3] * 2 != D:
-        raise ValueError("k codes must be [B, Hkv, Tmax, D/2]")
-    Hkv, Tmax = kq.shape[1], kq.shape[2]
-    if (vq.shape != kq.shape or tuple(ks.shape) != (B, Hkv, Tmax) or ks.shape != vs.shape
-            or kz.shape != ks.shape or vz.shape != ks.shape or tuple(seq_len.shape) != (B,)
-            or not seq_len.is_contiguous()):
-        raise ValueError("cache and seq_len shapes disagree")
-    if out is None:
-        out = torch.empty((B, H, D), dtype=torch.float16, device=q.device)
-    _dev(out, torch.float16, "out")
-    if tuple(out.shape) != (B, H, D) or not out.is_contiguous():
-        raise ValueError("out must be contiguous [B, H, D]")
-    return B, H, Hkv, D, Tmax, out
+    return _run().kv_quantize_pair(k, v, k_cache, v_cache, pos, clip)
 
 
 def atom_decode_attention_kv4(q: torch.Tensor, k_cache: Tuple[torch.Tensor, ...],
@@ -792,20 +480,7 @@ def atom_decode_attention_kv4(q: torch.Tensor, k_cache: Tuple[torch.Tensor, ...]
     """Attention of one query token per sequence over the INT4 cache.  ``q`` [B, H, D] fp16;
     each cache is ``(codes [B, Hkv, Tmax, D/2] uint8, scale [B, Hkv, Tmax] fp16,
     zero [B, Hkv, Tmax] int16)``; ``seq_len`` device int32 [B].  Returns [B, H, D] fp16."""
-    L = load_library()
-    B, H, Hkv, D, Tmax, out = _attention_args(q, k_cache, v_cache, seq_len, out)
-    kq, ks, kz = k_cache
-    vq, vs, vz = v_cache
-    need = int(L.atom_decode_attention_kv4_workspace_bytes(B, H, Hkv, D, Tmax))
-    if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = L.atom_decode_attention_kv4(_ptr(q), B, H, Hkv, D, Tmax, _ptr(seq_len), _ptr(kq), _ptr(ks),
-                                     _ptr(kz), _ptr(vq), _ptr(vs), _ptr(vz), sm_scale, _ptr(out),
-                                     _ptr(workspace), ws_bytes, _stream())
-    if st != 0:
-        raise AtomError(st, "atom_decode_attention_kv4")
-    return out
+    return _run().decode_attention_kv4(q, k_cache, v_cache, seq_len, sm_scale, out, workspace)
 
 
 def atom_static_scratch_bytes() -> int:
@@ -817,18 +492,9 @@ def atom_decode_attention_kv4_static(q: torch.Tensor, k_cache: Tuple[torch.Tenso
                                      sm_scale: float, out: torch.Tensor):
     """``atom_decode_attention_kv4`` through the entry point that allocates nothing: ``out`` is the
     caller's, the partials of a split launch live in the library's own per-GPU scratch array."""
-    L = load_library()
     if out is None:
         raise ValueError("out must be given: this call allocates nothing")
-    B, H, Hkv, D, Tmax, out = _attention_args(q, k_cache, v_cache, seq_len, out)
-    kq, ks, kz = k_cache
-    vq, vs, vz = v_cache
-    st = L.atom_decode_attention_kv4_static(_ptr(q), B, H, Hkv, D, Tmax, _ptr(seq_len), _ptr(kq), _ptr(ks),
-                                            _ptr(kz), _ptr(vq), _ptr(vs), _ptr(vz), sm_scale, _ptr(out),
-                                            _stream())
-    if st != 0:
-        raise AtomError(st, "atom_decode_attention_kv4_static")
-    return out
+    return _run().decode_attention_kv4_static(q, k_cache, v_cache, seq_len, sm_scale, out)
 
 
 def _mx_outputs(rows: int, K: int, n_outlier: int, device):
@@ -844,22 +510,7 @@ def atom_mx_quantize_act(x: torch.Tensor, gamma: Optional[torch.Tensor], eps: fl
                          out: Optional[Tuple[torch.Tensor, ...]] = None):
     """MX variant of the front end: RMSNorm -> reorder -> FP4 E2M1 (normal channels) / FP8 E4M3
     (outliers) with one E8M0 scale byte per 32 channels.  Returns ``(q4, q8, e8)``."""
-    L = load_library()
-    _dev(x, torch.float16, "x")
-    _dev(reorder_idx, torch.int32, "reorder_idx")
-    if gamma is not None:
-        _dev(gamma, torch.float16, "gamma")
-    if x.dim() != 2 or x.stride(1) != 1:
-        raise ValueError("x must be [M, K] with a contiguous last dimension")
-    M, K = x.shape
-    q4, q8, e8 = out if out is not None else _mx_outputs(M, K, n_outlier, x.device)
-    d = _Desc(K, 32, n_outlier, 4, 8)
-    st = L.atom_mx_quantize_act(_ptr(x), M, x.stride(0) if M > 1 else max(K, x.stride(0)), _ptr(gamma),
-                                eps, _ptr(reorder_idx), ctypes.byref(d), clip, _ptr(q4), _ptr(q8),
-                                _ptr(e8), _stream())
-    if st != 0:
-        raise AtomError(st, "atom_mx_quantize_act")
-    return q4, q8, e8
+    return _run().mx_quantize_act(x, gamma, eps, reorder_idx, n_outlier, clip, out)
 
 
 def atom_mx_quantize_weight(w: torch.Tensor, reorder_idx: torch.Tensor, n_outlier: int = 128,
@@ -884,30 +535,7 @@ def atom_mx_quantize_weight(w: torch.Tensor, reorder_idx: torch.Tensor, n_outlie
 def atom_mx_gemm(a_q4, a_q8, a_e8, w_q4, w_q8, w_e8, out: Optional[torch.Tensor] = None):
     """Y[M, N] fp16 from the two MX-quantised operands; the block scales are applied by the
     scaled MFMA instruction itself."""
-    L = load_library()
-    for t, nm in ((a_q4, "a_q4"), (a_q8, "a_q8"), (a_e8, "a_e8"), (w_q4, "w_q4"), (w_q8, "w_q8"),
-                  (w_e8, "w_e8")):
-        _dev(t, torch.uint8, nm)
-        if not t.is_contiguous():
-            raise ValueError(f"{nm} must be contiguous")
-    if a_q4.dim() != 3 or a_q8.dim() != 3 or w_q4.dim() != 3 or w_q8.dim() != 3:
-        raise ValueError("operands must be the step-major arrays atom_mx_quantize_* produce")
-    M, N = a_q8.shape[1], w_q8.shape[1]
-    O = a_q8.shape[0] * 64
-    K = a_q4.shape[0] * 128 + O
-    if (w_q4.shape[0] != a_q4.shape[0] or w_q8.shape[0] != a_q8.shape[0] or a_q4.shape[1] != M
-            or w_q4.shape[1] != N or tuple(a_e8.shape) != (K // 128, M, 4) or tuple(w_e8.shape) != (K // 128, N, 4)):
-        raise ValueError("activation and weight code shapes disagree")
-    if out is None:
-        out = torch.empty((M, N), dtype=torch.float16, device=a_q4.device)
-    _dev(out, torch.float16, "out")
-    d = _Desc(K, 32, O, 4, 8)
-    st = L.atom_mx_gemm(_ptr(a_q4), _ptr(a_q8), _ptr(a_e8), M, _ptr(w_q4), _ptr(w_q8), _ptr(w_e8), N,
-                        ctypes.byref(d), _ptr(out), out.stride(0) if M > 1 else max(N, out.stride(0)),
-                        _stream())
-    if st != 0:
-        raise AtomError(st, "atom_mx_gemm")
-    return out
+    return _run().mx_gemm(a_q4, a_q8, a_e8, w_q4, w_q8, w_e8, out)
 
 
 def atom_calibrate_reorder(x: torch.Tensor):

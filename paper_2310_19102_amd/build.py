@@ -16,6 +16,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libatom.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["atom_api.hip", "atom_quantize.hip", "atom_quantize_packed.hip", "atom_gemm.hip", "atom_gemm_big.hip", "atom_gemm_decode.hip", "atom_gemm_gs.hip", "atom_decode_fused.hip", "atom_gemm_f6.hip", "atom_kv.hip", "atom_mx.hip", "atom_calib.hip", "atom_probe.hip"]
 
 FLAGS = [
@@ -38,6 +39,22 @@ SOURCE_FLAGS = {"atom_mx.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=0"],
                 "atom_kv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
+def native_command(lib: str = LIB, out: str = NATIVE):
+    """The python extension (host code only: tensors in, calls into libatom.so)."""
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wno-attributes",
+            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-I" + os.path.join(ROOT, "include"), "-isystem", os.path.join(t, "include"),
+            "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+            "-isystem", os.path.join(rocm, "include"), "-I" + sysconfig.get_paths()["include"],
+            os.path.join(CSRC, "atom_torch.cpp"), "-o", out, lib, "-L" + os.path.join(t, "lib"), "-ltorch_python",
+            "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+
+
 def build(verbose: bool = False, extra_flags=(), lib: str = LIB, tag: str = "") -> str:
     """Compile every kernel file and link ``libatom.so`` next to this module."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -58,8 +75,10 @@ def build(verbose: bool = False, extra_flags=(), lib: str = LIB, tag: str = "") 
             raise RuntimeError(f"hipcc failed on {src}:\n{out.decode()}")
         if verbose and text:
             print(text, flush=True)
-    cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", lib]
+    cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-Wl,-soname," + os.path.basename(lib), "-o", lib]
     subprocess.run(cmd, check=True)
+    if lib == LIB:
+        subprocess.run(native_command(), check=True)
     return lib
 
 
