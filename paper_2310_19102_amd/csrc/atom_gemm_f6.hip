@@ -29,24 +29,15 @@
 //     scale at 8192 + 8 r.
 // Rows past the end of the matrix hold zero codes and zero scales.
 //
-// Kernel: 256 x 128 (or 128 x 128, 64 x 128) tile, wavefront tile 64 x 64 = four 32 x 32 sub-tiles,
-// NST LDS stages.  Per INT4 group and sub-tile: two FP6 MFMAs (64 channels each) and one fp16 MFMA
-// that forms the 32 x 32 tile of scale products a_scale[m] * w_scale[n] (rank 1, exact in fp32),
-// then 16 fused multiply-adds per lane.  Groups are added in ascending order, the INT8 group(s)
-// last, each by one fmaf: the accumulation chain of the definition.
-//
-// PERSIST (256-row tiles, one INT8 group, at least as many tiles as CUs): one workgroup per CU walks
-// its share of the tiles, and the stream of requests never stops at a tile's end.  The K loop's last
-// two steps, which have nothing of their own tile left to ask for, request groups 0 and 1 of the
-// next tile into the stages they have just freed; the INT8 group sits in the other two stages,
-// which afterwards hold the output staging areas and then, behind one barrier, the next tile's
-// groups 2 and 3.  The next tile starts with its first group long in LDS: no burst of four groups'
-// requests, no round trip to memory, no wait for another workgroup to be launched.  Same sums in
-// the same order as the one-tile kernel.  The waits count instructions (vmcnt returns in order),
-// so what lies between the requests of a tile's groups 3 and 4 is kept at exactly eight
-// vector-memory instructions: the eight 16-byte stores of the tile before, or eight dummy
-// requests (first tile; a wavefront whose part of the tile is cut by M or N stores first,
-// conditionally, and waits for all of it).
+// Three GEMM kernels share this layout and arithmetic, and give the same bits: groups are added in ascending
+// order, the INT8 group(s) last, each by one fmaf: the accumulation chain of the definition.
+//   atom_gemm_f6_thin.hip: launches of few tiles (one row of 32 x 32 blocks per wavefront).
+//   atom_gemm_f6_walk.hip: launches of many tiles (64 x 64 per wavefront, workgroups that walk tiles).
+//   w4a4_gemm_f6_kernel below: everything those two do not take (several INT8 groups, fewer than seven
+//     INT4 groups) and the dump of the integer sums.  256 x 128 (or 128 x 128, 64 x 128) tile, wavefront tile 64 x 64 = four
+//     32 x 32 sub-tiles, NST LDS stages.  Per INT4 group and sub-tile: two FP6 MFMAs (64 channels each) and one
+//     fp16 MFMA that forms the 32 x 32 tile of scale products a_scale[m] * w_scale[n] (rank 1, exact in fp32), then 16
+//     fused multiply-adds per lane.
 
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
@@ -54,30 +45,13 @@
 
 #include <type_traits>
 
-#include "atom_gemm_common.h"
+#include "atom_gemm_f6.h"
 #include "atom_internal.h"
 #include "atom_launch.h"
 
 namespace {
 
-using namespace atom_gemm;
-
-typedef int      v8i  __attribute__((ext_vector_type(8)));
-typedef int      v12i __attribute__((ext_vector_type(12)));
-typedef unsigned v6u  __attribute__((ext_vector_type(6)));
-typedef unsigned v2u  __attribute__((ext_vector_type(2)));
-typedef unsigned v4u  __attribute__((ext_vector_type(4)));
-typedef float    v16f __attribute__((ext_vector_type(16)));
-typedef _Float16 v32h __attribute__((ext_vector_type(32)));
-typedef _Float16 v4h  __attribute__((ext_vector_type(4)));
-
-constexpr int IMG4 = 6656;                // bytes of an INT4 group image of one unit
-constexpr int IMG8 = 8704;                // bytes of an INT8 group image of one unit
-constexpr int kU8  = 9216;                // pitch of the INT8 images in LDS where they are fetched during the K loop
-constexpr int SC4  = 6144;                // offset of the scales inside an INT4 image
-constexpr int SC8  = 8192;
-
-__host__ __device__ constexpr int round_kb(int x) { return (x + 1023) / 1024 * 1024; }
+using namespace atom_gemm_f6;
 
 // ------------------------------------------------------------------------------------------
 // Packing: canonical rows -> unit images.  One thread per 16-byte destination chunk.
@@ -150,46 +124,6 @@ void pack_rows_kernel(const PackParams p)
 // ------------------------------------------------------------------------------------------
 // The GEMM
 // ------------------------------------------------------------------------------------------
-struct F6Params {
-    const uint8_t *a_pk, *w_pk;           // unit images of the activations / weights
-    uint16_t *y; int32_t *partials;
-    int64_t M, N, ldy;
-    int     a_units, w_units, G4, G8;
-    int64_t ustride;
-};
-
-__device__ __forceinline__ void dma16(uint32_t lds, uint32_t voff, const uint8_t *sbase)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(lds), "v"(voff), "s"(sbase) : "memory", "m0");
-}
-
-// s_waitcnt immediate: vmcnt(n), lgkmcnt(0), expcnt untouched
-__host__ __device__ constexpr int wait_imm(int n) { return (n & 15) | (7 << 4) | (0 << 8) | ((n >> 4) << 14); }
-
-// A lane's operands of the two MFMAs of a group, as the three 128-bit fragment reads deliver them:
-// registers 0-5 feed the first MFMA (channels 0-63 of the group), registers 6-11 the second.
-template <int S>
-__device__ __forceinline__ v16f mfma_f6(const v12i &a, const v12i &b, v16f c)
-{
-    // cbsz = blgp = 3: both operands E3M2 (six registers each); scale bytes 127 = 2^0
-    const v8i a8 = __builtin_shufflevector(a, a, 6 * S, 6 * S + 1, 6 * S + 2, 6 * S + 3, 6 * S + 4, 6 * S + 5, -1, -1);
-    const v8i b8 = __builtin_shufflevector(b, b, 6 * S, 6 * S + 1, 6 * S + 2, 6 * S + 3, 6 * S + 4, 6 * S + 5, -1, -1);
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, c, 3, 3, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
-}
-
-// Order control.  MFMAs and fused multiply-adds have no side effects, so instruction selection
-// is free to let them drift towards their consumers, which bunches each MFMA with the
-// multiply-adds that wait for it.  An empty volatile asm that takes a value as an in/out operand
-// is ordered with the other volatile statements and with the scheduling fences: whatever produces
-// the value stays above it, whatever consumes it stays below.
-#define ATOM_F6_PIN(x) asm volatile("" : "+v"(x))
-#define ATOM_F6_SLOT_END()                         \
-    do {                                           \
-        asm volatile("" ::: "memory");             \
-        __builtin_amdgcn_sched_barrier(0);         \
-    } while (0)
-
 template <int WM>
 struct F6Geom {
     static constexpr int NWAVE = WM * 2;
@@ -210,7 +144,7 @@ struct F6Geom {
     static constexpr int LDS   = LDS0 > OUT ? LDS0 : OUT;
 };
 
-template <int WM, bool DBG, bool PERSIST = false>
+template <int WM, bool DBG>
 __global__ __launch_bounds__(WM * 128, 2)
 void w4a4_gemm_f6_kernel(const F6Params p)
 {
@@ -229,19 +163,7 @@ void w4a4_gemm_f6_kernel(const F6Params p)
     // tile of this workgroup: M-tiles fastest, in bands of up to eight M-tiles so that the tiles an
     // XCD works on at one time share both activation and weight units in its L2
     const int TM = (p.a_units + WM - 1) / WM, TN = (p.w_units + 1) / 2;
-    // PERSIST: a workgroup walks tiles logical, logical + lstep, ... < lend of its XCD's contiguous share
-    int logical, lstep = 1, lend;
-    if constexpr (PERSIST) {
-        const int ntiles = TM * TN, nb = gridDim.x, xcd = blockIdx.x & 7;
-        const int per = ntiles >> 3, rem = ntiles & 7;
-        const int start = xcd * per + (xcd < rem ? xcd : rem);
-        logical = start + (int)(blockIdx.x >> 3);
-        lstep   = (nb - xcd + 7) >> 3;
-        lend    = start + per + (xcd < rem ? 1 : 0);
-    } else {
-        logical = xcd_contiguous_block_id();
-        lend    = logical + 1;
-    }
+    const int logical = xcd_contiguous_block_id();
     constexpr int LPWc = Gm::LPW;
     struct Tile {
         int a_valid, w_valid;
@@ -249,9 +171,6 @@ void w4a4_gemm_f6_kernel(const F6Params p)
         int64_t m_w, n_w;
         uint32_t voff[LPWc];
     };
-    // (the lane number as the per-tile code sees it: made opaque once per tile, so that what is
-    // derived from it is recomputed there and does not hold registers through the K loop)
-    int lane_t = lane;
     auto tile_of = [&](int lt) __attribute__((always_inline)) -> Tile {
         Tile t;
         const int band = 8 * TN, b = lt / band, rem = lt - b * band;
@@ -268,7 +187,7 @@ void w4a4_gemm_f6_kernel(const F6Params p)
         for (int k = 0; k < LPW; ++k) {
             const int j0 = wave + NWAVE * k, j = j0 < NI ? j0 : wave;
             const bool isa = j < NA;
-            int q = 64 * (isa ? j : j - NA) + lane_t;             // 16-byte chunk within the part
+            int q = 64 * (isa ? j : j - NA) + lane;             // 16-byte chunk within the part
             const int nq = (isa ? WM : 2) * (IMG4 / 16);
             q = q < nq ? q : nq - 1;
             int unit = q / (IMG4 / 16);
@@ -279,8 +198,7 @@ void w4a4_gemm_f6_kernel(const F6Params p)
         }
         return t;
     };
-    Tile T = tile_of(logical), Tn = T;
-    uint32_t more_mask = 0;
+    const Tile T = tile_of(logical);
 
     // ---- loader: DMA instruction j of a stage fills LDS bytes [1024 j, 1024 j + 1024) of the
     // stage; j < NA: activation units, else weight units.  Wavefront w issues j = w, w + NWAVE, ...
@@ -298,14 +216,6 @@ void w4a4_gemm_f6_kernel(const F6Params p)
         const uint32_t dst = spare + ((lds0 + stage * STAGE + 1024 * j - spare) & mk);
         dma16(dst, T.voff[k], (j < NA ? T.a_tile : T.w_tile) + (int64_t)v * IMG4);
     };
-    // the same for group v of the workgroup's next tile (nothing real when there is none: the
-    // current tile's bytes go to the spare kilobyte)
-    auto request_next = [&](int k, int v, int stage) __attribute__((always_inline)) {
-        const int j0 = wave + NWAVE * k, j = j0 < NI ? j0 : wave;
-        const uint32_t mk = (NWAVE * (k + 1) <= NI ? ~0u : 0u - (uint32_t)(j0 < NI)) & more_mask;
-        const uint32_t dst = spare + ((lds0 + stage * STAGE + 1024 * j - spare) & mk);
-        dma16(dst, Tn.voff[k], (j < NA ? Tn.a_tile : Tn.w_tile) + (int64_t)v * IMG4);
-    };
     // Past the last INT4 group the same number of instructions is issued, so that the count a wait
     // refers to never changes: every lane reads the tile's first 16 bytes (one cache line per
     // instruction) into the spare kilobyte.
@@ -321,7 +231,7 @@ void w4a4_gemm_f6_kernel(const F6Params p)
         const int unit = j / 9, jin = j - 9 * unit;               // (uniform)
         const int valid = act ? T.a_valid : T.w_valid;
         const int src_unit = unit < valid ? unit : valid - 1;     // ragged tiles repeat their last unit
-        int chunk = 64 * jin + lane_t;                            // 16-byte chunk of the image; its last instruction is half empty
+        int chunk = 64 * jin + lane;                            // 16-byte chunk of the image; its last instruction is half empty
         chunk = chunk < IMG8 / 16 ? chunk : IMG8 / 16 - 1;
         const uint32_t vo = (uint32_t)src_unit * (uint32_t)p.ustride + 16u * chunk;
         const uint32_t dst = real ? lds0 + stage * STAGE + unit * kU8 + 1024 * jin : spare;
@@ -371,30 +281,14 @@ void w4a4_gemm_f6_kernel(const F6Params p)
         }
     };
 
-    // PERSIST: extra vector-memory instructions that stand between the requests of groups 3 and 4
-    // of a tile: the eight stores of the tile before (the first tile: eight dummy requests)
-    constexpr int XTRA = PERSIST ? 8 : 0;
-    int base = 0;                               // stage of the current tile's group 0
-    bool first = true;
     v12i af0, bf0;
     v2u sa[2], sb[2];
     v16f c_pend, s_pend;
     int  u_pend;
     int cur;
     uint32_t a_cur, b_cur;
-    for (;;) {
-    if constexpr (PERSIST) {
-        int tz = 0;
-        asm volatile("" : "+s"(tz));
-        lane_t = lane + tz;
-        const int nlogical = logical + lstep;
-        const bool more = nlogical < lend;
-        more_mask = more ? ~0u : 0u;
-        Tn = tile_of(more ? nlogical : logical);
-    }
-    // ---- prologue: the first NST groups are requested (a later tile of a persistent workgroup: they
-    // were, by the tile before), the first one has landed
-    if (first) {
+    // ---- prologue: the first NST groups are requested, the first one has landed
+    {
 #pragma unroll
         for (int v = 0; v < NST; ++v) {
             if (v < G4) {
@@ -405,22 +299,19 @@ void w4a4_gemm_f6_kernel(const F6Params p)
                 for (int k = 0; k < LPW; ++k) request_dummy();
             }
         }
-#pragma unroll
-        for (int k = 0; k < XTRA; ++k) request_dummy();
-        first = false;
     }
-    __builtin_amdgcn_s_waitcnt(wait_imm((NST - 1) * LPW + XTRA));
+    __builtin_amdgcn_s_waitcnt(wait_imm((NST - 1) * LPW));
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < 4; ++t) acc[t] = zf;
-    cur = base; a_cur = a_off + base * STAGE; b_cur = b_off + base * STAGE;
+    cur = 0; a_cur = a_off; b_cur = b_off;
     // carried from step to step: the fragments of sub-tile row 0 / column 0 and the scale operands of
     // the coming step, and the integer and scale tiles of the last sub-tile of the step before
     af0 = read_pair(a_cur, 0); bf0 = read_pair(b_cur, 0);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        sa[i] = read_scale(sa_off + base * STAGE, i);
-        sb[i] = read_scale(sb_off + base * STAGE, i);
+        sa[i] = read_scale(sa_off, i);
+        sb[i] = read_scale(sb_off, i);
         sb[i][0] = g == 0 ? sb[i][0] : 0u;     // zero on one side keeps k-slots 4..7 of the fp16 MFMA empty
     }
     c_pend = zf; s_pend = zf;
@@ -439,13 +330,9 @@ void w4a4_gemm_f6_kernel(const F6Params p)
     // three slots: issued in one burst the requests fill the address queue and hold up MFMAs.
     // A step has no branch (one inside it lets the compiler sink MFMAs past the barrier): MODE says
     // at compile time what the step requests: 0 group u + NST, 1 nothing (dummies), 2 / 3 the
-    // activation / weight part of the first INT8 group, 4 / 5 group 0 / 1 of the next tile; LOOSE
-    // how many vector-memory instructions beside the requests of two groups may be outstanding at
-    // the step's wait (the first three steps of a tile of a persistent workgroup: the eight that
-    // stand between groups 3 and 4).
-    auto step = [&](int u, auto mode_c, auto loose_c) __attribute__((always_inline)) {
+    // activation / weight part of the first INT8 group.
+    auto step = [&](int u, auto mode_c) __attribute__((always_inline)) {
         constexpr int MODE = decltype(mode_c)::value;
-        constexpr int LOOSE = decltype(loose_c)::value;
         const int nxt = cur + 1 == NST ? 0 : cur + 1;
         // lane addresses in the next stage (they become the current ones of the next step)
         const uint32_t a_nxt = a_off + nxt * STAGE, b_nxt = b_off + nxt * STAGE;
@@ -461,8 +348,6 @@ void w4a4_gemm_f6_kernel(const F6Params p)
                     if constexpr (MODE == 0)      request_one(kreq, u + NST, cur);
                     else if constexpr (MODE == 2) request_int8(kreq, cur, true);
                     else if constexpr (MODE == 3) request_int8(kreq, cur, false);
-                    else if constexpr (MODE == 4) request_next(kreq, 0, cur);
-                    else if constexpr (MODE == 5) request_next(kreq, 1, cur);
                     else                          request_dummy();
                 }
             }
@@ -488,7 +373,7 @@ void w4a4_gemm_f6_kernel(const F6Params p)
         dequant(u_pend, 1, 1, c_pend, s_pend, 8, 16);
         ATOM_F6_PIN(acc[3]);
         ATOM_F6_SLOT_END();
-        __builtin_amdgcn_s_waitcnt(wait_imm((NST - 2) * LPW + LOOSE));
+        __builtin_amdgcn_s_waitcnt(wait_imm((NST - 2) * LPW));
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);
         // slot 3
@@ -571,20 +456,12 @@ void w4a4_gemm_f6_kernel(const F6Params p)
     {
         using std::integral_constant;
         int u = 0;
-        if constexpr (PERSIST) {                // (G4 >= NST + 3: the launcher sees to it)
-            for (; u < 3; ++u) step(u, integral_constant<int, 0>{}, integral_constant<int, XTRA>{});
-        }
-        for (; u + NST < G4; ++u) step(u, integral_constant<int, 0>{}, integral_constant<int, 0>{});
+        for (; u + NST < G4; ++u) step(u, integral_constant<int, 0>{});
         if (pre8) {
-            stage8a = cur; step(u++, integral_constant<int, 2>{}, integral_constant<int, 0>{});
-            stage8w = cur; step(u++, integral_constant<int, 3>{}, integral_constant<int, 0>{});
+            stage8a = cur; step(u++, integral_constant<int, 2>{});
+            stage8w = cur; step(u++, integral_constant<int, 3>{});
         }
-        if constexpr (PERSIST) {
-            step(u++, integral_constant<int, 4>{}, integral_constant<int, 0>{});
-            step(u++, integral_constant<int, 5>{}, integral_constant<int, 0>{});
-        } else {
-            for (; u < G4; ++u) step(u, integral_constant<int, 1>{}, integral_constant<int, 0>{});
-        }
+        for (; u < G4; ++u) step(u, integral_constant<int, 1>{});
     }
     dequant(u_pend, 1, 1, c_pend, s_pend, 0, 16);
 
@@ -596,7 +473,7 @@ void w4a4_gemm_f6_kernel(const F6Params p)
         for (int k = 0; k < LPW8; ++k) {
             const int j = wave + NWAVE * k;
             const bool isa = j < NA8;
-            int q = 64 * (isa ? j : j - NA8) + lane_t;
+            int q = 64 * (isa ? j : j - NA8) + lane;
             const int nq = (isa ? WM : 2) * (IMG8 / 16);
             q = q < nq ? q : nq - 1;
             int unit = q / (IMG8 / 16);
@@ -607,9 +484,8 @@ void w4a4_gemm_f6_kernel(const F6Params p)
         }
         int ck[4];                                                 // byte offset of chunk 2 kk + g of row r
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) ck[kk] = 128 * (lane_t & 31) + 16 * (((2 * kk + (lane_t >> 5)) ^ (lane_t & 31) ^ (((lane_t & 31) >> 3) & 1)) & 7);
-        // the requests of the K loop's last steps (PERSIST: all but the next tile's two groups)
-        __builtin_amdgcn_s_waitcnt(wait_imm(PERSIST ? 2 * LPW : 0));
+        for (int kk = 0; kk < 4; ++kk) ck[kk] = 128 * (lane & 31) + 16 * (((2 * kk + (lane >> 5)) ^ (lane & 31) ^ (((lane & 31) >> 3) & 1)) & 7);
+        __builtin_amdgcn_s_waitcnt(wait_imm(0));                    // the requests of the K loop's last steps
         for (int g8 = 0; g8 < p.G8; ++g8) {
             const bool here = pre8 && g8 == 0;                     // requested during the K loop, in two stages
             const int a_unit8 = here ? stage8a * STAGE + wm * kU8 : wm * IMG8;
@@ -652,15 +528,12 @@ void w4a4_gemm_f6_kernel(const F6Params p)
                 }
         }
     }
-    __syncthreads();                                               // LDS is free (PERSIST: but for the two stages of the next tile)
+    __syncthreads();                                               // LDS is free
 
     // ---- store: the 64 x 64 fp16 tile of a wavefront goes through LDS so that global memory sees
-    // whole 128-byte rows (a lane holds one column of the MFMA layout).  PERSIST: the staging areas lie
-    // in the two stages the INT8 group was in.
+    // whole 128-byte rows (a lane holds one column of the MFMA layout).
     constexpr int OSTRIDE = Gm::OSTRIDE;
-    static_assert(!PERSIST || (NWAVE / 2) * 64 * OSTRIDE <= STAGE, "four staging areas per stage");
-    unsigned char *ot = PERSIST ? smem + (wave < NWAVE / 2 ? stage8a : stage8w) * STAGE + (wave % (NWAVE / 2)) * (64 * OSTRIDE)
-                                : smem + wave * (64 * OSTRIDE);
+    unsigned char *ot = smem + wave * (64 * OSTRIDE);
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -670,101 +543,66 @@ void w4a4_gemm_f6_kernel(const F6Params p)
             *reinterpret_cast<uint16_t *>(ot + row * OSTRIDE + col * 2) = __half_as_ushort(__float2half_rn(acc[t][e]));
         }
     const bool vec_ok = ((reinterpret_cast<uintptr_t>(p.y) | (uintptr_t)(p.ldy * 2)) & 15) == 0;
-    if constexpr (!PERSIST) {
-        __builtin_amdgcn_s_waitcnt(wait_imm(0));                   // the wavefront reads only what it wrote itself
+    __builtin_amdgcn_s_waitcnt(wait_imm(0));                   // the wavefront reads only what it wrote itself
 #pragma unroll
-        for (int it = 0; it < 8; ++it) {
-            const int row = it * 8 + (lane >> 3), ch = lane & 7;
-            const int64_t m = T.m_w + row, n = T.n_w + ch * 8;
-            if (m >= p.M || n >= p.N) continue;
-            const uint4 v = *reinterpret_cast<const uint4 *>(ot + row * OSTRIDE + ch * 16);
-            uint16_t *dst = p.y + m * p.ldy + n;
-            if (vec_ok && n + 8 <= p.N) {
-                *reinterpret_cast<uint4 *>(dst) = v;
-            } else {
-                const uint16_t *hv = reinterpret_cast<const uint16_t *>(&v);
-#pragma unroll
-                for (int k = 0; k < 8; ++k)
-                    if (n + k < p.N) dst[k] = hv[k];
-            }
-        }
-        break;
-    } else {
-        __builtin_amdgcn_s_waitcnt(wait_imm(63));                  // (LDS only: the wavefront reads what it wrote itself)
-        uint4 ov[8];
-#pragma unroll
-        for (int it = 0; it < 8; ++it) ov[it] = *reinterpret_cast<const uint4 *>(ot + (it * 8 + (lane >> 3)) * OSTRIDE + (lane & 7) * 16);
-        __builtin_amdgcn_s_waitcnt(wait_imm(63));
-        __syncthreads();                                           // every staging area is read: the two stages are free
-        const bool full = vec_ok && T.m_w + 64 <= p.M && T.n_w + 64 <= p.N;    // (the same in all lanes of a wavefront)
-        auto store_rows = [&](auto full_c) __attribute__((always_inline)) {
-#pragma unroll
-            for (int it = 0; it < 8; ++it) {
-                const int row = it * 8 + (lane >> 3), ch = lane & 7;
-                const int64_t m = T.m_w + row, n = T.n_w + ch * 8;
-                uint16_t *dst = p.y + m * p.ldy + n;
-                if constexpr (decltype(full_c)::value) {
-                    *reinterpret_cast<uint4 *>(dst) = ov[it];
-                } else if (m < p.M && n < p.N) {
-                    if (vec_ok && n + 8 <= p.N) {
-                        *reinterpret_cast<uint4 *>(dst) = ov[it];
-                    } else {
-                        const uint16_t *hv = reinterpret_cast<const uint16_t *>(&ov[it]);
-#pragma unroll
-                        for (int k = 0; k < 8; ++k)
-                            if (n + k < p.N) dst[k] = hv[k];
-                    }
-                }
-            }
-        };
-        // The next tile's groups 2 and 3, then exactly eight more vector-memory instructions: the K
-        // loop's first waits count on them.  A wavefront whose part of the tile is cut by M or N
-        // stores first, waits for everything, and issues eight dummy requests in their place.
-        if (!full) {
-            store_rows(std::false_type());
-            __builtin_amdgcn_s_waitcnt(wait_imm(0));
-        }
-#pragma unroll
-        for (int k = 0; k < LPW; ++k) request_next(k, 2, stage8a);
-#pragma unroll
-        for (int k = 0; k < LPW; ++k) request_next(k, 3, stage8w);
-        if (full) {
-            store_rows(std::true_type());
+    for (int it = 0; it < 8; ++it) {
+        const int row = it * 8 + (lane >> 3), ch = lane & 7;
+        const int64_t m = T.m_w + row, n = T.n_w + ch * 8;
+        if (m >= p.M || n >= p.N) continue;
+        const uint4 v = *reinterpret_cast<const uint4 *>(ot + row * OSTRIDE + ch * 16);
+        uint16_t *dst = p.y + m * p.ldy + n;
+        if (vec_ok && n + 8 <= p.N) {
+            *reinterpret_cast<uint4 *>(dst) = v;
         } else {
+            const uint16_t *hv = reinterpret_cast<const uint16_t *>(&v);
 #pragma unroll
-            for (int k = 0; k < XTRA; ++k) request_dummy();
+            for (int k = 0; k < 8; ++k)
+                if (n + k < p.N) dst[k] = hv[k];
         }
-        if (more_mask == 0) {
-            // (the last requests went to the spare kilobyte: they have landed before the workgroup's LDS is given up)
-            __builtin_amdgcn_s_waitcnt(wait_imm(0));
-            break;
-        }
-        logical += lstep;
-        T = Tn;
-        base = (base + G4 - 2) % NST;
-    }
     }
 }
 
-template <int WM, bool DBG, bool PERSIST = false>
+template <int WM, bool DBG>
 hipError_t launch_f6_cfg(const F6Params &p, hipStream_t stream)
 {
     using Gm = F6Geom<WM>;
     static_assert(Gm::LDS <= 160 * 1024, "LDS of a compute unit");
     static_assert(Gm::LPW * (Gm::NST - 1) <= 63, "vmcnt is a 6-bit counter");
     const int64_t TM = (p.a_units + WM - 1) / WM, TN = (p.w_units + 1) / 2;
-    auto kern = &w4a4_gemm_f6_kernel<WM, DBG, PERSIST>;
+    auto kern = &w4a4_gemm_f6_kernel<WM, DBG>;
     static atom_launch::LdsOptIn opt_in;   // one attribute call per kernel variant and device
     hipError_t err = atom_launch::ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(kern), Gm::LDS);
     if (err != hipSuccess) return err;
-    const int64_t grid = PERSIST ? (int64_t)atom_launch::compute_units() : TM * TN;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Gm::NT), Gm::LDS, stream, p);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(TM * TN)), dim3(Gm::NT), Gm::LDS, stream, p);
     return hipGetLastError();
 }
 
 }  // namespace
 
 namespace atom_internal {
+
+// Tile of a launch: 0, 1, 2 = thin 64 x 64, 64 x 128, 128 x 128; 3, 4 = walking 128 x 128, 256 x 128; -1: fewer units
+// than any of them has.  The estimate is the time per INT4 group in units of 10 ns: rounds of tiles over the
+// compute units times what a tile's step takes (measured at K = 4096 to 16384).  Thin tiles win where large ones leave
+// compute units without work; beyond the first round (64 x 64: the third) they pay prologue and store in the open
+// and fetch more bytes per multiply-add than the walking ones.
+static int pick_tile(int64_t au, int64_t wu, int64_t cus)
+{
+    struct { int ua, uw, rounds, first, more; } const tile[5] = {
+        {1, 1, 3, 13, 21}, {1, 2, 1, 21, 37}, {2, 2, 1, 37, 60}, {2, 2, 1, 45, 0}, {4, 2, 1, 79, 79}};
+    int best = -1;
+    int64_t least = INT64_MAX;
+    for (int i = 0; i < 5; ++i) {
+        if (au < tile[i].ua || wu < tile[i].uw) continue;
+        const int64_t tiles = ((au + tile[i].ua - 1) / tile[i].ua) * ((wu + tile[i].uw - 1) / tile[i].uw);
+        const int64_t n = (tiles + cus - 1) / cus;
+        const int64_t cost = n <= tile[i].rounds ? n * tile[i].first
+                           : i == 3 ? n * 45 - n / 2 * 3       // (two workgroups per compute unit: the pair costs a little less)
+                                    : n * tile[i].more;
+        if (cost < least) { least = cost; best = i; }
+    }
+    return best;
+}
 
 size_t f6_packed_bytes(int64_t rows, int K, int O)
 {
@@ -798,20 +636,15 @@ hipError_t launch_f6_gemm(const void *a_pk, int64_t M, const void *w_pk, int64_t
     p.a_units = (int)((M + 63) / 64); p.w_units = (int)((N + 63) / 64);
     p.G4 = (K - O) >> 7; p.G8 = O >> 7;
     p.ustride = (int64_t)p.G4 * IMG4 + (int64_t)p.G8 * IMG8;
-    // 256-row tiles halve the weight traffic per row but want at least four rounds of tiles over the
-    // 256 compute units (measured: M = 4096 shapes of 1024 tiles and more are 5-7 % faster with
-    // them, M = 1024 shapes 4-15 % slower); 128-row tiles run two workgroups per compute unit,
-    // which hides one's prologue, barriers and store behind the other's K loop
-    const int64_t tiles256 = ((M + 255) / 256) * ((N + 127) / 128);
-    // (the dump of the integer sums runs the same tile shape as the plain call)
-    if (M > 128 && tiles256 >= 1024) {
-        if (partials) return launch_f6_cfg<4, true>(p, stream);
-        // one workgroup per CU that walks the tiles (see PERSIST in the file header): M = 4096, K = 8192:
-        // N = 57344 1649 -> 1587 us, N = 10240 322 -> 314 us; K = 28672, N = 8192 787 us either way
-        if (p.G8 == 1 && p.G4 >= F6Geom<4>::NST + 3 && tiles256 >= atom_launch::compute_units())
-            return launch_f6_cfg<4, false, true>(p, stream);
-        return launch_f6_cfg<4, false>(p, stream);
+    if (!partials) {
+        const int pick = pick_tile(p.a_units, p.w_units, atom_launch::compute_units());
+        if (p.G8 == 1 && p.G4 >= 7 && pick >= 0) return pick < 3 ? launch_thin(p, pick, stream) : launch_walk(p, pick - 3, stream);
     }
+    // 256-row tiles halve the weight traffic per row but want at least four rounds of tiles over the
+    // 256 compute units; 128-row tiles run two workgroups per compute unit, which hides one's prologue,
+    // barriers and store behind the other's K loop
+    const int64_t tiles256 = ((M + 255) / 256) * ((N + 127) / 128);
+    if (M > 128 && tiles256 >= 1024) return partials ? launch_f6_cfg<4, true>(p, stream) : launch_f6_cfg<4, false>(p, stream);
     if (M > 64) return partials ? launch_f6_cfg<2, true>(p, stream) : launch_f6_cfg<2, false>(p, stream);
     return partials ? launch_f6_cfg<1, true>(p, stream) : launch_f6_cfg<1, false>(p, stream);
 }
