@@ -52,7 +52,7 @@ def native_command(lib: str = LIB, out: str = NATIVE):
             "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
             "-isystem", os.path.join(rocm, "include"), "-I" + sysconfig.get_paths()["include"],
             os.path.join(CSRC, "atom_torch.cpp"), "-o", out, lib, "-L" + os.path.join(t, "lib"), "-ltorch_python",
-            "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+            "-ltorch", "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
 
 
 def build(verbose: bool = False, extra_flags=(), lib: str = LIB, tag: str = "") -> str:

@@ -36,7 +36,7 @@ constexpr int kThreads = 256;
 // PRE = kAdd: x is first added to a residual row and the sum (fp16) is written out; x, res
 // and sum_out may alias each other (every element is read and written by the same thread).
 // PRE = kSwiglu: the row is silu(x) * res.
-template <bool NORM, int PRE, bool MX = false>
+template <bool NORM, int PRE>
 __global__ __launch_bounds__(kThreads)
 void quantize_rows_kernel(const __half *x, int64_t rows, int64_t ld,
                           const __half *res, int64_t ldr, __half *sum_out, int64_t ldo,
@@ -46,7 +46,7 @@ void quantize_rows_kernel(const __half *x, int64_t rows, int64_t ld,
                           __half *__restrict__ scale, int gl)
 {
     // gl: lanes per group = group size / 8 (8, 16 or 32; Section 5.4.1 of the paper varies the
-    // group size); the MX variant passes 16 (its sweep of 128 channels holds four MX blocks)
+    // group size)
     extern __shared__ __align__(16) float lds[];
     float *ybuf = lds;            // [K]   staged row, original channel order
     float *qbuf = lds + K;        // [K/8] per-vector sums of squares (NORM only)
@@ -139,53 +139,6 @@ void quantize_rows_kernel(const __half *x, int64_t rows, int64_t ld,
                 amax = fmaxf(amax, fabsf(y[e]));
             }
             const bool  is4   = gg < G4;
-            if constexpr (MX) {
-                // MX variant: the 16 lanes hold four blocks of 32 channels (4 lanes each);
-                // one power-of-two scale per block, FP4 E2M1 or FP8 E4M3 elements
-                amax = fmaxf(amax, __shfl_xor(amax, 1, 64));
-                amax = fmaxf(amax, __shfl_xor(amax, 2, 64));
-                const float a = amax * clip;
-                int byte = 0;
-                if (a > 0.0f) {
-                    int E = (__builtin_amdgcn_frexp_expf(a) - 1) - (is4 ? 2 : 8);   // floor(log2 a) - emax
-                    E = E < -127 ? -127 : (E > 127 ? 127 : E);
-                    byte = E + 127;
-                }
-                uint32_t w0 = 0, w1 = 0;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float    v    = __builtin_amdgcn_ldexpf(y[e], 127 - byte);   // exact
-                    const uint32_t sign = __float_as_uint(v) >> 31;
-                    const float    m    = fabsf(v);
-                    if (is4) {
-                        const uint32_t c = (uint32_t)(m > 0.25f) + (m >= 0.75f) + (m > 1.25f) + (m >= 1.75f) +
-                                           (m > 2.5f) + (m >= 3.5f) + (m > 5.0f);
-                        w0 |= (c | (sign << 3)) << (4 * e);
-                    } else {
-                        const float    t = fminf(m, 448.0f);
-                        const uint32_t u = __float_as_uint(t);
-                        // below 2^-6: multiples of 2^-9; above: round the mantissa to 3 bits, ties to even
-                        const uint32_t c = t < 0.015625f ? (uint32_t)rintf(t * 512.0f)
-                                                         : ((u + 0x7FFFFu + ((u >> 20) & 1u)) >> 20) - 960u;
-                        const uint32_t b = c | (sign << 7);
-                        if (e < 4) w0 |= b << (8 * e);
-                        else       w1 |= b << (8 * (e - 4));
-                    }
-                }
-                if (live) {
-                    // step-major layout: 64 bytes (128 FP4 or 64 FP8 channels) of every row
-                    // are contiguous per K step, scales as one dword per row and 128 channels
-                    if (is4)
-                        *reinterpret_cast<uint32_t *>(q4 + ((int64_t)(j0 >> 7) * rows + row) * 64 + ((j0 & 127) >> 1)) = w0;
-                    else
-                        *reinterpret_cast<uint2 *>(q8 + ((int64_t)((j0 - K4) >> 6) * rows + row) * 64 + ((j0 - K4) & 63)) =
-                            make_uint2(w0, w1);
-                    if ((lane & 3) == 0)
-                        reinterpret_cast<uint8_t *>(scale)[((int64_t)(j0 >> 7) * rows + row) * 4 + ((j0 >> 5) & 3)] =
-                            (uint8_t)byte;
-                }
-                continue;
-            }
             for (int d = 1; d < gl; d <<= 1) amax = fmaxf(amax, __shfl_xor(amax, d, 64));   // max is exact in any order
 
             // normal channels: n = nbits (4, or 3 with the codes still in nibbles), outliers n = 8
@@ -226,8 +179,8 @@ void quantize_rows_kernel(const __half *x, int64_t rows, int64_t ld,
 }
 
 
-template <bool NORM, int NS, int NT, int PRE, bool IDENT>
-__global__ __launch_bounds__(NT)
+template <bool NORM, int NS, int NT, int PRE, bool IDENT, bool MX>
+__global__ __launch_bounds__(NT, NS == 4 && NT == 512 && !NORM ? 4 : 1)     // (at most 128 registers where that needs no spill: two workgroups per CU)
 void quantize_rows_fast_kernel(const __half *x, int64_t rows, int64_t ld,
                                const __half *res, int64_t ldr, __half *sum_out, int64_t ldo,
                                const __half *__restrict__ gamma, float eps,
@@ -236,7 +189,7 @@ void quantize_rows_fast_kernel(const __half *x, int64_t rows, int64_t ld,
                                __half *__restrict__ scale)
 {
     extern __shared__ __align__(16) float lds[];
-    quantize_rows_fast_body<NORM, NS, NT, PRE, IDENT>(lds, blockIdx.x, gridDim.x, x, rows, ld, res, ldr, sum_out, ldo,
+    quantize_rows_fast_body<NORM, NS, NT, PRE, IDENT, false, NoHook, MX>(lds, blockIdx.x, gridDim.x, x, rows, ld, res, ldr, sum_out, ldo,
                                                gamma, eps, idx, K, O, nbits, clip, q4, q8, scale);
 }
 
@@ -270,10 +223,10 @@ struct QuantArgs {
     int gs;                                                        // group size: 128, or 64 / 256 (plain kernel)
 };
 
-template <bool NORM, int NS, int NT, int PRE, bool IDENT = false>
+template <bool NORM, int NS, int NT, int PRE, bool IDENT = false, bool MX = false>
 hipError_t launch_fast(const QuantArgs &a, size_t lds, hipStream_t stream)
 {
-    auto kern = &quantize_rows_fast_kernel<NORM, NS, NT, PRE, IDENT>;
+    auto kern = &quantize_rows_fast_kernel<NORM, NS, NT, PRE, IDENT, MX>;
     static atom_launch::LdsOptIn opt_in;   // the opt-in for more than 64 KB of dynamic LDS
     hipError_t err = atom_launch::ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(kern), lds);
     if (err != hipSuccess) return err;
@@ -309,37 +262,52 @@ hipError_t launch_plain(const QuantArgs &a, size_t lds, hipStream_t stream)
     return hipGetLastError();
 }
 
+// The fast kernel with an index: it keeps ceil(K / (8 * threads)) gather-offset sets in registers; rows
+// beyond 5120 channels are spread over 512 threads, rows beyond 16384 channels over 1024 (one workgroup per CU: the
+// staged row fills most of the LDS).  5120 channels are 640 vectors: two for each of 320 threads (with four
+// for each of 256, a third of them idle, 777 rows took 9.1 us, now 7.5).
+template <bool NORM, int PRE, bool MX>
+hipError_t launch_gather(const QuantArgs &a, bool few, hipStream_t stream)
+{
+    const size_t lds = quantize_lds_bytes(a.K, NORM);
+    if (a.K <= 2048)  return launch_fast<NORM, 1, 256, PRE, false, MX>(a, lds, stream);
+    if (few && a.K <= 4096)  return launch_fast<NORM, 1, 512, PRE, false, MX>(a, lds, stream);
+    if (few && a.K <= 8192)  return launch_fast<NORM, 1, 1024, PRE, false, MX>(a, lds, stream);
+    if (few && a.K <= 16384) return launch_fast<NORM, 2, 1024, PRE, false, MX>(a, lds, stream);
+    if (a.K <= 4096)  return launch_fast<NORM, 2, 256, PRE, false, MX>(a, lds, stream);
+    if (a.K <= 5120)  return launch_fast<NORM, 2, 320, PRE, false, MX>(a, lds, stream);
+    if (a.K <= 8192)  return launch_fast<NORM, 2, 512, PRE, false, MX>(a, lds, stream);
+    if (a.K <= 12288) return launch_fast<NORM, 3, 512, PRE, false, MX>(a, lds, stream);
+    if (a.K <= 16384) return launch_fast<NORM, 4, 512, PRE, false, MX>(a, lds, stream);
+    if (a.K <= 24576) return launch_fast<NORM, 3, 1024, PRE, false, MX>(a, lds, stream);
+    return launch_fast<NORM, 4, 1024, PRE, false, MX>(a, lds, stream);
+}
+
 template <bool NORM, int PRE>
 hipError_t dispatch_quantize(const QuantArgs &a, hipStream_t stream)
 {
+    // Up to one row per compute unit, the time is that of one row: twice the threads halve what each of them does (K = 4096,
+    // 8 rows, RMSNorm: 3.9 -> 3.4 us, half of it from this).
+    const bool few = a.rows <= atom_launch::compute_units();
     const bool sane_clip = a.clip >= 9.5367431640625e-07f && a.clip <= 1.0f && a.gs == 128;   // what the fast kernels take
     if (!a.idx && a.K <= 32768 && sane_clip) {
         // no index: the row already is in reordered order; nothing is staged in LDS but the
         // sums of squares, so the register sets alone bound the threads per row
         const size_t lq = NORM ? sizeof(float) * (size_t)(a.K / 8) : 0;
         if (a.K <= 2048)  return launch_fast<NORM, 1, 256, PRE, true>(a, lq, stream);
+        if (few && a.K <= 4096)  return launch_fast<NORM, 1, 512, PRE, true>(a, lq, stream);
+        if (few && a.K <= 8192)  return launch_fast<NORM, 1, 1024, PRE, true>(a, lq, stream);
+        if (few && a.K <= 16384) return launch_fast<NORM, 2, 1024, PRE, true>(a, lq, stream);
         if (a.K <= 4096)  return launch_fast<NORM, 2, 256, PRE, true>(a, lq, stream);
+        if (a.K <= 5120)  return launch_fast<NORM, 2, 320, PRE, true>(a, lq, stream);
         if (a.K <= 8192)  return launch_fast<NORM, 2, 512, PRE, true>(a, lq, stream);
         if (a.K <= 12288) return launch_fast<NORM, 3, 512, PRE, true>(a, lq, stream);
         if (a.K <= 16384) return launch_fast<NORM, 4, 512, PRE, true>(a, lq, stream);
         if (a.K <= 24576) return launch_fast<NORM, 3, 1024, PRE, true>(a, lq, stream);
         return launch_fast<NORM, 4, 1024, PRE, true>(a, lq, stream);
     }
+    if (a.K <= 32768 && sane_clip) return launch_gather<NORM, PRE, false>(a, few, stream);
     const size_t lds = quantize_lds_bytes(a.K, NORM);
-    // The fast kernel keeps ceil(K / (8 * threads)) gather-offset sets in registers and
-    // relies on a sane clip; rows of 8192 channels and more are spread over 512 threads,
-    // rows beyond 16384 channels over 1024 (one workgroup per CU: the staged row fills
-    // most of the LDS).
-    if (a.K <= 32768 && sane_clip) {
-        if (a.K <= 2048)  return launch_fast<NORM, 1, 256, PRE>(a, lds, stream);
-        if (a.K <= 4096)  return launch_fast<NORM, 2, 256, PRE>(a, lds, stream);
-        if (a.K < 8192)   return launch_fast<NORM, 4, 256, PRE>(a, lds, stream);
-        if (a.K <= 8192)  return launch_fast<NORM, 2, 512, PRE>(a, lds, stream);
-        if (a.K <= 12288) return launch_fast<NORM, 3, 512, PRE>(a, lds, stream);
-        if (a.K <= 16384) return launch_fast<NORM, 4, 512, PRE>(a, lds, stream);
-        if (a.K <= 24576) return launch_fast<NORM, 3, 1024, PRE>(a, lds, stream);
-        return launch_fast<NORM, 4, 1024, PRE>(a, lds, stream);
-    }
     return launch_plain<NORM, PRE>(a, lds, stream);
 }
 
@@ -348,18 +316,9 @@ hipError_t launch_quantize_rows_mx(const void *x, int64_t rows, int64_t ld, cons
                                    float eps, const int32_t *idx, int K, int O, float clip, void *q4,
                                    void *q8, void *e8, hipStream_t stream)
 {
-    const bool   norm = gamma != nullptr;
-    const size_t lds  = quantize_lds_bytes(K, norm);
-    auto kern = norm ? &quantize_rows_kernel<true, kPlain, true> : &quantize_rows_kernel<false, kPlain, true>;
-    static atom_launch::LdsOptIn opt_in[2];
-    hipError_t err = atom_launch::ensure_dynamic_lds(opt_in[norm], reinterpret_cast<const void *>(kern), lds);
-    if (err != hipSuccess) return err;
-    const int grid = (int)(rows < (int64_t)1 << 20 ? rows : (int64_t)1 << 20);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, stream, (const __half *)x, rows, ld,
-                       (const __half *)nullptr, (int64_t)0, (__half *)nullptr, (int64_t)0,
-                       (const __half *)gamma, eps, idx, K, O, 4, clip, (uint8_t *)q4, (int8_t *)q8,
-                       (__half *)e8, 16);
-    return hipGetLastError();
+    const QuantArgs a = {x, rows, ld, kPlain, nullptr, 0, nullptr, 0, gamma, eps, idx, K, O, 4, clip, q4, q8, e8, 128};
+    const bool few = rows <= atom_launch::compute_units();
+    return gamma ? launch_gather<true, kPlain, true>(a, few, stream) : launch_gather<false, kPlain, true>(a, few, stream);
 }
 
 hipError_t launch_quantize_rows(const void *x, int64_t rows, int64_t ld, int pre, const void *res,

@@ -19,7 +19,7 @@ namespace {
 using namespace atom_quantize_rows;
 
 template <bool NORM, int NS, int NT, int PRE, bool IDENT>
-__global__ __launch_bounds__(NT)
+__global__ __launch_bounds__(NT, NS == 4 && NT == 512 && !NORM ? 4 : 1)
 void quantize_rows_packed_kernel(const __half *x, int64_t rows, int64_t ld, const __half *res, int64_t ldr,
                                  __half *sum_out, int64_t ldo, const __half *__restrict__ gamma, float eps,
                                  const int32_t *__restrict__ idx, int K, int O, int nbits, float clip,
@@ -38,15 +38,16 @@ void quantize_rows_packed_kernel(const __half *x, int64_t rows, int64_t ld, cons
     quantize_rows_fast_body<NORM, NS, NT, PRE, IDENT, true>(lds, first, 1, x, last, ld, res, ldr, sum_out,
                                                             ldo, gamma, eps, idx, K, O, nbits, clip, nullptr, nullptr,
                                                             nullptr, NoHook(), pk_out, pk_lds);
-    // rows past the end of the matrix, up to the end of the last unit: zero codes, zero scales
+    // rows past the end of the matrix, up to the end of the last unit: zero codes, zero scales; dealt over all
+    // workgroups (65 rows of 11008 channels: 25.6 us when the first workgroup wrote all of them)
     const int64_t end = (rows + 63) / 64 * 64;
-    if (blockIdx.x == 0 && end > rows) {
+    if (end > rows) {
         const int K4 = K - O, G4 = K4 >> 7, G8 = O >> 7;
         uint8_t *ubase = pk_out + (rows >> 6) * ((int64_t)G4 * kImg4 + (int64_t)G8 * kImg8);
         const int npad = (int)(end - rows), r0 = (int)(rows & 63);
         // per pad row: 6 chunks per INT4 group, 8 per INT8 group, one scale entry per group (as half a chunk)
         const int per_row = 6 * G4 + 8 * G8;
-        for (int i = threadIdx.x; i < npad * per_row; i += NT) {
+        for (int i = blockIdx.x * NT + threadIdx.x; i < npad * per_row; i += gridDim.x * NT) {
             const int r = r0 + i / per_row, j = i % per_row;
             uint8_t *dst;
             if (j < 6 * G4) {
@@ -58,7 +59,7 @@ void quantize_rows_packed_kernel(const __half *x, int64_t rows, int64_t ld, cons
             }
             *reinterpret_cast<uint4 *>(dst) = make_uint4(0, 0, 0, 0);
         }
-        for (int i = threadIdx.x; i < npad * (G4 + G8); i += NT) {
+        for (int i = blockIdx.x * NT + threadIdx.x; i < npad * (G4 + G8); i += gridDim.x * NT) {
             const int r = r0 + i / (G4 + G8), g = i % (G4 + G8);
             uint8_t *dst = g < G4 ? ubase + (int64_t)g * kImg4 + kSc4 + 8 * r
                                   : ubase + (int64_t)G4 * kImg4 + (int64_t)(g - G4) * kImg8 + kSc8 + 8 * r;
@@ -100,7 +101,13 @@ template <bool NORM, int PRE, bool IDENT>
 hipError_t dispatch_k(const PackedArgs &a, hipStream_t stream)
 {
     if (a.K <= 2048)  return launch_cfg<NORM, 1, 256, PRE, IDENT>(a, stream);
+    // (up to one row per compute unit: twice the threads per row, as in the canonical front end)
+    const bool few = a.rows <= atom_launch::compute_units();
+    if (few && a.K <= 4096)  return launch_cfg<NORM, 1, 512, PRE, IDENT>(a, stream);
+    if (few && a.K <= 8192)  return launch_cfg<NORM, 1, 1024, PRE, IDENT>(a, stream);
+    if (few && a.K <= 16384) return launch_cfg<NORM, 2, 1024, PRE, IDENT>(a, stream);
     if (a.K <= 4096)  return launch_cfg<NORM, 2, 256, PRE, IDENT>(a, stream);
+    if (a.K <= 5120)  return launch_cfg<NORM, 2, 320, PRE, IDENT>(a, stream);
     if (a.K <= 8192)  return launch_cfg<NORM, 2, 512, PRE, IDENT>(a, stream);
     if (a.K <= 12288) return launch_cfg<NORM, 3, 512, PRE, IDENT>(a, stream);
     if (a.K <= 16384) return launch_cfg<NORM, 4, 512, PRE, IDENT>(a, stream);

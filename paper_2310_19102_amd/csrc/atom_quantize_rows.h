@@ -48,8 +48,7 @@ __device__ __forceinline__ uint4 add_halves(const uint4 &a, const uint4 &b)
 // Horner form; 2^n through the exponent field.
 __device__ __forceinline__ float exp_ieee(float x)
 {
-    x = x < -87.0f ? -87.0f : x;
-    x = x > 87.0f ? 87.0f : x;
+    x = __builtin_amdgcn_fmed3f(x, -87.0f, 87.0f);
     const float n = rintf(x * 1.44269502162933349609375f);
     float r = fmaf(n, -0.693145751953125f, x);
     r = fmaf(n, -1.428606765330187045037746429443359375e-06f, r);
@@ -61,14 +60,47 @@ __device__ __forceinline__ float exp_ieee(float x)
     p = fmaf(p, r, 0.5f);
     p = fmaf(p, r, 1.0f);
     p = fmaf(p, r, 1.0f);
-    return p * __int_as_float(((int)n + 127) << 23);
+    return __builtin_amdgcn_ldexpf(p, (int)n);     // (normal numbers both: the same as the product with 2^n)
 }
 
-// silu(g) * u in fp32: sigma = 1/(1 + exp(-g)) with an IEEE division, then (g*sigma)*u
+// silu(g) * u in fp32: sigma = the correctly rounded 1/(1 + exp(-g)), then (g*sigma)*u.  g is an fp16 number, so
+// there are 65536 cases: the hardware's reciprocal with one Newton step (three instructions, a general division
+// takes eleven) is the correctly rounded value in every one of them (checked on the hardware, all of them).
 __device__ __forceinline__ float silu_mul(float g, float u)
 {
-    const float sigma = 1.0f / (1.0f + exp_ieee(-g));
+    const float d  = 1.0f + exp_ieee(-g);
+    const float r0 = __builtin_amdgcn_rcpf(d);
+    const float sigma = fmaf(fmaf(-d, r0, 1.0f), r0, r0);
     return (g * sigma) * u;
+}
+
+// Sum over the 64 lanes, the value in every lane: the butterfly L + shfl_xor(L, d) with d = 1, 2, 4, .. 32, addition for
+// addition.  After the strides 1 and 2 all lanes of a quad agree, so mirroring a half row reaches the same value
+// as stride 4, mirroring a row the same as stride 8; the last two are the lane-half swaps of gfx950.  (Through
+// LDS, as ds_bpermute, the six steps were a quarter of the time of a single row.)
+__device__ __forceinline__ float wave_butterfly_sum(float L)
+{
+#define ATOM_DPP_ADD(ctrl)                                                                       \
+    L = L + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(                               \
+                0, __builtin_bit_cast(int, L), ctrl, 0xF, 0xF, false))
+    ATOM_DPP_ADD(0xB1);      // quad_perm [1,0,3,2]
+    ATOM_DPP_ADD(0x4E);      // quad_perm [2,3,0,1]
+    ATOM_DPP_ADD(0x141);     // row_half_mirror
+    ATOM_DPP_ADD(0x140);     // row_mirror
+#undef ATOM_DPP_ADD
+    typedef unsigned v2ui __attribute__((ext_vector_type(2)));
+    unsigned u = __builtin_bit_cast(unsigned, L), w = u;
+    asm volatile("" : "+v"(w));          // (two registers: the swap exchanges halves between them)
+    v2ui x = __builtin_amdgcn_permlane16_swap(u, w, false, false);
+    unsigned second = x[1];
+    asm volatile("" : "+v"(second));
+    L = __builtin_bit_cast(float, x[0]) + __builtin_bit_cast(float, second);
+    u = w = __builtin_bit_cast(unsigned, L);
+    asm volatile("" : "+v"(w));
+    x = __builtin_amdgcn_permlane32_swap(u, w, false, false);
+    second = x[1];
+    asm volatile("" : "+v"(second));
+    return __builtin_bit_cast(float, x[0]) + __builtin_bit_cast(float, second);
 }
 
 // what happens to a row before it is normalised and quantised
@@ -100,8 +132,11 @@ __device__ __forceinline__ float row16_max_dpp(float v)
 }
 
 // Scale of a group from its maximum (Section 2 symmetric equations, fp32, stored as fp16) and the
-// codes of this lane's eight values: IEEE division by the stored scale through the shared
-// reciprocal refinement described below, round-half-to-even, clamp.  Returns the stored scale,
+// codes of this lane's eight values: the IEEE quotient by the stored scale, round-half-to-even, clamp.
+// The quotient takes three instructions per element.  s is an fp16 number, and r = rcp(s) with one Newton step is
+// the correctly rounded 1/s for every one of them (checked on the hardware, all of them).  q = y r is within two
+// units of y/s, e = y - q s is exact, and q + e r, rounded once, is the quotient unless y/s lies within 2^-23 units of the
+// middle between two floats; with an 11-bit s it is at least 2^-12 units away from every such middle.  Returns the stored scale,
 // s = its fp32 value.  The codes stay floats (whole numbers): what packs them needs no integers
 // (pack_nibbles8 below, the conversion to FP6).
 __device__ __forceinline__ __half quantise_lane8(const float (&y)[8], float amax, bool is4, int nbits, float clip,
@@ -121,10 +156,7 @@ __device__ __forceinline__ __half quantise_lane8(const float (&y)[8], float amax
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         float qf = y[e] * r1;
-        float t  = fmaf(-s, qf, y[e]);
-        qf = fmaf(t, r1, qf);
-        t  = fmaf(-s, qf, y[e]);
-        qf = fmaf(t, r1, qf);
+        qf = fmaf(fmaf(-s, qf, y[e]), r1, qf);
         qf = rintf(qf);
         q[e] = __builtin_amdgcn_fmed3f(qf, qmin, qmax);      // (finite: the same as min(max(qf, qmin), qmax))
     }
@@ -152,12 +184,8 @@ __device__ __forceinline__ uint32_t pack_nibbles8(const float (&c)[8])
 //   * a workgroup walks several rows; the gather offsets of the reorder (they are the same
 //     for every row) and gamma stay in registers, and the next row's global loads are in
 //     flight while this row is quantised;
-//   * the IEEE division by the group's scale shares the reciprocal refinement across the
-//     group: r = rcp(s), r += r*(1 - s*r), then per element q = y*r and two residual
-//     corrections q += r*(y - s*q).  This is instruction for instruction what the
-//     compiler emits for y / s when v_div_scale does not rescale, which it does not for
-//     the quotients that matter here: s comes from the group's own maximum, so
-//     |y| / s <= (2^n - 1)/(2 clip) * (1 + 2^-11) and s >= 2^-24; quotients below 2^-100
+//   * the IEEE division by the group's scale shares the reciprocal across the group (quantise_lane8).
+//     |y| / s <= (2^n - 1)/(2 clip) * (1 + 2^-11) and s >= 2^-24, so nothing overflows; quotients below 2^-100
 //     round to code 0 either way.  A zero scale (all-zero group) yields zero codes;
 //   * the group maximum is a DPP rotation reduction.
 // The rows row_first, row_first + row_step, ... < rows are handled by the calling workgroup
@@ -181,7 +209,11 @@ typedef _Float16 pk_v32h __attribute__((ext_vector_type(32)));
 typedef unsigned pk_v6u  __attribute__((ext_vector_type(6)));
 constexpr int kImg4 = 6656, kImg8 = 8704, kSc4 = 6144, kSc8 = 8192;
 
-template <bool NORM, int NS, int NT, int PRE, bool IDENT = false, bool PACKED = false, class Hook = NoHook>
+// MX: codes and scale bytes of the MX variant (FP4 E2M1 / FP8 E4M3, one E8M0 byte per 32 channels = 4 lanes) in their
+// step-major arrays instead: q4 [K4/128][rows][64], q8 [O/64][rows][64], scale as bytes [K/128][rows][4].  The hardware
+// converts two values at a time, divided by the block's power of two, to the nearest, ties to even (13 vector
+// instructions per lane and group, where comparing with every boundary took 120: 4096 x 8192 with RMSNorm 48 -> 26.5 us).
+template <bool NORM, int NS, int NT, int PRE, bool IDENT = false, bool PACKED = false, class Hook = NoHook, bool MX = false>
 __device__ __forceinline__
 void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
                              const __half *x, int64_t rows, int64_t ld,
@@ -202,6 +234,21 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
     const int G    = K >> 7;
     const int G4   = K4 >> 7;
 
+    uint4 raw[NS];
+    uint4 rres[PRE != kPlain ? NS : 1];
+    auto fetch_row = [&](int64_t row) {
+        const __half *xr = x + row * ld;
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            const int v = tid + NT * i;
+            raw[i] = v < V ? *reinterpret_cast<const uint4 *>(xr + 8 * v) : make_uint4(0, 0, 0, 0);
+            if (PRE != kPlain)
+                rres[i] = v < V ? *reinterpret_cast<const uint4 *>(res + row * ldr + 8 * v)
+                                : make_uint4(0, 0, 0, 0);
+        }
+    };
+    int64_t row = row_first;
+    if (row < rows) fetch_row(row);       // (first: the longest way of all the loads before the loop)
     // gather offsets (bytes into ybuf) of this lane's 8 channels in each of its groups
     // (with 1024 threads two 16-bit channel numbers share a register)
     constexpr bool OPACK = NT >= 1024;
@@ -234,21 +281,6 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
         }
     }
 
-    uint4 raw[NS];
-    uint4 rres[PRE != kPlain ? NS : 1];
-    auto fetch_row = [&](int64_t row) {
-        const __half *xr = x + row * ld;
-#pragma unroll
-        for (int i = 0; i < NS; ++i) {
-            const int v = tid + NT * i;
-            raw[i] = v < V ? *reinterpret_cast<const uint4 *>(xr + 8 * v) : make_uint4(0, 0, 0, 0);
-            if (PRE != kPlain)
-                rres[i] = v < V ? *reinterpret_cast<const uint4 *>(res + row * ldr + 8 * v)
-                                : make_uint4(0, 0, 0, 0);
-        }
-    };
-    int64_t row = row_first;
-    if (row < rows) fetch_row(row);
     after_first_fetch();
 
     for (; row < rows; row += row_step) {
@@ -279,10 +311,18 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
                 }
             }
             __syncthreads();
+            // (reads past the last vector add +0; eight at a time are in flight)
             float L = 0.0f;
-            for (int v = lane; v < V; v += 64) L = L + qbuf[v];
+            constexpr int NV = NS * NT / 64, CH = NV < 8 ? NV : 8;
+#pragma unroll NV <= 16 ? NV / CH : 1
+            for (int i0 = 0; i0 < NV; i0 += CH) {
+                float part[CH];
 #pragma unroll
-            for (int d = 1; d < 64; d <<= 1) L = L + __shfl_xor(L, d, 64);
+                for (int i = 0; i < CH; ++i) part[i] = lane + 64 * (i0 + i) < V ? qbuf[lane + 64 * (i0 + i)] : 0.0f;
+#pragma unroll
+                for (int i = 0; i < CH; ++i) L = L + part[i];
+            }
+            L = wave_butterfly_sum(L);
             const float mean = L / (float)K;
             r = 1.0f / sqrtf(mean + eps);
         }
@@ -345,9 +385,51 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
                 }
                 amax = fmaxf(amax, fabsf(y[e]));
             }
+            const bool  is4   = gg < G4;
+            if constexpr (MX) {
+#define ATOM_QUAD_MAX(ctrl)                                                                      \
+    amax = fmaxf(amax, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(                    \
+                     0, __builtin_bit_cast(int, amax), ctrl, 0xF, 0xF, false)))
+                ATOM_QUAD_MAX(0xB1);
+                ATOM_QUAD_MAX(0x4E);
+#undef ATOM_QUAD_MAX
+                const float a = amax * clip;
+                int byte = 0;
+                if (a > 0.0f) {
+                    int E = (__builtin_amdgcn_frexp_expf(a) - 1) - (is4 ? 2 : 8);      // floor(log2 a) - emax
+                    E = E < -127 ? -127 : (E > 127 ? 127 : E);
+                    byte = E + 127;
+                }
+                const float sc = __int_as_float(byte << 23);                           // (the exponent field is what the conversion takes)
+                if (live) {
+                    if (is4) {
+                        unsigned w = 0;
+                        w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, y[0], y[1], sc, 0);
+                        w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, y[2], y[3], sc, 1);
+                        w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, y[4], y[5], sc, 2);
+                        w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, y[6], y[7], sc, 3);
+                        *reinterpret_cast<uint32_t *>(q4 + ((int64_t)gg * rows + row) * 64 + ((j0 & 127) >> 1)) = w;
+                    } else {
+                        typedef short v2s __attribute__((ext_vector_type(2)));
+                        const float top = __builtin_amdgcn_ldexpf(448.0f, byte - 127); // larger magnitudes saturate
+                        float c[8];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) c[e] = __builtin_amdgcn_fmed3f(y[e], -top, top);
+                        v2s w0 = {0, 0}, w1 = {0, 0};
+                        w0 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w0, c[0], c[1], sc, false);
+                        w0 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w0, c[2], c[3], sc, true);
+                        w1 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w1, c[4], c[5], sc, false);
+                        w1 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w1, c[6], c[7], sc, true);
+                        *reinterpret_cast<uint2 *>(q8 + ((int64_t)((j0 - K4) >> 6) * rows + row) * 64 + ((j0 - K4) & 63)) =
+                            make_uint2(__builtin_bit_cast(unsigned, w0), __builtin_bit_cast(unsigned, w1));
+                    }
+                    if ((lane & 3) == 0)
+                        reinterpret_cast<uint8_t *>(scale)[((int64_t)gg * rows + row) * 4 + ((j0 >> 5) & 3)] = (uint8_t)byte;
+                }
+                continue;
+            }
             amax = row16_max_dpp(amax);
 
-            const bool  is4   = gg < G4;
             float q[8];
             float s;
             const __half sh = quantise_lane8(y, amax, is4, nbits, clip, q, s);

@@ -10,7 +10,7 @@
 
 #include <Python.h>
 
-#include <ATen/ops/empty.h>
+#include <ATen/hip/EmptyTensor.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -99,10 +99,14 @@ int64_t groups(int64_t K, int64_t gs) { return gs > 0 ? K / gs : 0; }
 
 void *stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
-Tensor make(std::initializer_list<int64_t> shape, Kind k, const Tensor &like)
+// A new tensor on the device of `like`: what at::empty ends at after its dispatch (0.6 us each, and a front-end call
+// makes three).
+Tensor make(at::IntArrayRef shape, Kind k, const Tensor &like)
 {
-    return at::empty(at::IntArrayRef(shape), at::TensorOptions().dtype(k.type).device(like.device()));
+    return Tensor(at::detail::empty_cuda(shape, k.type, like.device(), std::nullopt));
 }
+
+Tensor make(std::initializer_list<int64_t> shape, Kind k, const Tensor &like) { return make(at::IntArrayRef(shape), k, like); }
 
 // Row stride of a matrix with `cols` columns (a single row may report any stride).
 int64_t ld(const Tensor &t, int64_t rows, int64_t cols)
@@ -519,11 +523,10 @@ PyObject *kv_quantize(Args a)
         auto lead = x.sizes().slice(0, (size_t)x.dim() - 1);
         c10::SmallVector<int64_t, 8> cshape(lead.begin(), lead.end());
         cshape.push_back(D / 2);
-        const auto opt = at::TensorOptions().device(x.device());
         Out c, sc, z;
-        c.fresh(at::empty(cshape, opt.dtype(at::kByte)));
-        sc.fresh(at::empty(lead, opt.dtype(at::kHalf)));
-        z.fresh(at::empty(lead, opt.dtype(at::kShort)));
+        c.fresh(make(at::IntArrayRef(cshape), kByte, x));
+        sc.fresh(make(lead, kHalf, x));
+        z.fresh(make(lead, kShort, x));
         check(call([&](void *s) {
             return atom_kv_quantize(data(x), R, D, (int32_t)D, clip, nullptr, 0, 0, c.data(), sc.data(), z.data(), s);
         }), "atom_kv_quantize");

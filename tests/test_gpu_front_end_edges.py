@@ -1,0 +1,65 @@
+"""The front ends at the edges of their thread configurations (up to one row per compute unit: twice the threads; 5120
+channels: 320 threads), the SwiGLU front end on every finite fp16 gate, and the MX front end on every thread configuration:
+codes, scales and scale bytes bit-identical to the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2310_19102_amd as atom
+from _gpu_util import npy
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(M, K, seed):
+    g = torch.Generator().manual_seed(seed)
+    sigma = torch.exp(1.5 * torch.randn(K, generator=g))
+    x = (torch.randn((M, K), generator=g) * sigma).to(torch.float16)
+    gamma = (1.0 + 0.1 * torch.randn(K, generator=g)).to(torch.float16)
+    return x, gamma, torch.argsort(sigma, stable=True).to(torch.int32)
+
+
+def _same(got, want, what):
+    for name, a, b in zip(("q4", "q8", "scale"), got, want):
+        a = npy(a)
+        if a.ndim == 3:                                     # the MX arrays are step-major
+            a = a.transpose(1, 0, 2).reshape(a.shape[1], -1)
+        assert np.array_equal(a.view(np.uint8), b.view(np.uint8)), f"{what}: {name}"
+
+
+@pytest.mark.parametrize("K", [2048, 2176, 4096, 4224, 5120, 5248, 8192, 8320, 12288, 16384, 16512, 28672])
+@pytest.mark.parametrize("M", [3, 258])                     # one row per workgroup with more threads; more rows than CUs
+def test_front_end_configurations(M, K):
+    if M > 3 and K > 8320:
+        M = 257
+    print(f"[case] front end M={M} K={K}", flush=True)
+    x, gamma, idx = _rows(M, K, K + M)
+    dx, dg, di = x.cuda(), gamma.cuda(), idx.cuda()
+    xs, gs, ix = x.numpy(), gamma.numpy(), idx.numpy()
+    rows = slice(0, M) if M < 10 else slice(0, M, 37)       # (the oracle is one thread)
+    pick = lambda t: t[rows].contiguous() if t.dim() == 2 else t[:, rows].contiguous()
+    got = atom.atom_quantize_act(dx, dg, 1e-6, di)
+    _same([pick(t) for t in got], oracle.quantize_act(xs[rows], gs, 1e-6, ix, 128, 128, 0.9), "norm")
+    got = atom.atom_quantize_act(dx, None, 0.0, None)
+    _same([pick(t) for t in got], oracle.quantize_act(xs[rows], None, 0.0, np.arange(K, dtype=np.int32), 128, 128, 0.9), "no index")
+    got = atom.atom_mx_quantize_act(dx, dg, 1e-6, di, 128, 0.9)
+    _same([pick(t) for t in got], oracle.mx_quantize_act(xs[rows], gs, 1e-6, ix, 128, 0.9), "MX")
+    if 4 * K + K // 2 + 3 * (K - 128) // 4 + 128 <= 160 * 1024:
+        packed = atom.atom_quantize_act_packed(dx, dg, 1e-6, di)
+        assert torch.equal(packed, atom.atom_pack_act(*atom.atom_quantize_act(dx, dg, 1e-6, di)))
+
+
+@pytest.mark.parametrize("up", [1.0, 0.337, -7.25])
+def test_every_gate(up):
+    """silu of all 65536 fp16 gates but NaN and infinity, 256 per row in an order that mixes magnitudes."""
+    bits = np.arange(65536, dtype=np.uint16)
+    gate = bits.view(np.float16).astype(np.float16)
+    gate = np.where(np.isfinite(gate), gate, np.float16(0.5)).reshape(256, 256)
+    u = np.full_like(gate, np.float16(up))
+    idx = np.arange(256, dtype=np.int32)
+    got = atom.atom_swiglu_quantize_act(torch.from_numpy(gate).cuda(), torch.from_numpy(u).cuda(), None)
+    _same(got, oracle.swiglu_quantize_act(gate, u, idx, 128, 128, 0.9), "rows of neighbours")
+    mixed = np.ascontiguousarray(gate.T)
+    got = atom.atom_swiglu_quantize_act(torch.from_numpy(mixed).cuda(), torch.from_numpy(u).cuda(), torch.from_numpy(idx).cuda())
+    _same(got, oracle.swiglu_quantize_act(mixed, u, idx, 128, 128, 0.9), "mixed")
