@@ -17,7 +17,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libatom.so")
 NATIVE = os.path.join(HERE, "_native.so")
-SOURCES = ["atom_api.hip", "atom_quantize.hip", "atom_quantize_packed.hip", "atom_gemm.hip", "atom_gemm_big.hip", "atom_gemm_decode.hip", "atom_gemm_gs.hip", "atom_decode_fused.hip", "atom_gemm_f6.hip", "atom_gemm_f6_walk.hip", "atom_gemm_f6_thin.hip", "atom_kv.hip", "atom_mx.hip", "atom_calib.hip", "atom_probe.hip"]
+SOURCES = ["atom_api.hip", "atom_quantize.hip", "atom_quantize_packed.hip", "atom_gemm.hip", "atom_gemm_big.hip", "atom_gemm_decode.hip", "atom_gemm_gs.hip", "atom_decode_fused.hip", "atom_gemm_f6.hip", "atom_gemm_f6_walk.hip", "atom_gemm_f6_thin.hip", "atom_kv.hip", "atom_kv_quantize.hip", "atom_mx.hip", "atom_calib.hip", "atom_probe.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -36,7 +36,8 @@ FLAGS = [
 # attention kernel rescales its accumulators with the vector ALU (online softmax), and with them
 # in AccVGPRs every step copied all 32 of them out for a rescaling that rarely runs
 SOURCE_FLAGS = {"atom_mx.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=0"],
-                "atom_kv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+                "atom_kv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+                "atom_kv_quantize.hip": ["-fno-honor-nans"]}
 
 
 def native_command(lib: str = LIB, out: str = NATIVE):

@@ -1,7 +1,5 @@
-// INT4 KV cache for gfx950: asymmetric per-head quantisation (Section 2 of the paper,
-// asymmetric equations; Section 4.4: granularity of one attention head) and decode-stage
-// attention that reads the cache in 4 bits and dequantises inside the operator
-// (Sections 4.4 and 4.5).
+// Decode-stage attention over the INT4 KV cache for gfx950: reads the cache in 4 bits and dequantises
+// inside the operator (Sections 4.4 and 4.5 of the paper); atom_kv_quantize.hip fills it.
 //
 // Cache layout (one K cache and one V cache, same shape):
 //   codes [B, Hkv, Tmax, D/2] bytes, two codes per byte, even d in the low nibble
@@ -20,138 +18,6 @@
 namespace {
 
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-
-// ---------------------------------------------------------------- quantise rows
-
-// max / min over the LPR (8 or 16) lanes that share a row; LPR lanes are consecutive and
-// aligned, so rotations inside the 16-lane DPP row stay inside the row for LPR = 16, and an
-// xor butterfly is used for LPR = 8
-template <int LPR>
-__device__ __forceinline__ void row_minmax(float &mx, float &mn)
-{
-    if constexpr (LPR == 16) {            // DPP rotations of the 16-lane row: vector-ALU speed, no LDS crossbar
-#define ATOM_ROW_ROR(n)                                                                              \
-        mx = fmaxf(mx, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(                        \
-                           0, __builtin_bit_cast(int, mx), 0x120 | (n), 0xF, 0xF, false)));          \
-        mn = fminf(mn, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(                        \
-                           0, __builtin_bit_cast(int, mn), 0x120 | (n), 0xF, 0xF, false)))
-        ATOM_ROW_ROR(8);
-        ATOM_ROW_ROR(4);
-        ATOM_ROW_ROR(2);
-        ATOM_ROW_ROR(1);
-#undef ATOM_ROW_ROR
-    } else {
-#pragma unroll
-        for (int d = 1; d < LPR; d <<= 1) {
-            mx = fmaxf(mx, __shfl_xor(mx, d, 64));
-            mn = fminf(mn, __shfl_xor(mn, d, 64));
-        }
-    }
-}
-
-// One row of D = 8 * LPR values per LPR lanes, 64 / LPR rows per wavefront.
-//   s = fp16(((max - min) * clip) / 15), z = clamp(rne(-min / s)), code = clamp(rne(x/s) + z, 0, 15)
-// with correctly rounded fp32 quotients by the stored scale; a zero scale gives zero codes and z = 0.
-// Output row index: r (pos == nullptr), or r * Tmax + pos[r / rows_per_seq] (append one
-// token per sequence: row r = (sequence, head)); rows whose position is outside
-// [0, Tmax) write nothing.
-// kRows: rows per lane group, i.e. loads in flight per lane: 4 for bulk quantisation, 1 for the
-// append of a few hundred rows (there four rows per lane group only quarter the grid)
-template <int LPR, int kRows>
-__global__ __launch_bounds__(256)
-void kv_quantize_kernel(const __half *__restrict__ x0, int64_t R, int64_t ldx, float clip,
-                        const int32_t *__restrict__ pos, int32_t rows_per_seq, int64_t Tmax,
-                        uint8_t *__restrict__ q0, __half *__restrict__ scale0,
-                        int16_t *__restrict__ zero0, const __half *__restrict__ x1,
-                        uint8_t *__restrict__ q1, __half *__restrict__ scale1,
-                        int16_t *__restrict__ zero1)
-{
-    constexpr int D = 8 * LPR;
-    // grid.y = 2: the same rows of a second tensor into a second cache (K and V of one append)
-    const bool second = blockIdx.y != 0;
-    const __half *__restrict__ x     = second ? x1 : x0;
-    uint8_t      *__restrict__ q     = second ? q1 : q0;
-    __half       *__restrict__ scale = second ? scale1 : scale0;
-    int16_t      *__restrict__ zero  = second ? zero1 : zero0;
-    const int64_t r0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPR;
-    const int64_t stride = (int64_t)gridDim.x * (256 / LPR);
-    const int     j = threadIdx.x % LPR;
-    uint4 raws[kRows];
-#pragma unroll
-    for (int u = 0; u < kRows; ++u) {
-        const int64_t ru = r0 + u * stride;
-        const int64_t rr = ru < R ? ru : R - 1;          // idle lanes repeat the last row
-        raws[u] = *reinterpret_cast<const uint4 *>(x + rr * ldx + 8 * j);
-    }
-#pragma unroll
-    for (int u = 0; u < kRows; ++u) {
-    const int64_t r = r0 + u * stride;
-    const bool live = r < R;
-    const uint4 raw = raws[u];
-    const __half2 *hp = reinterpret_cast<const __half2 *>(&raw);
-    float f[8];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float2 t = __half22float2(hp[i]);
-        f[2 * i] = t.x;
-        f[2 * i + 1] = t.y;
-    }
-    float mx = f[0], mn = f[0];
-#pragma unroll
-    for (int i = 1; i < 8; ++i) {
-        mx = fmaxf(mx, f[i]);
-        mn = fminf(mn, f[i]);
-    }
-    row_minmax<LPR>(mx, mn);
-    const float  s32 = ((mx - mn) * clip) / 15.0f;
-    const __half sh  = (s32 > 65504.0f) ? __ushort_as_half((unsigned short)0x7bffu) : __float2half_rn(s32);
-    const float  s   = __half2float(sh);
-    int z = 0;
-    uint32_t w = 0;
-    if (s != 0.0f) {
-        // Nine quotients by the same divisor: one refined reciprocal, then two residual
-        // corrections per quotient (q += (y - s q) / s, the residual exact in an fma) give the
-        // correctly rounded y / s that the IEEE division sequence gives, at a third of its
-        // instructions.  y and s are fp16 numbers (s >= 2^-24, |y| <= 65504): no quotient,
-        // reciprocal or residual leaves the fp32 range.
-        const float r0 = __builtin_amdgcn_rcpf(s);
-        const float r1 = fmaf(fmaf(-s, r0, 1.0f), r0, r0);
-        auto div_s = [&](float y) {
-            float qf = y * r1;
-            qf = fmaf(fmaf(-s, qf, y), r1, qf);
-            qf = fmaf(fmaf(-s, qf, y), r1, qf);
-            return qf;
-        };
-        float zf = rintf(div_s(-mn));
-        zf = fminf(fmaxf(zf, -32768.0f), 32767.0f);
-        z = (int)zf;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            float t = rintf(div_s(f[i]));
-            t = fminf(fmaxf(t, -100000.0f), 100000.0f);
-            int c = (int)t + z;
-            c = c < 0 ? 0 : (c > 15 ? 15 : c);
-            w |= (uint32_t)c << (4 * i);
-        }
-    }
-    if (live) {
-        int64_t orow = r;
-        bool    keep = true;
-        if (pos) {                                       // a position outside the cache is dropped
-            const int64_t p = pos[r / rows_per_seq];
-            keep = p >= 0 && p < Tmax;
-            orow = r * Tmax + p;
-        }
-        if (keep) {
-            *reinterpret_cast<uint32_t *>(q + orow * (D / 2) + 4 * j) = w;
-            if (j == 0) {
-                scale[orow] = sh;
-                zero[orow]  = (int16_t)z;
-            }
-        }
-    }
-    }   // rows of this lane group
-}
 
 // ---------------------------------------------------------------- decode attention
 
@@ -876,26 +742,6 @@ void decode_attention_merge_kernel(const float *__restrict__ part, int S, __half
 }  // namespace
 
 namespace atom_internal {
-
-hipError_t launch_kv_quantize(const void *x, int64_t R, int64_t ldx, int D, float clip,
-                              const int32_t *pos, int32_t rows_per_seq, int64_t Tmax, void *q,
-                              void *scale, void *zero, hipStream_t stream, const void *x2, void *q2,
-                              void *scale2, void *zero2)
-{
-    const int     lpr  = D / 8;
-    const bool    bulk = R >= 65536;                    // four rows per lane group
-    const int64_t per  = (bulk ? 4 : 1) * (256 / lpr);  // rows per workgroup
-    const int64_t grid = (R + per - 1) / per;
-#define ATOM_KVQ_LAUNCH(LPR, ROWS)                                                                    \
-    hipLaunchKernelGGL((kv_quantize_kernel<LPR, ROWS>), dim3((unsigned)grid, x2 ? 2 : 1), dim3(256),  \
-                       0, stream, (const __half *)x, R, ldx, clip, pos, rows_per_seq, Tmax,           \
-                       (uint8_t *)q, (__half *)scale, (int16_t *)zero, (const __half *)x2,            \
-                       (uint8_t *)q2, (__half *)scale2, (int16_t *)zero2)
-    if (D == 128) { if (bulk) ATOM_KVQ_LAUNCH(16, 4); else ATOM_KVQ_LAUNCH(16, 1); }
-    else          { if (bulk) ATOM_KVQ_LAUNCH(8, 4);  else ATOM_KVQ_LAUNCH(8, 1); }
-#undef ATOM_KVQ_LAUNCH
-    return hipGetLastError();
-}
 
 // Shape of the launch.  B * H workgroups of four wavefronts fill the GPU from about five per
 // compute unit; a grid of at most 384 workgroups first gets 16 wavefronts per workgroup (the token range is

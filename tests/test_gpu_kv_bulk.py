@@ -1,0 +1,29 @@
+"""The bulk form of the KV quantiser (from 16384 rows) at the edges of its wavefronts' and workgroups' rows, with rows of
+every kind among them: bit-identical to the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2310_19102_amd as atom
+from _gpu_util import npy
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("R", [16383, 16384, 16385, 16384 + 63, 20001])
+def test_kv_quantize_bulk_edges(R, D):
+    print(f"[case] kv bulk R={R} D={D}", flush=True)
+    g = torch.Generator().manual_seed(R + D)
+    x = torch.randn((R, D), generator=g) * torch.exp(4.0 * torch.randn((R, 1), generator=g)) + 50.0 * torch.randn((R, 1), generator=g)
+    x = x.clamp(-65504.0, 65504.0).to(torch.float16)
+    x[5] = 3.25                                             # scale 0
+    x[6, ::2], x[6, 1::2] = -65504.0, 65504.0               # the widest range
+    x[7] = torch.linspace(0, 1e-7, D).to(torch.float16)
+    x[R - 1] = 1000.0 + (torch.arange(D) % 7).to(torch.float16)
+    x[R - 2] = (torch.arange(D) % 31) * 0.5 - 7.5       # ties
+    out = atom.atom_kv_quantize(x.cuda(), 0.95)
+    want = oracle.kv_quantize(x.numpy(), 0.95)
+    for name, a, b in zip(("codes", "scale", "zero"), out, want):
+        assert np.array_equal(npy(a).view(np.uint8), b.view(np.uint8)), name
