@@ -130,26 +130,35 @@ void check(int status, const char *where)
     throw Raised();
 }
 
-// The call into the library on the current stream: other python threads run meanwhile.
+// Other python threads run while this lives; it takes the interpreter back also where an exception leaves the scope
+// (a tensor without memory, as tracing makes them, throws when its address is asked for).
+struct Released {
+    PyThreadState *state = PyEval_SaveThread();
+    Released() = default;
+    ~Released() { PyEval_RestoreThread(state); }
+    Released(const Released &) = delete;
+    Released &operator=(const Released &) = delete;
+};
+
+// The call into the library on the current stream.
 template <class F> int call(F f)
 {
-    int st;
     void *s = stream();
-    Py_BEGIN_ALLOW_THREADS
-    st = f(s);
-    Py_END_ALLOW_THREADS
-    return st;
+    const Released others;
+    return f(s);
 }
 
-// A python result object: the caller's own (out= arguments) or a new tensor's.
+// A python result object: the caller's own (out= arguments, held until the call is over: an iterator gives its only
+// reference) or a new tensor's.
 struct Out {
     PyObject *o = nullptr;
     const Tensor *t = nullptr;
     Tensor own;
     Out() = default;
+    ~Out() { Py_XDECREF(o); }
     Out(const Out &) = delete;
     Out &operator=(const Out &) = delete;
-    void given(PyObject *p, const char *name) { o = p; t = &tensor(p, name); }
+    void given(PyObject *p, const char *name) { t = &tensor(p, name); o = p; Py_INCREF(o); }
     void fresh(Tensor &&n) { own = std::move(n); t = &own; }
     void take(PyObject *p, const char *name, std::initializer_list<int64_t> shape, Kind k, const Tensor &like)
     {
@@ -417,10 +426,16 @@ PyObject *quantize_act_packed(Args a)
     return out.give();
 }
 
+// The packed forms take a second operand with more rows or columns than the first and read its first ones.
+bool covers(const Tensor &t, const Tensor &x)
+{
+    return t.dim() == 2 && t.stride(1) == 1 && t.size(0) >= x.size(0) && t.size(1) >= x.size(1);
+}
+
 PyObject *add_quantize_act_packed(Args a)
 {
     const Tensor &x = device(a[0], kHalf, "x"), &r = device(a[1], kHalf, "residual");
-    if (x.dim() != 2 || x.stride(1) != 1 || r.sizes() != x.sizes() || r.stride(1) != 1)
+    if (x.dim() != 2 || x.stride(1) != 1 || !covers(r, x))
         value_error("x and residual must be [M, K] with a contiguous last dimension");
     void *idx = maybe(a[4], kInt, "reorder_idx"), *gamma = maybe(a[2], kHalf, "gamma");
     const int64_t M = x.size(0), K = x.size(1);
@@ -440,7 +455,7 @@ PyObject *add_quantize_act_packed(Args a)
 PyObject *swiglu_quantize_act_packed(Args a)
 {
     const Tensor &g = device(a[0], kHalf, "gate"), &u = device(a[1], kHalf, "up");
-    if (g.dim() != 2 || g.stride(1) != 1 || u.sizes() != g.sizes() || u.stride(1) != 1)
+    if (g.dim() != 2 || g.stride(1) != 1 || !covers(u, g))
         value_error("gate and up must be [M, K] with a contiguous last dimension");
     void *idx = maybe(a[2], kInt, "reorder_idx");
     const int64_t M = g.size(0), K = g.size(1);
