@@ -837,7 +837,7 @@ def main():
         # figure against the dense INT8 peak, which the benchmark spec quotes its target in, beside it
         roof = {"bound": "mfma", "achieved": achieved, "peak": PEAK_FP6_TFLOPS, "unit": "TFLOP/s",
                 "frac": achieved / PEAK_FP6_TFLOPS, "traffic": measured_traffic(args.config),
-                "kernel": "w4a4_gemm_f6_kernel",
+                "kernel": "w4a4_gemm_f6_walk_kernel, w4a4_gemm_f6_thin_kernel",
                 "mfma_dtype": "fp6 e3m2 (exact carrier of the INT4 codes) for the INT4 groups, int8 for the outlier group",
                 "frac_of_int8_mfma_peak": achieved / PEAK_INT8_TOPS,
                 "frac_of_measured_fp6_mfma_rate": achieved / (rates["fp6_32x32x64"]["value"] * 1e3),
