@@ -119,6 +119,13 @@ void matrix(const Tensor &t, const char *text)
     if (t.dim() != 2 || t.stride(1) != 1) value_error(text);
 }
 
+// A code or scale array whose two sizes say what a call computes (weights stacked over layers, with a dimension in front,
+// are not one: their first sizes would be taken for rows and outliers).
+void rows_and_columns(const Tensor &t, const char *name)
+{
+    if (t.dim() != 2) value_error(name, "must have two dimensions");
+}
+
 size_t bytes(const Tensor &t) { return (size_t)t.numel() * t.element_size(); }
 
 void check(int status, const char *where)
@@ -300,6 +307,7 @@ PyObject *w4a4_gemm(Args a)
     const Tensor &a4 = contiguous(a[0], kByte, "a_q4"), &a8 = contiguous(a[1], kChar, "a_q8"),
                  &as = contiguous(a[2], kHalf, "a_scale"), &w4 = contiguous(a[3], kByte, "w_q4"),
                  &w8 = contiguous(a[4], kChar, "w_q8"), &ws = contiguous(a[5], kHalf, "w_scale");
+    rows_and_columns(a8, "a_q8");
     const int64_t M = a8.size(0), O = a8.size(1), N = w8.size(0), K = 2 * a4.size(1) + O, gs = whole(a[6]);
     if (w4.size(1) != a4.size(1) || w8.size(1) != O) value_error("activation and weight code shapes disagree");
     Out y;
@@ -325,6 +333,8 @@ PyObject *w4a4_gemm_decode_tiled(Args a)
 {
     const Tensor &a4 = tensor(a[0], "a_q4"), &a8 = tensor(a[1], "a_q8"), &as = tensor(a[2], "a_scale"),
                  &w4 = tensor(a[3], "w_q4_tiled"), &w8 = tensor(a[4], "w_q8_tiled"), &ws = tensor(a[5], "w_scale");
+    rows_and_columns(a8, "a_q8");
+    rows_and_columns(ws, "w_scale");
     const int64_t M = a8.size(0), O = a8.size(1), N = ws.size(0), gs = whole(a[6]), K = ws.size(1) * gs;
     Out y;
     y.take(a[7], "out", {M, N}, kHalf, a4);
@@ -343,6 +353,7 @@ PyObject *decode_linear(Args a)
     const Tensor &w4 = device(a[4], kByte, "w_q4"), &w8 = device(a[5], kChar, "w_q8"),
                  &ws = device(a[6], kHalf, "w_scale");
     matrix(x, "x must be [M, K] with a contiguous last dimension");
+    rows_and_columns(w8, "w_q8");
     const int64_t M = x.size(0), K = x.size(1), N = w8.size(0), O = w8.size(1), gs = whole(a[7]);
     const float eps = real(a[2]), clip = real(a[8]);
     Out y;
@@ -371,6 +382,7 @@ PyObject *decode_linear_coop(Args a)
     if (4 * (size_t)sync.numel() < atom_decode_linear_coop_sync_bytes() || !sync.is_contiguous())
         value_error("sync_words is too small: take atom_decode_linear_coop_sync()");
     matrix(x, "x must be [M, K] with a contiguous last dimension");
+    rows_and_columns(w8, "w_q8");
     const int64_t M = x.size(0), K = x.size(1), N = w8.size(0), O = w8.size(1), gs = whole(a[8]);
     const float eps = real(a[2]), clip = real(a[9]);
     Out y;
@@ -400,6 +412,7 @@ PyObject *pack_act(Args a)
 {
     const Tensor &a4 = contiguous(a[0], kByte, "a_q4"), &a8 = contiguous(a[1], kChar, "a_q8"),
                  &as = contiguous(a[2], kHalf, "a_scale");
+    rows_and_columns(a8, "a_q8");
     const int64_t M = a8.size(0), O = a8.size(1), K = 2 * a4.size(1) + O;
     const atom_desc d = desc(K, whole(a[3]), O);
     Out out;
@@ -491,6 +504,7 @@ PyObject *w4a4_gemm_packed(Args a)
 {
     const Tensor &a4 = contiguous(a[0], kByte, "a_q4"), &a8 = contiguous(a[1], kChar, "a_q8"),
                  &as = contiguous(a[2], kHalf, "a_scale"), &wp = contiguous(a[3], kByte, "w_packed");
+    rows_and_columns(a8, "a_q8");
     const int64_t M = a8.size(0), O = a8.size(1), K = 2 * a4.size(1) + O, N = whole(a[4]), gs = whole(a[5]);
     const atom_desc d = desc(K, gs, O);
     if ((size_t)wp.numel() < atom_pack_weight_bytes(N, &d)) value_error("w_packed is smaller than atom_pack_weight_bytes(N)");
