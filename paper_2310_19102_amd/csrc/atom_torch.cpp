@@ -137,8 +137,7 @@ void check(int status, const char *where)
     throw Raised();
 }
 
-// Other python threads run while this lives; it takes the interpreter back also where an exception leaves the scope
-// (a tensor without memory, as tracing makes them, throws when its address is asked for).
+// Other python threads run while this lives; it takes the interpreter back also where an exception leaves the scope.
 struct Released {
     PyThreadState *state = PyEval_SaveThread();
     Released() = default;
@@ -147,13 +146,15 @@ struct Released {
     Released &operator=(const Released &) = delete;
 };
 
-// The call into the library on the current stream.
-template <class F> int call(F f)
+// The call into the library on the current stream.  Every address is an argument here, so all of them were read before other
+// threads may run.
+template <class F, class... A> int call(F f, A... a)
 {
     void *s = stream();
     const Released others;
-    return f(s);
+    return f(a..., s);
 }
+#define ATOM_CALL(f, ...) check(call(f, __VA_ARGS__), #f)
 
 // A python result object: the caller's own (out= arguments, held until the call is over: an iterator gives its only
 // reference) or a new tensor's.
@@ -189,19 +190,20 @@ PyObject *tuple(std::initializer_list<const Out *> v)
     return r;
 }
 
-// Three tensors given as any sequence (codes, outliers, scales / codes, scales, zeros).
+// Three tensors given as any iterable (codes, outliers, scales / codes, scales, zeros), held while this lives: a list may be
+// changed by another thread meanwhile, so its items are taken over into a tuple (a tuple is kept as it is).
 struct Three {
     PyObject *seq = nullptr;
-    PyObject **item = nullptr;
+    PyObject *item[3];
     explicit Three(PyObject *o)
     {
-        seq = PySequence_Fast(o, "expected three tensors");
+        seq = PySequence_Tuple(o);
         if (!seq) throw Raised();
-        if (PySequence_Fast_GET_SIZE(seq) != 3) {
+        if (PyTuple_GET_SIZE(seq) != 3) {
             Py_DECREF(seq);
             value_error("expected three tensors");
         }
-        item = PySequence_Fast_ITEMS(seq);
+        for (int i = 0; i < 3; ++i) item[i] = PyTuple_GET_ITEM(seq, i);
     }
     ~Three() { Py_XDECREF(seq); }
     Three(const Three &) = delete;
@@ -243,10 +245,8 @@ PyObject *quantize_act(Args a)
     Codes q;
     q.take(a[7], M, K, gs, O, x);
     const atom_desc d = desc(K, gs, O, whole(a[8]));
-    check(call([&](void *s) {
-        return atom_quantize_act(data(x), M, ld(x, M, K), gamma, eps, (const int32_t *)idx, &d, clip, q.q4.data(),
-                                 q.q8.data(), q.sc.data(), s);
-    }), "atom_quantize_act");
+    ATOM_CALL(atom_quantize_act, data(x), M, ld(x, M, K), gamma, eps, (const int32_t *)idx, &d, clip, q.q4.data(),
+              q.q8.data(), q.sc.data());
     return tuple({&q.q4, &q.q8, &q.sc});
 }
 
@@ -266,11 +266,8 @@ PyObject *add_quantize_act(Args a)
     Codes q;
     q.take(a[9], M, K, gs, O, x);
     const atom_desc d = desc(K, gs, O, whole(a[10]));
-    check(call([&](void *s) {
-        return atom_add_quantize_act(data(x), data(r), M, ld(x, M, K), ld(r, M, K), sum.data(), ld(*sum.t, M, K), gamma,
-                                     eps, (const int32_t *)idx, &d, clip, q.q4.data(), q.q8.data(), q.sc.data(),
-                                     s);
-    }), "atom_add_quantize_act");
+    ATOM_CALL(atom_add_quantize_act, data(x), data(r), M, ld(x, M, K), ld(r, M, K), sum.data(), ld(*sum.t, M, K), gamma,
+              eps, (const int32_t *)idx, &d, clip, q.q4.data(), q.q8.data(), q.sc.data());
     return tuple({&sum, &q.q4, &q.q8, &q.sc});
 }
 
@@ -285,10 +282,8 @@ PyObject *swiglu_quantize_act(Args a)
     Codes q;
     q.take(a[6], M, K, gs, O, g);
     const atom_desc d = desc(K, gs, O, whole(a[7]));
-    check(call([&](void *s) {
-        return atom_swiglu_quantize_act(data(g), data(u), M, ld(g, M, K), ld(u, M, K), (const int32_t *)idx, &d, clip,
-                                        q.q4.data(), q.q8.data(), q.sc.data(), s);
-    }), "atom_swiglu_quantize_act");
+    ATOM_CALL(atom_swiglu_quantize_act, data(g), data(u), M, ld(g, M, K), ld(u, M, K), (const int32_t *)idx, &d, clip,
+              q.q4.data(), q.q8.data(), q.sc.data());
     return tuple({&q.q4, &q.q8, &q.sc});
 }
 
@@ -322,10 +317,8 @@ PyObject *w4a4_gemm(Args a)
         own = make({(int64_t)need}, kByte, a4);
         w = &own;
     }
-    check(call([&](void *s) {
-        return atom_w4a4_gemm(data(a4), data(a8), data(as), M, data(w4), data(w8), data(ws), N, &d, y.data(),
-                              ld(*y.t, M, N), partials, w ? data(*w) : nullptr, w ? bytes(*w) : 0, s);
-    }), "atom_w4a4_gemm");
+    ATOM_CALL(atom_w4a4_gemm, data(a4), data(a8), data(as), M, data(w4), data(w8), data(ws), N, &d, y.data(),
+              ld(*y.t, M, N), partials, w ? data(*w) : nullptr, w ? bytes(*w) : 0);
     return y.give();
 }
 
@@ -339,10 +332,8 @@ PyObject *w4a4_gemm_decode_tiled(Args a)
     Out y;
     y.take(a[7], "out", {M, N}, kHalf, a4);
     const atom_desc d = desc(K, gs, O);
-    check(call([&](void *s) {
-        return atom_w4a4_gemm_decode_tiled(data(a4), data(a8), data(as), M, data(w4), data(w8), data(ws), N, &d,
-                                           y.data(), ld(*y.t, M, N), s);
-    }), "atom_w4a4_gemm_decode_tiled");
+    ATOM_CALL(atom_w4a4_gemm_decode_tiled, data(a4), data(a8), data(as), M, data(w4), data(w8), data(ws), N, &d,
+              y.data(), ld(*y.t, M, N));
     return y.give();
 }
 
@@ -363,11 +354,9 @@ PyObject *decode_linear(Args a)
     Codes q;
     if (debug) q.take(Py_None, M, K, gs, O, x);
     const atom_desc d = desc(K, gs, O, whole(a[11]));
-    check(call([&](void *s) {
-        return atom_decode_linear(data(x), M, ld(x, M, K), gamma, eps, (const int32_t *)idx, &d, clip, data(w4),
-                                  data(w8), data(ws), N, y.data(), ld(*y.t, M, N), debug ? q.q4.data() : nullptr,
-                                  debug ? q.q8.data() : nullptr, debug ? q.sc.data() : nullptr, s);
-    }), "atom_decode_linear");
+    ATOM_CALL(atom_decode_linear, data(x), M, ld(x, M, K), gamma, eps, (const int32_t *)idx, &d, clip, data(w4),
+              data(w8), data(ws), N, y.data(), ld(*y.t, M, N), debug ? q.q4.data() : nullptr,
+              debug ? q.q8.data() : nullptr, debug ? q.sc.data() : nullptr);
     if (!debug) return y.give();
     PyObject *codes = tuple({&q.q4, &q.q8, &q.sc});
     return Py_BuildValue("(NN)", y.give(), codes);
@@ -390,11 +379,8 @@ PyObject *decode_linear_coop(Args a)
     Codes q;
     q.take(a[11], M, K, gs, O, x);
     const atom_desc d = desc(K, gs, O, whole(a[12]));
-    check(call([&](void *s) {
-        return atom_decode_linear_coop(data(x), M, ld(x, M, K), gamma, eps, (const int32_t *)idx, &d, clip, data(w4),
-                                       data(w8), data(ws), N, y.data(), ld(*y.t, M, N), q.q4.data(), q.q8.data(),
-                                       q.sc.data(), data(sync), s);
-    }), "atom_decode_linear_coop");
+    ATOM_CALL(atom_decode_linear_coop, data(x), M, ld(x, M, K), gamma, eps, (const int32_t *)idx, &d, clip, data(w4),
+              data(w8), data(ws), N, y.data(), ld(*y.t, M, N), q.q4.data(), q.q8.data(), q.sc.data(), data(sync));
     PyObject *codes;
     if (a[11] != Py_None) { codes = a[11]; Py_INCREF(codes); }       // the caller's own sequence
     else codes = tuple({&q.q4, &q.q8, &q.sc});
@@ -417,8 +403,7 @@ PyObject *pack_act(Args a)
     const atom_desc d = desc(K, whole(a[3]), O);
     Out out;
     packed_out(out, a[4], M, d, a4);
-    check(call([&](void *s) { return atom_pack_act(data(a4), data(a8), data(as), M, &d, out.data(), (size_t)out.t->numel(), s); }),
-          "atom_pack_act");
+    ATOM_CALL(atom_pack_act, data(a4), data(a8), data(as), M, &d, out.data(), (size_t)out.t->numel());
     return out.give();
 }
 
@@ -432,10 +417,8 @@ PyObject *quantize_act_packed(Args a)
     const atom_desc d = desc(K, whole(a[4]), whole(a[5]), whole(a[8]));
     Out out;
     packed_out(out, a[7], M, d, x);
-    check(call([&](void *s) {
-        return atom_quantize_act_packed(data(x), M, ld(x, M, K), gamma, eps, (const int32_t *)idx, &d, clip, out.data(),
-                                        (size_t)out.t->numel(), s);
-    }), "atom_quantize_act_packed");
+    ATOM_CALL(atom_quantize_act_packed, data(x), M, ld(x, M, K), gamma, eps, (const int32_t *)idx, &d, clip, out.data(),
+              (size_t)out.t->numel());
     return out.give();
 }
 
@@ -457,11 +440,8 @@ PyObject *add_quantize_act_packed(Args a)
     h.take(a[8], "sum_out", {M, K}, kHalf, x);
     const atom_desc d = desc(K, whole(a[5]), whole(a[6]), whole(a[10]));
     packed_out(out, a[9], M, d, x);
-    check(call([&](void *s) {
-        return atom_add_quantize_act_packed(data(x), data(r), M, ld(x, M, K), ld(r, M, K), h.data(), ld(*h.t, M, K),
-                                            gamma, eps, (const int32_t *)idx, &d, clip, out.data(),
-                                            (size_t)out.t->numel(), s);
-    }), "atom_add_quantize_act_packed");
+    ATOM_CALL(atom_add_quantize_act_packed, data(x), data(r), M, ld(x, M, K), ld(r, M, K), h.data(), ld(*h.t, M, K),
+              gamma, eps, (const int32_t *)idx, &d, clip, out.data(), (size_t)out.t->numel());
     return tuple({&h, &out});
 }
 
@@ -476,10 +456,8 @@ PyObject *swiglu_quantize_act_packed(Args a)
     const atom_desc d = desc(K, whole(a[3]), whole(a[4]), whole(a[7]));
     Out out;
     packed_out(out, a[6], M, d, g);
-    check(call([&](void *s) {
-        return atom_swiglu_quantize_act_packed(data(g), data(u), M, ld(g, M, K), ld(u, M, K), (const int32_t *)idx, &d,
-                                               clip, out.data(), (size_t)out.t->numel(), s);
-    }), "atom_swiglu_quantize_act_packed");
+    ATOM_CALL(atom_swiglu_quantize_act_packed, data(g), data(u), M, ld(g, M, K), ld(u, M, K), (const int32_t *)idx, &d,
+              clip, out.data(), (size_t)out.t->numel());
     return out.give();
 }
 
@@ -494,9 +472,7 @@ PyObject *w4a4_gemm_prepacked(Args a)
     y.take(a[7], "out", {M, N}, kHalf, ap);
     if (y.o) device(y.o, kHalf, "out");
     int32_t *partials = partial_sums(a[8], M, N, groups(K, gs));
-    check(call([&](void *s) {
-        return atom_w4a4_gemm_prepacked(data(ap), M, data(wp), N, &d, y.data(), ld(*y.t, M, N), partials, s);
-    }), "atom_w4a4_gemm_prepacked");
+    ATOM_CALL(atom_w4a4_gemm_prepacked, data(ap), M, data(wp), N, &d, y.data(), ld(*y.t, M, N), partials);
     return y.give();
 }
 
@@ -519,10 +495,8 @@ PyObject *w4a4_gemm_packed(Args a)
         own = make({(int64_t)std::max<size_t>(need, 1)}, kByte, a4);
         w = &own;
     }
-    check(call([&](void *s) {
-        return atom_w4a4_gemm_packed(data(a4), data(a8), data(as), M, data(wp), N, &d, y.data(), ld(*y.t, M, N),
-                                     partials, data(*w), bytes(*w), s);
-    }), "atom_w4a4_gemm_packed");
+    ATOM_CALL(atom_w4a4_gemm_packed, data(a4), data(a8), data(as), M, data(wp), N, &d, y.data(), ld(*y.t, M, N),
+              partials, data(*w), bytes(*w));
     return y.give();
 }
 
@@ -556,9 +530,7 @@ PyObject *kv_quantize(Args a)
         c.fresh(make(at::IntArrayRef(cshape), kByte, x));
         sc.fresh(make(lead, kHalf, x));
         z.fresh(make(lead, kShort, x));
-        check(call([&](void *s) {
-            return atom_kv_quantize(data(x), R, D, (int32_t)D, clip, nullptr, 0, 0, c.data(), sc.data(), z.data(), s);
-        }), "atom_kv_quantize");
+        ATOM_CALL(atom_kv_quantize, data(x), R, D, (int32_t)D, clip, nullptr, 0, 0, c.data(), sc.data(), z.data());
         return tuple({&c, &sc, &z});
     }
     const Cache k(a[2], "cache codes", "cache scale", "cache zero");
@@ -570,10 +542,8 @@ PyObject *kv_quantize(Args a)
     if (x.size(0) != B || x.size(1) != H || k.codes.size(3) * 2 != D || !k.shaped(B, H, T, k.codes.size(3)) ||
         pos.dim() != 1 || pos.size(0) != B || !pos.is_contiguous())
         value_error("cache, x and pos shapes disagree");
-    check(call([&](void *s) {
-        return atom_kv_quantize(data(x), R, D, (int32_t)D, clip, (const int32_t *)data(pos), (int32_t)H, T, data(k.codes),
-                                data(k.scale), data(k.zero), s);
-    }), "atom_kv_quantize");
+    ATOM_CALL(atom_kv_quantize, data(x), R, D, (int32_t)D, clip, (const int32_t *)data(pos), (int32_t)H, T,
+              data(k.codes), data(k.scale), data(k.zero));
     return PyTuple_Pack(3, k.t.item[0], k.t.item[1], k.t.item[2]);
 }
 
@@ -594,11 +564,9 @@ PyObject *kv_quantize_pair(Args a)
         !vc.shaped(B, H, T, D / 2))
         value_error("cache and row shapes disagree");
     if (pos.dim() != 1 || pos.size(0) != B || !pos.is_contiguous()) value_error("pos must be contiguous int32 [B]");
-    check(call([&](void *s) {
-        return atom_kv_quantize_pair(data(k), data(v), B * H, D, (int32_t)D, clip, (const int32_t *)data(pos), (int32_t)H,
-                                     T, data(kc.codes), data(kc.scale), data(kc.zero), data(vc.codes), data(vc.scale),
-                                     data(vc.zero), s);
-    }), "atom_kv_quantize_pair");
+    ATOM_CALL(atom_kv_quantize_pair, data(k), data(v), B * H, D, (int32_t)D, clip, (const int32_t *)data(pos),
+              (int32_t)H, T, data(kc.codes), data(kc.scale), data(kc.zero), data(vc.codes), data(vc.scale),
+              data(vc.zero));
     return PyTuple_Pack(2, a[2], a[3]);
 }
 
@@ -627,11 +595,9 @@ PyObject *attention(Args a, bool fixed)
     const float sm = real(a[4]);
     const int32_t *n = (const int32_t *)data(len);
     if (fixed) {
-        check(call([&](void *s) {
-            return atom_decode_attention_kv4_static(data(q), (int32_t)B, (int32_t)H, (int32_t)Hkv, (int32_t)D, T, n,
-                                                    data(k.codes), data(k.scale), data(k.zero), data(v.codes),
-                                                    data(v.scale), data(v.zero), sm, out.data(), s);
-        }), "atom_decode_attention_kv4_static");
+        ATOM_CALL(atom_decode_attention_kv4_static, data(q), (int32_t)B, (int32_t)H, (int32_t)Hkv, (int32_t)D, T, n,
+                  data(k.codes), data(k.scale), data(k.zero), data(v.codes), data(v.scale), data(v.zero), sm,
+                  out.data());
         return out.give();
     }
     const size_t need = atom_decode_attention_kv4_workspace_bytes((int32_t)B, (int32_t)H, (int32_t)Hkv, (int32_t)D, T);
@@ -641,11 +607,9 @@ PyObject *attention(Args a, bool fixed)
         own = make({(int64_t)need}, kByte, q);
         w = &own;
     }
-    check(call([&](void *s) {
-        return atom_decode_attention_kv4(data(q), (int32_t)B, (int32_t)H, (int32_t)Hkv, (int32_t)D, T, n, data(k.codes),
-                                         data(k.scale), data(k.zero), data(v.codes), data(v.scale), data(v.zero), sm,
-                                         out.data(), w ? data(*w) : nullptr, w ? bytes(*w) : 0, s);
-    }), "atom_decode_attention_kv4");
+    ATOM_CALL(atom_decode_attention_kv4, data(q), (int32_t)B, (int32_t)H, (int32_t)Hkv, (int32_t)D, T, n, data(k.codes),
+              data(k.scale), data(k.zero), data(v.codes), data(v.scale), data(v.zero), sm, out.data(),
+              w ? data(*w) : nullptr, w ? bytes(*w) : 0);
     return out.give();
 }
 
@@ -671,10 +635,8 @@ PyObject *mx_quantize_act(Args a)
         e8.given(t.item[2], "e8");
     }
     const atom_desc d = desc(K, 32, O);
-    check(call([&](void *s) {
-        return atom_mx_quantize_act(data(x), M, ld(x, M, K), gamma, eps, (const int32_t *)data(idx), &d, clip, q4.data(),
-                                    q8.data(), e8.data(), s);
-    }), "atom_mx_quantize_act");
+    ATOM_CALL(atom_mx_quantize_act, data(x), M, ld(x, M, K), gamma, eps, (const int32_t *)data(idx), &d, clip,
+              q4.data(), q8.data(), e8.data());
     return tuple({&q4, &q8, &e8});
 }
 
@@ -694,10 +656,8 @@ PyObject *mx_gemm(Args a)
     y.take(a[6], "out", {M, N}, kHalf, a4);
     if (y.o) device(y.o, kHalf, "out");
     const atom_desc d = desc(K, 32, O);
-    check(call([&](void *s) {
-        return atom_mx_gemm(data(a4), data(a8), data(ae), M, data(w4), data(w8), data(we), N, &d, y.data(),
-                            ld(*y.t, M, N), s);
-    }), "atom_mx_gemm");
+    ATOM_CALL(atom_mx_gemm, data(a4), data(a8), data(ae), M, data(w4), data(w8), data(we), N, &d, y.data(),
+              ld(*y.t, M, N));
     return y.give();
 }
 

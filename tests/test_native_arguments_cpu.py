@@ -1,5 +1,7 @@
 """What the native entry points ask of their arguments, without a GPU: tensors that claim to be on one (fake tensors have no
 memory).  A call whose arguments pass gets as far as the device and raises RuntimeError there."""
+import weakref
+
 import pytest
 import torch
 from torch._subclasses.fake_tensor import FakeTensorMode
@@ -42,3 +44,28 @@ def test_stacked_operands_are_refused(name):
         CALLS[name](codes(L, M), codes(L, N))
     with pytest.raises((ValueError, IndexError)):           # nor are those of one dimension
         CALLS[name]([t[0] for t in codes(M)], [t[0] for t in codes(N)])
+
+
+@pytest.mark.filterwarnings("ignore:Accessing the data pointer")
+@pytest.mark.parametrize("static", [False, True])
+def test_tensors_of_a_list_are_held_through_the_call(static):
+    """A cache given as a list that changes while the call goes on (here in the conversion of a later argument, elsewhere in
+    another thread): the call keeps the tensors it was given."""
+    B, H, D, T = 2, 4, 128, 64
+    cache = [[fake(B, H, T, D // 2), fake(B, H, T, dtype=torch.float16), fake(B, H, T, dtype=torch.int16)] for _ in "kv"]
+    held = [weakref.ref(t) for c in cache for t in c]
+    alive = []
+
+    class Scale:
+        def __float__(self):
+            for c in cache:
+                c[:] = [None] * 3
+            alive.extend(r() is not None for r in held)
+            raise ArithmeticError("seen")                   # (nothing is read after this)
+
+    call = atom.atom_decode_attention_kv4_static if static else atom.atom_decode_attention_kv4
+    with pytest.raises(ArithmeticError):
+        call(fake(B, H, D, dtype=torch.float16), *cache, fake(B, dtype=torch.int32), Scale(),
+             out=fake(B, H, D, dtype=torch.float16))
+    assert alive == [True] * 6
+    assert not any(r() is not None for r in held)           # and lets them go
