@@ -62,7 +62,7 @@ __device__ __forceinline__ KvRow kv_quantize_row(const uint4 &raw, float clip)
     row_minmax<LPR>(mx, mn);
     const float  span = fminf((mx - mn) * clip, 982560.0f);  // 15 * 65504: the largest scale is the largest fp16
     const float  q15 = span * (1.0f / 15.0f);
-    float        s32 = fmaf(fmaf(-15.0f, q15, span), 1.0f / 15.0f, q15);
+    float        s32 = fmaf(fmaf(15.0f, q15, -span), -1.0f / 15.0f, q15);      // (in these signs a zero quotient keeps its sign)
     asm("" : "+v"(s32));                                   // (a fused form would round to fp16 once, not to fp32 first)
     const _Float16 sh = (_Float16)s32;
     const float  s  = (float)sh;

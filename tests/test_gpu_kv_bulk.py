@@ -27,3 +27,18 @@ def test_kv_quantize_bulk_edges(R, D):
     want = oracle.kv_quantize(x.numpy(), 0.95)
     for name, a, b in zip(("codes", "scale", "zero"), out, want):
         assert np.array_equal(npy(a).view(np.uint8), b.view(np.uint8)), name
+
+
+@pytest.mark.parametrize("clip", [0.0, -0.0, -0.75, 1e-30, 7.5])
+@pytest.mark.parametrize("R", [37, 16385])
+def test_kv_quantize_any_clip(R, clip):
+    """The equations hold for every factor: a zero scale has the sign of its quotient, a large one saturates."""
+    g = torch.Generator().manual_seed(R)
+    x = (torch.randn((R, 128), generator=g) * torch.exp(3.0 * torch.randn((R, 1), generator=g))).clamp(-65504.0, 65504.0).to(torch.float16)
+    x[0] = 0.0
+    x[1] = -3.25
+    x[2, ::2], x[2, 1::2] = -65504.0, 65504.0
+    out = atom.atom_kv_quantize(x.cuda(), clip)
+    want = oracle.kv_quantize(x.numpy(), clip)
+    for name, a, b in zip(("codes", "scale", "zero"), out, want):
+        assert np.array_equal(npy(a).view(np.uint8), b.view(np.uint8)), name
