@@ -36,8 +36,7 @@ FLAGS = [
 # attention kernel rescales its accumulators with the vector ALU (online softmax), and with them
 # in AccVGPRs every step copied all 32 of them out for a rescaling that rarely runs
 SOURCE_FLAGS = {"atom_mx.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=0"],
-                "atom_kv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
-                "atom_kv_quantize.hip": ["-fno-honor-nans"]}
+                "atom_kv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def native_command(lib: str = LIB, out: str = NATIVE):

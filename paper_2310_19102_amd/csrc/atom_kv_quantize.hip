@@ -1,7 +1,5 @@
 // INT4 KV cache for gfx950: asymmetric per-head quantisation (Section 2 of the paper,
 // asymmetric equations; Section 4.4: granularity of one attention head).
-// Compiled without NaNs (they are undefined inputs): every maximum of a loaded value or of another lane's would be
-// preceded by an instruction that quiets a signalling NaN.
 
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
@@ -13,18 +11,30 @@ namespace {
 
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 
-// max / min over the LPR (8 or 16) lanes that share a row; LPR lanes are consecutive and
+// Maxima of two pairs of fp16 values.  (As an instruction: the compiler puts one that quiets signalling NaNs in front of
+// every loaded or moved operand of its own maxima.  The instruction itself ignores NaNs.)
+__device__ __forceinline__ h2 pair_max(h2 a, h2 b)
+{
+    h2 r;
+    asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ h2 pair_min(h2 a, h2 b)
+{
+    h2 r;
+    asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// The maximum of both halves over the LPR (8 or 16) lanes that share a row; LPR lanes are consecutive and
 // aligned, so rotations inside the 16-lane DPP row stay inside the row for LPR = 16, and an
 // xor butterfly is used for LPR = 8
 template <int LPR>
-__device__ __forceinline__ void row_minmax(float &mx, float &mn)
+__device__ __forceinline__ h2 row_max(h2 v)
 {
     if constexpr (LPR == 16) {            // DPP rotations of the 16-lane row: vector-ALU speed, no LDS crossbar
-#define ATOM_ROW_ROR(n)                                                                              \
-        mx = fmaxf(mx, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(                        \
-                           0, __builtin_bit_cast(int, mx), 0x120 | (n), 0xF, 0xF, false)));          \
-        mn = fminf(mn, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(                        \
-                           0, __builtin_bit_cast(int, mn), 0x120 | (n), 0xF, 0xF, false)))
+#define ATOM_ROW_ROR(n) \
+        v = pair_max(v, __builtin_bit_cast(h2, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x120 | (n), 0xF, 0xF, true)))
         ATOM_ROW_ROR(8);
         ATOM_ROW_ROR(4);
         ATOM_ROW_ROR(2);
@@ -32,11 +42,10 @@ __device__ __forceinline__ void row_minmax(float &mx, float &mn)
 #undef ATOM_ROW_ROR
     } else {
 #pragma unroll
-        for (int d = 1; d < LPR; d <<= 1) {
-            mx = fmaxf(mx, __shfl_xor(mx, d, 64));
-            mn = fminf(mn, __shfl_xor(mn, d, 64));
-        }
+        for (int d = 1; d < LPR; d <<= 1)
+            v = pair_max(v, __builtin_bit_cast(h2, __shfl_xor(__builtin_bit_cast(int, v), d, 64)));
     }
+    return v;
 }
 
 // One row of D = 8 * LPR values on LPR lanes (this lane's eight are `raw`):
@@ -56,11 +65,12 @@ template <int LPR>
 __device__ __forceinline__ KvRow kv_quantize_row(const uint4 &raw, float clip)
 {
     const h2 *hp = reinterpret_cast<const h2 *>(&raw);
-    const h2 hx = __builtin_elementwise_max(__builtin_elementwise_max(hp[0], hp[1]), __builtin_elementwise_max(hp[2], hp[3]));
-    const h2 hn = __builtin_elementwise_min(__builtin_elementwise_min(hp[0], hp[1]), __builtin_elementwise_min(hp[2], hp[3]));
-    float mx = fmaxf((float)hx[0], (float)hx[1]), mn = fminf((float)hn[0], (float)hn[1]);
-    row_minmax<LPR>(mx, mn);
-    const float  span = fminf((mx - mn) * clip, 982560.0f);  // 15 * 65504: the largest scale is the largest fp16
+    const h2 hx = pair_max(pair_max(hp[0], hp[1]), pair_max(hp[2], hp[3]));
+    const h2 hn = pair_min(pair_min(hp[0], hp[1]), pair_min(hp[2], hp[3]));
+    const h2 m = row_max<LPR>(pair_max(h2{hx[0], -hn[0]}, h2{hx[1], -hn[1]}));
+    const float  mx = (float)m[0], mn = -(float)m[1];
+    float        span = (mx - mn) * clip;
+    span = span > 982560.0f ? 982560.0f : span;              // 15 * 65504: the largest scale is the largest fp16 (a NaN stays one)
     const float  q15 = span * (1.0f / 15.0f);
     float        s32 = fmaf(fmaf(15.0f, q15, -span), -1.0f / 15.0f, q15);      // (in these signs a zero quotient keeps its sign)
     asm("" : "+v"(s32));                                   // (a fused form would round to fp16 once, not to fp32 first)

@@ -42,3 +42,19 @@ def test_kv_quantize_any_clip(R, clip):
     want = oracle.kv_quantize(x.numpy(), clip)
     for name, a, b in zip(("codes", "scale", "zero"), out, want):
         assert np.array_equal(npy(a).view(np.uint8), b.view(np.uint8)), name
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("R", [37, 16385])
+def test_kv_quantize_infinities(R, D):
+    """A row of one infinity has no span: its scale is no number and its codes are zero.  An infinity among numbers gives the
+    largest scale; the other rows are untouched."""
+    g = torch.Generator().manual_seed(R)
+    x = torch.randn((R, D), generator=g).to(torch.float16)
+    x[0], x[1], x[2, 3], x[3, D - 1] = float("inf"), -float("inf"), float("inf"), -float("inf")
+    codes, scale, zero = (npy(t) for t in atom.atom_kv_quantize(x.cuda()))
+    want = oracle.kv_quantize(x[4:].numpy(), 1.0)
+    for name, a, b in zip(("codes", "scale", "zero"), (codes[4:], scale[4:], zero[4:]), want):
+        assert np.array_equal(a.view(np.uint8), b.view(np.uint8)), name
+    assert np.isnan(scale[:2]).all() and (scale[2:4] == 65504.0).all()
+    assert (codes[:4] == 0).all() and zero[:4].tolist() == [-32768, -32768, 0, -32768]
