@@ -383,10 +383,21 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
                     }
                     y[e] = *reinterpret_cast<const float *>(reinterpret_cast<const unsigned char *>(ybuf) + o);
                 }
-                amax = fmaxf(amax, fabsf(y[e]));
+                if constexpr (MX) amax = __builtin_elementwise_maximum(amax, fabsf(y[e]));    // (a NaN if any value is one)
+                else              amax = fmaxf(amax, fabsf(y[e]));
             }
             const bool  is4   = gg < G4;
             if constexpr (MX) {
+                // The block's scale is that of its numbers.  A NaN among them (an infinite channel times the zero factor of its
+                // own norm) becomes a zero in FP4 and the largest value in FP8, with its sign.
+                if (__builtin_expect(amax != amax, 0)) {
+                    amax = 0.0f;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        amax = fmaxf(amax, fabsf(y[e]));
+                        y[e] = y[e] == y[e] ? y[e] : copysignf(is4 ? 0.0f : __builtin_inff(), y[e]);
+                    }
+                }
 #define ATOM_QUAD_MAX(ctrl)                                                                      \
     amax = fmaxf(amax, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(                    \
                      0, __builtin_bit_cast(int, amax), ctrl, 0xF, 0xF, false)))

@@ -63,3 +63,25 @@ def test_every_gate(up):
     mixed = np.ascontiguousarray(gate.T)
     got = atom.atom_swiglu_quantize_act(torch.from_numpy(mixed).cuda(), torch.from_numpy(u).cuda(), torch.from_numpy(idx).cuda())
     _same(got, oracle.swiglu_quantize_act(mixed, u, idx, 128, 128, 0.9), "mixed")
+
+
+@pytest.mark.parametrize("M", [4, 258])
+def test_mx_of_no_number(M):
+    """A NaN is a zero in FP4 and the largest value in FP8, with its sign; the scale is that of the block's numbers."""
+    K, K4 = 1024, 896
+    x, _, _ = _rows(M, K, M)
+    x = x.numpy().copy()
+    at = [(0, 3, 1.0), (0, 500, -1.0), (1, K4 + 2, 1.0), (1, K4 + 99, -1.0)] + [(2, k, 1.0) for k in range(32)]
+    for i, k, sign in at:
+        x[i, k] = np.copysign(np.float16(np.nan), np.float16(sign))
+    idx = torch.arange(K, dtype=torch.int32)
+    got = [npy(t) for t in atom.atom_mx_quantize_act(torch.from_numpy(x).cuda(), None, 0.0, idx.cuda(), 128, 0.9)]
+    numbers = np.where(np.isnan(x), np.copysign(np.float16(0.0), x), x)
+    q4, q8, e8 = oracle.mx_quantize_act(numbers, None, 0.0, idx.numpy(), 128, 0.9)
+    q8 = q8.copy()
+    for i, k, sign in at:
+        if k >= K4:
+            q8.view(np.uint8)[i, k - K4] = 0x7E if sign > 0 else 0xFE
+    for name, a, b in zip(("q4", "q8", "e8"), got, (q4, q8, e8)):
+        a = a.transpose(1, 0, 2).reshape(a.shape[1], -1)
+        assert np.array_equal(a.view(np.uint8), b.view(np.uint8)), name
