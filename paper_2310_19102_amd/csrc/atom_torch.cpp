@@ -422,10 +422,15 @@ PyObject *quantize_act_packed(Args a)
     return out.give();
 }
 
-// The packed forms take a second operand with more rows or columns than the first and read its first ones.
+// The packed forms take as second operand whatever holds the first one's rows at its first stride: a matrix with more rows or
+// columns (its first ones are read), one with dimensions of one element in between, for one row anything contiguous.
 bool covers(const Tensor &t, const Tensor &x)
 {
-    return t.dim() == 2 && t.stride(1) == 1 && t.size(0) >= x.size(0) && t.size(1) >= x.size(1);
+    const int64_t M = x.size(0), K = x.size(1);
+    if (t.dim() == 2 && t.stride(1) == 1 && t.size(0) >= M && t.size(1) >= K) return true;
+    if (t.dim() < 1) return false;
+    if (M == 1 && t.is_contiguous()) return t.numel() >= K;
+    return t.dim() > 2 && t.size(0) >= M && t.select(0, 0).is_contiguous() && t.numel() >= t.size(0) * K;
 }
 
 PyObject *add_quantize_act_packed(Args a)

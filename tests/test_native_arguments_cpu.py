@@ -69,3 +69,18 @@ def test_tensors_of_a_list_are_held_through_the_call(static):
              out=fake(B, H, D, dtype=torch.float16))
     assert alive == [True] * 6
     assert not any(r() is not None for r in held)           # and lets them go
+
+
+@pytest.mark.filterwarnings("ignore:Accessing the data pointer")
+@pytest.mark.parametrize("rows,shape,taken", [
+    (1, (K,), True), (1, (1, 1, K), True), (1, (2, K), True), (1, (8, K // 4), True), (4, (4, K), True), (4, (5, K + 128), True),
+    (4, (4, 1, K), True), (4, (4, 2, K), True), (1, (K - 128,), False), (4, (K,), False), (4, (4 * K,), False),
+    (4, (1, 4, K), False), (4, (4, K - 128), False), (4, (3, K), False), (1, (), False)])
+def test_second_operand_of_the_packed_front_ends(rows, shape, taken):
+    """Anything that holds the rows at its first stride is taken; what would be read past its end is refused."""
+    x, r = (fake(*s, dtype=torch.float16) for s in ((rows, K), shape))
+    out = fake(1 << 20)
+    for call in (lambda: atom.atom_add_quantize_act_packed(x, r, None, 0.0, None, sum_out=fake(rows, K, dtype=torch.float16), out=out),
+                 lambda: atom.atom_swiglu_quantize_act_packed(x, r, None, out=out)):
+        with pytest.raises(RuntimeError if taken else ValueError):
+            call()
