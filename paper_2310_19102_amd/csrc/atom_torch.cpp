@@ -190,14 +190,26 @@ PyObject *tuple(std::initializer_list<const Out *> v)
     return r;
 }
 
+PyObject *first_three(PyObject *o)
+{
+    PyObject *r = PyTuple_New(3);
+    for (Py_ssize_t i = 0; r && i < 3; ++i) {
+        PyObject *n = PyLong_FromSsize_t(i), *item = n ? PyObject_GetItem(o, n) : nullptr;
+        Py_XDECREF(n);
+        if (item) PyTuple_SET_ITEM(r, i, item);
+        else Py_CLEAR(r);
+    }
+    return r;
+}
+
 // Three tensors given as any iterable (codes, outliers, scales / codes, scales, zeros), held while this lives: a list may be
 // changed by another thread meanwhile, so its items are taken over into a tuple (a tuple is kept as it is).
 struct Three {
     PyObject *seq = nullptr;
     PyObject *item[3];
-    explicit Three(PyObject *o)
+    explicit Three(PyObject *o, bool indexed = false)      // indexed: items 0, 1 and 2 of what may have more
     {
-        seq = PySequence_Tuple(o);
+        seq = indexed ? first_three(o) : PySequence_Tuple(o);
         if (!seq) throw Raised();
         if (PyTuple_GET_SIZE(seq) != 3) {
             Py_DECREF(seq);
@@ -213,14 +225,14 @@ struct Three {
 // Codes, outliers and scales of `rows` rows: the caller's or new ones.
 struct Codes {
     Out q4, q8, sc;
-    void take(PyObject *out, int64_t rows, int64_t K, int64_t gs, int64_t O, const Tensor &like)
+    void take(PyObject *out, int64_t rows, int64_t K, int64_t gs, int64_t O, const Tensor &like, bool indexed = false)
     {
         if (out == Py_None) {
             q4.fresh(make({rows, (K - O) / 2}, kByte, like));
             q8.fresh(make({rows, O}, kChar, like));
             sc.fresh(make({rows, groups(K, gs)}, kHalf, like));
         } else {
-            Three t(out);
+            Three t(out, indexed);
             q4.given(t.item[0], "q4");
             q8.given(t.item[1], "q8");
             sc.given(t.item[2], "scale");
@@ -377,7 +389,7 @@ PyObject *decode_linear_coop(Args a)
     Out y;
     y.take(a[10], "out", {M, N}, kHalf, x);
     Codes q;
-    q.take(a[11], M, K, gs, O, x);
+    q.take(a[11], M, K, gs, O, x, true);
     const atom_desc d = desc(K, gs, O, whole(a[12]));
     ATOM_CALL(atom_decode_linear_coop, data(x), M, ld(x, M, K), gamma, eps, (const int32_t *)idx, &d, clip, data(w4),
               data(w8), data(ws), N, y.data(), ld(*y.t, M, N), q.q4.data(), q.q8.data(), q.sc.data(), data(sync));

@@ -84,3 +84,12 @@ def test_second_operand_of_the_packed_front_ends(rows, shape, taken):
                  lambda: atom.atom_swiglu_quantize_act_packed(x, r, None, out=out)):
         with pytest.raises(RuntimeError if taken else ValueError):
             call()
+
+
+@pytest.mark.filterwarnings("ignore:Accessing the data pointer")
+def test_codes_of_the_cooperative_linear_are_taken_by_index():
+    """The first three of whatever can be indexed."""
+    y, sync = fake(M, N, dtype=torch.float16), fake(1 << 16, dtype=torch.int32)
+    for given, error in ((codes(M) + [None], RuntimeError), (dict(enumerate(codes(M))), RuntimeError), (codes(M)[:2], IndexError)):
+        with pytest.raises(error):
+            atom.atom_decode_linear_coop(X(), None, 0.0, None, *codes(N), sync, out=y, codes=given)
