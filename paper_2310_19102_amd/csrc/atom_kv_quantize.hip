@@ -71,6 +71,7 @@ __device__ __forceinline__ KvRow kv_quantize_row(const uint4 &raw, float clip)
     const float  mx = (float)m[0], mn = -(float)m[1];
     float        span = (mx - mn) * clip;
     span = span > 982560.0f ? 982560.0f : span;              // 15 * 65504: the largest scale is the largest fp16 (a NaN stays one)
+    span = span < -1000000.0f ? -1000000.0f : span;          // (a scale of minus infinity, also from a span that is infinite)
     const float  q15 = span * (1.0f / 15.0f);
     float        s32 = fmaf(fmaf(15.0f, q15, -span), -1.0f / 15.0f, q15);      // (in these signs a zero quotient keeps its sign)
     asm("" : "+v"(s32));                                   // (a fused form would round to fp16 once, not to fp32 first)
