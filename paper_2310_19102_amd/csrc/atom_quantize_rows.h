@@ -134,7 +134,7 @@ __device__ __forceinline__ float row16_max_dpp(float v)
 // Scale of a group from its maximum (Section 2 symmetric equations, fp32, stored as fp16) and the
 // codes of this lane's eight values: the IEEE quotient by the stored scale, round-half-to-even, clamp.
 // The quotient takes three instructions per element.  s is an fp16 number, and r = rcp(s) with one Newton step is
-// the correctly rounded 1/s for every one of them (checked on the hardware, all of them).  q = y r is within two
+// the correctly rounded 1/s for every one of them (every scale is tested, at its ties and beside them).  q = y r is within two
 // units of y/s, e = y - q s is exact, and q + e r, rounded once, is the quotient unless y/s lies within 2^-23 units of the
 // middle between two floats; with an 11-bit s it is at least 2^-12 units away from every such middle.  Returns the stored scale,
 // s = its fp32 value.  The codes stay floats (whole numbers): what packs them needs no integers
@@ -184,9 +184,11 @@ __device__ __forceinline__ uint32_t pack_nibbles8(const float (&c)[8])
 //   * a workgroup walks several rows; the gather offsets of the reorder (they are the same
 //     for every row) and gamma stay in registers, and the next row's global loads are in
 //     flight while this row is quantised;
-//   * the IEEE division by the group's scale shares the reciprocal across the group (quantise_lane8).
-//     |y| / s <= (2^n - 1)/(2 clip) * (1 + 2^-11) and s >= 2^-24, so nothing overflows; quotients below 2^-100
-//     round to code 0 either way.  A zero scale (all-zero group) yields zero codes;
+//   * the IEEE division by the group's scale shares the reciprocal across the group (quantise_lane8).  Nothing
+//     overflows: a scale that is not zero is at least 2^-24, and |y| < 2^33 for finite inputs (a normalised value is at most
+//     sqrt(K), gamma below 2^16; silu(g) u below 2^32).  How far beyond the codes y / s lies is not bounded by the clip factor
+//     alone: a subnormal scale can be two thirds of its quotient, one that saturates at 65504 any small part of it.  The
+//     clamp takes those; quotients below 2^-100 round to code 0 either way.  A zero scale yields zero codes;
 //   * the group maximum is a DPP rotation reduction.
 // The rows row_first, row_first + row_step, ... < rows are handled by the calling workgroup
 // (NT threads, all of them call); lds holds K + (NORM ? K / 8 : 0) floats.  q4, q8 and scale

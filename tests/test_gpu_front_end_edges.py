@@ -85,3 +85,47 @@ def test_mx_of_no_number(M):
     for name, a, b in zip(("q4", "q8", "e8"), got, (q4, q8, e8)):
         a = a.transpose(1, 0, 2).reshape(a.shape[1], -1)
         assert np.array_equal(a.view(np.uint8), b.view(np.uint8)), name
+
+
+def _around_ties(a, u, rng):
+    """128 pairs of fp16 factors for a group of the scale 2 a u: their products are all 16 ties (k + 1/2) of INT4 (the outermost
+    two are the group's maximum), values next to them, and values in between."""
+    t = 2.0 * np.arange(-8, 8) + 1.0
+    a = np.float16(a)
+    below, above = np.nextafter(a, np.float16(0.0)), np.nextafter(a, np.float16(np.inf))
+    first = np.repeat(np.array([a, below, above, a]), (16, 16, 14, 82))
+    second = u * np.concatenate([t, t, t[1:-1], np.round(rng.uniform(-14.8, 14.8, 82) * 8.0) / 8.0])
+    return first, second.astype(np.float16)
+
+
+def test_every_scale():
+    """Every positive fp16 scale: all codes of a group share the scale's reciprocal, and an exact tie has to stay one.  The
+    values are exact products of two fp16 numbers: a gate whose sigma is 1 and the up operand, or, for the 63 smallest scales, a row and
+    gamma where the factor of the norm is 1."""
+    rng = np.random.default_rng(5)
+    scales = [(m, e) for e in range(-24, 6) for m in range(1024, 2048)] + [(m, -24) for m in range(64, 1024)]
+    rows = -(-len(scales) // 127)
+    K = 128 * 128                                            # 127 INT4 groups per row, and the outliers
+    gate, up = np.full((rows, K), 32.0, np.float16), np.full((rows, K), 0.25, np.float16)
+    for i, (m, e) in enumerate(scales):
+        b = m.bit_length()                                   # gates in [32, 64)
+        at = np.s_[i // 127, 128 * (i % 127):128 * (i % 127) + 128]
+        gate[at], up[at] = _around_ties(m * 2.0 ** (6 - b), 2.0 ** (e + b - 7), rng)
+    ident = np.arange(K, dtype=np.int32)
+    want = oracle.swiglu_quantize_act(gate, up, ident, 128, 128, 1.0)
+    stored = want[2][:, :127].reshape(-1)[:len(scales)]
+    assert np.array_equal(stored.astype(np.float64), [m * 2.0 ** e for m, e in scales])
+    dg, du = torch.from_numpy(gate).cuda(), torch.from_numpy(up).cuda()
+    _same(atom.atom_swiglu_quantize_act(dg, du, None, 128, 128, 1.0), want, "in order")
+    _same(atom.atom_swiglu_quantize_act(dg, du, torch.from_numpy(ident).cuda(), 128, 128, 1.0), want, "gathered")
+
+    K = 64 * 128
+    x, gamma = np.full((1, K), 2.0 ** -15, np.float16), np.ones(K, np.float16)
+    for m in range(1, 64):
+        at = np.s_[128 * (m - 1):128 * m]
+        x[0, at], gamma[at] = _around_ties(m * 2.0 ** -20, 2.0 ** -5, rng)
+    ident = np.arange(K, dtype=np.int32)
+    want = oracle.quantize_act(x, gamma, 1.0, ident, 128, 128, 1.0)
+    assert np.array_equal(want[2][0, :63].astype(np.float64), np.arange(1, 64) * 2.0 ** -24)
+    got = atom.atom_quantize_act(*(torch.from_numpy(v).cuda() for v in (x, gamma)), 1.0, torch.from_numpy(ident).cuda(), 128, 128, 1.0)
+    _same(got, want, "norm")
