@@ -286,20 +286,26 @@ hipError_t launch_gather(const QuantArgs &a, bool few, hipStream_t stream)
 template <bool NORM, int PRE>
 hipError_t dispatch_quantize(const QuantArgs &a, hipStream_t stream)
 {
-    // Up to one row per compute unit, the time is that of one row: twice the threads halve what each of them does (K = 4096,
-    // 8 rows, RMSNorm: 3.9 -> 3.4 us, half of it from this).
+    // Up to one row per compute unit, the time is that of one row: twice the threads do half the work each, but have more wavefronts
+    // to bring to a barrier.  8 rows, times with the threads of many rows and with twice as many: RMSNorm 3.6 / 3.4 us
+    // (K = 4096), 4.3 / 4.2 (8192), 5.3 / 5.4 (11008), 6.6 / 6.0 (16384); without a norm 2.9 / 2.7, 3.4 / 3.3, 4.1 / 4.1, 4.7 / 4.5;
+    // SwiGLU 3.6 / 3.2, 4.4 / 4.0, 5.6 / 5.2, 7.0 / 6.1; MX 3.4 / 3.2, 4.1 / 3.9, 5.1 / 5.0, 6.1 / 5.4.  At 512 rows and more it is up to a third slower.
     const bool few = a.rows <= atom_launch::compute_units();
     const bool sane_clip = a.clip >= 9.5367431640625e-07f && a.clip <= 1.0f && a.gs == 128;   // what the fast kernels take
     if (!a.idx && a.K <= 32768 && sane_clip) {
         // no index: the row already is in reordered order; nothing is staged in LDS but the
-        // sums of squares, so the register sets alone bound the threads per row
+        // sums of squares, so the register sets alone bound the threads per row.
+        // 4097 to 8192 channels: a row in order has one barrier with a norm and none without.  With a norm 512 threads beat 1024 for
+        // few rows (8 rows of 8192: 3.8 / 4.0 us, of 5120: 3.5 / 3.6), and 320 threads beat 512 for more rows of at most 5120 (1024
+        // rows: 7.2 / 8.6 us); without one 1024 threads are best for few rows (8 rows of 8192: 2.7 / 2.9 us) and 512 beat 320
+        // (4096 rows of 5120: 12.0 / 13.5 us, SwiGLU 23.7 / 27.4).
         const size_t lq = NORM ? sizeof(float) * (size_t)(a.K / 8) : 0;
         if (a.K <= 2048)  return launch_fast<NORM, 1, 256, PRE, true>(a, lq, stream);
         if (few && a.K <= 4096)  return launch_fast<NORM, 1, 512, PRE, true>(a, lq, stream);
-        if (few && a.K <= 8192)  return launch_fast<NORM, 1, 1024, PRE, true>(a, lq, stream);
-        if (few && a.K <= 16384) return launch_fast<NORM, 2, 1024, PRE, true>(a, lq, stream);
+        if (few && a.K <= 8192 && !NORM) return launch_fast<NORM, 1, 1024, PRE, true>(a, lq, stream);
+        if (few && a.K <= 16384 && a.K > 8192) return launch_fast<NORM, 2, 1024, PRE, true>(a, lq, stream);
         if (a.K <= 4096)  return launch_fast<NORM, 2, 256, PRE, true>(a, lq, stream);
-        if (a.K <= 5120)  return launch_fast<NORM, 2, 320, PRE, true>(a, lq, stream);
+        if (NORM && !few && a.K <= 5120) return launch_fast<NORM, 2, 320, PRE, true>(a, lq, stream);
         if (a.K <= 8192)  return launch_fast<NORM, 2, 512, PRE, true>(a, lq, stream);
         if (a.K <= 12288) return launch_fast<NORM, 3, 512, PRE, true>(a, lq, stream);
         if (a.K <= 16384) return launch_fast<NORM, 4, 512, PRE, true>(a, lq, stream);

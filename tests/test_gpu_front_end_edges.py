@@ -43,6 +43,9 @@ def test_front_end_configurations(M, K):
     _same([pick(t) for t in got], oracle.quantize_act(xs[rows], gs, 1e-6, ix, 128, 128, 0.9), "norm")
     got = atom.atom_quantize_act(dx, None, 0.0, None)
     _same([pick(t) for t in got], oracle.quantize_act(xs[rows], None, 0.0, np.arange(K, dtype=np.int32), 128, 128, 0.9), "no index")
+    got = atom.atom_quantize_act(dx, dg, 1e-6, None)
+    _same([pick(t) for t in got], oracle.quantize_act(xs[rows], gs, 1e-6, np.arange(K, dtype=np.int32), 128, 128, 0.9), "norm, no index")
+    assert torch.equal(atom.atom_quantize_act_packed(dx, dg, 1e-6, None), atom.atom_pack_act(*got))
     got = atom.atom_mx_quantize_act(dx, dg, 1e-6, di, 128, 0.9)
     _same([pick(t) for t in got], oracle.mx_quantize_act(xs[rows], gs, 1e-6, ix, 128, 0.9), "MX")
     if 4 * K + K // 2 + 3 * (K - 128) // 4 + 128 <= 160 * 1024:
