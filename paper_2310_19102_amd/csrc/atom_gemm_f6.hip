@@ -581,11 +581,19 @@ hipError_t launch_f6_cfg(const F6Params &p, hipStream_t stream)
 
 namespace atom_internal {
 
-// Tile of a launch: 0, 1, 2 = thin 64 x 64, 64 x 128, 128 x 128; 3, 4 = walking 128 x 128, 256 x 128; -1: fewer units
-// than any of them has.  The estimate is the time per INT4 group in units of 10 ns: rounds of tiles over the
-// compute units times what a tile's step takes (measured at K = 4096 to 16384).  Thin tiles win where large ones leave
-// compute units without work; beyond the first round (64 x 64: the third) they pay prologue and store in the open
-// and fetch more bytes per multiply-add than the walking ones.
+// Tile of a launch: 0, 1, 2 = thin 64 x 64, 64 x 128, 128 x 128; 3, 4 = walking 128 x 128, 256 x 128; -1: the general
+// kernel.  The estimate is the time per INT4 group in units of 10 ns: rounds of tiles over the compute units times what a
+// tile's step takes.  Thin tiles win where large ones leave compute units without work; beyond the first round (64 x 64: the
+// third) they pay prologue and store in the open and fetch more bytes per multiply-add than the walking ones.  Two lines
+// beside that, both at K = 4096 / 11008, weights from HBM:
+//   * 128 x 128 with hardly more tiles than compute units: the few that share one cost less than a full second round (M = 384,
+//     N = 11008, 258 tiles: 27.5 / 59.2 us, 256 x 128 30.4 / 64.8; M = 896, N = 4992, 273 tiles: 28.1 / 58.6 and 29.5 / 62.6).  With
+//     how many tiles that ends differs with the rows of tiles (after 264, 264, 275, 270 and 280 tiles of 3, 4, 5, 6 and 8 rows:
+//     M = 512, N = 8576, 268 tiles: 32.9 / 73.8 us, 256 x 128 30.1 / 64.1); with two rows 258 tiles are slow already;
+//   * three units of rows: the general kernel leaves the fourth unit of its two rows of tiles out of its requests, the walking one
+//     moves the last tile back and fetches three units twice (M = 192, K = 8192, N = 28672: 66.6 us, walking 71.9; N = 57344:
+//     130 / 139).
+// Every tile on 83 sizes, and what the rule takes: profiles/w4a4_gemm_f6_tiles.txt.
 static int pick_tile(int64_t au, int64_t wu, int64_t cus)
 {
     struct { int ua, uw, rounds, first, more; } const tile[5] = {
@@ -594,14 +602,22 @@ static int pick_tile(int64_t au, int64_t wu, int64_t cus)
     int64_t least = INT64_MAX;
     for (int i = 0; i < 5; ++i) {
         if (au < tile[i].ua || wu < tile[i].uw) continue;
-        const int64_t tiles = ((au + tile[i].ua - 1) / tile[i].ua) * ((wu + tile[i].uw - 1) / tile[i].uw);
+        const int64_t rows = (au + tile[i].ua - 1) / tile[i].ua, tiles = rows * ((wu + tile[i].uw - 1) / tile[i].uw);
         const int64_t n = (tiles + cus - 1) / cus;
         const int64_t cost = n <= tile[i].rounds ? n * tile[i].first
+                           : i == 3 && n == 2 && rows >= 3 && tiles - cus < 3 * (rows < 8 ? rows : 8) ? 72
                            : i == 3 ? n * 45 - n / 2 * 3       // (two workgroups per compute unit: the pair costs a little less)
                                     : n * tile[i].more;
         if (cost < least) { least = cost; best = i; }
     }
-    return best;
+    return best == 3 && au == 3 ? -1 : best;
+}
+
+// The same for the sizes of a call without a dump; -1: the general kernel.
+static int tile_of_launch(int64_t M, int64_t N, int K, int O, int64_t cus)
+{
+    const int G4 = (K - O) >> 7, G8 = O >> 7;
+    return G8 == 1 && G4 >= 7 ? pick_tile((M + 63) / 64, (N + 63) / 64, cus) : -1;
 }
 
 size_t f6_packed_bytes(int64_t rows, int K, int O)
@@ -636,10 +652,8 @@ hipError_t launch_f6_gemm(const void *a_pk, int64_t M, const void *w_pk, int64_t
     p.a_units = (int)((M + 63) / 64); p.w_units = (int)((N + 63) / 64);
     p.G4 = (K - O) >> 7; p.G8 = O >> 7;
     p.ustride = (int64_t)p.G4 * IMG4 + (int64_t)p.G8 * IMG8;
-    if (!partials) {
-        const int pick = pick_tile(p.a_units, p.w_units, atom_launch::compute_units());
-        if (p.G8 == 1 && p.G4 >= 7 && pick >= 0) return pick < 3 ? launch_thin(p, pick, stream) : launch_walk(p, pick - 3, stream);
-    }
+    const int pick = partials ? -1 : tile_of_launch(M, N, K, O, atom_launch::compute_units());
+    if (pick >= 0) return pick < 3 ? launch_thin(p, pick, stream) : launch_walk(p, pick - 3, stream);
     // 256-row tiles halve the weight traffic per row but want at least four rounds of tiles over the
     // 256 compute units; 128-row tiles run two workgroups per compute unit, which hides one's prologue,
     // barriers and store behind the other's K loop
@@ -650,3 +664,9 @@ hipError_t launch_f6_gemm(const void *a_pk, int64_t M, const void *w_pk, int64_t
 }
 
 }  // namespace atom_internal
+
+// For the tests of the tiles: which one a call takes on a card of `cus` compute units.
+extern "C" int atom_internal_packed_tile(int64_t M, int64_t N, int32_t K, int32_t O, int64_t cus)
+{
+    return atom_internal::tile_of_launch(M, N, K, O, cus);
+}
