@@ -19,6 +19,7 @@ of the dominant kernel (the group GEMM) from HIP-event timings of its launches
 inside the timed region, and the CPU oracle timed on a bounded row sample.
 """
 import argparse
+import ctypes
 import json
 import os
 import sys
@@ -47,13 +48,14 @@ WORKLOAD_NAMES = {
 
 
 def streams_weights(lin, compute_units=256):
-    """Whether atom_w4a4_gemm takes its weight-streaming kernels for this linear layer (the library's
-    rule: up to 64 rows always, up to 256 rows when the workgroups of the blocks of 64 rows pass in
-    at most three rounds); such a layer keeps the canonical weights, larger ones the packed ones."""
+    """Whether a layer keeps canonical weights because atom_w4a4_gemm streams them faster than the packed GEMM runs: up to 64
+    rows always, up to 128 rows when the workgroups of the blocks of 64 rows pass in at most three rounds (M = 128, K = 4096: N = 4096
+    8.1 us against 11.6 packed, N = 11008 20.9 against 16.8).  The library streams up to 256 rows so, which the packed tiles of
+    few rows have overtaken (M = 256, K = N = 4096, step in a graph: 18.0 us, packed 13.3)."""
     G = lin.K // lin.group_size
     if lin.M <= 64:
         return True
-    if lin.M > 256 or lin.n_outlier != 128 or G % 2 or G < 8 or lin.group_size != 128:
+    if lin.M > 128 or lin.n_outlier != 128 or G % 2 or G < 8 or lin.group_size != 128:
         return False
     blocks, yb = (lin.N + 15) // 16, (lin.M + 63) // 64
     wgs = blocks * yb if blocks * yb <= compute_units else (blocks + 1) // 2 * yb
@@ -745,9 +747,22 @@ def mlp_block_chain():
             "swiglu_front_end_no_index_hbm_frac": sw_bytes / t_swiglu_in_order / 1e9 / PEAK_HBM_GBS}
 
 
-def measured_traffic(config):
+def packed_kernels(layers):
+    """Names of the kernels that the packed GEMM of these layers takes (the library's choice), in the order of the layers."""
+    pick = ctypes.CDLL(atom.binding._LIB_PATH).atom_internal_packed_tile
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    names = []
+    for L in layers:
+        tile = pick(ctypes.c_int64(L.M), ctypes.c_int64(L.N), L.K, L.lin.n_outlier, ctypes.c_int64(cus))
+        name = "w4a4_gemm_f6_kernel" if tile < 0 else "w4a4_gemm_f6_thin_kernel" if tile < 3 else "w4a4_gemm_f6_walk_kernel"
+        if name not in names:
+            names.append(name)
+    return ", ".join(names)
+
+
+def measured_traffic(config, kernel):
     """HBM bytes per GEMM launch from the committed rocprofv3 --pmc summary of this
-    workload (FETCH_SIZE + WRITE_SIZE, scaled by a plain copy of known size), or None."""
+    workload (FETCH_SIZE + WRITE_SIZE, scaled by a plain copy of known size), or None if there is none of these kernels."""
     path = os.path.join(ROOT, "profiles", f"traffic_config{config}.txt")
     if not os.path.exists(path):
         return None
@@ -756,8 +771,8 @@ def measured_traffic(config):
         for line in f:
             if line.strip() and not line.startswith("#") and "=" in line:
                 k, v = line.split("=", 1)
-                vals[k.strip()] = float(v.split()[0])
-    if "gemm_fetch_bytes_per_launch" in vals and "gemm_write_bytes_per_launch" in vals:
+                vals[k.strip()] = v.strip() if k.strip() == "kernel" else float(v.split()[0])
+    if vals.get("kernel") == kernel and "gemm_fetch_bytes_per_launch" in vals and "gemm_write_bytes_per_launch" in vals:
         return vals["gemm_fetch_bytes_per_launch"] + vals["gemm_write_bytes_per_launch"]
     return None
 
@@ -830,21 +845,21 @@ def main():
     if hbm_bound:
         roof = {"bound": "hbm", "achieved": gemm_bytes / gemm_sec / 1e9, "peak": PEAK_HBM_GBS,
                 "unit": "GB/s", "frac": gemm_bytes / gemm_sec / 1e9 / PEAK_HBM_GBS,
-                "traffic": measured_traffic(args.config), "kernel": "w4a4_gemm_decode_kernel"}
+                "traffic": measured_traffic(args.config, "w4a4_gemm_decode_kernel"), "kernel": "w4a4_gemm_decode_kernel"}
     elif packed:
         # the INT4 groups (all but one group in 32 to 224) are contracted by the FP6 matrix
         # instruction, so the kernel is priced against that instruction's dense peak; the same
         # figure against the dense INT8 peak, which the benchmark spec quotes its target in, beside it
         roof = {"bound": "mfma", "achieved": achieved, "peak": PEAK_FP6_TFLOPS, "unit": "TFLOP/s",
-                "frac": achieved / PEAK_FP6_TFLOPS, "traffic": measured_traffic(args.config),
-                "kernel": "w4a4_gemm_f6_walk_kernel, w4a4_gemm_f6_thin_kernel",
+                "frac": achieved / PEAK_FP6_TFLOPS, "traffic": measured_traffic(args.config, packed_kernels(layers)),
+                "kernel": packed_kernels(layers),
                 "mfma_dtype": "fp6 e3m2 (exact carrier of the INT4 codes) for the INT4 groups, int8 for the outlier group",
                 "frac_of_int8_mfma_peak": achieved / PEAK_INT8_TOPS,
                 "frac_of_measured_fp6_mfma_rate": achieved / (rates["fp6_32x32x64"]["value"] * 1e3),
                 "frac_of_measured_int8_mfma_rate": achieved / (rates["int8_32x32x32"]["value"] * 1e3)}
     else:
         roof = {"bound": "mfma", "achieved": achieved, "peak": PEAK_INT8_TOPS, "unit": "TOP/s",
-                "frac": achieved / PEAK_INT8_TOPS, "traffic": measured_traffic(args.config),
+                "frac": achieved / PEAK_INT8_TOPS, "traffic": measured_traffic(args.config, "w4a4_gemm_big_kernel"),
                 "kernel": "w4a4_gemm_big_kernel"}
     roof.update({"launches_per_step": n_gemm, "avg_launch_us": gemm_sec / n_gemm * 1e6,
                  "front_end_us_per_step": fe_sec * 1e6, "retile_us_per_step": pack_sec * 1e6,
