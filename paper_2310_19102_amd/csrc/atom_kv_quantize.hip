@@ -52,8 +52,8 @@ __device__ __forceinline__ h2 row_max(h2 v)
 //   s = fp16(((max - min) * clip) / 15), z = clamp(rne(-min / s)), code = clamp(rne(x/s) + z, 0, 15)
 // with correctly rounded fp32 quotients by the stored scale; a zero scale gives zero codes and z = 0.
 //   * max and min of the fp16 values two at a time, as fp16;
-//   * the nine quotients share the reciprocal r = RN(1/s), exact for every fp16 s after one Newton step (checked on the
-//     hardware, all of them); q = y r, then q + (y - q s) r rounded once is the quotient: q is within two units of it,
+//   * the nine quotients share the reciprocal r = RN(1/s), exact for every fp16 s after one Newton step (every
+//     scale is tested); q = y r, then q + (y - q s) r rounded once is the quotient: q is within two units of it,
 //     the residual is exact, and y/s lies at least 2^-12 units from the middle of two floats (s has 11 bits); the
 //     quotient by 15 likewise (a quotient so small that its residual would be inexact is a zero scale);
 //   * clamp(rne(v) + z, 0, 15) = rne(clamp(v, -z, 15 - z)) + z; adding 1.5 * 2^23 rounds to the nearest even integer and
@@ -69,9 +69,8 @@ __device__ __forceinline__ KvRow kv_quantize_row(const uint4 &raw, float clip)
     const h2 hn = pair_min(pair_min(hp[0], hp[1]), pair_min(hp[2], hp[3]));
     const h2 m = row_max<LPR>(pair_max(h2{hx[0], -hn[0]}, h2{hx[1], -hn[1]}));
     const float  mx = (float)m[0], mn = -(float)m[1];
-    float        span = (mx - mn) * clip;
-    span = span > 982560.0f ? 982560.0f : span;              // 15 * 65504: the largest scale is the largest fp16 (a NaN stays one)
-    span = span < -1000000.0f ? -1000000.0f : span;          // (a scale of minus infinity, also from a span that is infinite)
+    // Within 15 * 65504 (the largest scale is the largest fp16) and what gives minus infinity; a NaN stays one (these two hand it on).
+    const float  span = __builtin_elementwise_maximum(__builtin_elementwise_minimum((mx - mn) * clip, 982560.0f), -1000000.0f);
     const float  q15 = span * (1.0f / 15.0f);
     float        s32 = fmaf(fmaf(15.0f, q15, -span), -1.0f / 15.0f, q15);      // (in these signs a zero quotient keeps its sign)
     asm("" : "+v"(s32));                                   // (a fused form would round to fp16 once, not to fp32 first)
