@@ -1,4 +1,4 @@
-// Definitions shared by the FP6 group-GEMM kernels (atom_gemm_f6.hip, atom_gemm_f6_walk.hip): the unit
+// Definitions shared by the FP6 group-GEMM kernels (atom_gemm_f6.hip, atom_gemm_f6_thin.hip, atom_gemm_f6_walk.hip): the unit
 // images of the packed operands, the kernel parameters, the matrix instructions and the order control.
 #ifndef ATOM_GEMM_F6_H
 #define ATOM_GEMM_F6_H
@@ -65,9 +65,6 @@ __device__ __forceinline__ v16f mfma_f6(const v12i &a, const v12i &b, v16f c)
         asm volatile("" ::: "memory");             \
         __builtin_amdgcn_sched_barrier(0);         \
     } while (0)
-
-typedef float    v2f __attribute__((ext_vector_type(2)));
-typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 
 // One LDS-DMA request: every active lane moves 16 bytes from base + voff into LDS, lane l to lds + 16 l.
 __device__ __forceinline__ void dma16(uint32_t lds, uint32_t voff, const uint8_t *base)

@@ -9,8 +9,8 @@
 //     set, so nothing waits for LDS, and the stage just read is free at once;
 //   * the loop is unrolled over the LDS stages, so that every LDS address is a register plus an immediate and a
 //     request is one scalar addition and the load: 13 scalar instructions per step instead of 42.
-// K = 4096, weights from HBM: M = 256, N = 4096 19.2 -> 8.5 us (64 x 64); M = 512, N = 4096 19.6 -> 12.3 us (64 x 128); M = 256,
-// N = 12288 22.4 -> 20.9 us (128 x 128; weights from the last-level cache 17.5 us); M = 128, N = 22016 24.6 -> 22.4 us.
+// K = 4096, weights from HBM, general kernel and this one: M = 256, N = 4096 21.0 -> 11.7 us (64 x 64); M = 512, N = 4096
+// 20.9 -> 15.3 us (64 x 128); M = 256, N = 12288 23.2 -> 21.0 us, M = 128, N = 22016 25.1 -> 22.9 us (128 x 128).
 // Which tile a launch gets: pick_tile in atom_gemm_f6.hip.
 
 #include <hip/hip_runtime.h>

@@ -15,9 +15,12 @@
 //     it is whole (what two tiles share they both compute, to the same bits);
 //   * the weights are the row operand of the MFMA, so that a lane holds four consecutive columns of a row of Y and the
 //     output staging is a quarter of the LDS writes.
-// M = 4096, K = 8192, N = 57344: 1611 -> 1526 us; K = 28672, N = 8192: 744 -> 715 us; M = 1024, K = 4096, N = 22016: 102 -> 91 us;
-// M = 777, K = 5120, N = 13824 (WR = 2): 65.0 -> 63.3 us.  Wider tiles (64 x 96 per wavefront: 1515 us on the first shape;
-// 64 x 128 does not fit the registers) fetch fewer bytes and lose it again to the power limit and to partial rounds.
+// Against the walking kernel before this one (in turn on one card, half a second each): M = 4096, K = 8192, N = 57344: 1531 -> 1516 us;
+// N = 10240: 272.5 -> 268.6 us; K = 28672, N = 8192: 718.9 -> 717.9 us (under the power limit, which decides there); M = 1024,
+// K = 4096, N = 22016: 91.8 -> 83.8 us; M = 777, K = 5120, N = 13824 (WR = 2): 59.9 -> 57.6 us.  Wider tiles (64 x 96 per
+// wavefront; 64 x 128 does not fit the registers) fetch fewer bytes and lose it again to the power limit and to partial rounds.
+// A moved-back tile that leaves out the stores of what the tile before it stores is no faster (M = 192, N = 28672: 38.2 us, 37.9) and
+// costs 1 % elsewhere.
 //
 // Workgroups walk tiles, and the stream of requests never stops at a tile's end.  The K loop's last NST steps have
 // nothing of their own INT4 groups left to ask for: two of them fetch the two parts of the INT8 group, the others the

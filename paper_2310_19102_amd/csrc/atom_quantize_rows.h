@@ -65,7 +65,7 @@ __device__ __forceinline__ float exp_ieee(float x)
 
 // silu(g) * u in fp32: sigma = the correctly rounded 1/(1 + exp(-g)), then (g*sigma)*u.  g is an fp16 number, so
 // there are 65536 cases: the hardware's reciprocal with one Newton step (three instructions, a general division
-// takes eleven) is the correctly rounded value in every one of them (checked on the hardware, all of them).
+// takes eleven) is the correctly rounded value in every one of them (all of them are tested).
 __device__ __forceinline__ float silu_mul(float g, float u)
 {
     const float d  = 1.0f + exp_ieee(-g);
