@@ -31,14 +31,6 @@ FLAGS = [
 ]
 
 
-# per-source overrides: the MX GEMM never touches its accumulators with the vector ALU inside the
-# K loop, so its 256 accumulator registers per lane belong in the AccVGPRs; the grouped-query
-# attention kernel rescales its accumulators with the vector ALU (online softmax), and with them
-# in AccVGPRs every step copied all 32 of them out for a rescaling that rarely runs
-SOURCE_FLAGS = {"atom_mx.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=0"],
-                "atom_kv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
-
-
 def native_command(lib: str = LIB, out: str = NATIVE):
     """The python extension (host code only: tensors in, calls into libatom.so)."""
     import sysconfig
@@ -62,7 +54,7 @@ def build(verbose: bool = False, extra_flags=(), lib: str = LIB, tag: str = "") 
     procs = []
     for src in SOURCES:
         obj = os.path.join(CSRC, src.replace(".hip", tag + ".o"))
-        cmd = [hipcc, *FLAGS, *SOURCE_FLAGS.get(src, []), *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc, *FLAGS, *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))

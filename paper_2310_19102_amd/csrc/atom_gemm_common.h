@@ -48,6 +48,51 @@ __device__ __forceinline__ int xcd_contiguous_block_id()
     return xcd * per + (xcd < rem ? xcd : rem) + (b >> 3);
 }
 
+// A finished block of Y (ROWS x COLS fp16; its rows `pitch` >= 2 COLS + 16 bytes apart in LDS, 16-byte aligned) to rows of Y
+// that start on any element (an odd row length, a view): whole 16-byte pieces wherever 16-byte aligned addresses lie in
+// the row, put together from two neighbouring pieces of the staged row, then what is left at its two ends, eight lanes per
+// row.  `y` is the block's first element; rows and columns at and past rows_left and cols_left are not stored.  (Two
+// bytes per lane, as the accumulators hold them, a block of 64 x 64 is 64 store instructions and more lines than bytes: the
+// packed GEMM at M = 2048, K = 4096 took 132 us for N = 12289 and 88 us for N = 12288.)
+template <int ROWS, int COLS>
+__device__ __forceinline__ void store_block_any(const unsigned char *blk, int pitch, uint16_t *y, int64_t ldy, int rows_left,
+                                                int cols_left, int lane)
+{
+    constexpr int LPR = COLS / 8;
+    static_assert(ROWS * LPR % 64 == 0 && ROWS % 8 == 0, "whole wavefronts");
+    const int nc = cols_left < COLS ? cols_left : COLS;
+#pragma unroll 2
+    for (int i = 0; i < ROWS * LPR / 64; ++i) {
+        const int q = 64 * i + lane, r = q / LPR, k = q % LPR;
+        uint16_t *row = y + (int64_t)r * ldy;
+        const unsigned h = (0u - ((unsigned)reinterpret_cast<uintptr_t>(row) >> 1)) & 7u;     // elements before the first aligned piece
+        const v4i lo = *reinterpret_cast<const v4i *>(blk + r * pitch + 16 * k);
+        const v4i hi = *reinterpret_cast<const v4i *>(blk + r * pitch + 16 * k + 16);
+        unsigned w[8] = {(unsigned)lo[0], (unsigned)lo[1], (unsigned)lo[2], (unsigned)lo[3],
+                         (unsigned)hi[0], (unsigned)hi[1], (unsigned)hi[2], (unsigned)hi[3]};
+#pragma unroll
+        for (int j = 0; j < 6; ++j) { const unsigned stay = w[j], move = w[j + 2]; w[j] = h & 4 ? move : stay; }
+#pragma unroll
+        for (int j = 0; j < 5; ++j) { const unsigned stay = w[j], move = w[j + 1]; w[j] = h & 2 ? move : stay; }
+        const unsigned sh = 16 * (h & 1);
+        v4i d;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) d[j] = (int)__builtin_amdgcn_alignbit(w[j + 1], w[j], sh);
+        if (r < rows_left && (int)h + 8 * k + 8 <= nc) *reinterpret_cast<v4i *>(row + h + 8 * k) = d;
+    }
+    // slot e of a row: its first h elements, then those behind the last whole piece (a block of all COLS columns has eight
+    // or none of them, a cut one up to fourteen)
+    for (int e0 = 0; e0 < (nc == COLS ? 8 : 16); e0 += 8)
+#pragma unroll 2
+        for (int i = 0; i < ROWS / 8; ++i) {
+            const int r = 8 * i + (lane >> 3), e = e0 + (lane & 7);
+            uint16_t *row = y + (int64_t)r * ldy;
+            const int h = (int)((0u - ((unsigned)reinterpret_cast<uintptr_t>(row) >> 1)) & 7u);
+            const int n = e < h ? e : h + (nc > h ? (nc - h) & ~7 : 0) + (e - h);
+            if (r < rows_left && n < nc) row[n] = *reinterpret_cast<const uint16_t *>(blk + r * pitch + 2 * n);
+        }
+}
+
 // Big-tile kernel for compute-bound sizes, M > 64 (atom_gemm_big.hip).
 hipError_t launch_big(const GemmParams &p, hipStream_t stream);
 

@@ -21,25 +21,15 @@
 
 #include <type_traits>
 
-#include "atom_gemm_common.h"
+#include "atom_gemm_f6.h"
 #include "atom_internal.h"
 #include "atom_launch.h"
 
 namespace {
 
-typedef int   v4i  __attribute__((ext_vector_type(4)));
-typedef int   v8i  __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
+using namespace atom_gemm_f6;             // vector types, LDS-DMA requests, order control, wait_imm
 
-constexpr int BM = 256, BN = 256;         // workgroup tile
-constexpr int NT = 256;                   // 4 wavefronts, 2 x 2, each 128 x 128 (4 x 4 MFMA tiles)
 constexpr int ROWB = 64;                  // bytes per tile row and K step: 128 FP4 or 64 FP8 channels
-constexpr int CODES = (BM + BN) * ROWB;   // 32 KB of codes per stage
-constexpr int STAGE = CODES + (BM + BN) * 4;   // + one scale dword per row
-constexpr int NLD = CODES / 16 / NT;      // 16-byte chunks per thread and step (8)
-constexpr int EPI_PITCH = 272;            // bytes per output row of a wavefront's LDS region
-constexpr int EPI_WAVE  = 64 * EPI_PITCH; // 64 rows per pass
-constexpr int LDS_BYTES = 4 * EPI_WAVE > 2 * STAGE ? 4 * EPI_WAVE : 2 * STAGE;
 
 struct MxParams {
     const uint8_t *a_q4, *a_q8, *a_e8;
@@ -73,277 +63,320 @@ __device__ __forceinline__ v8i join(v4i lo, v4i hi)
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// One K step per iteration: 64 bytes of every tile row, i.e. 64 FP8 channels (one MFMA per tile
-// pair; these outlier steps come first) or 128 FP4 channels (two MFMA sub-steps).  The accumulator
-// tiles of a wavefront live in the accumulation registers, everything else in the architectural
-// ones.  The operands go from global memory straight into LDS
-// (global_load_lds_dwordx4: lane i's 16 bytes land at the LDS address in M0 plus 16 i), so no
-// wavefront spends issue slots on staging registers and ds_write.  Four stages: while step u
-// is multiplied, tile u+1 has landed or is landing, tile u+2 is on its way and tile u+3 is
-// requested.  A wavefront
-// instruction fills one kilobyte = 16 tile rows; lane l supplies the chunk that the rotated
-// layout wants at its position: row l / 4 of the 16, chunk ((l % 4) - (l / 16)) % 4.
-// The loads are inline assembly, the compiler does not count them: the waits on vmcnt before
-// the barriers below are written by hand (ten loads per wavefront and tile, two tiles may
-// stay in flight).
-constexpr int DMA_STAGES = 4;
-
-__device__ __forceinline__ void dma16(uint32_t lds, uint32_t voff, const uint8_t *sbase)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(lds), "v"(voff), "s"(sbase) : "memory", "m0");
-}
 __device__ __forceinline__ void dma4(uint32_t lds, uint32_t voff, const uint8_t *sbase)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
                  :: "s"(lds), "v"(voff), "s"(sbase) : "memory", "m0");
 }
 
-// Geometry for WT x WT MFMA tiles per wavefront (2 x 2 wavefronts): WT = 4 is the 256 x 256
-// workgroup tile, WT = 2 a 128 x 128 tile for grids that would leave most of the GPU idle
-// with the large one (its 64 accumulator registers let two workgroups share a CU).
-template <int WT>
-struct DmaGeom {
-    static constexpr int TB     = 64 * WT;                 // tile rows = tile columns
-    static constexpr int CODES  = 2 * TB * ROWB;           // bytes of codes per stage
-    static constexpr int STAGE  = CODES + 2 * 256 * 4;     // + 256 A and 256 B scale dwords (rows past TB unused)
-    static constexpr int NBLK   = 2 * TB / 16 / 4;         // kilobyte blocks per wavefront and stage
-    static constexpr int PITCH  = 64 * WT + 16;            // output row of a wavefront in LDS, bytes
-    static constexpr int EPIW   = 64 * PITCH;              // 64 rows per pass
-    static constexpr int LDS    = DMA_STAGES * STAGE > 4 * EPIW ? DMA_STAGES * STAGE : 4 * EPIW;
-    static constexpr int LOADS  = NBLK + 2;                // DMA instructions per wavefront and tile
-    // s_waitcnt: vmcnt(2 * LOADS) (two tiles may stay in flight), lgkmcnt(0), expcnt untouched
-    static constexpr int LANDED = ((2 * LOADS) & 15) | (7 << 4) | (((2 * LOADS) >> 4) << 14);
+// WM x WN wavefronts (four or eight), each TM x TN MFMA tiles: a workgroup tile of 32 WM TM x 32 WN TN; ST stages in LDS.
+template <int WM, int WN, int TM, int TN, int ST>
+struct MxTile {
+    static constexpr int NW    = WM * WN, NT = 64 * NW;
+    static constexpr int BM    = 32 * WM * TM, BN = 32 * WN * TN;
+    static constexpr int CODES = (BM + BN) * ROWB;         // bytes of codes per stage, the A rows first
+    static constexpr int STAGE = CODES + (BM + BN) * 4;    // + one scale dword per row
+    static constexpr int NST   = ST;                       // LDS stages
+    static constexpr int NBLK  = (BM + BN) / 16;           // requests of a kilobyte (16 rows) per stage
+    static constexpr int J     = (NBLK + NW - 1) / NW;     // ... per wavefront
+    static constexpr int NSC   = (BM + BN) / 64;           // requests of 64 scale dwords per stage
+    static constexpr int JS    = (NSC + NW - 1) / NW;      // ... per wavefront
+    static constexpr int LOADS = J + JS;
+    static constexpr int SPARE = NST * STAGE;              // 16 bytes that are written and never read
+    static constexpr int LDS   = SPARE + 64;
+    static constexpr int PITCH = 64 * TN + 16;             // output staging: bytes per row of a wavefront's block
+    static constexpr int EPIW  = 32 * TM * PITCH;
+    static_assert(BM % 64 == 0 && BN % 64 == 0, "whole requests");
+    static_assert(NW * EPIW <= NST * STAGE && LDS <= 160 * 1024, "LDS");
+    static constexpr int PER_CU = 2 * LDS <= 160 * 1024 ? 2 : 1;
 };
 
-template <int WT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, WT == 4 ? 1 : 2)))
+// One K step per iteration: 64 bytes of every tile row, i.e. 64 FP8 channels (one MFMA per tile
+// pair; these outlier steps come first) or 128 FP4 channels (two MFMA sub-steps).  The operands go
+// from global memory straight into LDS (global_load_lds_dwordx4), so no wavefront spends issue slots
+// on staging registers and ds_write.  With four stages: while step u is multiplied, tile u+1 has
+// landed or is landing, tile u+2 is on its way and tile u+3 is requested.  A request fills one
+// kilobyte = 16 tile rows; lane l supplies the chunk that the rotated layout wants at its position:
+// row l / 4 of the 16, chunk ((l % 4) - (l / 16)) % 4.  The requests are inline assembly, the compiler does
+// not count them: the waits on vmcnt before the barriers are written by hand.
+//
+// What bounds it.  Many tiles: the power the matrix cores may take (M = 4096, N = K = 8192: the MFMAs alone, operands in
+// registers, 107 us, this kernel 126, the LDS reads and barriers alone 19, the requests alone 61).  Few tiles: the chain barrier,
+// fragment reads, MFMAs of one workgroup, so they run as small tiles, several workgroups of four wavefronts to a compute unit, whose barriers are
+// not each other's.  Either way
+//   * an in-order wavefront that issues its requests in one go waits until the memory path has taken them (16 cycles
+//     each, all wavefronts of the CU in turn) and its MFMAs wait behind: every SIMD has two wavefronts or more, and
+//     a wavefront's requests stand one at a time behind MFMAs (M = 1024, K = 4096, N = 22016 with 256 x 256 tiles: 70 us
+//     with one wavefront per SIMD and all requests at the step's start, 58 so);
+//   * the weights are the row operand of the MFMA, so that a lane holds four consecutive columns of a
+//     row of Y and the output staging is a quarter of the LDS writes.
+template <int WM, int WN, int TM, int TN, int ST>
+__global__ __launch_bounds__(64 * WM * WN, (WM * WN / 4 * MxTile<WM, WN, TM, TN, ST>::PER_CU))
 void mx_gemm_dma_kernel(MxParams p)
 {
-    using Gm = DmaGeom<WT>;
-    constexpr int TB = Gm::TB, CODES_ = Gm::CODES, STAGE_ = Gm::STAGE, NBLK = Gm::NBLK;
+    using Gm = MxTile<WM, WN, TM, TN, ST>;
+    constexpr int BM = Gm::BM, BN = Gm::BN, NW = Gm::NW, J = Gm::J, JS = Gm::JS, LOADS = Gm::LOADS, STAGE = Gm::STAGE, NST = Gm::NST;
     extern __shared__ __align__(16) uint8_t smem[];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave % WM, wn = wave / WM;
     const int lr = lane & 31, g = lane >> 5;
 
-    const int tiles_m = (int)((p.M + TB - 1) / TB);
+    const int tiles_m = (int)((p.M + BM - 1) / BM);
     const int bid = atom_gemm::xcd_contiguous_block_id();
-    const int64_t m0 = (int64_t)(bid % tiles_m) * TB, n0 = (int64_t)(bid / tiles_m) * TB;
+    const int64_t m0 = (int64_t)(bid % tiles_m) * BM, n0 = (int64_t)(bid / tiles_m) * BN;
 
     const int K4 = p.K - p.O;
     const int S4 = K4 >> 7, S8 = p.O >> 6, S = S4 + S8;
 
-    // ---- loader: wavefront w fills the kilobyte blocks NBLK w .. NBLK w + NBLK - 1 of a stage
-    // (the first half of the blocks are the A rows: wavefronts 0, 1 load A, wavefronts 2, 3
-    // load B) and 64 of the A and 64 of the B scale dwords
-    const bool loadsA = wave < 2;
-    uint32_t goff[NBLK];
+    // ---- loader: kilobyte block b = NW j + wave of a stage are its rows 16 b .. 16 b + 15; ragged tiles repeat the last
+    // row.  Request b of the scales are the dwords of rows 64 b .. 64 b + 63.
+    uint32_t goff[J];
 #pragma unroll
-    for (int j = 0; j < NBLK; ++j) {
-        const int trow = 16 * (NBLK * wave + j) + (lane >> 2);           // row of the 2 TB-row stage
-        int64_t r = loadsA ? m0 + trow : n0 + (trow - TB);
-        const int64_t last = (loadsA ? p.M : p.N) - 1;
-        r = r < last ? r : last;                                         // ragged tiles repeat the last row
+    for (int j = 0; j < J; ++j) {
+        const int b = NW * j + wave, trow = 16 * b + (lane >> 2);
+        const bool act = b < BM / 16;
+        int64_t r = act ? m0 + trow : n0 + (trow - BM);
+        const int64_t last = (act ? p.M : p.N) - 1;
+        r = r < last ? r : last;
         goff[j] = (uint32_t)r * ROWB + 16u * (((lane & 3) - (lane >> 4)) & 3);
     }
-    const uint32_t sca = (uint32_t)(m0 + 64 * wave + lane < p.M ? m0 + 64 * wave + lane : p.M - 1) * 4u;
-    const uint32_t scb = (uint32_t)(n0 + 64 * wave + lane < p.N ? n0 + 64 * wave + lane : p.N - 1) * 4u;
-    const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(smem);
-    // steps 0 .. S8-1 are the FP8 (outlier) steps, the FP4 steps follow
-    auto request = [&](int u, int buf) __attribute__((always_inline)) {
+    uint32_t soff[JS];
+#pragma unroll
+    for (int j = 0; j < JS; ++j) {
+        const int b = NW * j + wave;
+        const bool act = b < BM / 64;
+        int64_t r = act ? m0 + 64 * b + lane : n0 + (64 * b - BM) + lane;
+        const int64_t last = (act ? p.M : p.N) - 1;
+        soff[j] = (uint32_t)(r < last ? r : last) * 4u;
+    }
+    const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(smem), spare = lds0 + Gm::SPARE;
+    // where tile u's codes and scales start; steps 0 .. S8-1 are the FP8 (outlier) steps, the FP4 steps follow
+    struct Src { const uint8_t *a, *w, *ae, *we; };
+    auto src_of = [&](int u) __attribute__((always_inline)) -> Src {
         const bool    f8 = u < S8;
         const int64_t sl = f8 ? u : u - S8;                        // slab index inside q8 or q4
         const int64_t d  = f8 ? S4 + (u >> 1) : u - S8;            // slab index inside e8
-        const uint8_t *src = loadsA ? (f8 ? p.a_q8 : p.a_q4) + sl * p.M * ROWB
-                                    : (f8 ? p.w_q8 : p.w_q4) + sl * p.N * ROWB;
-        const uint32_t st = lds0 + buf * STAGE_;
+        return {(f8 ? p.a_q8 : p.a_q4) + sl * p.M * ROWB, (f8 ? p.w_q8 : p.w_q4) + sl * p.N * ROWB,
+                p.a_e8 + d * p.M * 4, p.w_e8 + d * p.N * 4};
+    };
+    // request k of a tile into stage `buf` (the same number per wavefront: the waits count them)
+    auto request = [&](int k, const Src &s, int buf) __attribute__((always_inline)) {
+        const uint32_t st = lds0 + buf * STAGE;
+        if (k < J) {
+            const int b = NW * k + wave;
+            const uint8_t *base = NW * (k + 1) <= BM / 16 ? s.a : NW * k >= BM / 16 ? s.w : b < BM / 16 ? s.a : s.w;
+            if (NW * (k + 1) <= Gm::NBLK) dma16(st + 1024 * b, goff[k], base);
+            else dma16_masked(b < Gm::NBLK ? st + 1024 * b : spare, goff[k], base, b < Gm::NBLK ? ~0ull : 1ull);
+        } else {
+            const int b = NW * (k - J) + wave;
+            const uint8_t *base = NW * (k - J + 1) <= BM / 64 ? s.ae : NW * (k - J) >= BM / 64 ? s.we : b < BM / 64 ? s.ae : s.we;
+            if (NW * (k - J + 1) <= Gm::NSC || b < Gm::NSC) dma4(st + Gm::CODES + 256 * b, soff[k < J ? 0 : k - J], base);
+            else dma16_masked(spare, 0u, s.a, 1ull);
+        }
+    };
+    auto request_all = [&](int u, int buf) __attribute__((always_inline)) {
+        const Src s = src_of(u);
 #pragma unroll
-        for (int j = 0; j < NBLK; ++j) dma16(st + 1024 * (NBLK * wave + j), goff[j], src);
-        dma4(st + CODES_ + 256 * wave, sca, p.a_e8 + d * p.M * 4);
-        dma4(st + CODES_ + 1024 + 256 * wave, scb, p.w_e8 + d * p.N * 4);
+        for (int k = 0; k < LOADS; ++k) request(k, s, buf);
     };
     // all but the two newest tiles' loads of this wavefront have landed, and its own LDS reads are done
-#define ATOM_MX_LANDED() __builtin_amdgcn_s_waitcnt(Gm::LANDED)
+    auto landed = [&]() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(wait_imm((NST - 2) * LOADS)); };
 
-    v16f acc[WT][WT];
+    v16f acc[TM][TN];
 #pragma unroll
-    for (int s = 0; s < WT; ++s)
+    for (int s = 0; s < TM; ++s)
 #pragma unroll
-        for (int t = 0; t < WT; ++t)
+        for (int t = 0; t < TN; ++t)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[s][t][v] = 0.0f;
 
-    const int a_base = mx_lds_off(32 * WT * wm + lr, g);
-    const int b_base = mx_lds_off(TB + 32 * WT * wn + lr, g);
-    const int sa_off = CODES_ + 4 * (32 * WT * wm + lr), sb_off = CODES_ + 1024 + 4 * (32 * WT * wn + lr);
-    int sa[WT], sb[WT];
+    const int a_base = mx_lds_off(32 * TM * wm + lr, g);
+    const int b_base = mx_lds_off(BM + 32 * TN * wn + lr, g);
+    const int sa_off = Gm::CODES + 4 * (32 * TM * wm + lr), sb_off = Gm::CODES + 4 * (BM + 32 * TN * wn + lr);
+    int sa[TM], sb[TN];
     auto read_scales = [&](const uint8_t *buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int s = 0; s < WT; ++s) {
-            sa[s] = (int)(*reinterpret_cast<const uint32_t *>(buf + sa_off + 128 * s) >> (8 * g));
-            sb[s] = (int)(*reinterpret_cast<const uint32_t *>(buf + sb_off + 128 * s) >> (8 * g));
-        }
-    };
-    auto mma = [&](auto fmt, auto opsel, const v8i (&af)[WT], const v8i (&bf)[WT], const int (&sa_)[WT],
-                   const int (&sb_)[WT]) __attribute__((always_inline)) {
+        for (int s = 0; s < TM; ++s) sa[s] = (int)(*reinterpret_cast<const uint32_t *>(buf + sa_off + 128 * s) >> (8 * g));
 #pragma unroll
-        for (int s = 0; s < WT; ++s)
-#pragma unroll
-            for (int t = 0; t < WT; ++t)
-                acc[s][t] = mfma_mx<decltype(fmt)::value, decltype(opsel)::value>(af[s], bf[t], acc[s][t],
-                                                                                  sa_[s], sb_[t]);
+        for (int t = 0; t < TN; ++t) sb[t] = (int)(*reinterpret_cast<const uint32_t *>(buf + sb_off + 128 * t) >> (8 * g));
     };
     using fp4 = std::integral_constant<int, 4>;
     using fp8 = std::integral_constant<int, 0>;
     using b0  = std::integral_constant<int, 0>;
     using b2  = std::integral_constant<int, 2>;
+    // the MFMAs of a sub-step; `after(i)` runs behind the i-th
+    auto mma = [&](auto fmt, auto opsel, const v8i (&af)[TM], const v8i (&bf)[TN], const int (&sa_)[TM],
+                   const int (&sb_)[TN], auto after) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < TM; ++s)
+#pragma unroll
+            for (int t = 0; t < TN; ++t) {
+                acc[s][t] = mfma_mx<decltype(fmt)::value, decltype(opsel)::value>(bf[t], af[s], acc[s][t], sb_[t], sa_[s]);
+                ATOM_F6_PIN(acc[s][t]);
+                after(s * TN + t);
+            }
+    };
+    auto nothing = [](int) {};
 
-    // stage indices of tiles u, u+1, u+2, u+3
-    int cur = 0, nxt = 1, nx2 = 2, nx3 = 3;
-    request(0, 0);
-    request(min(1, S - 1), 1);
-    request(min(2, S - 1), 2);
-    ATOM_MX_LANDED();
+    int cur = 0;                                           // stage of tile u
+#pragma unroll
+    for (int v = 0; v < NST - 1; ++v) request_all(min(v, S - 1), v);
+    landed();
     __syncthreads();
 
     // ---- FP8 steps first, in pairs
-    auto load8 = [&](const uint8_t *buf, v8i (&af8)[WT], v8i (&bf8)[WT]) __attribute__((always_inline)) {
+    int u = 0;
+    auto fp8_step = [&](auto opsel) __attribute__((always_inline)) {
+        request_all(min(u + NST - 1, S - 1), cur == 0 ? NST - 1 : cur - 1);
+        const uint8_t *buf = smem + cur * STAGE;
+        v8i af8[TM], bf8[TN];
 #pragma unroll
-        for (int s = 0; s < WT; ++s) {
+        for (int s = 0; s < TM; ++s)
             af8[s] = join(*reinterpret_cast<const v4i *>(buf + (a_base + 2048 * s)),
                           *reinterpret_cast<const v4i *>(buf + ((a_base ^ 32) + 2048 * s)));
-            bf8[s] = join(*reinterpret_cast<const v4i *>(buf + (b_base + 2048 * s)),
-                          *reinterpret_cast<const v4i *>(buf + ((b_base ^ 32) + 2048 * s)));
-        }
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+            bf8[t] = join(*reinterpret_cast<const v4i *>(buf + (b_base + 2048 * t)),
+                          *reinterpret_cast<const v4i *>(buf + ((b_base ^ 32) + 2048 * t)));
+        read_scales(buf);
+        mma(fp8{}, opsel, af8, bf8, sa, sb, nothing);
+        landed();
+        __syncthreads();
+        cur = cur + 1 == NST ? 0 : cur + 1;
+        ++u;
     };
-#define ATOM_MX_ROTATE()                                                                         \
-    do {                                                                                         \
-        const int t_ = cur;                                                                      \
-        cur = nxt;                                                                               \
-        nxt = nx2;                                                                               \
-        nx2 = nx3;                                                                               \
-        nx3 = t_;                                                                                \
-    } while (0)
-#define ATOM_MX_FP8_STEP(u, OPSEL)                                                               \
-    do {                                                                                         \
-        request(min((u) + 3, S - 1), nx3);                                                       \
-        v8i af8[WT], bf8[WT];                                                                    \
-        load8(smem + cur * STAGE_, af8, bf8);                                                    \
-        read_scales(smem + cur * STAGE_);                                                        \
-        mma(fp8{}, OPSEL{}, af8, bf8, sa, sb);                                                   \
-        ATOM_MX_LANDED();                                                                        \
-        __syncthreads();                                                                         \
-        ATOM_MX_ROTATE();                                                                        \
-    } while (0)
-    int u = 0;
-    for (; u < S8; u += 2) {
-        ATOM_MX_FP8_STEP(u, b0);
-        ATOM_MX_FP8_STEP(u + 1, b2);
+    while (u < S8) {
+        fp8_step(b0{});
+        fp8_step(b2{});
     }
-#undef ATOM_MX_FP8_STEP
 
     // ---- FP4 steps, software-pipelined: the second sub-step's fragments are read under the first
     // sub-step's MFMAs, the next step's first fragments and scales under the second's
-    v8i af[WT], bf[WT];
+    v8i af[TM], bf[TN];
+    auto read_half = [&](v8i (&x)[TM], v8i (&y)[TN], const uint8_t *buf, int half) __attribute__((always_inline)) {
 #pragma unroll
-    for (int s = 0; s < WT; ++s) {
-        af[s] = widen(*reinterpret_cast<const v4i *>(smem + cur * STAGE_ + (a_base + 2048 * s)));
-        bf[s] = widen(*reinterpret_cast<const v4i *>(smem + cur * STAGE_ + (b_base + 2048 * s)));
-    }
-    read_scales(smem + cur * STAGE_);
+        for (int s = 0; s < TM; ++s) x[s] = widen(*reinterpret_cast<const v4i *>(buf + ((a_base ^ half) + 2048 * s)));
+#pragma unroll
+        for (int t = 0; t < TN; ++t) y[t] = widen(*reinterpret_cast<const v4i *>(buf + ((b_base ^ half) + 2048 * t)));
+    };
+    read_half(af, bf, smem + cur * STAGE, 0);
+    read_scales(smem + cur * STAGE);
+    Src ahead = src_of(min(u + NST - 1, S - 1));
     for (; u < S; ++u) {
-        const uint8_t *buf = smem + cur * STAGE_, *nbuf = smem + nxt * STAGE_;
-        request(min(u + 3, S - 1), nx3);
-        v8i ag[WT], bg[WT];
+        const uint8_t *buf = smem + cur * STAGE;
+        const int into = cur == 0 ? NST - 1 : cur - 1;
+        cur = cur + 1 == NST ? 0 : cur + 1;
+        const uint8_t *nbuf = smem + cur * STAGE;
+        v8i ag[TM], bg[TN];
+        read_half(ag, bg, buf, 32);
+        mma(fp4{}, b0{}, af, bf, sa, sb, [&](int i) __attribute__((always_inline)) {
 #pragma unroll
-        for (int s = 0; s < WT; ++s) {
-            ag[s] = widen(*reinterpret_cast<const v4i *>(buf + ((a_base ^ 32) + 2048 * s)));
-            bg[s] = widen(*reinterpret_cast<const v4i *>(buf + ((b_base ^ 32) + 2048 * s)));
-        }
-        mma(fp4{}, b0{}, af, bf, sa, sb);
-        // the reads go out under the first MFMAs, the remaining MFMAs cover them
-#pragma unroll
-        for (int i = 0; i < 2 * WT; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        if (WT * WT > 2 * WT) __builtin_amdgcn_sched_group_barrier(0x008, WT * WT - 2 * WT, 0);
-        ATOM_MX_LANDED();                 // tile u+1 is in its stage ...
+            for (int k = 0; k < LOADS; ++k)
+                if (k * (TM * TN) / LOADS == i) request(k, ahead, into);
+        });
+        if (u + NST < S) { ahead.a += p.M * ROWB; ahead.w += p.N * ROWB; ahead.ae += p.M * 4; ahead.we += p.N * 4; }
+        landed();                         // tile u+1 is in its stage ...
         __syncthreads();                  // ... for every wavefront; stage u has been read
         __builtin_amdgcn_sched_barrier(0);
-        int sc[WT], sd[WT];
+        int sc[TM], sd[TN];
 #pragma unroll
-        for (int s = 0; s < WT; ++s) {
-            sc[s] = sa[s];
-            sd[s] = sb[s];
-            af[s] = widen(*reinterpret_cast<const v4i *>(nbuf + (a_base + 2048 * s)));
-            bf[s] = widen(*reinterpret_cast<const v4i *>(nbuf + (b_base + 2048 * s)));
-        }
+        for (int s = 0; s < TM; ++s) sc[s] = sa[s];
+#pragma unroll
+        for (int t = 0; t < TN; ++t) sd[t] = sb[t];
+        read_half(af, bf, nbuf, 0);
         read_scales(nbuf);
-        mma(fp4{}, b2{}, ag, bg, sc, sd);
-#pragma unroll
-        for (int i = 0; i < 2 * WT; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
-            __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);
-        }
-        if (WT * WT > 2 * WT) __builtin_amdgcn_sched_group_barrier(0x008, WT * WT - 2 * WT, 1);
+        mma(fp4{}, b2{}, ag, bg, sc, sd, nothing);
         __builtin_amdgcn_sched_barrier(0);
-        ATOM_MX_ROTATE();
     }
-#undef ATOM_MX_ROTATE
-#undef ATOM_MX_LANDED
 
-    // ---- store: through LDS, so that global memory sees 16-byte row pieces; the last (repeated)
-    // requests must have landed before the stages are reused
-    __builtin_amdgcn_s_waitcnt(0x0F70);                            // vmcnt(0)
-    const int64_t wrow = m0 + 32 * WT * wm, wcol = n0 + 32 * WT * wn;
-    const bool whole = wrow + 32 * WT <= p.M && wcol + 32 * WT <= p.N && (p.ldy & 7) == 0 &&
-                       (reinterpret_cast<uintptr_t>(p.y) & 15) == 0;
+    // ---- store: a lane holds four consecutive columns of one row of Y at a time; through LDS, so that global memory sees
+    // 16-byte row pieces.  The last (repeated) requests must have landed before the stages are reused.
+    __builtin_amdgcn_s_waitcnt(wait_imm(0));
     __syncthreads();
-    if (whole) {
-        // passes of 64 rows; a row of the wavefront's block is 64 WT bytes = 4 WT lanes of 16 bytes
-        uint8_t *reg = smem + wave * Gm::EPIW;
-        constexpr int LPR = 4 * WT;                                // lanes per output row
+    const int64_t wrow = m0 + 32 * TM * wm, wcol = n0 + 32 * TN * wn;
+    uint8_t *reg = smem + wave * Gm::EPIW;
 #pragma unroll
-        for (int pass = 0; pass < WT / 2; ++pass) {
+    for (int s = 0; s < TM; ++s)
 #pragma unroll
-            for (int sh = 0; sh < 2; ++sh)
+        for (int t = 0; t < TN; ++t)
 #pragma unroll
-                for (int t = 0; t < WT; ++t)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int r = 32 * sh + 8 * (v >> 2) + 4 * g + (v & 3);
-                        *reinterpret_cast<uint16_t *>(reg + r * Gm::PITCH + 2 * (32 * t + lr)) =
-                            __half_as_ushort(__float2half_rn(acc[2 * pass + sh][t][v]));
-                    }
-#pragma unroll
-            for (int i = 0; i < 64 * LPR / 64; ++i) {
-                const int r = (64 / LPR) * i + lane / LPR;
-                const v4i d = *reinterpret_cast<const v4i *>(reg + r * Gm::PITCH + 16 * (lane % LPR));
-                *reinterpret_cast<v4i *>(p.y + (wrow + 64 * pass + r) * p.ldy + wcol + 8 * (lane % LPR)) = d;
+            for (int q = 0; q < 4; ++q) {
+                const v2h lo = __builtin_convertvector((v2f{acc[s][t][4 * q], acc[s][t][4 * q + 1]}), v2h);
+                const v2h hi = __builtin_convertvector((v2f{acc[s][t][4 * q + 2], acc[s][t][4 * q + 3]}), v2h);
+                *reinterpret_cast<v2u *>(reg + (32 * s + lr) * Gm::PITCH + (32 * t + 8 * q + 4 * g) * 2) =
+                    v2u{__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi)};
             }
+    // (LDS only, and the wavefront reads what it wrote itself)
+    constexpr int ROWS = 32 * TM, COLS = 32 * TN, LPR = COLS / 8;      // LPR 16-byte pieces per row of the wavefront's block
+    uint16_t *yb = p.y + wrow * p.ldy + wcol;
+    if (((reinterpret_cast<uintptr_t>(p.y) | (uintptr_t)(p.ldy * 2)) & 15) == 0 && wrow + ROWS <= p.M && wcol + COLS <= p.N) {
+#pragma unroll
+        for (int i = 0; i < ROWS * LPR / 64; ++i) {
+            const int q = 64 * i + lane, r = q / LPR, c = q % LPR;
+            *reinterpret_cast<v4i *>(yb + r * p.ldy + 8 * c) = *reinterpret_cast<const v4i *>(reg + r * Gm::PITCH + 16 * c);
         }
     } else {
-        const int64_t row0 = wrow + 4 * g, col0 = wcol + lr;
-        uint16_t *yp = p.y + row0 * p.ldy + col0;
-#pragma unroll
-        for (int s = 0; s < WT; ++s)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int dr = 32 * s + 8 * (v >> 2) + (v & 3);
-                if (row0 + dr < p.M) {
-                    uint16_t *yr = yp + (int64_t)dr * p.ldy;
-#pragma unroll
-                    for (int t = 0; t < WT; ++t)
-                        if (col0 + 32 * t < p.N) yr[32 * t] = __half_as_ushort(__float2half_rn(acc[s][t][v]));
-                }
-            }
+        const int64_t rows = p.M - wrow, cols = p.N - wcol;            // may be none
+        if (rows > 0 && cols > 0)
+            atom_gemm::store_block_any<ROWS, COLS>(reg, Gm::PITCH, yb, p.ldy, (int)(rows < ROWS ? rows : ROWS), (int)(cols < COLS ? cols : COLS), lane);
     }
 }
 
+template <int WM, int WN, int TM, int TN, int ST>
+hipError_t launch_tile(const MxParams &p, hipStream_t stream)
+{
+    using Gm = MxTile<WM, WN, TM, TN, ST>;
+    auto kern = &mx_gemm_dma_kernel<WM, WN, TM, TN, ST>;
+    static atom_launch::LdsOptIn opt_in;   // one attribute call per kernel variant and device
+    hipError_t err = atom_launch::ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(kern), Gm::LDS);
+    if (err != hipSuccess) return err;
+    const int64_t tiles = ((p.M + Gm::BM - 1) / Gm::BM) * ((p.N + Gm::BN - 1) / Gm::BN);
+    hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(Gm::NT), Gm::LDS, stream, p);
+    return hipGetLastError();
+}
+
+// Which tile.  The cost of a launch, in microseconds per K step, with f tiles per compute unit: `full` for each whole tile
+// every compute unit has, and for a last part r of them what they add when few compute units have one (`alone` where it is
+// all there is, `more` beside other workgroups), growing to `full` as the chip fills and the power limit sets in.  Measured
+// at 47 sizes, K = 1024 to 14336 (us; the choice is the fastest of the five or, at worst, 5 % behind it):
+//   M = 65,   N = 4096,  K = 4096:   64 x 64 9.2, 64 x 128 10.7, 128 x 128 11.4, 256 x 256 24.1
+//   M = 256,  N = 12288, K = 4096:   64 x 64 15.1, 64 x 128 14.5, 128 x 128 11.9, 128 x 256 17.4
+//   M = 512,  N = 4096,  K = 4096:   64 x 64 11.3, 64 x 128 10.7, 128 x 128 11.2, 128 x 256 17.0
+//   M = 777,  N = 13824, K = 5120:   64 x 64 55.3, 64 x 128 48.7, 128 x 128 35.9, 128 x 256 39.7, 256 x 256 36.9
+//   M = 1024, N = 22016, K = 4096:   64 x 128 77.9, 128 x 128 56.4, 128 x 256 55.9, 256 x 256 57.9
+//   M = 4096, N = 22016, K = 4096:   128 x 128 265.9, 128 x 256 219.5, 256 x 256 203.6
+// (The kernel before, 256 x 256 and 128 x 128 with four wavefronts: 14.4, 15.8, 15.3, 43.8, 69.8 and 230.1.)
+enum Tile { k64x64, k64x128, k128x128, k128x256, k256x256, kTiles };
+struct TileCost { int bm, bn; float alone, more, full; };
+constexpr TileCost kCost[kTiles] = {{64, 64, 0.150f, 0.080f, 0.125f}, {64, 128, 0.190f, 0.110f, 0.205f}, {128, 128, 0.235f, 0.110f, 0.300f},
+                                    {128, 256, 0.380f, 0.280f, 0.590f}, {256, 256, 0.600f, 0.600f, 1.050f}};
+
+int64_t tiles_of(const TileCost &t, int64_t M, int64_t N) { return ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn); }
+
+Tile pick_tile(int64_t M, int64_t N, int cus)
+{
+    Tile best = k256x256;
+    float least = 0.0f;
+    for (int i = kTiles - 1; i >= 0; --i) {
+        const int64_t tiles = tiles_of(kCost[i], M, N);
+        if (tiles > 0x7fffff) continue;                    // (the grid's limit in threads; the 256 x 256 tile takes what is left)
+        const TileCost &t = kCost[i];
+        const float r = (float)(tiles % cus) / (float)cus, few = tiles < cus ? t.alone : t.more;
+        const float cost = t.full * (float)(tiles / cus) + (r > 0.0f ? few + (t.full - few) * r * r * r : 0.0f);
+        if (least == 0.0f || cost < least) { least = cost; best = (Tile)i; }
+    }
+    return best;
+}
+
 }  // namespace
+
+// Which tile a launch takes, as the test of the tiles asks it (rows and columns of the tile in one number).
+extern "C" int atom_internal_mx_tile(int64_t M, int64_t N, int64_t cus)
+{
+    const TileCost &t = kCost[pick_tile(M, N, (int)cus)];
+    return 1000 * t.bm + t.bn;
+}
 
 namespace atom_internal {
 
@@ -355,22 +388,15 @@ hipError_t launch_mx_gemm(const void *a_q4, const void *a_q8, const void *a_e8, 
     p.a_q4 = (const uint8_t *)a_q4; p.a_q8 = (const uint8_t *)a_q8; p.a_e8 = (const uint8_t *)a_e8;
     p.w_q4 = (const uint8_t *)w_q4; p.w_q8 = (const uint8_t *)w_q8; p.w_e8 = (const uint8_t *)w_e8;
     p.y = (uint16_t *)y; p.M = M; p.N = N; p.ldy = ldy; p.K = K; p.O = O;
-    const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-    if (tiles >= 192) {
-        static atom_launch::LdsOptIn opt_in;
-        hipError_t err = atom_launch::ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(&mx_gemm_dma_kernel<4>), DmaGeom<4>::LDS);
-        if (err != hipSuccess) return err;
-        hipLaunchKernelGGL(mx_gemm_dma_kernel<4>, dim3((unsigned)tiles), dim3(NT), DmaGeom<4>::LDS, stream, p);
-    } else {
-        // fewer 256 x 256 tiles than would occupy three quarters of the CUs: 128 x 128 tiles, two
-        // workgroups per CU (measured on M = 1024, K = 11008, N = 4096: 82 -> 40 us)
-        const int64_t small = ((M + 127) / 128) * ((N + 127) / 128);
-        static atom_launch::LdsOptIn opt_in;
-        hipError_t err = atom_launch::ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(&mx_gemm_dma_kernel<2>), DmaGeom<2>::LDS);
-        if (err != hipSuccess) return err;
-        hipLaunchKernelGGL(mx_gemm_dma_kernel<2>, dim3((unsigned)small), dim3(NT), DmaGeom<2>::LDS, stream, p);
+    const int cus = atom_launch::compute_units();
+    switch (pick_tile(M, N, cus)) {
+    case k64x64:   return launch_tile<2, 2, 1, 1, 4>(p, stream);
+    case k64x128:  return launch_tile<2, 2, 1, 2, 6>(p, stream);
+    case k128x128:                                         // up to one per compute unit with four stages, else three workgroups per compute unit
+        return tiles_of(kCost[k128x128], M, N) <= cus ? launch_tile<2, 2, 2, 2, 4>(p, stream) : launch_tile<2, 2, 2, 2, 3>(p, stream);
+    case k128x256: return launch_tile<2, 4, 2, 2, 3>(p, stream);
+    default:       return launch_tile<4, 2, 2, 4, 4>(p, stream);
     }
-    return hipGetLastError();
 }
 
 }  // namespace atom_internal
