@@ -395,24 +395,7 @@ void w4a4_gemm_big_kernel(const GemmParams p)
     }
     __syncthreads();
     if (ks != 0) return;
-    const int64_t mw = m0 + wm * 64, nw = n0 + wn * 64;
-    const bool vec_ok = ((reinterpret_cast<uintptr_t>(p.y) | (uintptr_t)(p.ldy * 2)) & 15) == 0;
-#pragma unroll
-    for (int it = 0; it < 8; ++it) {
-        const int row = it * 8 + (lane >> 3), ch = lane & 7;
-        const int64_t m = mw + row, n = nw + ch * 8;
-        if (m >= p.M || n >= p.N) continue;
-        const uint4 v = *reinterpret_cast<const uint4 *>(ot + row * OSTRIDE + ch * 16);
-        uint16_t *dst = p.y + m * p.ldy + n;
-        if (vec_ok && n + 8 <= p.N) {
-            *reinterpret_cast<uint4 *>(dst) = v;
-        } else {
-            const uint16_t *hv = reinterpret_cast<const uint16_t *>(&v);
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (n + k < p.N) dst[k] = hv[k];
-        }
-    }
+    store_block<64, 64>(ot, OSTRIDE, p.y, p.ldy, m0 + wm * 64, n0 + wn * 64, p.M, p.N, lane);
 }
 
 template <int BM, int BN, int KS, bool DBG>

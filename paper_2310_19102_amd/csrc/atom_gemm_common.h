@@ -48,6 +48,27 @@ __device__ __forceinline__ int xcd_contiguous_block_id()
     return xcd * per + (xcd < rem ? xcd : rem) + (b >> 3);
 }
 
+// Eight fp16 elements from element h (0 .. 7) of the sixteen in (lo, hi).
+__device__ __forceinline__ v4i from_element(const v4i &lo, const v4i &hi, unsigned h)
+{
+    unsigned w[8] = {(unsigned)lo[0], (unsigned)lo[1], (unsigned)lo[2], (unsigned)lo[3],
+                     (unsigned)hi[0], (unsigned)hi[1], (unsigned)hi[2], (unsigned)hi[3]};
+#pragma unroll
+    for (int j = 0; j < 6; ++j) { const unsigned stay = w[j], move = w[j + 2]; w[j] = h & 4 ? move : stay; }
+#pragma unroll
+    for (int j = 0; j < 5; ++j) { const unsigned stay = w[j], move = w[j + 1]; w[j] = h & 2 ? move : stay; }
+    v4i d;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) d[j] = (int)__builtin_amdgcn_alignbit(w[j + 1], w[j], 16 * (h & 1));
+    return d;
+}
+
+// Elements of a row in front of its first 16-byte aligned one.
+__device__ __forceinline__ unsigned to_aligned(const uint16_t *row)
+{
+    return (0u - ((unsigned)reinterpret_cast<uintptr_t>(row) >> 1)) & 7u;
+}
+
 // A finished block of Y (ROWS x COLS fp16; its rows `pitch` >= 2 COLS + 16 bytes apart in LDS, 16-byte aligned) to rows of Y
 // that start on any element (an odd row length, a view): whole 16-byte pieces wherever 16-byte aligned addresses lie in
 // the row, put together from two neighbouring pieces of the staged row, then what is left at its two ends, eight lanes per
@@ -62,35 +83,49 @@ __device__ __forceinline__ void store_block_any(const unsigned char *blk, int pi
     static_assert(ROWS * LPR % 64 == 0 && ROWS % 8 == 0, "whole wavefronts");
     const int nc = cols_left < COLS ? cols_left : COLS;
 #pragma unroll 2
-    for (int i = 0; i < ROWS * LPR / 64; ++i) {
+    for (int i = 0; i < ROWS * LPR / 64 && 64 * i < LPR * rows_left; ++i) {
         const int q = 64 * i + lane, r = q / LPR, k = q % LPR;
         uint16_t *row = y + (int64_t)r * ldy;
-        const unsigned h = (0u - ((unsigned)reinterpret_cast<uintptr_t>(row) >> 1)) & 7u;     // elements before the first aligned piece
+        const unsigned h = to_aligned(row);
         const v4i lo = *reinterpret_cast<const v4i *>(blk + r * pitch + 16 * k);
         const v4i hi = *reinterpret_cast<const v4i *>(blk + r * pitch + 16 * k + 16);
-        unsigned w[8] = {(unsigned)lo[0], (unsigned)lo[1], (unsigned)lo[2], (unsigned)lo[3],
-                         (unsigned)hi[0], (unsigned)hi[1], (unsigned)hi[2], (unsigned)hi[3]};
-#pragma unroll
-        for (int j = 0; j < 6; ++j) { const unsigned stay = w[j], move = w[j + 2]; w[j] = h & 4 ? move : stay; }
-#pragma unroll
-        for (int j = 0; j < 5; ++j) { const unsigned stay = w[j], move = w[j + 1]; w[j] = h & 2 ? move : stay; }
-        const unsigned sh = 16 * (h & 1);
-        v4i d;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) d[j] = (int)__builtin_amdgcn_alignbit(w[j + 1], w[j], sh);
+        const v4i d = from_element(lo, hi, h);
         if (r < rows_left && (int)h + 8 * k + 8 <= nc) *reinterpret_cast<v4i *>(row + h + 8 * k) = d;
     }
     // slot e of a row: its first h elements, then those behind the last whole piece (a block of all COLS columns has eight
     // or none of them, a cut one up to fourteen)
+    if (((reinterpret_cast<uintptr_t>(y) | (uintptr_t)(ldy * 2)) & 15) == 0 && (nc & 7) == 0) return;
     for (int e0 = 0; e0 < (nc == COLS ? 8 : 16); e0 += 8)
 #pragma unroll 2
-        for (int i = 0; i < ROWS / 8; ++i) {
+        for (int i = 0; i < ROWS / 8 && 8 * i < rows_left; ++i) {
             const int r = 8 * i + (lane >> 3), e = e0 + (lane & 7);
             uint16_t *row = y + (int64_t)r * ldy;
-            const int h = (int)((0u - ((unsigned)reinterpret_cast<uintptr_t>(row) >> 1)) & 7u);
+            const int h = (int)to_aligned(row);
             const int n = e < h ? e : h + (nc > h ? (nc - h) & ~7 : 0) + (e - h);
             if (r < rows_left && n < nc) row[n] = *reinterpret_cast<const uint16_t *>(blk + r * pitch + 2 * n);
         }
+}
+
+// The block of Y whose first element is (m, n), cut at M and N.
+template <int ROWS, int COLS>
+__device__ __forceinline__ void store_block(const unsigned char *blk, int pitch, uint16_t *y, int64_t ldy, int64_t m, int64_t n,
+                                            int64_t M, int64_t N, int lane)
+{
+    constexpr int LPR = COLS / 8;
+    static_assert(64 % LPR == 0, "a step of the loop is whole rows");
+    if (m >= M || n >= N) return;
+    const int rows = (int)(M - m < ROWS ? M - m : ROWS);
+    uint16_t *first = y + m * ldy + n;
+    if (((reinterpret_cast<uintptr_t>(y) | (uintptr_t)(ldy * 2)) & 15) == 0 && n + COLS <= N) {
+        const int r = lane / LPR, k = lane % LPR;
+        uint16_t *const mine = first + r * ldy + 8 * k;
+#pragma unroll
+        for (int i = 0; i < ROWS * LPR / 64; ++i)
+            if (i * (64 / LPR) + r < rows)
+                *reinterpret_cast<v4i *>(mine + i * (64 / LPR) * ldy) = *reinterpret_cast<const v4i *>(blk + (i * (64 / LPR) + r) * pitch + 16 * k);
+    } else {
+        store_block_any<ROWS, COLS>(blk, pitch, first, ldy, rows, (int)(N - n < COLS ? N - n : COLS), lane);
+    }
 }
 
 // Big-tile kernel for compute-bound sizes, M > 64 (atom_gemm_big.hip).

@@ -542,24 +542,8 @@ void w4a4_gemm_f6_kernel(const F6Params p)
             const int col = 32 * (t & 1) + r;
             *reinterpret_cast<uint16_t *>(ot + row * OSTRIDE + col * 2) = __half_as_ushort(__float2half_rn(acc[t][e]));
         }
-    const bool vec_ok = ((reinterpret_cast<uintptr_t>(p.y) | (uintptr_t)(p.ldy * 2)) & 15) == 0;
     __builtin_amdgcn_s_waitcnt(wait_imm(0));                   // the wavefront reads only what it wrote itself
-#pragma unroll
-    for (int it = 0; it < 8; ++it) {
-        const int row = it * 8 + (lane >> 3), ch = lane & 7;
-        const int64_t m = T.m_w + row, n = T.n_w + ch * 8;
-        if (m >= p.M || n >= p.N) continue;
-        const uint4 v = *reinterpret_cast<const uint4 *>(ot + row * OSTRIDE + ch * 16);
-        uint16_t *dst = p.y + m * p.ldy + n;
-        if (vec_ok && n + 8 <= p.N) {
-            *reinterpret_cast<uint4 *>(dst) = v;
-        } else {
-            const uint16_t *hv = reinterpret_cast<const uint16_t *>(&v);
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (n + k < p.N) dst[k] = hv[k];
-        }
-    }
+    store_block<64, 64>(ot, OSTRIDE, p.y, p.ldy, T.m_w, T.n_w, p.M, p.N, lane);
 }
 
 template <int WM, bool DBG>

@@ -268,7 +268,7 @@ void w4a4_gemm_f6_thin_kernel(const F6Params p)
 
     // ---- store: a lane holds four consecutive columns of one row of Y at a time (the weights are the row operand of the
     // MFMA); through LDS so that global memory sees whole row pieces
-    constexpr int OSTR = Gm::OSTR, CPR = 4 * NJ;               // 16-byte pieces per row
+    constexpr int OSTR = Gm::OSTR;
     unsigned char *ot = smem + wave * (32 * OSTR);
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
@@ -280,24 +280,7 @@ void w4a4_gemm_f6_thin_kernel(const F6Params p)
                 v2u{__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi)};
         }
     __builtin_amdgcn_s_waitcnt(wait_imm(63));                  // (LDS only: the wavefront reads what it wrote itself)
-    const bool vec_ok = ((reinterpret_cast<uintptr_t>(p.y) | (uintptr_t)(p.ldy * 2)) & 15) == 0;
-    const int64_t m0 = (int64_t)au0 * 64 + 32 * wr, n0 = (int64_t)wu0 * 64 + 32 * cb;
-#pragma unroll
-    for (int it = 0; it < 2 * NJ; ++it) {
-        const int row = it * (64 / CPR) + lane / CPR, ch = lane % CPR;
-        const int64_t m = m0 + row, n = n0 + ch * 8;
-        if (m >= p.M || n >= p.N) continue;
-        const uint4 v = *reinterpret_cast<const uint4 *>(ot + row * OSTR + ch * 16);
-        uint16_t *dst = p.y + m * p.ldy + n;
-        if (vec_ok && n + 8 <= p.N) {
-            *reinterpret_cast<uint4 *>(dst) = v;
-        } else {
-            const uint16_t *hv = reinterpret_cast<const uint16_t *>(&v);
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (n + k < p.N) dst[k] = hv[k];
-        }
-    }
+    store_block<32, 32 * NJ>(ot, OSTR, p.y, p.ldy, (int64_t)au0 * 64 + 32 * wr, (int64_t)wu0 * 64 + 32 * cb, p.M, p.N, lane);
 }
 
 template <int WR, int WC, int NJ, int STAGES, int OCC>

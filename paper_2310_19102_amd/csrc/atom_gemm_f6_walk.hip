@@ -338,7 +338,6 @@ void w4a4_gemm_f6_walk_kernel(const F6Params p)
         // that global memory sees whole 128-byte rows
         constexpr int OSTR = Gm::OSTR;
         unsigned char *ot = smem + (wave < NW / 2 ? stage8a : stage8w) * STAGE + (wave % (NW / 2)) * (64 * OSTR);
-        const bool vec_ok = ((reinterpret_cast<uintptr_t>(p.y) | (uintptr_t)(p.ldy * 2)) & 15) == 0;
 #pragma unroll
         for (int t = 0; t < T; ++t)
 #pragma unroll
@@ -349,43 +348,32 @@ void w4a4_gemm_f6_walk_kernel(const F6Params p)
                     v2u{__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi)};
             }
         __builtin_amdgcn_s_waitcnt(wait_imm(63));              // (LDS only: the wavefront reads what it wrote itself)
-        uint4 ov[XTRA];
-#pragma unroll
-        for (int it = 0; it < XTRA; ++it) ov[it] = *reinterpret_cast<const uint4 *>(ot + (it * 8 + (lane >> 3)) * OSTR + (lane & 7) * 16);
-        __builtin_amdgcn_s_waitcnt(wait_imm(63));
-        __syncthreads();                                       // every staging area is read: the two stages are free
+        const bool vec_ok = ((reinterpret_cast<uintptr_t>(p.y) | (uintptr_t)(p.ldy * 2)) & 15) == 0;
         const int64_t m_w = 64 * (int64_t)(cur_t.au0 + wm), n_w = 64 * (int64_t)(cur_t.wu0 + wn);
-        const bool full = vec_ok && m_w + 64 <= p.M && n_w + 64 <= p.N;                // (the same in all lanes)
-        auto store_rows = [&](auto full_c) __attribute__((always_inline)) {
+        uint16_t *const yb = p.y + m_w * p.ldy + n_w;
+        auto request_two = [&]() __attribute__((always_inline)) {
 #pragma unroll
-            for (int o = 0; o < XTRA; ++o) {
-                const int64_t m = m_w + o * 8 + (lane >> 3), n = n_w + (lane & 7) * 8;
-                uint16_t *dst = p.y + m * p.ldy + n;
-                if constexpr (decltype(full_c)::value) {
-                    *reinterpret_cast<uint4 *>(dst) = ov[o];
-                } else if (m < p.M && n < p.N) {
-                    if (vec_ok && n + 8 <= p.N) {
-                        *reinterpret_cast<uint4 *>(dst) = ov[o];
-                    } else {
-                        const uint16_t *hv = reinterpret_cast<const uint16_t *>(&ov[o]);
+            for (int k = 0; k < LPW; ++k) request(k, nxt_t.a + (NST - 2) * IMG4, nxt_t.w + (NST - 2) * IMG4, stage8a, more);
 #pragma unroll
-                        for (int k = 0; k < 8; ++k)
-                            if (n + k < p.N) dst[k] = hv[k];
-                    }
-                }
-            }
+            for (int k = 0; k < LPW; ++k) request(k, nxt_t.a + (NST - 1) * IMG4, nxt_t.w + (NST - 1) * IMG4, stage8w, more);
         };
-        if (!full) {
-            store_rows(std::false_type());
-            __builtin_amdgcn_s_waitcnt(wait_imm(0));
-        }
+        // (the same decision in all lanes; each arm passes the one barrier)
+        if (vec_ok && m_w + 64 <= p.M && n_w + 64 <= p.N) {
+            v4i ov[XTRA];
 #pragma unroll
-        for (int k = 0; k < LPW; ++k) request(k, nxt_t.a + (NST - 2) * IMG4, nxt_t.w + (NST - 2) * IMG4, stage8a, more);
+            for (int it = 0; it < XTRA; ++it) ov[it] = *reinterpret_cast<const v4i *>(ot + (it * 8 + (lane_t >> 3)) * OSTR + (lane_t & 7) * 16);
+            __builtin_amdgcn_s_waitcnt(wait_imm(63));
+            __syncthreads();                                   // every staging area is read: the two stages are free
+            request_two();
+            uint16_t *const yl = yb + (lane_t >> 3) * p.ldy + (lane_t & 7) * 8;
 #pragma unroll
-        for (int k = 0; k < LPW; ++k) request(k, nxt_t.a + (NST - 1) * IMG4, nxt_t.w + (NST - 1) * IMG4, stage8w, more);
-        if (full) {
-            store_rows(std::true_type());
+            for (int it = 0; it < XTRA; ++it) *reinterpret_cast<v4i *>(yl + it * 8 * p.ldy) = ov[it];
         } else {
+            if (m_w < p.M && n_w < p.N)
+                store_block_any<64, 64>(ot, OSTR, yb, p.ldy, (int)(p.M - m_w < 64 ? p.M - m_w : 64), (int)(p.N - n_w < 64 ? p.N - n_w : 64), lane_t);
+            __syncthreads();
+            __builtin_amdgcn_s_waitcnt(wait_imm(0));
+            request_two();
 #pragma unroll
             for (int k = 0; k < XTRA; ++k) dummy();
         }

@@ -308,19 +308,7 @@ void mx_gemm_dma_kernel(MxParams p)
                     v2u{__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi)};
             }
     // (LDS only, and the wavefront reads what it wrote itself)
-    constexpr int ROWS = 32 * TM, COLS = 32 * TN, LPR = COLS / 8;      // LPR 16-byte pieces per row of the wavefront's block
-    uint16_t *yb = p.y + wrow * p.ldy + wcol;
-    if (((reinterpret_cast<uintptr_t>(p.y) | (uintptr_t)(p.ldy * 2)) & 15) == 0 && wrow + ROWS <= p.M && wcol + COLS <= p.N) {
-#pragma unroll
-        for (int i = 0; i < ROWS * LPR / 64; ++i) {
-            const int q = 64 * i + lane, r = q / LPR, c = q % LPR;
-            *reinterpret_cast<v4i *>(yb + r * p.ldy + 8 * c) = *reinterpret_cast<const v4i *>(reg + r * Gm::PITCH + 16 * c);
-        }
-    } else {
-        const int64_t rows = p.M - wrow, cols = p.N - wcol;            // may be none
-        if (rows > 0 && cols > 0)
-            atom_gemm::store_block_any<ROWS, COLS>(reg, Gm::PITCH, yb, p.ldy, (int)(rows < ROWS ? rows : ROWS), (int)(cols < COLS ? cols : COLS), lane);
-    }
+    atom_gemm::store_block<32 * TM, 32 * TN>(reg, Gm::PITCH, p.y, p.ldy, wrow, wcol, p.M, p.N, lane);
 }
 
 template <int WM, int WN, int TM, int TN, int ST>
