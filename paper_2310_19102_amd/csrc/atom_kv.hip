@@ -367,12 +367,6 @@ typedef float    v4f __attribute__((ext_vector_type(4)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ v4h pair_operand(uint32_t lo, uint32_t hi)
-{
-    const v2u t = {lo, hi};
-    return __builtin_bit_cast(v4h, t);
-}
-
 __device__ __forceinline__ v8h quad_operand(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
 {
     const v4u t = {a, b, c, d};
@@ -391,6 +385,40 @@ __device__ __forceinline__ void unpack8_16_mfma(uint32_t w, uint32_t mask, uint3
     pr[3] = ((w >> 6) & mask) | magic;
 }
 
+// One step of a maximum of four values over the lanes l, l ^ 16, l ^ 32, l ^ 48, each result in one chunk of lanes: that of
+// a's own and its partner row's (half's) value in the rows (the half) that keep a, likewise of b in the others.
+template <int WIDTH>
+__device__ __forceinline__ float swap_max(float a, float b)
+{
+    const unsigned ua = __builtin_bit_cast(unsigned, a), ub = __builtin_bit_cast(unsigned, b);
+    v2u r;
+    if constexpr (WIDTH == 16) r = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane16_swap(ua, ub, false, false));
+    else                       r = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane32_swap(ua, ub, false, false));
+    unsigned second = r[1];
+    asm volatile("" : "+v"(second));      // (as in max_across_chunks)
+    return fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, second));
+}
+
+// The way back: o[i] = the value of lane 16 i + (l & 15) in every lane l.
+__device__ __forceinline__ void spread(float v, float (&o)[4])
+{
+    unsigned u = __builtin_bit_cast(unsigned, v), w = u;
+    asm volatile("" : "+v"(w));           // (two registers: a swap exchanges parts of them)
+    const v2u r = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane32_swap(u, w, false, false));
+    unsigned a = r[0], b = r[1];
+    asm volatile("" : "+v"(b));           // (as in max_across_chunks)
+    unsigned a2 = a, b2 = b;
+    asm volatile("" : "+v"(a2), "+v"(b2));
+    const v2u x = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane16_swap(a, a2, false, false));
+    const v2u y = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane16_swap(b, b2, false, false));
+    unsigned x1 = x[1], y1 = y[1];
+    asm volatile("" : "+v"(x1), "+v"(y1));
+    o[0] = __builtin_bit_cast(float, (unsigned)x[0]);
+    o[1] = __builtin_bit_cast(float, x1);
+    o[2] = __builtin_bit_cast(float, (unsigned)y[0]);
+    o[3] = __builtin_bit_cast(float, y1);
+}
+
 constexpr int kGqaWaves    = 4;
 constexpr int kGqaMaxHeads = 16;          // query heads per cache head served by one MFMA column block
 constexpr int kGqaHeadPitch = 4 * 33 + 1; // floats per head in the merge area (32 + 1 per chunk, + 1)
@@ -399,17 +427,17 @@ constexpr int kGqaHeadPitch = 4 * 33 + 1; // floats per head in the merge area (
 // query heads that share a cache head (2 <= Gq <= 16) share every load and every unpacked
 // code, and both contractions run on the fp16 MFMA 16x16x32 (lane l supplies row or column
 // l & 15 and the eight k of chunk l >> 4; the result has column l & 15 in lane l and rows
-// 4 (l >> 4) + e in register e).  A wavefront owns every fourth group of 64 tokens and walks
-// it in four steps of 16 tokens, as in the per-head kernel.
+// 4 (l >> 4) + e in register e).  A wavefront owns every fourth group of 64 tokens, four steps of 16 tokens.
 //   scores  : S[t, h] = sum_d (16 + code[t, d]) q[h, d]: the row operand is the K codes as
 //             fp16 16 + c (lane = token l & 15, 32 head dimensions of chunk l >> 4, four
 //             MFMAs), the column operand q in the same order of d (registers, loaded once);
 //             the result leaves head h = l & 15 and tokens 4 (l >> 4) + e in lane l, and
-//             score = k_scale sm_scale (S - (16 + k_zero) sum_d q).
-//   softmax : online per head; the four lanes of a head agree on the maximum, each keeps
-//             the partial sums of its own tokens; accumulators are rescaled when the
-//             maximum moves.
-//   values  : out^T[d, h] = sum_t (16 + code[t, d]) w[t, h]: the weights are already laid
+//             score = k_scale sm_scale (S - (16 + k_zero) sum_d q).  All four steps first: their
+//             chains of MFMAs and the exchanges of the maximum are independent of each other.
+//   softmax : online per head and step; the four lanes of a head agree on the maxima of the four steps (three
+//             swaps of lane halves gather them, three bring them back), each keeps the partial sums of its own tokens;
+//             accumulators are rescaled when the maximum moves.
+//   values  : out^T[d, h] = sum_t (code[t, d] - zero[t]) w[t, h]: the weights are already laid
 //             out as the column operand (tokens 4 (l >> 4) + i of head l & 15); the row
 //             operand wants four TOKENS of one d per lane, so the V codes are loaded four
 //             bytes per lane and token (lane = d group l & 15 of 8 head dimensions, tokens
@@ -423,15 +451,19 @@ constexpr int kGqaHeadPitch = 4 * 33 + 1; // floats per head in the merge area (
 //             fp16 number down to 2^-29 of that.  One fp16 number per weight is not enough (its rounding alone shows
 //             as 1e-2 of the small outputs of a head): w travels as fp16 hi + fp16 lo, one
 //             16x16x16 MFMA for each against the same value operand.
-//             The 16 and the zero point leave BEFORE the contraction: (16 + code) - (16 + zero)
-//             is exact in fp16 (one packed subtraction per pair of codes), so the sums carry
-//             no offset that a long context would have to cancel.  Zero points beyond +-1000
+//             The zero point leaves BEFORE the contraction, so the sums carry no offset that a long context
+//             would have to cancel: bits 0..3 of a half word are the (subnormal) fp16 number code 2^-24, bits 4..7 code
+//             2^-20, and one packed fma makes (code - zero) 2^-9 of either, exactly.  Zero points beyond +-1000
 //             (rows whose values all sit far on one side of zero) are taken out up to that
 //             bound, the rest leaves through sum_t w * rest as in the per-head kernel.
 //   scales  : lane l reads the scale and zero point of token l of the group (one cache line
-//             per array), turns them into four floats and parks them in LDS, where the step
-//             reads the four tokens it needs as broadcast 16-byte reads.
-__global__ __launch_bounds__(kGqaWaves * 64)               // (capped at 168 registers it spills and runs slower)
+//             per array) and parks what the steps need in LDS, where a step reads its four tokens' worth as broadcasts.
+// What bounds it: the chain of instructions of a wavefront (the grid leaves one or two per SIMD).  A group takes about 5300
+// cycles alone on its SIMD, 630 to 770 of vector ALU instructions at 4 cycles, and 80 MFMAs at 16 of which the scheduling below
+// hides most.  Alone, 64 heads on 8, lengths from T / 4 to T, us, against one step after the other with its own maximum, clamped
+// addresses and loads that waited for the scales: 16 sequences of 4096 25.2 -> 23.0, 128 of 2048 58.1 -> 50.2, 64 of
+// 1024 21.7 -> 19.3, 100 of 500 21.4 -> 17.8, 1 of 16384 16.0 -> 14.9.  Every sum keeps its order: the same bits.
+__global__ __launch_bounds__(kGqaWaves * 64)
 void decode_attention_kv4_gqa_kernel(const __half *__restrict__ q, int H, int Hkv, int64_t Tmax,
                                      const int32_t *__restrict__ seq_len,
                                      const uint8_t *__restrict__ kq, const __half *__restrict__ ks,
@@ -442,8 +474,9 @@ void decode_attention_kv4_gqa_kernel(const __half *__restrict__ q, int H, int Hk
 {
     constexpr int D = 128;
     constexpr int kWaves = kGqaWaves;
-    __shared__ float4 s_meta[kWaves][kTokens];
-    __shared__ float  s_rest[kWaves][kTokens];
+    __shared__ __align__(16) float s_meta[kWaves][3][kTokens];
+    __shared__ __align__(16) _Float16 s_zero[kWaves][kTokens];
+    __shared__ __align__(16) float s_rest[kWaves][kTokens];
     __shared__ float  s_m[kWaves][kGqaMaxHeads], s_l[kWaves][kGqaMaxHeads];
     extern __shared__ __align__(16) float s_acc[];        // [kWaves][Gq][kGqaHeadPitch]
 
@@ -452,6 +485,8 @@ void decode_attention_kv4_gqa_kernel(const __half *__restrict__ q, int H, int Hk
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int x = lane & 15, c = lane >> 4;
+    // (every argument is fetched before the first wait for any: the compiler would leave most for after the length)
+    asm volatile("" : : "s"(q), "s"(kq), "s"(ks), "s"(kz), "s"(vq), "s"(vs), "s"(vz), "s"(sm_scale), "s"(groups_per_split));
     int T = seq_len[b];
     T = T < 0 ? 0 : (T > Tmax ? (int)Tmax : T);
     const int64_t base = ((int64_t)b * Hkv + kvh) * Tmax;
@@ -465,20 +500,22 @@ void decode_attention_kv4_gqa_kernel(const __half *__restrict__ q, int H, int Hk
     const bool alive = G < g_end;                        // then T >= 1: clamped addresses are valid
     const int  t_last = min(T, g_end * kTokens) - 1;     // loads never leave this split's tokens
 
-    struct Stage { uint4 k; uint32_t v0, v1, v2, v3; };
-    Stage st[4];
+    uint4 kst[4];
+    struct Rows { uint32_t v0, v1, v2, v3; };
+    Rows vst[4];
     const float k_mul = sm_scale * 1.44269504088896340736f;   // scores in units of log2: exp2 below
-    // byte offsets inside this cache head: a tile is 16 rows of 64 bytes; rows past t_last
-    // (masked tokens, steps past the end) read row t_last instead
-    const uint32_t k_lane = 64u * x + 16u * c, k_last = 64u * (uint32_t)max(t_last, 0) + 16u * c;
-    const uint32_t v_lane = 64u * (4u * c) + 4u * x, v_last = 64u * (uint32_t)max(t_last, 0) + 4u * x;
-    auto fetch = [&](Stage &s_, int tile) {
-        const uint32_t t0 = (uint32_t)tile * (kTile * 64u);
-        s_.k  = *reinterpret_cast<const uint4 *>(kb + min(t0 + k_lane, k_last));
-        s_.v0 = *reinterpret_cast<const uint32_t *>(vb + min(t0 + v_lane, v_last));
-        s_.v1 = *reinterpret_cast<const uint32_t *>(vb + min(t0 + v_lane + 64u, v_last));
-        s_.v2 = *reinterpret_cast<const uint32_t *>(vb + min(t0 + v_lane + 128u, v_last));
-        s_.v3 = *reinterpret_cast<const uint32_t *>(vb + min(t0 + v_lane + 192u, v_last));
+    // A step is 16 rows of 64 bytes.  Rows past t_last (masked tokens, steps past the end) lie past the end of the buffer that
+    // the descriptors state: they read as 0 and touch no memory.
+    const uint32_t k_lane = 64u * x + 16u * c, v_lane = 64u * (4u * c) + 4u * x;
+    const auto k_rows = __builtin_amdgcn_make_buffer_rsrc((void *)kb, 0, 64u * (uint32_t)(t_last + 1), 0x00020000);
+    const auto v_rows = __builtin_amdgcn_make_buffer_rsrc((void *)vb, 0, 64u * (uint32_t)(t_last + 1), 0x00020000);
+    auto k_of = [&](int tile) {
+        return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(k_rows, (uint32_t)tile * (kTile * 64u) + k_lane, 0, 0));
+    };
+    auto v_of = [&](int tile) {
+        const uint32_t t0 = (uint32_t)tile * (kTile * 64u) + v_lane;
+        return Rows{__builtin_amdgcn_raw_buffer_load_b32(v_rows, t0, 0, 0), __builtin_amdgcn_raw_buffer_load_b32(v_rows, t0 + 64u, 0, 0),
+                    __builtin_amdgcn_raw_buffer_load_b32(v_rows, t0 + 128u, 0, 0), __builtin_amdgcn_raw_buffer_load_b32(v_rows, t0 + 192u, 0, 0)};
     };
     // scales and zero points of token `lane` of group g, raw
     struct Meta { __half ks, vs; int16_t kz, vz; };
@@ -487,7 +524,7 @@ void decode_attention_kv4_gqa_kernel(const __half *__restrict__ q, int H, int Hk
         t = t <= t_last ? t : t_last;
         return Meta{ksb[(uint32_t)t], vsb[(uint32_t)t], kzb[(uint32_t)t], vzb[(uint32_t)t]};
     };
-    v4f acc[8];                           // acc[j][e] <-> out[head x][d = 32c + 8e + j], in units of R / 2^15
+    v4f acc[8];                           // acc[j][e] <-> out[head x][d = 32c + 8e + j], in units of R / 2^6
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
     float m_run = -INFINITY, l_run = 0.0f, off_run = 0.0f;    // l and off: this lane's tokens only
@@ -495,8 +532,8 @@ void decode_attention_kv4_gqa_kernel(const __half *__restrict__ q, int H, int Hk
     unsigned c_zero = 0u;
     asm volatile("" : "+s"(c_zero));
     bool  has_rest = false;               // some zero point of the current group was clamped
-    // ... as (k_scale sm_scale log2 e, 16 + k_zero, v_scale * 2^15 / R, 16 + v_zero clamped to
-    // +-1000) into LDS, what the clamp cut off beside it
+    // ... as k_scale sm_scale log2 e, 16 + k_zero, v_scale * 2^15 / R and (16 - (16 + v_zero clamped to +-1000)) / 2^9 into
+    // LDS, what the clamp cut off (/ 2^9) beside it
     auto install_meta = [&](const Meta &mt) {
         const float v_s = __half2float(mt.vs);
         const float Rn  = fmaxf(R, max_across_chunks(row16_max(v_s), c_zero));
@@ -510,144 +547,163 @@ void decode_attention_kv4_gqa_kernel(const __half *__restrict__ q, int H, int Hk
         const float rinv  = R > 0.0f ? 32768.0f / R : 0.0f;
         const float v_off = 16.0f + (float)mt.vz;
         const float v_cut = fminf(fmaxf(v_off, -1000.0f), 1000.0f);
-        s_meta[wave][lane] = make_float4(__half2float(mt.ks) * k_mul, 16.0f + (float)mt.kz, v_s * rinv, v_cut);
-        s_rest[wave][lane] = v_off - v_cut;
+        s_meta[wave][0][lane] = __half2float(mt.ks) * k_mul;
+        s_meta[wave][1][lane] = 16.0f + (float)mt.kz;
+        s_meta[wave][2][lane] = v_s * rinv;
+        s_zero[wave][lane] = (_Float16)((16.0f - v_cut) * (1.0f / 512.0f));
+        s_rest[wave][lane] = (v_off - v_cut) * (1.0f / 512.0f);
         has_rest = __ballot(v_off != v_cut) != 0;
     };
-    if (alive) {                          // the first loads leave before q is read
-        install_meta(fetch_meta(G));
-#pragma unroll
-        for (int i = 0; i < 4; ++i) fetch(st[i], 4 * G + i);
-    }
-
-    // q of head x as the column operand: MFMA j of a step contracts, for chunk c, the head
-    // dimensions 32c + 8j + {0, 4, 1, 5, 2, 6, 3, 7} (the order unpack8_16 delivers)
-    v8h qb[4];
-    float qsum = 0.0f;
-    {
-        const bool live = x < Gq;
-        const __half *qv = q + ((int64_t)b * H + (int64_t)kvh * Gq + (live ? x : 0)) * D + 32 * c;
-        uint4 qraw[4];                    // 64 bytes as four loads
-#pragma unroll
-        for (int j = 0; j < 4; ++j) qraw[j] = *reinterpret_cast<const uint4 *>(qv + 8 * j);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float e[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) e[i] = live ? half_of(qraw, 8 * j + (i >> 1) + 4 * (i & 1)) : 0.0f;
-            qb[j] = v8h{(_Float16)e[0], (_Float16)e[1], (_Float16)e[2], (_Float16)e[3],
-                        (_Float16)e[4], (_Float16)e[5], (_Float16)e[6], (_Float16)e[7]};
-            qsum += ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
-        }
-        qsum += __shfl_xor(qsum, 16, 64);
-        qsum += __shfl_xor(qsum, 32, 64);
-    }
-
-    uint32_t c_mask = 0x03C003C0u, c_magic = 0x4C004C00u;
-    asm volatile("" : "+s"(c_mask));
-    asm volatile("" : "+v"(c_magic));
-
-    // `masked_c`: the group holds the end of the sequence, some tokens of the step may lie beyond it
-    auto consume = [&](const Stage &s_, int tile, int slot, auto masked_c) __attribute__((always_inline)) {
-        // ---- scores
-        const uint32_t kw[4] = {s_.k.x, s_.k.y, s_.k.z, s_.k.w};
-        v4f sa = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            uint32_t pr[4];
-            unpack8_16_mfma(kw[j], c_mask, c_magic, pr);
-            sa = __builtin_amdgcn_mfma_f32_16x16x32_f16(quad_operand(pr[0], pr[1], pr[2], pr[3]), qb[j], sa, 0, 0, 0);
-        }
-        float4 mt[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) mt[e] = s_meta[wave][16 * slot + 4 * c + e];
-        float sc[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sc[e] = mt[e].x * fmaf(-mt[e].y, qsum, sa[e]);
-        if constexpr (decltype(masked_c)::value) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (tile * kTile + 4 * c + e >= T) sc[e] = -INFINITY;
-        }
-        // ---- online softmax per head: the four lanes of a head take the same decisions
-        float mx = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
-        const float m_new = fmaxf(m_run, max_across_chunks(mx, c_zero));
-        if (m_new > m_run) {
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first step
-            l_run *= alpha;
-            off_run *= alpha;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] *= alpha;
-            m_run = m_new;
-        }
-        // w = hi + lo: hi by the packed conversion (which truncates: any rounding will do, lo
-        // takes what hi leaves), two tokens per instruction
-        float w[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float p = __builtin_amdgcn_exp2f(sc[e] - m_run);
-            l_run += p;
-            w[e] = p * mt[e].z;
-        }
-        const h2 hi01 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(w[0], w[1]));
-        const h2 hi23 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(w[2], w[3]));
-        const h2 lo01 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(w[0] - (float)hi01[0], w[1] - (float)hi01[1]));
-        const h2 lo23 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(w[2] - (float)hi23[0], w[3] - (float)hi23[1]));
-        if (has_rest) {                   // rare: the part of a zero point the operands cannot carry
-            const float *rs = &s_rest[wave][16 * slot + 4 * c];   // (hi + lo is w to 2^-22)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) off_run = fmaf(w[e], rs[e], off_run);
-        }
-        const v4h pb_hi = {hi01[0], hi01[1], hi23[0], hi23[1]}, pb_lo = {lo01[0], lo01[1], lo23[0], lo23[1]};
-        // (16 + zero) of tokens (0, 1) and (2, 3) of this lane as fp16 pairs
-        const h2 z01 = {(_Float16)mt[0].w, (_Float16)mt[1].w}, z23 = {(_Float16)mt[2].w, (_Float16)mt[3].w};
-
-        // ---- values: byte transpose (token i of this lane = dword v_i), then two tokens per unpack
-        const uint32_t w0 = s_.v0, w1 = s_.v1, w2 = s_.v2, w3 = s_.v3;
-        // v_perm_b32 picks each result byte out of eight: 0-3 the second operand's, 4-7 the first's
-        constexpr uint32_t kZipLo = 0x05010400u;          // [b.0 a.0 b.1 a.1] of perm(a, b)
-        constexpr uint32_t kZipHi = 0x07030602u;          // [b.2 a.2 b.3 a.3]
-        // L01 = [t0.b0 t1.b0 t0.b1 t1.b1], H01 = [t0.b2 t1.b2 t0.b3 t1.b3] (byte 0 first)
-        const uint32_t L01 = __builtin_amdgcn_perm(w1, w0, kZipLo), H01 = __builtin_amdgcn_perm(w1, w0, kZipHi);
-        const uint32_t L23 = __builtin_amdgcn_perm(w3, w2, kZipLo), H23 = __builtin_amdgcn_perm(w3, w2, kZipHi);
-        // Y_b = [t0.b t2.b t1.b t3.b]: the codes of tokens 0 and 1 sit 16 bits apart, as do 2 and 3
-        uint32_t Y[4];
-        Y[0] = __builtin_amdgcn_perm(L23, L01, kZipLo);
-        Y[1] = __builtin_amdgcn_perm(L23, L01, kZipHi);
-        Y[2] = __builtin_amdgcn_perm(H23, H01, kZipLo);
-        Y[3] = __builtin_amdgcn_perm(H23, H01, kZipHi);
-#pragma unroll
-        for (int bt = 0; bt < 4; ++bt) {
-            uint32_t pr[4];               // (t0,t1).lo  (t0,t1).hi  (t2,t3).lo  (t2,t3).hi of byte bt
-            unpack8_16_mfma(Y[bt], c_mask, c_magic, pr);
-            const uint32_t e01 = __builtin_bit_cast(uint32_t, __builtin_bit_cast(h2, pr[0]) - z01);
-            const uint32_t o01 = __builtin_bit_cast(uint32_t, __builtin_bit_cast(h2, pr[1]) - z01);
-            const uint32_t e23 = __builtin_bit_cast(uint32_t, __builtin_bit_cast(h2, pr[2]) - z23);
-            const uint32_t o23 = __builtin_bit_cast(uint32_t, __builtin_bit_cast(h2, pr[3]) - z23);
-            const v4h ve = pair_operand(e01, e23), vo = pair_operand(o01, o23);     // even / odd d of byte bt
-            acc[2 * bt]     = __builtin_amdgcn_mfma_f32_16x16x16f16(ve, pb_hi, acc[2 * bt], 0, 0, 0);
-            acc[2 * bt]     = __builtin_amdgcn_mfma_f32_16x16x16f16(ve, pb_lo, acc[2 * bt], 0, 0, 0);
-            acc[2 * bt + 1] = __builtin_amdgcn_mfma_f32_16x16x16f16(vo, pb_hi, acc[2 * bt + 1], 0, 0, 0);
-            acc[2 * bt + 1] = __builtin_amdgcn_mfma_f32_16x16x16f16(vo, pb_lo, acc[2 * bt + 1], 0, 0, 0);
-        }
-    };
-
     if (alive) {
+        // every first load leaves before any is waited for, in the order in which they are needed
+        const bool live = x < Gq;
+        uint4 qraw[4];                        // 64 bytes as four loads
+        {
+            const __half *qv = q + ((int64_t)b * H + (int64_t)kvh * Gq + (live ? x : 0)) * D + 32 * c;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) qraw[j] = *reinterpret_cast<const uint4 *>(qv + 8 * j);
+        }
+        const Meta first = fetch_meta(G);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) kst[i] = k_of(4 * G + i);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) vst[i] = v_of(4 * G + i);
+        __builtin_amdgcn_sched_barrier(0);    // (or the waits for the scales move between the loads)
+        install_meta(first);
+
+        // q of head x as the column operand: MFMA j of a step contracts, for chunk c, the head
+        // dimensions 32c + 8j + {0, 4, 1, 5, 2, 6, 3, 7} (the order unpack8_16 delivers)
+        v8h qb[4];
+        float qsum = 0.0f;
+        {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float e[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) e[i] = live ? half_of(qraw, 8 * j + (i >> 1) + 4 * (i & 1)) : 0.0f;
+                qb[j] = v8h{(_Float16)e[0], (_Float16)e[1], (_Float16)e[2], (_Float16)e[3],
+                            (_Float16)e[4], (_Float16)e[5], (_Float16)e[6], (_Float16)e[7]};
+                qsum += ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
+            }
+            qsum += __shfl_xor(qsum, 16, 64);
+            qsum += __shfl_xor(qsum, 32, 64);
+        }
+
+        uint32_t c_mask = 0x03C003C0u, c_magic = 0x4C004C00u;
+        asm volatile("" : "+s"(c_mask));
+        asm volatile("" : "+v"(c_magic));
+
+        const h2 c_even = {(_Float16)32768.0f, (_Float16)32768.0f}, c_odd = {(_Float16)2048.0f, (_Float16)2048.0f};
         while (G < g_end) {
             const int Gn = G + kWaves;                    // past the end: clamped, unused loads
             const Meta meta_next = fetch_meta(Gn);
-            if ((G + 1) * kTokens <= T) {                 // every token of the group is inside the sequence
+            // ---- scores of the four steps
+            float sc[4][4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    consume(st[i], 4 * G + i, i, std::false_type{});
-                    fetch(st[i], 4 * Gn + i);             // the slot's next use is four steps away
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t kw[4] = {kst[i].x, kst[i].y, kst[i].z, kst[i].w};
+                v4f sa = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    uint32_t pr[4];
+                    unpack8_16_mfma(kw[j], c_mask, c_magic, pr);
+                    sa = __builtin_amdgcn_mfma_f32_16x16x32_f16(quad_operand(pr[0], pr[1], pr[2], pr[3]), qb[j], sa, 0, 0, 0);
                 }
-            } else {
+                kst[i] = k_of(4 * Gn + i);
+                const float4 ks4 = *reinterpret_cast<const float4 *>(&s_meta[wave][0][16 * i + 4 * c]);
+                const float4 kz4 = *reinterpret_cast<const float4 *>(&s_meta[wave][1][16 * i + 4 * c]);
+                sc[i][0] = ks4.x * fmaf(-kz4.x, qsum, sa[0]);
+                sc[i][1] = ks4.y * fmaf(-kz4.y, qsum, sa[1]);
+                sc[i][2] = ks4.z * fmaf(-kz4.z, qsum, sa[2]);
+                sc[i][3] = ks4.w * fmaf(-kz4.w, qsum, sa[3]);
+            }
+            if ((G + 1) * kTokens > T) {                  // the end of the sequence: a weight of 0 from there on
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int tile = 4 * G + i;
-                    if (tile * kTile < T) consume(st[i], tile, i, std::true_type{});
-                    fetch(st[i], 4 * Gn + i);
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (G * kTokens + 16 * i + 4 * c + e >= T) sc[i][e] = -INFINITY;
+            }
+            // ---- online softmax per head, step by step: the four lanes of a head take the same decisions
+            float mx[4], m[5];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) mx[i] = fmaxf(fmaxf(sc[i][0], sc[i][1]), fmaxf(sc[i][2], sc[i][3]));
+            spread(swap_max<32>(swap_max<16>(mx[0], mx[1]), swap_max<16>(mx[2], mx[3])), mx);
+            m[0] = m_run;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) m[i + 1] = fmaxf(m[i], mx[i]);
+            m_run = m[4];
+            float w[4][4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float4 vs4 = *reinterpret_cast<const float4 *>(&s_meta[wave][2][16 * i + 4 * c]);
+                const float vs_[4] = {vs4.x, vs4.y, vs4.z, vs4.w};
+                if (m[i + 1] > m[i]) l_run *= __builtin_amdgcn_exp2f(m[i] - m[i + 1]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float p = __builtin_amdgcn_exp2f(sc[i][e] - m[i + 1]);
+                    l_run += p;
+                    w[i][e] = p * vs_[e];
+                }
+            }
+            // ---- values
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (__any(m[i + 1] > m[i])) {
+                    const float alpha = m[i + 1] > m[i] ? __builtin_amdgcn_exp2f(m[i] - m[i + 1]) : 1.0f;   // 0 on the first step
+                    off_run *= alpha;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) acc[j] *= alpha;
+                }
+                // w = hi + lo: hi by the packed conversion (which truncates: any rounding will do, lo
+                // takes what hi leaves), two tokens per instruction
+                const h2 hi01 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(w[i][0], w[i][1]));
+                const h2 hi23 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(w[i][2], w[i][3]));
+                const h2 lo01 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(w[i][0] - (float)hi01[0], w[i][1] - (float)hi01[1]));
+                const h2 lo23 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(w[i][2] - (float)hi23[0], w[i][3] - (float)hi23[1]));
+                if (has_rest) {               // rare: the part of a zero point the operands cannot carry
+                    const float *rs = &s_rest[wave][16 * i + 4 * c];   // (hi + lo is w to 2^-22)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) off_run = fmaf(w[i][e], rs[e], off_run);
+                }
+                const v4h pb_hi = {hi01[0], hi01[1], hi23[0], hi23[1]}, pb_lo = {lo01[0], lo01[1], lo23[0], lo23[1]};
+                const v4h z4 = *reinterpret_cast<const v4h *>(&s_zero[wave][16 * i + 4 * c]);
+                const h2 z01 = {z4[0], z4[1]}, z23 = {z4[2], z4[3]};
+
+                // byte transpose (token i of this lane = dword v_i), then two tokens per unpack
+                const uint32_t w0 = vst[i].v0, w1 = vst[i].v1, w2 = vst[i].v2, w3 = vst[i].v3;
+                // v_perm_b32 picks each result byte out of eight: 0-3 the second operand's, 4-7 the first's
+                constexpr uint32_t kZipLo = 0x05010400u;          // [b.0 a.0 b.1 a.1] of perm(a, b)
+                constexpr uint32_t kZipHi = 0x07030602u;          // [b.2 a.2 b.3 a.3]
+                // L01 = [t0.b0 t1.b0 t0.b1 t1.b1], H01 = [t0.b2 t1.b2 t0.b3 t1.b3] (byte 0 first)
+                const uint32_t L01 = __builtin_amdgcn_perm(w1, w0, kZipLo), H01 = __builtin_amdgcn_perm(w1, w0, kZipHi);
+                const uint32_t L23 = __builtin_amdgcn_perm(w3, w2, kZipLo), H23 = __builtin_amdgcn_perm(w3, w2, kZipHi);
+                // Y_b = [t0.b t2.b t1.b t3.b]: the codes of tokens 0 and 1 sit 16 bits apart, as do 2 and 3
+                uint32_t Y[4];
+                Y[0] = __builtin_amdgcn_perm(L23, L01, kZipLo);
+                Y[1] = __builtin_amdgcn_perm(L23, L01, kZipHi);
+                Y[2] = __builtin_amdgcn_perm(H23, H01, kZipLo);
+                Y[3] = __builtin_amdgcn_perm(H23, H01, kZipHi);
+#pragma unroll
+                for (int bt = 0; bt < 4; ++bt) {
+                    const uint32_t up = Y[bt] >> 8;
+                    const h2 e01 = __builtin_elementwise_fma(__builtin_bit_cast(h2, Y[bt] & 0x000F000Fu), c_even, z01);
+                    const h2 o01 = __builtin_elementwise_fma(__builtin_bit_cast(h2, Y[bt] & 0x00F000F0u), c_odd, z01);
+                    const h2 e23 = __builtin_elementwise_fma(__builtin_bit_cast(h2, up & 0x000F000Fu), c_even, z23);
+                    const h2 o23 = __builtin_elementwise_fma(__builtin_bit_cast(h2, up & 0x00F000F0u), c_odd, z23);
+                    const v4h ve = {e01[0], e01[1], e23[0], e23[1]}, vo = {o01[0], o01[1], o23[0], o23[1]};     // even / odd d of byte bt
+                    acc[2 * bt]     = __builtin_amdgcn_mfma_f32_16x16x16f16(ve, pb_hi, acc[2 * bt], 0, 0, 0);
+                    acc[2 * bt + 1] = __builtin_amdgcn_mfma_f32_16x16x16f16(vo, pb_hi, acc[2 * bt + 1], 0, 0, 0);
+                    acc[2 * bt]     = __builtin_amdgcn_mfma_f32_16x16x16f16(ve, pb_lo, acc[2 * bt], 0, 0, 0);
+                    acc[2 * bt + 1] = __builtin_amdgcn_mfma_f32_16x16x16f16(vo, pb_lo, acc[2 * bt + 1], 0, 0, 0);
+                }
+                vst[i] = v_of(4 * Gn + i);
+                // an MFMA takes the matrix core 16 cycles: three vector instructions between one and the next, as far as they go
+                __builtin_amdgcn_sched_group_barrier(0x002, 40, 0);
+#pragma unroll
+                for (int n = 0; n < 16; ++n) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
                 }
             }
             if (has_rest) {                               // what the operands could not carry of the zero points
@@ -671,13 +727,14 @@ void decode_attention_kv4_gqa_kernel(const __half *__restrict__ q, int H, int Hk
 #pragma unroll
         for (int j = 0; j < 8; ++j)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) dst[8 * e + j] = acc[j][e] * (R * (1.0f / 32768.0f));
+            for (int e = 0; e < 4; ++e) dst[8 * e + j] = acc[j][e] * (R * (1.0f / 64.0f));
         if (c == 0) {
             s_m[wave][x] = m_run;
             s_l[wave][x] = l_run;
         }
     }
     __syncthreads();
+#pragma unroll 4
     for (int idx = tid; idx < Gq * D; idx += kWaves * 64) {
         const int hh = idx >> 7, d = idx & (D - 1);
         float M = s_m[0][hh];

@@ -1,0 +1,37 @@
+"""Decode attention at the edges of its 64-token groups and 16-token steps, over caches written by hand: value scales among
+fp16's subnormals, zero points near the end of int16's range, key codes all 0 or all 15."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2310_19102_amd as atom
+
+pytestmark = pytest.mark.gpu
+
+LENS = [0, 1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 255, 256, 257, 320, 400]
+
+
+@pytest.mark.parametrize("H,Hkv", [(2, 2), (4, 2)])
+@pytest.mark.parametrize("kind", ["plain", "subnormal"])
+def test_attention_at_group_edges(H, Hkv, kind):
+    B, T, D = len(LENS), 400, 128
+    print(f"[case] attention at group edges H={H} Hkv={Hkv} {kind}", flush=True)
+    rng = np.random.default_rng(7 * H + Hkv)
+    codes = lambda: rng.integers(0, 256, (B, Hkv, T, D // 2), dtype=np.uint8)
+    k = [codes(), (0.05 + 0.05 * rng.random((B, Hkv, T))).astype(np.float16), rng.integers(0, 16, (B, Hkv, T)).astype(np.int16)]
+    v = [codes(), (0.01 + 0.1 * rng.random((B, Hkv, T))).astype(np.float16), rng.integers(0, 16, (B, Hkv, T)).astype(np.int16)]
+    k[0][:, :, 5::64], k[0][:, :, 6::64] = 0x00, 0xFF
+    if kind == "subnormal":       # outputs of about 30000 * 2^-23: normal fp16, all of it from the zero points
+        v[1] = (rng.integers(1, 4, (B, Hkv, T)) * 2.0 ** -24).astype(np.float16)
+        v[2] = rng.integers(-32768, -30000, (B, Hkv, T)).astype(np.int16)
+    q = rng.standard_normal((B, H, D)).astype(np.float16)
+    lens = np.array(LENS, dtype=np.int32)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    out = atom.atom_decode_attention_kv4(dev(q), [dev(a) for a in k], [dev(a) for a in v], dev(lens), D ** -0.5).cpu().numpy()
+    ref = oracle.decode_attention_kv4(q, *k, *v, lens, D ** -0.5)
+    assert not out[0].any()
+    # fp16 rounds by 2^-11 of a value; what is summed in fp32 adds less than that again
+    floor = 1e-2 * np.abs(ref).max(axis=(1, 2), keepdims=True)
+    err = np.abs(out.astype(np.float64) - ref)[1:] / np.maximum(np.abs(ref), floor)[1:]
+    assert err.max() <= 2.0 ** -10, err.max(axis=(1, 2))
