@@ -481,6 +481,193 @@ void w4a4_gemm_decode16_kernel(const GemmParams p)
     }
 }
 
+constexpr int kResidentRows = 32;           // rows of a workgroup of the next kernel
+
+// Many blocks of channels per compute unit, 17 rows and more, K from 3841 to 8192: a workgroup takes 32 rows and a run of
+// channel blocks, and every wavefront keeps the activation operand of its K-slice (NBK blocks of four groups) in registers
+// for all of them.  w4a4_gemm_decode16_kernel reads the activations again for each block or two, more bytes from the L2 than
+// the weights are, and every workgroup pays its own start and its own meeting of slices; here only weights stream, those of
+// the next two blocks in flight while one is multiplied.  Same sums in the same order: the same bits.
+// Canonical weights from memory, us, that kernel and this one: K = 4096: M = 32, N = 22016 17.1 / 14.5; M = 64, N = 8999
+// 14.9 / 11.1, 22016 22.8 / 20.4; K = 5120, N = 27648: M = 32 27.8 / 24.8, M = 64 42.7 / 38.3; K = 8192: M = 20, N = 57344
+// 71.7 / 55.5, M = 64, N = 9000 27.2 / 20.9.  What bounds it now: the weights (9.0 us for 22016 x 4096 when only read) behind a
+// start of 4 us in which the activations arrive, and at 64 rows the two passes over the weights.  64 rows per workgroup read
+// them once, but the widening for twice the rows stands in the way (N = 22016 21.1); weights three blocks ahead: no faster.
+template <int NBK, int TAIL>
+__global__ __launch_bounds__(NT, 2)
+void w4a4_gemm_decode_resident_kernel(const GemmParams p)
+{
+    constexpr int RB = kResidentRows / 16;
+    // [parity of the pair of channel blocks][which of the pair][K-slice][row block, lane, register]
+    constexpr int RED = RB * 256;
+    __shared__ __align__(16) float red[4 * NW * RED];
+
+    const int tid  = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, kc = lane >> 4;
+    const int K4 = p.K - 128, G = p.K >> 7;
+    const int row0 = (int)blockIdx.y * (16 * RB);
+    const int M = min((int)p.M - row0, 16 * RB);          // rows of this workgroup
+    constexpr bool A8 = TAIL == 3;
+    const int nblk    = (G + 3) >> 2;
+    const int g_begin = 4 * (int)((int64_t)wave * nblk / NW);
+    const int g_end   = min(G, 4 * (int)((int64_t)(wave + 1) * nblk / NW));
+    const uint8_t *w8b = reinterpret_cast<const uint8_t *>(p.w_q8), *a8b = reinterpret_cast<const uint8_t *>(p.a_q8);
+    // this workgroup's blocks of 16 channels
+    const int nb16  = (int)((p.N + TN - 1) / TN);
+    const int first = (int)((int64_t)blockIdx.x * nb16 / gridDim.x), last = (int)((int64_t)(blockIdx.x + 1) * nb16 / gridDim.x);
+
+    const v4i   zi = {0, 0, 0, 0};
+    const v4f32 zf = {0.0f, 0.0f, 0.0f, 0.0f};
+
+    // the last wavefront's last block of groups holds the INT8 group; with NBK = 2 the others may have one block only
+    auto run = [&](auto has8_c) __attribute__((always_inline)) {
+        constexpr bool HAS8 = decltype(has8_c)::value;
+        const int  cnt  = (g_end - g_begin + 3) >> 2;
+        const bool full = HAS8 || cnt == NBK;             // otherwise slot NBK - 1 repeats what slot 0 reads and is not used
+        int gb[NBK];
+#pragma unroll
+        for (int j = 0; j < NBK; ++j) gb[j] = j < cnt ? g_begin + 4 * j : g_begin;
+        auto ng4 = [](int j) constexpr { return HAS8 && j == NBK - 1 ? TAIL : 4; };      // INT4 groups of slot j
+
+        struct Weights { uint4 q[NBK][4], x; uint2 s[NBK]; };
+        auto fetch = [&](Weights &w, int blk) __attribute__((always_inline)) {
+            blk = blk < last ? blk : last - 1;            // past the end: the last block once more, not used
+            int64_t wr = (int64_t)blk * TN + col;         // clamped: columns >= N are computed and never stored
+            wr = wr < p.N ? wr : p.N - 1;
+            const uint32_t w4o = (uint32_t)(wr * (K4 >> 1)) + kc * 16, w8o = (uint32_t)(wr * 128) + kc * 16;
+#pragma unroll
+            for (int j = 0; j < NBK; ++j) {
+                w.s[j] = load_scales<A8>(p.w_scale, (uint32_t)wr * (uint32_t)G, gb[j], G);
+#pragma unroll
+                for (int d = 0; d < ng4(j); ++d) w.q[j][d] = *reinterpret_cast<const uint4 *>(p.w_q4 + (w4o + (uint32_t)(gb[j] + d) * 64u));
+            }
+            if constexpr (HAS8) {
+                w.q[NBK - 1][TAIL] = *reinterpret_cast<const uint4 *>(w8b + w8o);
+                w.x                = *reinterpret_cast<const uint4 *>(w8b + (w8o + 64u));
+            }
+        };
+        Weights wa, wb;
+
+        // the activation operand of the wavefront's groups (row 16 rb + col of this lane; rows >= M read row 0 and are never
+        // stored), ahead of the weights in the order of the requests
+        uint4 aq[NBK][RB][4], ax[RB];
+        uint2 avs[NBK][RB];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const uint32_t ar = row0 + (16 * rb + col < M ? 16 * rb + col : 0);
+            const uint32_t a4o = ar * (uint32_t)(K4 >> 1) + kc * 16, a8o = ar * 128u + kc * 16;
+#pragma unroll
+            for (int j = 0; j < NBK; ++j) {
+                avs[j][rb] = load_scales<A8>(p.a_scale, ar * (uint32_t)G, gb[j], G);
+#pragma unroll
+                for (int d = 0; d < ng4(j); ++d) aq[j][rb][d] = *reinterpret_cast<const uint4 *>(p.a_q4 + (a4o + (uint32_t)(gb[j] + d) * 64u));
+            }
+            if constexpr (HAS8) {
+                aq[NBK - 1][rb][TAIL] = *reinterpret_cast<const uint4 *>(a8b + a8o);
+                ax[rb]                = *reinterpret_cast<const uint4 *>(a8b + (a8o + 64u));
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // (every wavefront's activations, hits in the L2, before any weights: loads return in order)
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(wa, first);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(wb, first + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (kc != 0) {                                    // k-slots 4 .. 15 of the scale MFMA stay empty
+#pragma unroll
+            for (int j = 0; j < NBK; ++j)
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) avs[j][rb] = make_uint2(0, 0);
+        }
+
+        auto step = [&](Weights &w, int blk, int slot_of) __attribute__((always_inline)) {
+            float acc[RB][4];
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[rb][e] = 0.0f;
+            // (the widened codes are made again for every block: hoisted out of the loop they would take twice the registers)
+#pragma unroll
+            for (int j = 0; j < NBK; ++j)
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+                    for (int d = 0; d < ng4(j); ++d)
+                        asm volatile("" : "+v"(aq[j][rb][d].x), "+v"(aq[j][rb][d].y), "+v"(aq[j][rb][d].z), "+v"(aq[j][rb][d].w));
+                    asm volatile("" : "+v"(avs[j][rb].x), "+v"(avs[j][rb].y));
+                }
+            auto group = [&](auto jc, auto dc) __attribute__((always_inline)) {
+                constexpr int J = decltype(jc)::value, D = decltype(dc)::value;
+                constexpr bool INT8 = HAS8 && J == NBK - 1 && D == TAIL;
+                const v4i b0 = INT8 ? __builtin_bit_cast(v4i, w.q[J][D]) : widen_lo(w.q[J][D]);
+                const v4i b1 = INT8 ? __builtin_bit_cast(v4i, w.x) : widen_hi(w.q[J][D]);
+                const uint2 ws = kc != 0 ? make_uint2(0, 0) : w.s[J];
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    const v4i x0 = INT8 ? __builtin_bit_cast(v4i, aq[J][rb][D]) : widen_lo(aq[J][rb][D]);
+                    const v4i x1 = INT8 ? __builtin_bit_cast(v4i, ax[rb]) : widen_hi(aq[J][rb][D]);
+                    v4i c = __builtin_amdgcn_mfma_i32_16x16x64_i8(x0, b0, zi, 0, 0, 0);
+                    c = __builtin_amdgcn_mfma_i32_16x16x64_i8(x1, b1, c, 0, 0, 0);
+                    const v4f32 sc = __builtin_amdgcn_mfma_f32_16x16x16f16(scale_operand<D>(avs[J][rb]), scale_operand<D>(ws), zf, 0, 0, 0);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[rb][e] = fmaf((float)c[e], INT8 ? 256.0f * sc[e] : sc[e], acc[rb][e]);
+                }
+            };
+            auto slot = [&](auto jc) __attribute__((always_inline)) {
+                constexpr int J = decltype(jc)::value;
+                group(jc, std::integral_constant<int, 0>());
+                group(jc, std::integral_constant<int, 1>());
+                if constexpr (!(HAS8 && J == NBK - 1 && TAIL == 1)) {
+                    group(jc, std::integral_constant<int, 2>());
+                    group(jc, std::integral_constant<int, 3>());
+                }
+            };
+            slot(std::integral_constant<int, 0>());
+            if constexpr (NBK > 1) { if (full) slot(std::integral_constant<int, 1>()); }
+            // the requests for the block after the next, as soon as these registers are free
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(w, blk + 2);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+                *reinterpret_cast<float4 *>(&red[(slot_of * NW + wave) * RED + (rb * 64 + lane) * 4]) =
+                    make_float4(acc[rb][0] * (1.0f / 256.0f), acc[rb][1] * (1.0f / 256.0f), acc[rb][2] * (1.0f / 256.0f), acc[rb][3] * (1.0f / 256.0f));
+        };
+        // The eight K-slices meet in LDS and are added in slice order, two blocks of channels at a time: one barrier for a pair
+        // (its part of LDS was last read two pairs ago, before the barrier in between).
+        int parity = 0;
+        for (int blk = first; blk < last; blk += 2, parity ^= 2) {
+            step(wa, blk, parity);
+            if (blk + 1 < last) step(wb, blk + 1, parity + 1);
+            __syncthreads();
+            for (int idx = tid; idx < RB * 256; idx += NT) {      // two outputs each: rows m and m + 1 of a column
+                const int one = idx >= RB * 128 ? 1 : 0, t = idx - one * RB * 128;
+                if (blk + one >= last) break;
+                float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll
+                for (int v = 0; v < NW; ++v) {
+                    const float2 f = *reinterpret_cast<const float2 *>(&red[((parity + one) * NW + v) * RED + 2 * t]);
+                    s0 += f.x;
+                    s1 += f.y;
+                }
+                const int l = (t >> 1) & 63, rb = t >> 7, m = 16 * rb + 4 * (l >> 4) + 2 * (t & 1);
+                const int64_t n = (int64_t)(blk + one) * TN + (l & 15);
+                uint16_t *y = p.y + (int64_t)(row0 + m) * p.ldy + n;
+                if (n < p.N) {
+                    if (m < M) y[0] = __half_as_ushort(__float2half_rn(s0));
+                    if (m + 1 < M) y[p.ldy] = __half_as_ushort(__float2half_rn(s1));
+                }
+            }
+        }
+    };
+    if (wave == NW - 1) run(std::true_type());
+    else                run(std::false_type());
+}
+
 // One block of activation rows (M <= 16): decode_staged_body of atom_gemm_decode_staged.h.
 template <int SI, bool TILED, int TAIL>
 __global__ __launch_bounds__(NT, 6)
@@ -490,6 +677,21 @@ void w4a4_gemm_decode_staged_kernel(const GemmParams p)
     decode_staged_body<SI, TILED, TAIL, false>(p, (int)blockIdx.x, stage, NoWait());
 }
 
+// Canonical weights, 17 to 64 rows and K such that every wavefront has one or two blocks of four groups (registers for the
+// activations): the kernel that keeps the activations, where a compute unit has more than four blocks of 16 channels and 32
+// rows to do.  Up to there the other kernels' workgroups are resident together or nearly so, and the start counts: K = 4096, that
+// kernel and the others, M = 32: N = 8192 8.5 / 7.8 us, 11008 9.7 / 10.0, 22016 15.0 / 17.2; M = 64: N = 8192 10.2 / 9.0, 9999 11.7 / 14.9.
+template <int TAIL>
+bool launch_resident(const GemmParams &p, unsigned blocks, hipStream_t stream)
+{
+    const int nblk = ((p.K >> 7) + 3) >> 2, cus = atom_launch::compute_units();
+    const unsigned yb = (unsigned)((p.M + kResidentRows - 1) / kResidentRows);
+    if (p.M > 64 || nblk < NW || nblk > 2 * NW || (int64_t)blocks * yb <= 4 * (int64_t)cus) return false;
+    auto kern = nblk == NW ? &w4a4_gemm_decode_resident_kernel<1, TAIL> : &w4a4_gemm_decode_resident_kernel<2, TAIL>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)cus / yb, yb), dim3(NT), 0, stream, p);      // (fewer workgroups than blocks: every one has some)
+    return true;
+}
+
 // The kernels of the common case: M <= 16 staged, else blocks of 16 rows.
 template <bool TILED, int TAIL>
 void launch_common(const GemmParams &p, unsigned blocks, hipStream_t stream)
@@ -497,6 +699,7 @@ void launch_common(const GemmParams &p, unsigned blocks, hipStream_t stream)
     if (p.M <= 4)       hipLaunchKernelGGL((w4a4_gemm_decode_staged_kernel<1, TILED, TAIL>), dim3(blocks), dim3(NT), 0, stream, p);
     else if (p.M <= 8)  hipLaunchKernelGGL((w4a4_gemm_decode_staged_kernel<2, TILED, TAIL>), dim3(blocks), dim3(NT), 0, stream, p);
     else if (p.M <= 16) hipLaunchKernelGGL((w4a4_gemm_decode_staged_kernel<4, TILED, TAIL>), dim3(blocks), dim3(NT), 0, stream, p);
+    else if (!TILED && launch_resident<TAIL>(p, blocks, stream)) return;
     else if (p.M <= 32) hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<2, 1, TILED, TAIL>), dim3(blocks), dim3(NT), 0, stream, p);
     // Four row blocks (and with more than 64 rows further sets of workgroups for rows 64 and up: the
     // weights of a channel block are then read again, out of the caches): two channel
