@@ -151,6 +151,10 @@ constexpr int kTokens = 64;                // tokens per wavefront group: four s
 //             token l of the 64, one full cache line per array, and reach the lane that
 //             needs them through ds_bpermute: 2-byte loads per step would have several
 //             wavefronts wait on the same line, which stalls the vector cache.
+//             q is asked for before everything else: loads return in order, and a conversion of q that waits for the first
+//             rows as well delays every wavefront's first scores.  Lengths from T / 4 to T, us, q behind the rows and in
+//             front of them: 256 heads, T = 1024 12.8 -> 12.0; 512 heads, T = 700 16.1 -> 15.3; 4096 heads, T = 200 28.9 ->
+//             27.4; 1200 heads, T = 3000 67.2 -> 64.9; 2048 heads, T = 2048 (5.1 TB/s of cache bytes) 74.2 -> 73.6.
 template <int kWaves>                     // wavefronts per workgroup: 4, or 16 when B * H alone is a thin grid
 __global__ __launch_bounds__(kWaves * 64)
 void decode_attention_kv4_kernel(const __half *__restrict__ q, int H, int Hkv, int64_t Tmax,
@@ -170,6 +174,9 @@ void decode_attention_kv4_kernel(const __half *__restrict__ q, int H, int Hkv, i
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tl = lane & 15, c = lane >> 4;
+    uint4 qraw[4];                        // this lane's 32 query values (32 two-byte loads cost a microsecond of prologue)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) qraw[j] = *reinterpret_cast<const uint4 *>(q + ((int64_t)b * H + h) * D + 32 * c + 8 * j);
     int T = seq_len[b];
     T = T < 0 ? 0 : (T > Tmax ? (int)Tmax : T);          // never read past the cache
     const int64_t base = ((int64_t)b * Hkv + kvh) * Tmax;
@@ -200,98 +207,92 @@ void decode_attention_kv4_kernel(const __half *__restrict__ q, int H, int Hkv, i
         km = (uint32_t)__half_as_ushort(ksb[(uint32_t)t]) | ((uint32_t)(uint16_t)kzb[(uint32_t)t] << 16);
         vm = (uint32_t)__half_as_ushort(vsb[(uint32_t)t]) | ((uint32_t)(uint16_t)vzb[(uint32_t)t] << 16);
     };
-    if (alive) {                          // the first loads leave before q is read
-        fetch_meta(G, kmeta, vmeta);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) fetch(st[i], 4 * G + i);
-    }
-
-    // this lane's 32 query values as 16 pairs in the order unpack8 delivers the codes of a
-    // dword (dword j holds d = 32c + 8j + 0..7), and the sums that take the offsets back out
-    h2 qp[16];
-    float qsum = 0.0f, qoff = 0.0f;       // sum(q), sum(offset(d) * q)
-    {
-        const __half *qv = q + ((int64_t)b * H + h) * D + 32 * c;
-        uint4 qraw[4];                    // 64 bytes as four loads (32 two-byte loads cost a microsecond of prologue)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) qraw[j] = *reinterpret_cast<const uint4 *>(qv + 8 * j);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const float lo = half_of(qraw, 8 * j + kNib[k]), hi = half_of(qraw, 8 * j + kNib[k] + 4);
-                qp[4 * j + k] = h2{(_Float16)lo, (_Float16)hi};
-                qsum += lo + hi;
-                qoff += kOff[k] * (lo + hi);
-            }
-    }
-
-    unsigned c_zero = 0u;                 // a zero the compiler cannot see (sum_across_chunks)
-    asm volatile("" : "+s"(c_zero));
     float acc[32];                        // acc[8j + 2k + half] <-> d = 32c + 8j + k + 4 half
 #pragma unroll
     for (int i = 0; i < 32; ++i) acc[i] = 0.0f;
-    float wsum = 0.0f, zacc = 0.0f;       // sums of w = p * v_scale and of w * v_zero since the last flush
     float m_run = -INFINITY, l_run = 0.0f;
-
-    auto consume = [&](const Stage &s_, int tile, int slot) {
-        // this token's scale and zero point sit in lane 16 * slot + tl
-        const int src = (16 * slot + tl) << 2;
-        const uint32_t km = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)kmeta);
-        const uint32_t vm = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)vmeta);
-
-        // ---- scores
-        const uint32_t kw[4] = {s_.k.x, s_.k.y, s_.k.z, s_.k.w};
-        float dot = 0.0f;
+    if (alive) {                          // every first load leaves before any is waited for, q first: loads return in order
+        fetch_meta(G, kmeta, vmeta);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            uint32_t pr[4];
-            unpack8(kw[j], pr);
+        for (int i = 0; i < 4; ++i) fetch(st[i], 4 * G + i);
+        __builtin_amdgcn_sched_barrier(0);
+        // this lane's 32 query values as 16 pairs in the order unpack8 delivers the codes of a
+        // dword (dword j holds d = 32c + 8j + 0..7), and the sums that take the offsets back out
+        h2 qp[16];
+        float qsum = 0.0f, qoff = 0.0f;       // sum(q), sum(offset(d) * q)
+        {
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                dot = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, pr[k]), qp[4 * j + k], dot, false);
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float lo = half_of(qraw, 8 * j + kNib[k]), hi = half_of(qraw, 8 * j + kNib[k] + 4);
+                    qp[4 * j + k] = h2{(_Float16)lo, (_Float16)hi};
+                    qsum += lo + hi;
+                    qoff += kOff[k] * (lo + hi);
+                }
         }
-        const float k_s = __half2float(__ushort_as_half((unsigned short)(km & 0xFFFFu)));
-        const float k_z = (float)(int16_t)(km >> 16);
-        const float part_ = sum_across_chunks(dot - fmaf(k_z, qsum, qoff), c_zero);
-        const bool valid = tile * kTile + tl < T;
-        const float score = valid ? part_ * (k_s * sm_scale) : -INFINITY;
 
-        // ---- online softmax (every lane of the wavefront ends up with the same m and l)
-        const float m_new = fmaxf(m_run, row16_max(score));
-        if (m_new > m_run) {                              // rare after the first few steps
-            const float alpha = __expf(m_run - m_new);    // 0 on the first step
-            l_run *= alpha;
-            wsum *= alpha;
-            zacc *= alpha;
-#pragma unroll
-            for (int i = 0; i < 32; ++i) acc[i] *= alpha;
-            m_run = m_new;
-        }
-        const float p = __expf(score - m_run);
-        l_run += row16_sum(p);
+        unsigned c_zero = 0u;                 // a zero the compiler cannot see (sum_across_chunks)
+        asm volatile("" : "+s"(c_zero));
+        float wsum = 0.0f, zacc = 0.0f;       // sums of w = p * v_scale and of w * v_zero since the last flush
 
-        // ---- values: the fp16 halves go straight into mixed-precision fmas
-        const float v_s = __half2float(__ushort_as_half((unsigned short)(vm & 0xFFFFu)));
-        const float v_z = (float)(int16_t)(vm >> 16);
-        const float wgt = p * v_s;
-        wsum += wgt;
-        zacc = fmaf(wgt, v_z, zacc);
-        const uint32_t vw[4] = {s_.v.x, s_.v.y, s_.v.z, s_.v.w};
+        auto consume = [&](const Stage &s_, int tile, int slot) {
+            // this token's scale and zero point sit in lane 16 * slot + tl
+            const int src = (16 * slot + tl) << 2;
+            const uint32_t km = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)kmeta);
+            const uint32_t vm = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)vmeta);
+
+            // ---- scores
+            const uint32_t kw[4] = {s_.k.x, s_.k.y, s_.k.z, s_.k.w};
+            float dot = 0.0f;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            uint32_t pr[4];
-            unpack8_16(vw[j], pr);
+            for (int j = 0; j < 4; ++j) {
+                uint32_t pr[4];
+                unpack8(kw[j], pr);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const h2 cv = __builtin_bit_cast(h2, pr[k]);
-                acc[8 * j + 2 * k]     = fmaf(wgt, (float)cv[0], acc[8 * j + 2 * k]);
-                acc[8 * j + 2 * k + 1] = fmaf(wgt, (float)cv[1], acc[8 * j + 2 * k + 1]);
+                for (int k = 0; k < 4; ++k)
+                    dot = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, pr[k]), qp[4 * j + k], dot, false);
             }
-        }
-    };
+            const float k_s = __half2float(__ushort_as_half((unsigned short)(km & 0xFFFFu)));
+            const float k_z = (float)(int16_t)(km >> 16);
+            const float part_ = sum_across_chunks(dot - fmaf(k_z, qsum, qoff), c_zero);
+            const bool valid = tile * kTile + tl < T;
+            const float score = valid ? part_ * (k_s * sm_scale) : -INFINITY;
 
-    if (alive) {
+            // ---- online softmax (every lane of the wavefront ends up with the same m and l)
+            const float m_new = fmaxf(m_run, row16_max(score));
+            if (m_new > m_run) {                              // rare after the first few steps
+                const float alpha = __expf(m_run - m_new);    // 0 on the first step
+                l_run *= alpha;
+                wsum *= alpha;
+                zacc *= alpha;
+#pragma unroll
+                for (int i = 0; i < 32; ++i) acc[i] *= alpha;
+                m_run = m_new;
+            }
+            const float p = __expf(score - m_run);
+            l_run += row16_sum(p);
+
+            // ---- values: the fp16 halves go straight into mixed-precision fmas
+            const float v_s = __half2float(__ushort_as_half((unsigned short)(vm & 0xFFFFu)));
+            const float v_z = (float)(int16_t)(vm >> 16);
+            const float wgt = p * v_s;
+            wsum += wgt;
+            zacc = fmaf(wgt, v_z, zacc);
+            const uint32_t vw[4] = {s_.v.x, s_.v.y, s_.v.z, s_.v.w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                uint32_t pr[4];
+                unpack8_16(vw[j], pr);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const h2 cv = __builtin_bit_cast(h2, pr[k]);
+                    acc[8 * j + 2 * k]     = fmaf(wgt, (float)cv[0], acc[8 * j + 2 * k]);
+                    acc[8 * j + 2 * k + 1] = fmaf(wgt, (float)cv[1], acc[8 * j + 2 * k + 1]);
+                }
+            }
+        };
+
         while (G < g_end) {
             const int Gn = G + kWaves;                    // past the end: clamped, unused loads
             uint32_t nk, nv;
