@@ -776,6 +776,12 @@ void decode_attention_merge_kernel(const float *__restrict__ part, int S, __half
     __shared__ float s_den;
     const float *src = part + (int64_t)blockIdx.x * S * (D + 2);
     const int tid = threadIdx.x;
+    // the first splits' values leave before the weights are known: a load behind the barrier costs a latency of its own (attention and
+    // merge, 128 cache heads in 4 splits 23.0 -> 22.7 us, 512 heads in 2 15.3 -> 14.8, 32 heads in 40 23.2 -> 22.2)
+    constexpr int AHEAD = 8;
+    float ahead[AHEAD];
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s) ahead[s] = src[(s < S ? s : S - 1) * (D + 2) + 2 + tid];
     if (tid < 64) {
         const float ms = tid < S ? src[tid * (D + 2)] : -INFINITY;
         const float dn = tid < S ? src[tid * (D + 2) + 1] : 0.0f;
@@ -791,8 +797,10 @@ void decode_attention_merge_kernel(const float *__restrict__ part, int S, __half
     }
     __syncthreads();
     float num = 0.0f;
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s) num = s < S ? fmaf(s_e[s], ahead[s], num) : num;
 #pragma unroll 8
-    for (int s = 0; s < S; ++s) num = fmaf(s_e[s], src[s * (D + 2) + 2 + tid], num);
+    for (int s = AHEAD; s < S; ++s) num = fmaf(s_e[s], src[s * (D + 2) + 2 + tid], num);
     const float den = s_den;
     out[(int64_t)blockIdx.x * D + tid] = __float2half_rn(den > 0.0f ? num / den : 0.0f);
 }
