@@ -6,6 +6,8 @@
 #include <hip/hip_fp16.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace atom_gemm {
 
 typedef int v4i  __attribute__((ext_vector_type(4)));
@@ -71,39 +73,64 @@ __device__ __forceinline__ unsigned to_aligned(const uint16_t *row)
 
 // A finished block of Y (ROWS x COLS fp16; its rows `pitch` >= 2 COLS + 16 bytes apart in LDS, 16-byte aligned) to rows of Y
 // that start on any element (an odd row length, a view): whole 16-byte pieces wherever 16-byte aligned addresses lie in
-// the row, put together from two neighbouring pieces of the staged row, then what is left at its two ends, eight lanes per
+// the row, put together from two neighbouring pieces of the staged row, and what is left at its two ends, eight lanes per
 // row.  `y` is the block's first element; rows and columns at and past rows_left and cols_left are not stored.  (Two
 // bytes per lane, as the accumulators hold them, a block of 64 x 64 is 64 store instructions and more lines than bytes: the
 // packed GEMM at M = 2048, K = 4096 took 132 us for N = 12289 and 88 us for N = 12288.)
+// What bounds it in a launch of few tiles is latency, one wavefront per SIMD: a chunk of rows reads everything from LDS before it
+// stores anything, and eight rows or fewer are a chunk of their own.  (Packed GEMM, N = 100, Y off the grid, K = 512: M = 65 8.0 us with
+// two bytes per lane, 9.0 step by step, 8.2 so; M = 777 8.4, 9.3, 8.3; K = 4096, M = 4096, N = 12289 280, 226, 221.)
 template <int ROWS, int COLS>
 __device__ __forceinline__ void store_block_any(const unsigned char *blk, int pitch, uint16_t *y, int64_t ldy, int rows_left,
                                                 int cols_left, int lane)
 {
-    constexpr int LPR = COLS / 8;
-    static_assert(ROWS * LPR % 64 == 0 && ROWS % 8 == 0, "whole wavefronts");
+    constexpr int LPR = COLS / 8, RPS = 64 / LPR;          // lanes per row, rows that a wavefront's 16-byte pieces cover
+    static_assert(64 % LPR == 0 && RPS <= 16 && ROWS % 32 == 0, "whole wavefronts");
     const int nc = cols_left < COLS ? cols_left : COLS;
-#pragma unroll 2
-    for (int i = 0; i < ROWS * LPR / 64 && 64 * i < LPR * rows_left; ++i) {
-        const int q = 64 * i + lane, r = q / LPR, k = q % LPR;
-        uint16_t *row = y + (int64_t)r * ldy;
-        const unsigned h = to_aligned(row);
-        const v4i lo = *reinterpret_cast<const v4i *>(blk + r * pitch + 16 * k);
-        const v4i hi = *reinterpret_cast<const v4i *>(blk + r * pitch + 16 * k + 16);
-        const v4i d = from_element(lo, hi, h);
-        if (r < rows_left && (int)h + 8 * k + 8 <= nc) *reinterpret_cast<v4i *>(row + h + 8 * k) = d;
-    }
-    // slot e of a row: its first h elements, then those behind the last whole piece (a block of all COLS columns has eight
-    // or none of them, a cut one up to fourteen)
-    if (((reinterpret_cast<uintptr_t>(y) | (uintptr_t)(ldy * 2)) & 15) == 0 && (nc & 7) == 0) return;
-    for (int e0 = 0; e0 < (nc == COLS ? 8 : 16); e0 += 8)
-#pragma unroll 2
-        for (int i = 0; i < ROWS / 8 && 8 * i < rows_left; ++i) {
-            const int r = 8 * i + (lane >> 3), e = e0 + (lane & 7);
-            uint16_t *row = y + (int64_t)r * ldy;
-            const int h = (int)to_aligned(row);
-            const int n = e < h ? e : h + (nc > h ? (nc - h) & ~7 : 0) + (e - h);
-            if (r < rows_left && n < nc) row[n] = *reinterpret_cast<const uint16_t *>(blk + r * pitch + 2 * n);
+    const bool ends = ((reinterpret_cast<uintptr_t>(y) | (uintptr_t)(ldy * 2)) & 15) != 0 || (nc & 7) != 0;
+    const int k = lane % LPR, e = lane & 7;
+    auto chunk = [&](auto rows_c, int r0) __attribute__((always_inline)) {
+        constexpr int C = decltype(rows_c)::value, P = C > RPS ? C / RPS : 1, E = C / 8;
+        const int rp = r0 + lane / LPR, re = r0 + (lane >> 3);
+        uint16_t *const yp = y + rp * ldy, *const ye = y + re * ldy;
+        v4i d[P];
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            const unsigned char *src = blk + (rp + RPS * j) * pitch + 16 * k;
+            d[j] = from_element(*reinterpret_cast<const v4i *>(src), *reinterpret_cast<const v4i *>(src + 16), to_aligned(yp + RPS * j * ldy));
         }
+        // slot e of a row: its first h elements, then those behind the last whole piece (a block of all COLS columns has eight
+        // or none of them, a cut one up to fourteen: slot e + 8)
+        uint16_t one[E], two[E];
+        int n[E], n2[E];
+        if (ends) {
+#pragma unroll
+            for (int j = 0; j < E; ++j) {
+                const uint16_t *src = reinterpret_cast<const uint16_t *>(blk + (re + 8 * j) * pitch);
+                const int h = (int)to_aligned(ye + 8 * j * ldy), whole = nc > h ? (nc - h) & ~7 : 0;
+                n[j]  = e < h ? e : whole + e;
+                n2[j] = whole + e + 8;
+                one[j] = src[n[j]];
+                two[j] = nc < COLS ? src[n2[j]] : 0;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            uint16_t *row = yp + RPS * j * ldy;
+            const int h = (int)to_aligned(row);
+            if (rp + RPS * j < rows_left && h + 8 * k + 8 <= nc) *reinterpret_cast<v4i *>(row + h + 8 * k) = d[j];
+        }
+        if (ends) {
+#pragma unroll
+            for (int j = 0; j < E; ++j) {
+                uint16_t *row = ye + 8 * j * ldy;
+                if (re + 8 * j < rows_left && n[j] < nc) row[n[j]] = one[j];
+                if (re + 8 * j < rows_left && nc < COLS && n2[j] < nc) row[n2[j]] = two[j];
+            }
+        }
+    };
+    if (rows_left <= 8) return chunk(std::integral_constant<int, 8>(), 0);
+    for (int r0 = 0; r0 < ROWS && r0 < rows_left; r0 += 32) chunk(std::integral_constant<int, 32>(), r0);
 }
 
 // The block of Y whose first element is (m, n), cut at M and N.

@@ -35,6 +35,7 @@ def tile(M, N):
     ("128x256", 2049, 256, 15001),       # a last row tile of one row
     ("256x256", 4096, 512, 8192),        # whole tiles, two rounds
     ("256x256", 3257, 384, 4099),        # ragged both ways
+    ("256x256", 3269, 384, 4099),        # ... and a last wavefront of five rows
 ])
 def test_mx_tiles(name, M, K, N):
     assert tile(M, N) == name

@@ -1,6 +1,6 @@
 """Rows of Y that start off the 16-byte grid (odd row lengths, views): the same bits as on the grid, and nothing written around
 the output.  Canonical GEMM (128 x 128 tiles with one and two wavefront sets, 256 x 128 tiles), packed GEMM (general kernel:
-two INT8 groups; the other tiles are in tests/test_gpu_packed_tiles.py)."""
+two INT8 groups; its 64 x 64 tiles with few rows; the other tiles are in tests/test_gpu_packed_tiles.py)."""
 import pytest
 import torch
 
@@ -19,6 +19,10 @@ BORDER = 3
     ("canonical", 2050, 256, 8201, 128),     # 256 x 128 tiles
     ("packed", 130, 640, 2059, 256),         # general kernel
     ("packed", 64, 512, 100, 256),
+    ("packed", 8, 1024, 203, 128),           # 64 x 64 tiles: eight rows of a wavefront's 32, the most that are stored in one go
+    ("packed", 9, 1024, 100, 128),           # ... and one more
+    ("packed", 97, 1024, 1003, 128),         # last wavefronts of one row
+    ("canonical", 265, 256, 8201, 128),      # 128 x 128 tiles: last wavefronts of nine rows
 ])
 def test_row_starts(path, M, K, N, O):
     print(f"[case] row starts {path} M={M} K={K} N={N} O={O}", flush=True)
