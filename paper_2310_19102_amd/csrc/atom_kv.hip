@@ -434,7 +434,10 @@ constexpr int kGqaHeadPitch = 4 * 33 + 1; // floats per head in the merge area (
 //             MFMAs), the column operand q in the same order of d (registers, loaded once);
 //             the result leaves head h = l & 15 and tokens 4 (l >> 4) + e in lane l, and
 //             score = k_scale sm_scale (S - (16 + k_zero) sum_d q).  All four steps first: their
-//             chains of MFMAs and the exchanges of the maximum are independent of each other.
+//             chains of MFMAs and the exchanges of the maximum are independent of each other.  The last group of a sequence does
+//             the MFMAs of the steps that hold tokens only (1 to 10 tokens, 64 heads on 8: 6.2 us, 5.3 so; 1 to 60 7.9, 7.3), but every
+//             load, tokens or not: where paths with and without loads meet, the wait for the next rows is for the fewer in
+//             flight (with the value loads left out too, 64 x 4096 tokens took 59.8 us instead of 56.4).
 //   softmax : online per head and step; the four lanes of a head agree on the maxima of the four steps (three
 //             swaps of lane halves gather them, three bring them back), each keeps the partial sums of its own tokens;
 //             accumulators are rescaled when the maximum moves.
@@ -598,25 +601,35 @@ void decode_attention_kv4_gqa_kernel(const __half *__restrict__ q, int H, int Hk
         while (G < g_end) {
             const int Gn = G + kWaves;                    // past the end: clamped, unused loads
             const Meta meta_next = fetch_meta(Gn);
+            const int steps = (T - G * kTokens + kTile - 1) / kTile;      // those that hold tokens: four and more but for a sequence's last group
             // ---- scores of the four steps
-            float sc[4][4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            v4f sa[4];
+            auto products = [&](int i) __attribute__((always_inline)) {
                 const uint32_t kw[4] = {kst[i].x, kst[i].y, kst[i].z, kst[i].w};
-                v4f sa = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     uint32_t pr[4];
                     unpack8_16_mfma(kw[j], c_mask, c_magic, pr);
-                    sa = __builtin_amdgcn_mfma_f32_16x16x32_f16(quad_operand(pr[0], pr[1], pr[2], pr[3]), qb[j], sa, 0, 0, 0);
+                    sa[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(quad_operand(pr[0], pr[1], pr[2], pr[3]), qb[j], sa[i], 0, 0, 0);
                 }
+            };
+            sa[0] = sa[1] = sa[2] = sa[3] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+            products(0);
+            if (steps > 1) {
+                products(1);
+                products(2);
+                products(3);
+            }
+            float sc[4][4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
                 kst[i] = k_of(4 * Gn + i);
                 const float4 ks4 = *reinterpret_cast<const float4 *>(&s_meta[wave][0][16 * i + 4 * c]);
                 const float4 kz4 = *reinterpret_cast<const float4 *>(&s_meta[wave][1][16 * i + 4 * c]);
-                sc[i][0] = ks4.x * fmaf(-kz4.x, qsum, sa[0]);
-                sc[i][1] = ks4.y * fmaf(-kz4.y, qsum, sa[1]);
-                sc[i][2] = ks4.z * fmaf(-kz4.z, qsum, sa[2]);
-                sc[i][3] = ks4.w * fmaf(-kz4.w, qsum, sa[3]);
+                sc[i][0] = ks4.x * fmaf(-kz4.x, qsum, sa[i][0]);
+                sc[i][1] = ks4.y * fmaf(-kz4.y, qsum, sa[i][1]);
+                sc[i][2] = ks4.z * fmaf(-kz4.z, qsum, sa[i][2]);
+                sc[i][3] = ks4.w * fmaf(-kz4.w, qsum, sa[i][3]);
             }
             if ((G + 1) * kTokens > T) {                  // the end of the sequence: a weight of 0 from there on
 #pragma unroll
@@ -650,62 +663,64 @@ void decode_attention_kv4_gqa_kernel(const __half *__restrict__ q, int H, int Hk
             // ---- values
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                if (__any(m[i + 1] > m[i])) {
-                    const float alpha = m[i + 1] > m[i] ? __builtin_amdgcn_exp2f(m[i] - m[i + 1]) : 1.0f;   // 0 on the first step
-                    off_run *= alpha;
+                if (i == 0 || i < steps) {
+                    if (__any(m[i + 1] > m[i])) {
+                        const float alpha = m[i + 1] > m[i] ? __builtin_amdgcn_exp2f(m[i] - m[i + 1]) : 1.0f;   // 0 on the first step
+                        off_run *= alpha;
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) acc[j] *= alpha;
-                }
-                // w = hi + lo: hi by the packed conversion (which truncates: any rounding will do, lo
-                // takes what hi leaves), two tokens per instruction
-                const h2 hi01 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(w[i][0], w[i][1]));
-                const h2 hi23 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(w[i][2], w[i][3]));
-                const h2 lo01 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(w[i][0] - (float)hi01[0], w[i][1] - (float)hi01[1]));
-                const h2 lo23 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(w[i][2] - (float)hi23[0], w[i][3] - (float)hi23[1]));
-                if (has_rest) {               // rare: the part of a zero point the operands cannot carry
-                    const float *rs = &s_rest[wave][16 * i + 4 * c];   // (hi + lo is w to 2^-22)
+                        for (int j = 0; j < 8; ++j) acc[j] *= alpha;
+                    }
+                    // w = hi + lo: hi by the packed conversion (which truncates: any rounding will do, lo
+                    // takes what hi leaves), two tokens per instruction
+                    const h2 hi01 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(w[i][0], w[i][1]));
+                    const h2 hi23 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(w[i][2], w[i][3]));
+                    const h2 lo01 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(w[i][0] - (float)hi01[0], w[i][1] - (float)hi01[1]));
+                    const h2 lo23 = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(w[i][2] - (float)hi23[0], w[i][3] - (float)hi23[1]));
+                    if (has_rest) {               // rare: the part of a zero point the operands cannot carry
+                        const float *rs = &s_rest[wave][16 * i + 4 * c];   // (hi + lo is w to 2^-22)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) off_run = fmaf(w[i][e], rs[e], off_run);
-                }
-                const v4h pb_hi = {hi01[0], hi01[1], hi23[0], hi23[1]}, pb_lo = {lo01[0], lo01[1], lo23[0], lo23[1]};
-                const v4h z4 = *reinterpret_cast<const v4h *>(&s_zero[wave][16 * i + 4 * c]);
-                const h2 z01 = {z4[0], z4[1]}, z23 = {z4[2], z4[3]};
+                        for (int e = 0; e < 4; ++e) off_run = fmaf(w[i][e], rs[e], off_run);
+                    }
+                    const v4h pb_hi = {hi01[0], hi01[1], hi23[0], hi23[1]}, pb_lo = {lo01[0], lo01[1], lo23[0], lo23[1]};
+                    const v4h z4 = *reinterpret_cast<const v4h *>(&s_zero[wave][16 * i + 4 * c]);
+                    const h2 z01 = {z4[0], z4[1]}, z23 = {z4[2], z4[3]};
 
-                // byte transpose (token i of this lane = dword v_i), then two tokens per unpack
-                const uint32_t w0 = vst[i].v0, w1 = vst[i].v1, w2 = vst[i].v2, w3 = vst[i].v3;
-                // v_perm_b32 picks each result byte out of eight: 0-3 the second operand's, 4-7 the first's
-                constexpr uint32_t kZipLo = 0x05010400u;          // [b.0 a.0 b.1 a.1] of perm(a, b)
-                constexpr uint32_t kZipHi = 0x07030602u;          // [b.2 a.2 b.3 a.3]
-                // L01 = [t0.b0 t1.b0 t0.b1 t1.b1], H01 = [t0.b2 t1.b2 t0.b3 t1.b3] (byte 0 first)
-                const uint32_t L01 = __builtin_amdgcn_perm(w1, w0, kZipLo), H01 = __builtin_amdgcn_perm(w1, w0, kZipHi);
-                const uint32_t L23 = __builtin_amdgcn_perm(w3, w2, kZipLo), H23 = __builtin_amdgcn_perm(w3, w2, kZipHi);
-                // Y_b = [t0.b t2.b t1.b t3.b]: the codes of tokens 0 and 1 sit 16 bits apart, as do 2 and 3
-                uint32_t Y[4];
-                Y[0] = __builtin_amdgcn_perm(L23, L01, kZipLo);
-                Y[1] = __builtin_amdgcn_perm(L23, L01, kZipHi);
-                Y[2] = __builtin_amdgcn_perm(H23, H01, kZipLo);
-                Y[3] = __builtin_amdgcn_perm(H23, H01, kZipHi);
+                    // byte transpose (token i of this lane = dword v_i), then two tokens per unpack
+                    const uint32_t w0 = vst[i].v0, w1 = vst[i].v1, w2 = vst[i].v2, w3 = vst[i].v3;
+                    // v_perm_b32 picks each result byte out of eight: 0-3 the second operand's, 4-7 the first's
+                    constexpr uint32_t kZipLo = 0x05010400u;          // [b.0 a.0 b.1 a.1] of perm(a, b)
+                    constexpr uint32_t kZipHi = 0x07030602u;          // [b.2 a.2 b.3 a.3]
+                    // L01 = [t0.b0 t1.b0 t0.b1 t1.b1], H01 = [t0.b2 t1.b2 t0.b3 t1.b3] (byte 0 first)
+                    const uint32_t L01 = __builtin_amdgcn_perm(w1, w0, kZipLo), H01 = __builtin_amdgcn_perm(w1, w0, kZipHi);
+                    const uint32_t L23 = __builtin_amdgcn_perm(w3, w2, kZipLo), H23 = __builtin_amdgcn_perm(w3, w2, kZipHi);
+                    // Y_b = [t0.b t2.b t1.b t3.b]: the codes of tokens 0 and 1 sit 16 bits apart, as do 2 and 3
+                    uint32_t Y[4];
+                    Y[0] = __builtin_amdgcn_perm(L23, L01, kZipLo);
+                    Y[1] = __builtin_amdgcn_perm(L23, L01, kZipHi);
+                    Y[2] = __builtin_amdgcn_perm(H23, H01, kZipLo);
+                    Y[3] = __builtin_amdgcn_perm(H23, H01, kZipHi);
 #pragma unroll
-                for (int bt = 0; bt < 4; ++bt) {
-                    const uint32_t up = Y[bt] >> 8;
-                    const h2 e01 = __builtin_elementwise_fma(__builtin_bit_cast(h2, Y[bt] & 0x000F000Fu), c_even, z01);
-                    const h2 o01 = __builtin_elementwise_fma(__builtin_bit_cast(h2, Y[bt] & 0x00F000F0u), c_odd, z01);
-                    const h2 e23 = __builtin_elementwise_fma(__builtin_bit_cast(h2, up & 0x000F000Fu), c_even, z23);
-                    const h2 o23 = __builtin_elementwise_fma(__builtin_bit_cast(h2, up & 0x00F000F0u), c_odd, z23);
-                    const v4h ve = {e01[0], e01[1], e23[0], e23[1]}, vo = {o01[0], o01[1], o23[0], o23[1]};     // even / odd d of byte bt
-                    acc[2 * bt]     = __builtin_amdgcn_mfma_f32_16x16x16f16(ve, pb_hi, acc[2 * bt], 0, 0, 0);
-                    acc[2 * bt + 1] = __builtin_amdgcn_mfma_f32_16x16x16f16(vo, pb_hi, acc[2 * bt + 1], 0, 0, 0);
-                    acc[2 * bt]     = __builtin_amdgcn_mfma_f32_16x16x16f16(ve, pb_lo, acc[2 * bt], 0, 0, 0);
-                    acc[2 * bt + 1] = __builtin_amdgcn_mfma_f32_16x16x16f16(vo, pb_lo, acc[2 * bt + 1], 0, 0, 0);
-                }
-                vst[i] = v_of(4 * Gn + i);
-                // an MFMA takes the matrix core 16 cycles: three vector instructions between one and the next, as far as they go
-                __builtin_amdgcn_sched_group_barrier(0x002, 40, 0);
+                    for (int bt = 0; bt < 4; ++bt) {
+                        const uint32_t up = Y[bt] >> 8;
+                        const h2 e01 = __builtin_elementwise_fma(__builtin_bit_cast(h2, Y[bt] & 0x000F000Fu), c_even, z01);
+                        const h2 o01 = __builtin_elementwise_fma(__builtin_bit_cast(h2, Y[bt] & 0x00F000F0u), c_odd, z01);
+                        const h2 e23 = __builtin_elementwise_fma(__builtin_bit_cast(h2, up & 0x000F000Fu), c_even, z23);
+                        const h2 o23 = __builtin_elementwise_fma(__builtin_bit_cast(h2, up & 0x00F000F0u), c_odd, z23);
+                        const v4h ve = {e01[0], e01[1], e23[0], e23[1]}, vo = {o01[0], o01[1], o23[0], o23[1]};     // even / odd d of byte bt
+                        acc[2 * bt]     = __builtin_amdgcn_mfma_f32_16x16x16f16(ve, pb_hi, acc[2 * bt], 0, 0, 0);
+                        acc[2 * bt + 1] = __builtin_amdgcn_mfma_f32_16x16x16f16(vo, pb_hi, acc[2 * bt + 1], 0, 0, 0);
+                        acc[2 * bt]     = __builtin_amdgcn_mfma_f32_16x16x16f16(ve, pb_lo, acc[2 * bt], 0, 0, 0);
+                        acc[2 * bt + 1] = __builtin_amdgcn_mfma_f32_16x16x16f16(vo, pb_lo, acc[2 * bt + 1], 0, 0, 0);
+                    }
+                    // an MFMA takes the matrix core 16 cycles: three vector instructions between one and the next, as far as they go
+                    __builtin_amdgcn_sched_group_barrier(0x002, 40, 0);
 #pragma unroll
-                for (int n = 0; n < 16; ++n) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+                    for (int n = 0; n < 16; ++n) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+                    }
                 }
+                vst[i] = v_of(4 * Gn + i);                // (on every path: the compiler counts the loads in flight)
             }
             if (has_rest) {                               // what the operands could not carry of the zero points
                 float off = off_run;

@@ -35,3 +35,26 @@ def test_attention_at_group_edges(H, Hkv, kind):
     floor = 1e-2 * np.abs(ref).max(axis=(1, 2), keepdims=True)
     err = np.abs(out.astype(np.float64) - ref)[1:] / np.maximum(np.abs(ref), floor)[1:]
     assert err.max() <= 2.0 ** -10, err.max(axis=(1, 2))
+
+
+@pytest.mark.parametrize("H,Hkv", [(2, 2), (4, 2)])
+def test_nothing_behind_the_end_counts(H, Hkv):
+    """The last group of a sequence: whatever its other rows hold (codes, scales that are no numbers, zero points), the bits are those
+    of a cache without them."""
+    B, T, D = len(LENS), 400, 128
+    print(f"[case] attention behind the end H={H} Hkv={Hkv}", flush=True)
+    rng = np.random.default_rng(H)
+    lens = np.array(LENS, dtype=np.int32)
+    behind = np.arange(T)[None, None, :] >= lens[:, None, None]
+    cache = []
+    for _ in range(2):
+        cache += [rng.integers(0, 256, (B, Hkv, T, D // 2), dtype=np.uint8), (0.05 + 0.05 * rng.random((B, Hkv, T))).astype(np.float16),
+                  rng.integers(0, 16, (B, Hkv, T)).astype(np.int16)]
+    other = [np.where(behind[..., None], 255 - cache[i], cache[i]) if i % 3 == 0 else
+             np.where(behind, np.float16("nan") if i == 1 else np.float16("inf"), cache[i]) if i % 3 == 1 else
+             np.where(behind, np.int16(-32768), cache[i]) for i in range(6)]
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    q = dev(rng.standard_normal((B, H, D)).astype(np.float16))
+    outs = [atom.atom_decode_attention_kv4(q, [dev(a) for a in c[:3]], [dev(a) for a in c[3:]], dev(lens), D ** -0.5) for c in (cache, other)]
+    assert bool(torch.isfinite(outs[1]).all())
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
