@@ -483,9 +483,9 @@ void w4a4_gemm_decode16_kernel(const GemmParams p)
 
 constexpr int kResidentRows = 32;           // rows of a workgroup of the next kernel
 
-// Many blocks of channels per compute unit, 17 rows and more, K from 3841 to 8192: a workgroup takes 32 rows and a run of
-// channel blocks, and every wavefront keeps the activation operand of its K-slice (NBK blocks of four groups) in registers
-// for all of them.  w4a4_gemm_decode16_kernel reads the activations again for each block or two, more bytes from the L2 than
+// Many blocks of channels per compute unit, 17 to 64 rows, K from 3840 to 8192 (30 to 64 groups): a workgroup takes 32 rows and a
+// run of channel blocks, and every wavefront keeps the activation operand of its K-slice (NBK blocks of four groups, or one less) in
+// registers for all of them.  w4a4_gemm_decode16_kernel reads the activations again for each block or two, more bytes from the L2 than
 // the weights are, and every workgroup pays its own start and its own meeting of slices; here only weights stream, those of
 // the next two blocks in flight while one is multiplied.  Same sums in the same order: the same bits.
 // Canonical weights from memory, us, that kernel and this one: K = 4096: M = 32, N = 22016 17.1 / 14.5; M = 64, N = 8999
@@ -493,6 +493,10 @@ constexpr int kResidentRows = 32;           // rows of a workgroup of the next k
 // 71.7 / 55.5, M = 64, N = 9000 27.2 / 20.9.  What bounds it now: the weights (9.0 us for 22016 x 4096 when only read) behind a
 // start of 4 us in which the activations arrive, and at 64 rows the two passes over the weights.  64 rows per workgroup read
 // them once, but the widening for twice the rows stands in the way (N = 22016 21.1); weights three blocks ahead: no faster.
+// A wavefront with one block where others have two (K from 4352 to 7680) is code of its own and requests only what it uses.  (With a
+// second request of its first block in the missing one's place six of eight wavefronts read their weights twice at K = 5120:
+// M = 33, N = 13824 22.8 us, 20.3 so, w4a4_gemm_decode16_kernel 22.6; M = 32, N = 16400 19.5, 17.7, 18.3; K = 4352, M = 33, N = 13824
+// 22.1, 16.6, 19.3.)
 template <int NBK, int TAIL>
 __global__ __launch_bounds__(NT, 2)
 void w4a4_gemm_decode_resident_kernel(const GemmParams p)
@@ -521,52 +525,49 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
     const v4i   zi = {0, 0, 0, 0};
     const v4f32 zf = {0.0f, 0.0f, 0.0f, 0.0f};
 
-    // the last wavefront's last block of groups holds the INT8 group; with NBK = 2 the others may have one block only
-    auto run = [&](auto has8_c) __attribute__((always_inline)) {
+    // NB: this wavefront's blocks of groups (NBK, or one less where eight K-slices do not share them evenly); the last wavefront
+    // has NBK, and its last block holds the INT8 group
+    auto run = [&](auto has8_c, auto blocks_c) __attribute__((always_inline)) {
         constexpr bool HAS8 = decltype(has8_c)::value;
-        const int  cnt  = (g_end - g_begin + 3) >> 2;
-        const bool full = HAS8 || cnt == NBK;             // otherwise slot NBK - 1 repeats what slot 0 reads and is not used
-        int gb[NBK];
-#pragma unroll
-        for (int j = 0; j < NBK; ++j) gb[j] = j < cnt ? g_begin + 4 * j : g_begin;
-        auto ng4 = [](int j) constexpr { return HAS8 && j == NBK - 1 ? TAIL : 4; };      // INT4 groups of slot j
+        constexpr int  NB   = decltype(blocks_c)::value;
+        auto ng4 = [](int j) constexpr { return HAS8 && j == NB - 1 ? TAIL : 4; };       // INT4 groups of block j
 
-        struct Weights { uint4 q[NBK][4], x; uint2 s[NBK]; };
+        struct Weights { uint4 q[NB][4], x; uint2 s[NB]; };
         auto fetch = [&](Weights &w, int blk) __attribute__((always_inline)) {
             blk = blk < last ? blk : last - 1;            // past the end: the last block once more, not used
             int64_t wr = (int64_t)blk * TN + col;         // clamped: columns >= N are computed and never stored
             wr = wr < p.N ? wr : p.N - 1;
             const uint32_t w4o = (uint32_t)(wr * (K4 >> 1)) + kc * 16, w8o = (uint32_t)(wr * 128) + kc * 16;
 #pragma unroll
-            for (int j = 0; j < NBK; ++j) {
-                w.s[j] = load_scales<A8>(p.w_scale, (uint32_t)wr * (uint32_t)G, gb[j], G);
+            for (int j = 0; j < NB; ++j) {
+                w.s[j] = load_scales<A8>(p.w_scale, (uint32_t)wr * (uint32_t)G, g_begin + 4 * j, G);
 #pragma unroll
-                for (int d = 0; d < ng4(j); ++d) w.q[j][d] = *reinterpret_cast<const uint4 *>(p.w_q4 + (w4o + (uint32_t)(gb[j] + d) * 64u));
+                for (int d = 0; d < ng4(j); ++d) w.q[j][d] = *reinterpret_cast<const uint4 *>(p.w_q4 + (w4o + (uint32_t)(g_begin + 4 * j + d) * 64u));
             }
             if constexpr (HAS8) {
-                w.q[NBK - 1][TAIL] = *reinterpret_cast<const uint4 *>(w8b + w8o);
-                w.x                = *reinterpret_cast<const uint4 *>(w8b + (w8o + 64u));
+                w.q[NB - 1][TAIL] = *reinterpret_cast<const uint4 *>(w8b + w8o);
+                w.x               = *reinterpret_cast<const uint4 *>(w8b + (w8o + 64u));
             }
         };
         Weights wa, wb;
 
         // the activation operand of the wavefront's groups (row 16 rb + col of this lane; rows >= M read row 0 and are never
         // stored), ahead of the weights in the order of the requests
-        uint4 aq[NBK][RB][4], ax[RB];
-        uint2 avs[NBK][RB];
+        uint4 aq[NB][RB][4], ax[RB];
+        uint2 avs[NB][RB];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             const uint32_t ar = row0 + (16 * rb + col < M ? 16 * rb + col : 0);
             const uint32_t a4o = ar * (uint32_t)(K4 >> 1) + kc * 16, a8o = ar * 128u + kc * 16;
 #pragma unroll
-            for (int j = 0; j < NBK; ++j) {
-                avs[j][rb] = load_scales<A8>(p.a_scale, ar * (uint32_t)G, gb[j], G);
+            for (int j = 0; j < NB; ++j) {
+                avs[j][rb] = load_scales<A8>(p.a_scale, ar * (uint32_t)G, g_begin + 4 * j, G);
 #pragma unroll
-                for (int d = 0; d < ng4(j); ++d) aq[j][rb][d] = *reinterpret_cast<const uint4 *>(p.a_q4 + (a4o + (uint32_t)(gb[j] + d) * 64u));
+                for (int d = 0; d < ng4(j); ++d) aq[j][rb][d] = *reinterpret_cast<const uint4 *>(p.a_q4 + (a4o + (uint32_t)(g_begin + 4 * j + d) * 64u));
             }
             if constexpr (HAS8) {
-                aq[NBK - 1][rb][TAIL] = *reinterpret_cast<const uint4 *>(a8b + a8o);
-                ax[rb]                = *reinterpret_cast<const uint4 *>(a8b + (a8o + 64u));
+                aq[NB - 1][rb][TAIL] = *reinterpret_cast<const uint4 *>(a8b + a8o);
+                ax[rb]               = *reinterpret_cast<const uint4 *>(a8b + (a8o + 64u));
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -579,7 +580,7 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
         __builtin_amdgcn_sched_barrier(0);
         if (kc != 0) {                                    // k-slots 4 .. 15 of the scale MFMA stay empty
 #pragma unroll
-            for (int j = 0; j < NBK; ++j)
+            for (int j = 0; j < NB; ++j)
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) avs[j][rb] = make_uint2(0, 0);
         }
@@ -592,7 +593,7 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
                 for (int e = 0; e < 4; ++e) acc[rb][e] = 0.0f;
             // (the widened codes are made again for every block: hoisted out of the loop they would take twice the registers)
 #pragma unroll
-            for (int j = 0; j < NBK; ++j)
+            for (int j = 0; j < NB; ++j)
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) {
 #pragma unroll
@@ -602,7 +603,7 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
                 }
             auto group = [&](auto jc, auto dc) __attribute__((always_inline)) {
                 constexpr int J = decltype(jc)::value, D = decltype(dc)::value;
-                constexpr bool INT8 = HAS8 && J == NBK - 1 && D == TAIL;
+                constexpr bool INT8 = HAS8 && J == NB - 1 && D == TAIL;
                 const v4i b0 = INT8 ? __builtin_bit_cast(v4i, w.q[J][D]) : widen_lo(w.q[J][D]);
                 const v4i b1 = INT8 ? __builtin_bit_cast(v4i, w.x) : widen_hi(w.q[J][D]);
                 const uint2 ws = kc != 0 ? make_uint2(0, 0) : w.s[J];
@@ -621,13 +622,13 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
                 constexpr int J = decltype(jc)::value;
                 group(jc, std::integral_constant<int, 0>());
                 group(jc, std::integral_constant<int, 1>());
-                if constexpr (!(HAS8 && J == NBK - 1 && TAIL == 1)) {
+                if constexpr (!(HAS8 && J == NB - 1 && TAIL == 1)) {
                     group(jc, std::integral_constant<int, 2>());
                     group(jc, std::integral_constant<int, 3>());
                 }
             };
             slot(std::integral_constant<int, 0>());
-            if constexpr (NBK > 1) { if (full) slot(std::integral_constant<int, 1>()); }
+            if constexpr (NB > 1) slot(std::integral_constant<int, 1>());
             // the requests for the block after the next, as soon as these registers are free
             __builtin_amdgcn_sched_barrier(0);
             fetch(w, blk + 2);
@@ -664,8 +665,13 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
             }
         }
     };
-    if (wave == NW - 1) run(std::true_type());
-    else                run(std::false_type());
+    if (wave == NW - 1) {
+        run(std::true_type(), std::integral_constant<int, NBK>());
+    } else {
+        if constexpr (NBK > 1)
+            if (g_end - g_begin < 4 * NBK) return run(std::false_type(), std::integral_constant<int, NBK - 1>());
+        run(std::false_type(), std::integral_constant<int, NBK>());
+    }
 }
 
 // One block of activation rows (M <= 16): decode_staged_body of atom_gemm_decode_staged.h.
@@ -681,15 +687,21 @@ void w4a4_gemm_decode_staged_kernel(const GemmParams p)
 // activations): the kernel that keeps the activations, where a compute unit has more than four blocks of 16 channels and 32
 // rows to do.  Up to there the other kernels' workgroups are resident together or nearly so, and the start counts: K = 4096, that
 // kernel and the others, M = 32: N = 8192 8.5 / 7.8 us, 11008 9.7 / 10.0, 22016 15.0 / 17.2; M = 64: N = 8192 10.2 / 9.0, 9999 11.7 / 14.9.
-template <int TAIL>
-bool launch_resident(const GemmParams &p, unsigned blocks, hipStream_t stream)
+// Just past the line, where the others' last round is one workgroup, they are as fast with 17 rows (K = 5120, N = 16400 17.1 / 16.3,
+// 17408 17.9 / 17.9, 18432 18.2 / 18.3); everywhere else of 539 sizes around the line this kernel is ahead.
+bool resident(int64_t M, int64_t N, int K, int64_t cus)
 {
-    const int nblk = ((p.K >> 7) + 3) >> 2, cus = atom_launch::compute_units();
-    const unsigned yb = (unsigned)((p.M + kResidentRows - 1) / kResidentRows);
-    if (p.M > 64 || nblk < NW || nblk > 2 * NW || (int64_t)blocks * yb <= 4 * (int64_t)cus) return false;
-    auto kern = nblk == NW ? &w4a4_gemm_decode_resident_kernel<1, TAIL> : &w4a4_gemm_decode_resident_kernel<2, TAIL>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)cus / yb, yb), dim3(NT), 0, stream, p);      // (fewer workgroups than blocks: every one has some)
-    return true;
+    const int     nblk = ((K >> 7) + 3) >> 2;
+    const int64_t blocks = (N + TN - 1) / TN, sets = (M + kResidentRows - 1) / kResidentRows;
+    return M > 16 && M <= 64 && nblk >= NW && nblk <= 2 * NW && blocks * sets > 4 * cus;
+}
+
+template <int TAIL>
+void launch_resident(const GemmParams &p, hipStream_t stream)
+{
+    const unsigned sets = (unsigned)((p.M + kResidentRows - 1) / kResidentRows);
+    auto kern = p.K <= 512 * NW ? &w4a4_gemm_decode_resident_kernel<1, TAIL> : &w4a4_gemm_decode_resident_kernel<2, TAIL>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)atom_launch::compute_units() / sets, sets), dim3(NT), 0, stream, p);   // (fewer workgroups than blocks: every one has some)
 }
 
 // The kernels of the common case: M <= 16 staged, else blocks of 16 rows.
@@ -699,7 +711,7 @@ void launch_common(const GemmParams &p, unsigned blocks, hipStream_t stream)
     if (p.M <= 4)       hipLaunchKernelGGL((w4a4_gemm_decode_staged_kernel<1, TILED, TAIL>), dim3(blocks), dim3(NT), 0, stream, p);
     else if (p.M <= 8)  hipLaunchKernelGGL((w4a4_gemm_decode_staged_kernel<2, TILED, TAIL>), dim3(blocks), dim3(NT), 0, stream, p);
     else if (p.M <= 16) hipLaunchKernelGGL((w4a4_gemm_decode_staged_kernel<4, TILED, TAIL>), dim3(blocks), dim3(NT), 0, stream, p);
-    else if (!TILED && launch_resident<TAIL>(p, blocks, stream)) return;
+    else if (!TILED && resident(p.M, p.N, p.K, atom_launch::compute_units())) launch_resident<TAIL>(p, stream);
     else if (p.M <= 32) hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<2, 1, TILED, TAIL>), dim3(blocks), dim3(NT), 0, stream, p);
     // Four row blocks (and with more than 64 rows further sets of workgroups for rows 64 and up: the
     // weights of a channel block are then read again, out of the caches): two channel
@@ -742,6 +754,9 @@ void tile_weight_kernel(const uint8_t *__restrict__ q4, const int8_t *__restrict
 }
 
 }  // namespace
+
+// Whether a decode GEMM of the common case on canonical weights takes the kernel that keeps the activations, as its test asks it.
+extern "C" int atom_internal_decode_resident(int64_t M, int64_t N, int K, int64_t cus) { return resident(M, N, K, cus); }
 
 namespace atom_gemm {
 
