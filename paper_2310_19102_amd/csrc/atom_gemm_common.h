@@ -73,15 +73,48 @@ __device__ __forceinline__ unsigned to_aligned(const uint16_t *row)
 
 // A finished block of Y (ROWS x COLS fp16; its rows `pitch` >= 2 COLS + 16 bytes apart in LDS, 16-byte aligned) to rows of Y
 // that start on any element (an odd row length, a view): whole 16-byte pieces wherever 16-byte aligned addresses lie in
-// the row, put together from two neighbouring pieces of the staged row, and what is left at its two ends, eight lanes per
+// the row, put together from two neighbouring pieces of the staged row, then what is left at its two ends, eight lanes per
 // row.  `y` is the block's first element; rows and columns at and past rows_left and cols_left are not stored.  (Two
 // bytes per lane, as the accumulators hold them, a block of 64 x 64 is 64 store instructions and more lines than bytes: the
 // packed GEMM at M = 2048, K = 4096 took 132 us for N = 12289 and 88 us for N = 12288.)
-// What bounds it in a launch of few tiles is latency, one wavefront per SIMD: a chunk of rows reads everything from LDS before it
-// stores anything, and eight rows or fewer are a chunk of their own.  (Packed GEMM, N = 100, Y off the grid, K = 512: M = 65 8.0 us with
-// two bytes per lane, 9.0 step by step, 8.2 so; M = 777 8.4, 9.3, 8.3; K = 4096, M = 4096, N = 12289 280, 226, 221.)
 template <int ROWS, int COLS>
 __device__ __forceinline__ void store_block_any(const unsigned char *blk, int pitch, uint16_t *y, int64_t ldy, int rows_left,
+                                                int cols_left, int lane)
+{
+    constexpr int LPR = COLS / 8;
+    static_assert(ROWS * LPR % 64 == 0 && ROWS % 8 == 0, "whole wavefronts");
+    const int nc = cols_left < COLS ? cols_left : COLS;
+#pragma unroll 2
+    for (int i = 0; i < ROWS * LPR / 64 && 64 * i < LPR * rows_left; ++i) {
+        const int q = 64 * i + lane, r = q / LPR, k = q % LPR;
+        uint16_t *row = y + (int64_t)r * ldy;
+        const unsigned h = to_aligned(row);
+        const v4i lo = *reinterpret_cast<const v4i *>(blk + r * pitch + 16 * k);
+        const v4i hi = *reinterpret_cast<const v4i *>(blk + r * pitch + 16 * k + 16);
+        const v4i d = from_element(lo, hi, h);
+        if (r < rows_left && (int)h + 8 * k + 8 <= nc) *reinterpret_cast<v4i *>(row + h + 8 * k) = d;
+    }
+    // slot e of a row: its first h elements, then those behind the last whole piece (a block of all COLS columns has eight
+    // or none of them, a cut one up to fourteen)
+    if (((reinterpret_cast<uintptr_t>(y) | (uintptr_t)(ldy * 2)) & 15) == 0 && (nc & 7) == 0) return;
+    for (int e0 = 0; e0 < (nc == COLS ? 8 : 16); e0 += 8)
+#pragma unroll 2
+        for (int i = 0; i < ROWS / 8 && 8 * i < rows_left; ++i) {
+            const int r = 8 * i + (lane >> 3), e = e0 + (lane & 7);
+            uint16_t *row = y + (int64_t)r * ldy;
+            const int h = (int)to_aligned(row);
+            const int n = e < h ? e : h + (nc > h ? (nc - h) & ~7 : 0) + (e - h);
+            if (r < rows_left && n < nc) row[n] = *reinterpret_cast<const uint16_t *>(blk + r * pitch + 2 * n);
+        }
+}
+
+// The same for the kernels of launches of few tiles.  What bounds it there is latency, one wavefront per SIMD: a chunk of rows reads
+// everything from LDS before it stores anything, and eight rows or fewer are a chunk of their own.  (Packed GEMM, N = 100, Y off the grid,
+// K = 512: M = 65 8.0 us with two bytes per lane, 9.0 step by step, 8.2 so; M = 777 8.4, 9.3, 8.3.  The kernels of many tiles keep the
+// steps: the registers and the code of this form cost the walking one 1 to 2.5 % at every size, M = 4096, K = 8192, N = 57344 1626 us,
+// 1663 so, and the canonical one 27.6 against 29.2 at M = 4096, K = 512, N = 4096 off the grid.)
+template <int ROWS, int COLS>
+__device__ __forceinline__ void store_block_few(const unsigned char *blk, int pitch, uint16_t *y, int64_t ldy, int rows_left,
                                                 int cols_left, int lane)
 {
     constexpr int LPR = COLS / 8, RPS = 64 / LPR;          // lanes per row, rows that a wavefront's 16-byte pieces cover
@@ -133,8 +166,8 @@ __device__ __forceinline__ void store_block_any(const unsigned char *blk, int pi
     for (int r0 = 0; r0 < ROWS && r0 < rows_left; r0 += 32) chunk(std::integral_constant<int, 32>(), r0);
 }
 
-// The block of Y whose first element is (m, n), cut at M and N.
-template <int ROWS, int COLS>
+// The block of Y whose first element is (m, n), cut at M and N.  FEW: a kernel of launches of few tiles.
+template <int ROWS, int COLS, bool FEW = false>
 __device__ __forceinline__ void store_block(const unsigned char *blk, int pitch, uint16_t *y, int64_t ldy, int64_t m, int64_t n,
                                             int64_t M, int64_t N, int lane)
 {
@@ -151,7 +184,8 @@ __device__ __forceinline__ void store_block(const unsigned char *blk, int pitch,
             if (i * (64 / LPR) + r < rows)
                 *reinterpret_cast<v4i *>(mine + i * (64 / LPR) * ldy) = *reinterpret_cast<const v4i *>(blk + (i * (64 / LPR) + r) * pitch + 16 * k);
     } else {
-        store_block_any<ROWS, COLS>(blk, pitch, first, ldy, rows, (int)(N - n < COLS ? N - n : COLS), lane);
+        if constexpr (FEW) store_block_few<ROWS, COLS>(blk, pitch, first, ldy, rows, (int)(N - n < COLS ? N - n : COLS), lane);
+        else               store_block_any<ROWS, COLS>(blk, pitch, first, ldy, rows, (int)(N - n < COLS ? N - n : COLS), lane);
     }
 }
 

@@ -543,7 +543,7 @@ void w4a4_gemm_f6_kernel(const F6Params p)
             *reinterpret_cast<uint16_t *>(ot + row * OSTRIDE + col * 2) = __half_as_ushort(__float2half_rn(acc[t][e]));
         }
     __builtin_amdgcn_s_waitcnt(wait_imm(0));                   // the wavefront reads only what it wrote itself
-    store_block<64, 64>(ot, OSTRIDE, p.y, p.ldy, T.m_w, T.n_w, p.M, p.N, lane);
+    store_block<64, 64, true>(ot, OSTRIDE, p.y, p.ldy, T.m_w, T.n_w, p.M, p.N, lane);
 }
 
 template <int WM, bool DBG>

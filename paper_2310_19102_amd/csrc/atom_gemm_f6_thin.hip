@@ -280,7 +280,7 @@ void w4a4_gemm_f6_thin_kernel(const F6Params p)
                 v2u{__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi)};
         }
     __builtin_amdgcn_s_waitcnt(wait_imm(63));                  // (LDS only: the wavefront reads what it wrote itself)
-    store_block<32, 32 * NJ>(ot, OSTR, p.y, p.ldy, (int64_t)au0 * 64 + 32 * wr, (int64_t)wu0 * 64 + 32 * cb, p.M, p.N, lane);
+    store_block<32, 32 * NJ, true>(ot, OSTR, p.y, p.ldy, (int64_t)au0 * 64 + 32 * wr, (int64_t)wu0 * 64 + 32 * cb, p.M, p.N, lane);
 }
 
 template <int WR, int WC, int NJ, int STAGES, int OCC>
