@@ -530,6 +530,9 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
     auto run = [&](auto has8_c, auto blocks_c) __attribute__((always_inline)) {
         constexpr bool HAS8 = decltype(has8_c)::value;
         constexpr int  NB   = decltype(blocks_c)::value;
+        int gb[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) gb[j] = g_begin + 4 * j;
         auto ng4 = [](int j) constexpr { return HAS8 && j == NB - 1 ? TAIL : 4; };       // INT4 groups of block j
 
         struct Weights { uint4 q[NB][4], x; uint2 s[NB]; };
@@ -540,9 +543,9 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
             const uint32_t w4o = (uint32_t)(wr * (K4 >> 1)) + kc * 16, w8o = (uint32_t)(wr * 128) + kc * 16;
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
-                w.s[j] = load_scales<A8>(p.w_scale, (uint32_t)wr * (uint32_t)G, g_begin + 4 * j, G);
+                w.s[j] = load_scales<A8>(p.w_scale, (uint32_t)wr * (uint32_t)G, gb[j], G);
 #pragma unroll
-                for (int d = 0; d < ng4(j); ++d) w.q[j][d] = *reinterpret_cast<const uint4 *>(p.w_q4 + (w4o + (uint32_t)(g_begin + 4 * j + d) * 64u));
+                for (int d = 0; d < ng4(j); ++d) w.q[j][d] = *reinterpret_cast<const uint4 *>(p.w_q4 + (w4o + (uint32_t)(gb[j] + d) * 64u));
             }
             if constexpr (HAS8) {
                 w.q[NB - 1][TAIL] = *reinterpret_cast<const uint4 *>(w8b + w8o);
@@ -561,9 +564,9 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
             const uint32_t a4o = ar * (uint32_t)(K4 >> 1) + kc * 16, a8o = ar * 128u + kc * 16;
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
-                avs[j][rb] = load_scales<A8>(p.a_scale, ar * (uint32_t)G, g_begin + 4 * j, G);
+                avs[j][rb] = load_scales<A8>(p.a_scale, ar * (uint32_t)G, gb[j], G);
 #pragma unroll
-                for (int d = 0; d < ng4(j); ++d) aq[j][rb][d] = *reinterpret_cast<const uint4 *>(p.a_q4 + (a4o + (uint32_t)(g_begin + 4 * j + d) * 64u));
+                for (int d = 0; d < ng4(j); ++d) aq[j][rb][d] = *reinterpret_cast<const uint4 *>(p.a_q4 + (a4o + (uint32_t)(gb[j] + d) * 64u));
             }
             if constexpr (HAS8) {
                 aq[NB - 1][rb][TAIL] = *reinterpret_cast<const uint4 *>(a8b + a8o);
