@@ -692,6 +692,8 @@ void w4a4_gemm_decode_staged_kernel(const GemmParams p)
 // kernel and the others, M = 32: N = 8192 8.5 / 7.8 us, 11008 9.7 / 10.0, 22016 15.0 / 17.2; M = 64: N = 8192 10.2 / 9.0, 9999 11.7 / 14.9.
 // Just past the line, where the others' last round is one workgroup, they are as fast with 17 rows (K = 5120, N = 16400 17.1 / 16.3,
 // 17408 17.9 / 17.9, 18432 18.2 / 18.3); everywhere else of 539 sizes around the line this kernel is ahead.
+// Re-tiled weights stay with w4a4_gemm_decode16_kernel.  Canonical and re-tiled, us: K = 4096, N = 22016: M = 32 15.4 / 16.7, M = 64 20.8 /
+// 22.8; K = 5120, N = 28672, M = 64 37.5 / 41.8; K = 8192: M = 32, N = 28672 33.2 / 39.2, M = 64, N = 13824 28.7 / 25.6.
 bool resident(int64_t M, int64_t N, int K, int64_t cus)
 {
     const int     nblk = ((K >> 7) + 3) >> 2;

@@ -462,7 +462,7 @@ constexpr int kGqaHeadPitch = 4 * 33 + 1; // floats per head in the merge area (
 //             bound, the rest leaves through sum_t w * rest as in the per-head kernel.
 //   scales  : lane l reads the scale and zero point of token l of the group (one cache line
 //             per array) and parks what the steps need in LDS, where a step reads its four tokens' worth as broadcasts.
-// What bounds it: the chain of instructions of a wavefront (the grid leaves one or two per SIMD).  A group takes about 5300
+// What bounds it: the chain of instructions of a wavefront (the grid leaves one to three per SIMD).  A group takes about 5300
 // cycles alone on its SIMD, 630 to 770 of vector ALU instructions at 4 cycles, and 80 MFMAs at 16 of which the scheduling below
 // hides most.  Alone, 64 heads on 8, lengths from T / 4 to T, us, against one step after the other with its own maximum, clamped
 // addresses and loads that waited for the scales: 16 sequences of 4096 25.2 -> 23.0, 128 of 2048 58.1 -> 50.2, 64 of
@@ -840,8 +840,10 @@ AttentionShape decode_attention_shape(int B, int H, int Hkv, int64_t Tmax)
     const int     Gq     = H / Hkv;
     if (Gq >= 2 && Gq <= kGqaMaxHeads) {
         const int64_t bk = (int64_t)B * Hkv;
-        // about 512 workgroups (two per CU, one round); measured against 768 to 4096: more splits only add
-        // prologues, epilogues and merge work
+        // about 512 workgroups, two per compute unit where three fit.  No target is the best one everywhere (64 heads on 8,
+        // lengths from T / 4 to T, attention and merge, us, targets of 256, 512, 768, 1024, 1536): 16 x 4096 tokens 23.9, 22.5, 24.5,
+        // 24.5, 24.6; 16 x 16384 67.8, 58.3, 58.2, 57.5, 58.6; 32 x 4096 36.0, 34.4, 33.6, 35.2, 36.1; 32 x 2048 21.2, 22.7, 23.1,
+        // 24.9, 24.9; 1 x 16384 12.8, 14.9 from 512 on; and from 257 cache heads on, not split, 48 x 4096 49.2, 49.3, 43.6, 43.2, 44.0
         int64_t want = 512 / bk, cap = groups / kGqaWaves;    // no split from 257 workgroups on
         if (want > cap) want = cap;
         if (want > 64) want = 64;

@@ -327,14 +327,15 @@ hipError_t launch_tile(const MxParams &p, hipStream_t stream)
 // Which tile.  The cost of a launch, in microseconds per K step, with f tiles per compute unit: `full` for each whole tile
 // every compute unit has, and for a last part r of them what they add when few compute units have one (`alone` where it is
 // all there is, `more` beside other workgroups), growing to `full` as the chip fills and the power limit sets in.  Measured
-// at 47 sizes, K = 1024 to 14336 (us; the choice is the fastest of the five or, at worst, 5 % behind it):
-//   M = 65,   N = 4096,  K = 4096:   64 x 64 9.2, 64 x 128 10.7, 128 x 128 11.4, 256 x 256 24.1
-//   M = 256,  N = 12288, K = 4096:   64 x 64 15.1, 64 x 128 14.5, 128 x 128 11.9, 128 x 256 17.4
-//   M = 512,  N = 4096,  K = 4096:   64 x 64 11.3, 64 x 128 10.7, 128 x 128 11.2, 128 x 256 17.0
-//   M = 777,  N = 13824, K = 5120:   64 x 64 55.3, 64 x 128 48.7, 128 x 128 35.9, 128 x 256 39.7, 256 x 256 36.9
-//   M = 1024, N = 22016, K = 4096:   64 x 128 77.9, 128 x 128 56.4, 128 x 256 55.9, 256 x 256 57.9
-//   M = 4096, N = 22016, K = 4096:   128 x 128 265.9, 128 x 256 219.5, 256 x 256 203.6
-// (The kernel before, 256 x 256 and 128 x 128 with four wavefronts: 14.4, 15.8, 15.3, 43.8, 69.8 and 230.1.)
+// at 43 sizes, K = 1024 to 14336 (profiles/mx_gemm_tiles.txt has all of them; us, weights from memory; the choice is within 5 % of the
+// best tile but at M = 256, N = 22016 and M = 2048, N = 12288, K = 4096, where 128 x 256 would be 8 and 10 % faster):
+//   M = 65,   N = 4096,  K = 4096:   64 x 64 9.2, 64 x 128 10.7, 128 x 128 11.3, 128 x 256 16.9, 256 x 256 23.7
+//   M = 256,  N = 12288, K = 4096:   64 x 64 18.2, 64 x 128 18.0, 128 x 128 14.2, 128 x 256 20.7, 256 x 256 25.5
+//   M = 512,  N = 4096,  K = 4096:   64 x 64 12.4, 64 x 128 11.5, 128 x 128 12.2, 128 x 256 17.7, 256 x 256 24.1
+//   M = 777,  N = 13824, K = 5120:   64 x 64 64.3, 64 x 128 54.7, 128 x 128 38.5, 128 x 256 43.3, 256 x 256 40.2
+//   M = 1024, N = 22016, K = 4096:   64 x 64 103.4, 64 x 128 85.5, 128 x 128 62.4, 128 x 256 55.9, 256 x 256 61.1
+//   M = 4096, N = 22016, K = 4096:   64 x 64 436.6, 64 x 128 331.6, 128 x 128 251.2, 128 x 256 207.0, 256 x 256 203.1
+// (The kernel before, 256 x 256 and 128 x 128 with four wavefronts: 15.0, 16.4, 15.7, 49.1, 73.5 and 242.3.)
 enum Tile { k64x64, k64x128, k128x128, k128x256, k256x256, kTiles };
 struct TileCost { int bm, bn; float alone, more, full; };
 constexpr TileCost kCost[kTiles] = {{64, 64, 0.150f, 0.080f, 0.125f}, {64, 128, 0.190f, 0.110f, 0.205f}, {128, 128, 0.235f, 0.110f, 0.300f},
