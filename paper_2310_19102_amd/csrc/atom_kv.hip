@@ -128,6 +128,19 @@ __device__ __forceinline__ float half_of(const uint4 (&raw)[4], int i)
     return __half2float(__ushort_as_half((unsigned short)((i & 1) ? w >> 16 : w & 0xFFFFu)));
 }
 
+// 16 bytes of the cache.  ONCE: with the hint that nothing reads them again (launches of a large cache, see launch_decode_attention_kv4).
+template <bool ONCE>
+__device__ __forceinline__ uint4 load_row(const uint8_t *p)
+{
+    typedef unsigned v4u_ __attribute__((ext_vector_type(4)));
+    if constexpr (ONCE) {
+        const v4u_ v = __builtin_nontemporal_load(reinterpret_cast<const v4u_ *>(p));
+        return make_uint4(v[0], v[1], v[2], v[3]);
+    } else {
+        return *reinterpret_cast<const uint4 *>(p);
+    }
+}
+
 constexpr int kTile  = 16;                // tokens per wavefront step
 constexpr int kTokens = 64;                // tokens per wavefront group: four steps, one per ring slot
 
@@ -155,7 +168,7 @@ constexpr int kTokens = 64;                // tokens per wavefront group: four s
 //             rows as well delays every wavefront's first scores.  Lengths from T / 4 to T, us, q behind the rows and in
 //             front of them: 256 heads, T = 1024 12.8 -> 12.0; 512 heads, T = 700 16.1 -> 15.3; 4096 heads, T = 200 28.9 ->
 //             27.4; 1200 heads, T = 3000 67.2 -> 64.9; 2048 heads, T = 2048 (5.1 TB/s of cache bytes) 74.2 -> 73.6.
-template <int kWaves>                     // wavefronts per workgroup: 4, or 16 when B * H alone is a thin grid
+template <int kWaves, bool ONCE>          // wavefronts per workgroup: 4, or 16 when B * H alone is a thin grid
 __global__ __launch_bounds__(kWaves * 64)
 void decode_attention_kv4_kernel(const __half *__restrict__ q, int H, int Hkv, int64_t Tmax,
                                  const int32_t *__restrict__ seq_len,
@@ -198,8 +211,8 @@ void decode_attention_kv4_kernel(const __half *__restrict__ q, int H, int Hkv, i
         int t = tile * kTile + tl;
         t = t <= t_last ? t : t_last;     // masked tokens and steps past the end repeat the last token
         const uint32_t off = (uint32_t)t * (D / 2) + 16u * c;
-        s_.k = *reinterpret_cast<const uint4 *>(kb + off);
-        s_.v = *reinterpret_cast<const uint4 *>(vb + off);
+        s_.k = load_row<ONCE>(kb + off);
+        s_.v = load_row<ONCE>(vb + off);
     };
     auto fetch_meta = [&](int g, uint32_t &km, uint32_t &vm) {
         int t = g * kTokens + lane;
@@ -467,6 +480,9 @@ constexpr int kGqaHeadPitch = 4 * 33 + 1; // floats per head in the merge area (
 // hides most.  Alone, 64 heads on 8, lengths from T / 4 to T, us, against one step after the other with its own maximum, clamped
 // addresses and loads that waited for the scales: 16 sequences of 4096 25.2 -> 23.0, 128 of 2048 58.1 -> 50.2, 64 of
 // 1024 21.7 -> 19.3, 100 of 500 21.4 -> 17.8, 1 of 16384 16.0 -> 14.9.  Every sum keeps its order: the same bits.
+// ONCE: the K rows are loaded with the hint that nothing reads them again; the V rows are not, since a 128-byte line of them holds two
+// tokens, which two of a wavefront's loads take.
+template <bool ONCE>
 __global__ __launch_bounds__(kGqaWaves * 64)
 void decode_attention_kv4_gqa_kernel(const __half *__restrict__ q, int H, int Hkv, int64_t Tmax,
                                      const int32_t *__restrict__ seq_len,
@@ -514,7 +530,7 @@ void decode_attention_kv4_gqa_kernel(const __half *__restrict__ q, int H, int Hk
     const auto k_rows = __builtin_amdgcn_make_buffer_rsrc((void *)kb, 0, 64u * (uint32_t)(t_last + 1), 0x00020000);
     const auto v_rows = __builtin_amdgcn_make_buffer_rsrc((void *)vb, 0, 64u * (uint32_t)(t_last + 1), 0x00020000);
     auto k_of = [&](int tile) {
-        return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(k_rows, (uint32_t)tile * (kTile * 64u) + k_lane, 0, 0));
+        return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(k_rows, (uint32_t)tile * (kTile * 64u) + k_lane, 0, ONCE ? 2 : 0));
     };
     auto v_of = [&](int tile) {
         const uint32_t t0 = (uint32_t)tile * (kTile * 64u) + v_lane;
@@ -883,23 +899,27 @@ hipError_t launch_decode_attention_kv4(const void *q, int B, int H, int Hkv, int
     int tps = S > 1 ? (groups + S - 1) / S : (groups > 0 ? groups : 1);
     if (sh.gqa) tps = (tps + kGqaWaves - 1) / kGqaWaves * kGqaWaves;   // whole rounds of the wavefronts
     float *part = S > 1 ? (float *)workspace : nullptr;
+    // A cache that the last-level cache (256 MB) does not keep until the next step is read with the hint that nothing reads it
+    // again: the memory then delivers 7.1 instead of 6.3 TB/s (a plain read of 400 MB and more).  Append and attention, lengths from T / 4 to
+    // T, us, without and with the hint; in MB the codes of all Tmax rows: 32 heads, 64 x 2048 (537 MB) 77.8, 68.7; 128 x 2048 139.2,
+    // 130.0; 90 x 1024 (377) 56.6, 54.1; 60 x 1024 (252) 42.1, 40.3; 40 x 1024 (168) 32.7, 31.9; 28 x 1024 (117) 28.6, 28.5;
+    // 20 x 1024 (84) 23.1, 23.3; 40 heads, 8 x 10000 (410) 64.1, 60.6; 85 x 161 (70) 24.7, 25.3; 64 heads on 8, 128 x 2048 (268) 56.3, 54.2.
+    const bool once = (int64_t)B * Hkv * Tmax * 128 >= (int64_t)1 << 27;
     if (sh.gqa) {
         const size_t lds = (size_t)kGqaWaves * (H / Hkv) * kGqaHeadPitch * sizeof(float);   // <= 34 KB
-        hipLaunchKernelGGL(decode_attention_kv4_gqa_kernel, dim3((unsigned)(B * Hkv), (unsigned)S),
+        auto kern = once ? &decode_attention_kv4_gqa_kernel<true> : &decode_attention_kv4_gqa_kernel<false>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(B * Hkv), (unsigned)S),
                            dim3(kGqaWaves * 64), lds, stream, (const __half *)q, H, Hkv, Tmax, seq_len,
                            (const uint8_t *)kq, (const __half *)ks, (const int16_t *)kz, (const uint8_t *)vq,
                            (const __half *)vs, (const int16_t *)vz, sm_scale, (__half *)out, tps, part);
-    } else if (sh.waves == 4)
-        hipLaunchKernelGGL(decode_attention_kv4_kernel<4>, dim3((unsigned)(B * H), (unsigned)S), dim3(256),
+    } else {
+        auto kern = sh.waves == 4 ? (once ? &decode_attention_kv4_kernel<4, true> : &decode_attention_kv4_kernel<4, false>)
+                                  : (once ? &decode_attention_kv4_kernel<16, true> : &decode_attention_kv4_kernel<16, false>);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(B * H), (unsigned)S), dim3((unsigned)(64 * sh.waves)),
                            0, stream, (const __half *)q, H, Hkv, Tmax, seq_len, (const uint8_t *)kq,
                            (const __half *)ks, (const int16_t *)kz, (const uint8_t *)vq,
                            (const __half *)vs, (const int16_t *)vz, sm_scale, (__half *)out, tps, part);
-    else
-        hipLaunchKernelGGL(decode_attention_kv4_kernel<16>, dim3((unsigned)(B * H), (unsigned)S),
-                           dim3(1024), 0, stream, (const __half *)q, H, Hkv, Tmax, seq_len,
-                           (const uint8_t *)kq, (const __half *)ks, (const int16_t *)kz,
-                           (const uint8_t *)vq, (const __half *)vs, (const int16_t *)vz, sm_scale,
-                           (__half *)out, tps, part);
+    }
     hipError_t err = hipGetLastError();
     if (err != hipSuccess || S == 1) return err;
     hipLaunchKernelGGL(decode_attention_merge_kernel, dim3((unsigned)(B * H)), dim3(128), 0, stream,

@@ -58,3 +58,24 @@ def test_nothing_behind_the_end_counts(H, Hkv):
     outs = [atom.atom_decode_attention_kv4(q, [dev(a) for a in c[:3]], [dev(a) for a in c[3:]], dev(lens), D ** -0.5) for c in (cache, other)]
     assert bool(torch.isfinite(outs[1]).all())
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+
+
+@pytest.mark.parametrize("B,H,Hkv,T", [(64, 32, 32, 512), (1, 32, 32, 32768), (128, 64, 8, 1024)])
+def test_attention_over_a_large_cache(B, H, Hkv, T):
+    """From 2^27 bytes of codes on the rows are loaded with another hint (four wavefronts, sixteen, grouped query): the bits are those of
+    the cache of one row less per sequence, which has as many groups and so the same splits."""
+    D = 128
+    assert B * Hkv * T * D == 1 << 27
+    print(f"[case] attention over a large cache B={B} H={H} Hkv={Hkv} T={T}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(B + H)
+    rnd = lambda lo, hi, *shape, dtype: torch.randint(lo, hi, shape, generator=g, device="cuda").to(dtype)
+    cache = [[rnd(0, 256, B, Hkv, T, D // 2, dtype=torch.uint8),
+              (torch.rand((B, Hkv, T), generator=g, device="cuda") * 0.05 + 0.05).half(),
+              rnd(0, 16, B, Hkv, T, dtype=torch.int16)] for _ in range(2)]
+    lens = rnd(1, T, B, dtype=torch.int32)
+    lens[B // 2] = T - 1
+    q = torch.randn((B, H, D), generator=g, device="cuda").half()
+    less = [[t[:, :, :T - 1].contiguous() for t in c] for c in cache]
+    large, small = (atom.atom_decode_attention_kv4(q, k, v, lens, D ** -0.5) for k, v in (cache, less))
+    assert bool(torch.isfinite(small).all())
+    assert torch.equal(large.view(torch.int16), small.view(torch.int16))
