@@ -54,7 +54,7 @@ namespace {
 using namespace atom_gemm_f6;
 
 // ------------------------------------------------------------------------------------------
-// Packing: canonical rows -> unit images.  One thread per 16-byte destination chunk.
+// Packing: canonical rows -> unit images.
 // ------------------------------------------------------------------------------------------
 struct PackParams {
     const uint8_t *q4; const int8_t *q8; const uint16_t *scale;
@@ -64,59 +64,86 @@ struct PackParams {
     int64_t ustride;                      // bytes per unit = G4 * IMG4 + G8 * IMG8
 };
 
+// The 32 codes of 16 bytes as FP6 E3M2 numbers: a code with its top bit flipped is 8 more than its value and, in the mantissa of
+// an fp16 number of exponent 10, reads as 1032 more; the conversion is a plain one (scale 1, every code is representable).
+__device__ __forceinline__ v6u codes_to_fp6(const v4u &w)
+{
+    typedef unsigned v16u __attribute__((ext_vector_type(16)));
+    v16u h;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const uint32_t even = w[d] & 0x0F0F0F0Fu, odd = (w[d] >> 4) & 0x0F0F0F0Fu;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t pair = __builtin_amdgcn_perm(odd, even, 0x0C000C00u | (unsigned)i | (unsigned)(4 + i) << 16);
+            h[4 * d + i] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(v2h, pair ^ 0x64086408u) - v2h{(_Float16)1032.0f, (_Float16)1032.0f});
+        }
+    }
+    return __builtin_amdgcn_cvt_scalef32_pk32_bf6_f16(__builtin_bit_cast(v32h, h), 1.0f);
+}
+
+// One workgroup: NG INT4 groups of a unit, or one INT8 group of it.  Bound by memory where there is much of it (4.2 to 5.5 TB/s read and written).
+// 4 NG lanes read the 64 NG bytes that a row has in those groups; the images are put together in LDS and leave as whole kilobytes.  (A
+// workgroup per group whose lanes took a row each read half a line of every row, and the other half was fetched by another XCD.)  Before
+// and now, us: 57344 x 8192 172.2, 114.7; 13824 x 5120 27.3, 22.5; 4096 x 28672 44.7, 34.4; 4096 x 8192 16.1, 12.8; 1024 x 4096 4.5, 4.1.
+template <int NG>
 __global__ __launch_bounds__(256)
 void pack_rows_kernel(const PackParams p)
 {
-    const int     G    = p.G4 + p.G8;
+    constexpr int LPR = 4 * NG, RPL = 256 / LPR, NL = 64 / RPL;       // lanes per row, rows per load, loads
+    __shared__ __align__(16) unsigned char img[NG * IMG4];
+    const int     G    = p.G4 + p.G8, parts = (p.G4 + NG - 1) / NG;
     const int64_t K4h  = (int64_t)p.G4 * 64;          // bytes of a canonical q4 row
-    const int     unit = blockIdx.y;
-    const int     g    = blockIdx.x;                   // group; INT4 groups first
-    uint8_t *img = p.out + (int64_t)unit * p.ustride + (g < p.G4 ? (int64_t)g * IMG4 : (int64_t)p.G4 * IMG4 + (int64_t)(g - p.G4) * IMG8);
-    const int t = threadIdx.x;
-    if (g < p.G4) {
-        // thread t < 128: row t % 64, half t / 64; its 48 bytes are pieces `half` and `half + 2` of
-        // the group (a piece = 32 consecutive channels = 16 canonical bytes = 24 bytes of FP6)
-        if (t >= 128) return;
-        const int row = t & 63, half = t >> 6;
-        const int64_t m = (int64_t)unit * 64 + row;
-        uint32_t out[12] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-        uint32_t sbits = 0;
-        if (m < p.rows) {
+    const int     unit = blockIdx.y, t = threadIdx.x;
+    const int64_t m0   = (int64_t)unit * 64;
+    uint8_t *const uout = p.out + (int64_t)unit * p.ustride;
+    if ((int)blockIdx.x < parts) {
+        const int g0 = NG * blockIdx.x, ng = p.G4 - g0 < NG ? p.G4 - g0 : NG;
+        // thread t: rows t / LPR + RPL j, piece t % LPR of the row (four per group: 32 consecutive channels, 16 canonical bytes,
+        // 24 bytes of FP6; piece q of a group is half q % 2 of MFMA q / 2)
+        const int row = t / LPR, gi = (t >> 2) % NG, half = t & 1, second = (t >> 1) & 1;
+        const bool here = gi < ng;
+        v4u w[NL];
 #pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const v4u w = *reinterpret_cast<const v4u *>(p.q4 + m * K4h + (int64_t)g * 64 + (half + 2 * s) * 16);
-                v32h h;
-#pragma unroll
-                for (int d = 0; d < 4; ++d)
-#pragma unroll
-                    for (int k = 0; k < 8; ++k)
-                        h[8 * d + k] = (_Float16)(((int)(w[d] << (28 - 4 * k))) >> 28);   // sign-extended nibble k
-                // the E3M2 number of each code (scale 1: a plain conversion; every code is representable)
-                const v6u packed = __builtin_amdgcn_cvt_scalef32_pk32_bf6_f16(h, 1.0f);
-#pragma unroll
-                for (int d = 0; d < 6; ++d) out[6 * s + d] = packed[d];
-            }
-            sbits = p.scale[m * G + g];
+        for (int j = 0; j < NL; ++j) {
+            const int64_t m = m0 + row + RPL * j;
+            w[j] = v4u{0u, 0u, 0u, 0u};
+            if (here && m < p.rows) w[j] = *reinterpret_cast<const v4u *>(p.q4 + m * K4h + (int64_t)g0 * 64 + 16 * (t % LPR));
         }
+        const int srow = t / NG, sg = t % NG;
+        uint32_t sbits = 0;
+        if (srow < 64 && sg < ng && m0 + srow < p.rows) sbits = p.scale[(m0 + srow) * G + g0 + sg];
+        unsigned char *const dst = img + gi * IMG4 + 1024 * half;
 #pragma unroll
-        for (int c = 0; c < 3; ++c)
-            *reinterpret_cast<v4u *>(img + 2048 * c + 1024 * half + 16 * row) = v4u{out[4 * c], out[4 * c + 1], out[4 * c + 2], out[4 * c + 3]};
-        if (half == 0) *reinterpret_cast<v2u *>(img + SC4 + 8 * row) = v2u{sbits, 0u};
+        for (int j = 0; j < NL; ++j) {
+            const v6u f = codes_to_fp6(w[j]);
+            unsigned char *const d = dst + 16 * (row + RPL * j);
+            // the first MFMA's 24 bytes: chunk 0 and the front of chunk 1; the second's: the back of chunk 1 and chunk 2
+            *reinterpret_cast<v4u *>(d + (second ? 4096 : 0)) = second ? v4u{f[2], f[3], f[4], f[5]} : v4u{f[0], f[1], f[2], f[3]};
+            *reinterpret_cast<v2u *>(d + 2048 + (second ? 8 : 0)) = second ? v2u{f[0], f[1]} : v2u{f[4], f[5]};
+        }
+        if (srow < 64) *reinterpret_cast<v2u *>(img + sg * IMG4 + SC4 + 8 * srow) = v2u{sbits, 0u};
+        __syncthreads();
+        uint8_t *const out = uout + (int64_t)g0 * IMG4;
+        for (int i = t; i < ng * (IMG4 / 16); i += 256)
+            *reinterpret_cast<v4u *>(out + 16 * i) = *reinterpret_cast<const v4u *>(img + 16 * i);
     } else {
         // two chunks per thread: chunk ids t and t + 256 of the 512; row id / 8, slot id % 8
+        const int g8 = blockIdx.x - parts;
+        uint8_t *const out = uout + (int64_t)p.G4 * IMG4 + (int64_t)g8 * IMG8;
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             const int id = t + 256 * half, row = id >> 3, slot = id & 7;
             const int chunk = (slot ^ row ^ ((row >> 3) & 1)) & 7;
-            const int64_t m = (int64_t)unit * 64 + row;
+            const int64_t m = m0 + row;
             v4u w = {0u, 0u, 0u, 0u};
             uint32_t sbits = 0;
             if (m < p.rows) {
-                w = *reinterpret_cast<const v4u *>(p.q8 + m * p.O + (int64_t)(g - p.G4) * 128 + chunk * 16);
-                sbits = p.scale[m * G + g];
+                w = *reinterpret_cast<const v4u *>(p.q8 + m * p.O + (int64_t)g8 * 128 + chunk * 16);
+                sbits = p.scale[m * G + p.G4 + g8];
             }
-            *reinterpret_cast<v4u *>(img + 16 * id) = w;
-            if (slot == 0) *reinterpret_cast<v2u *>(img + SC8 + 8 * row) = v2u{sbits, 0u};
+            *reinterpret_cast<v4u *>(out + 16 * id) = w;
+            if (slot == 0) *reinterpret_cast<v2u *>(out + SC8 + 8 * row) = v2u{sbits, 0u};
         }
     }
 }
@@ -622,7 +649,12 @@ hipError_t launch_f6_pack(const void *q4, const void *q8, const void *scale, int
     p.units = (int)((rows + 63) / 64);
     p.G4 = (K - O) >> 7; p.G8 = O >> 7; p.O = O;
     p.ustride = (int64_t)p.G4 * IMG4 + (int64_t)p.G8 * IMG8;
-    hipLaunchKernelGGL(pack_rows_kernel, dim3((unsigned)(p.G4 + p.G8), (unsigned)p.units), dim3(256), 0, stream, p);
+    // up to eight workgroups of one group per compute unit, one round of them: the time is that of one (1024 x 4096 4.1 us, with four groups
+    // 4.8; 1024 x 11008 5.9, 6.8; 4096 x 8192 is 4032 of them)
+    if ((int64_t)p.G4 * p.units <= 2048)
+        hipLaunchKernelGGL(pack_rows_kernel<1>, dim3((unsigned)(p.G4 + p.G8), (unsigned)p.units), dim3(256), 0, stream, p);
+    else
+        hipLaunchKernelGGL(pack_rows_kernel<4>, dim3((unsigned)((p.G4 + 3) / 4 + p.G8), (unsigned)p.units), dim3(256), 0, stream, p);
     return hipGetLastError();
 }
 
