@@ -159,8 +159,8 @@ atom_status atom_quantize_weight(const void *w_f16, int64_t N, int64_t ldw,
  * accumulated in fp32: one fused multiply-add per group, over ascending g
  * within a contiguous run of groups.  Large launches take all of K as one run;
  * launches of few rows or few tiles split K into 2, 4 or 8 contiguous runs
- * that are added in run order.  The order depends on the shape only, so
- * results are deterministic; they differ from a single ascending chain by
+ * that are added in run order.  The order depends on the shape and on whether
+ * such a workspace is given, so results are deterministic; they differ from a single ascending chain by
  * fp32 rounding (inside 1e-3 of the result's range).  The integer sums P are
  * exact in every case.
  *
@@ -171,7 +171,11 @@ atom_status atom_quantize_weight(const void *w_f16, int64_t N, int64_t ldw,
  *                 also written (a slow path meant for verification)
  *   workspace     device scratch of at least
  *                 atom_w4a4_gemm_workspace_bytes(M, N, d) bytes, 256-byte
- *                 aligned; may be NULL when that size is 0
+ *                 aligned; may be NULL when that size is 0.  With
+ *                 atom_w4a4_gemm_scratch_bytes(M, N, d) bytes (where that is
+ *                 not 0; without partials_dbg) the operands are packed into it
+ *                 first and the product is that of atom_w4a4_gemm_prepacked:
+ *                 up to 1.5 times as fast, all of K in one ascending run
  * Code pointers must be 16-byte aligned, scale pointers 2-byte aligned.
  * ATOM_ERR_UNSUPPORTED when a code or scale array of either operand reaches
  * 4 GiB (rows * K4 / 2, rows * O or rows * G >= 2^32: the kernels use 32-bit
@@ -321,6 +325,10 @@ size_t atom_decode_linear_lds_bytes(int64_t M, const atom_desc *d, int with_norm
 /* Scratch the GEMM needs for these sizes (0 when it needs none). */
 size_t atom_w4a4_gemm_workspace_bytes(int64_t M, int64_t N,
                                       const atom_desc *d);
+
+/* Workspace with which atom_w4a4_gemm is fastest for these sizes (0: none helps).  Never required. */
+size_t atom_w4a4_gemm_scratch_bytes(int64_t M, int64_t N,
+                                    const atom_desc *d);
 
 /*
  * The same GEMM on weights in an opaque tiled layout (Section 4.1: the weights

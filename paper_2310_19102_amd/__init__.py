@@ -27,6 +27,7 @@ from .binding import (  # noqa: F401
     atom_mfma_rate_probe,
     atom_w4a4_gemm,
     atom_w4a4_gemm_workspace_bytes,
+    atom_w4a4_gemm_scratch_bytes,
     atom_decode_linear,
     atom_decode_linear_coop,
     atom_decode_linear_coop_sync,

@@ -24,6 +24,7 @@ EXPORTS = (
     "atom_quantize_weight",
     "atom_w4a4_gemm",
     "atom_w4a4_gemm_workspace_bytes",
+    "atom_w4a4_gemm_scratch_bytes",
     "atom_tile_weight_decode_bytes",
     "atom_tile_weight_decode",
     "atom_w4a4_gemm_decode_tiled",
@@ -99,6 +100,8 @@ def load_library():
     L.atom_w4a4_gemm.argtypes = [vp, vp, vp, i64, vp, vp, vp, i64, dp, vp, i64, vp, vp, sz, vp]
     L.atom_w4a4_gemm_workspace_bytes.restype = sz
     L.atom_w4a4_gemm_workspace_bytes.argtypes = [i64, i64, dp]
+    L.atom_w4a4_gemm_scratch_bytes.restype = sz
+    L.atom_w4a4_gemm_scratch_bytes.argtypes = [i64, i64, dp]
     L.atom_tile_weight_decode_bytes.restype = sz
     L.atom_tile_weight_decode_bytes.argtypes = [i64, dp, i32]
     L.atom_tile_weight_decode.restype = ctypes.c_int
@@ -368,12 +371,19 @@ def atom_w4a4_gemm_workspace_bytes(M: int, N: int, K: int, group_size: int = 128
     return int(load_library().atom_w4a4_gemm_workspace_bytes(M, N, ctypes.byref(d)))
 
 
+def atom_w4a4_gemm_scratch_bytes(M: int, N: int, K: int, group_size: int = 128, n_outlier: int = 128) -> int:
+    """Workspace with which ``atom_w4a4_gemm`` packs its operands on the way (0 where that is not faster)."""
+    d = _desc(K, group_size, n_outlier)
+    return int(load_library().atom_w4a4_gemm_scratch_bytes(M, N, ctypes.byref(d)))
+
+
 def atom_w4a4_gemm(a_q4, a_q8, a_scale, w_q4, w_q8, w_scale, group_size: int = 128,
                    out: Optional[torch.Tensor] = None, partials: Optional[torch.Tensor] = None,
                    workspace: Optional[torch.Tensor] = None):
     """Y[M, N] fp16 = group-dequantised product of quantised activations and
     weights.  ``partials`` (int32 [M, N, G]) also receives every per-group
-    integer sum."""
+    integer sum.  Without a ``workspace`` of the caller's, sizes that gain from it
+    take ``atom_w4a4_gemm_scratch_bytes`` of scratch for the call."""
     return _run().w4a4_gemm(a_q4, a_q8, a_scale, w_q4, w_q8, w_scale, group_size, out, partials, workspace)
 
 

@@ -158,6 +158,12 @@ size_t atom_w4a4_gemm_workspace_bytes(int64_t M, int64_t N, const atom_desc *d)
     return atom_internal::gemm_workspace_bytes(M, N, d->K, d->n_outlier);
 }
 
+size_t atom_w4a4_gemm_scratch_bytes(int64_t M, int64_t N, const atom_desc *d)
+{
+    if (check_desc(d) != ATOM_OK || M <= 0 || N <= 0) return 0;
+    return atom_internal::gemm_scratch_bytes(M, N, d->K, d->n_outlier);
+}
+
 atom_status atom_w4a4_gemm(const void *a_q4, const void *a_q8, const void *a_scale, int64_t M,
                            const void *w_q4, const void *w_q8, const void *w_scale, int64_t N,
                            const atom_desc *d, void *y_f16, int64_t ldy, int32_t *partials_dbg,

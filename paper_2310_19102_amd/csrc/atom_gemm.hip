@@ -377,8 +377,51 @@ namespace atom_internal {
 
 size_t gemm_workspace_bytes(int64_t, int64_t, int, int) { return 0; }
 
+// Beyond 256 rows the kernels above are bound by what they do to every code and every integer sum on the vector ALU; the product on packed
+// operands takes about 0.6 of their time, and packing both is one pass at the memory's rate.  So where a caller has room for the
+// packed operands, they are packed on the way whenever that is estimated to pay.  Estimates in us, fitted to 120 sizes; a round of
+// workgroups of the kernels above costs a constant and a time per channel of K:
+//   tiles of 64 rows in up to 128, 256 and 512 workgroups   3 + 0.0021 K, 3 + 0.0028 K, 4 + 0.0050 K (K split four, four and two ways)
+//   tiles of 256 x 128, from 512 on, one per compute unit   4 + 0.0097 K
+//   tiles of 128 x 128, two per compute unit                4 + 0.0112 K; at most one of them (the last round) 4 + 0.0058 K
+// and against them stand the product as its tiles are chosen (f6_product_us), 5 for one more launch, 5 TB/s for the codes read and written.
+// Measured (GEMM alone, weights from memory; rows: kernels above, packed on the way): K = 5120, N = 13824: 257 62.6, 57.7; 777 103, 81.3;
+// 4096 406, 267; K = 11008, N = 4096: 257 55.9, 36.7; 1024 69.8, 59.0; 4096 247, 169; K = 4096, N = 4096: 1024 34.7, 29.8; 4096 103,
+// 76.3; K = 8192, N = 22016: 450 146, 132; 4096 993, 642.  Where the kernels above stay: K = 2048, N = 8192: 640 28.5, 29; K = 6400,
+// N = 1300: 257 16.4, 20.2.
+size_t gemm_scratch_bytes(int64_t M, int64_t N, int K, int O)
+{
+    if (M <= 256 || (M + 63) / 64 + (N + 63) / 64 > 65535) return 0;              // (grid rows of the packing launch)
+    const size_t bytes = f6_packed_bytes(M, K, O) + f6_packed_bytes(N, K, O);
+    if (bytes > (size_t)1 << 30) return 0;
+    const int64_t cus = atom_launch::compute_units();
+    const float product = f6_product_us(M, N, K, O, cus);
+    if (product == 0.0f) return 0;
+    const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64), t128 = ((M + 127) / 128) * ((N + 127) / 128), t256 = ((M + 255) / 256) * ((N + 127) / 128);
+    const float   k = (float)K;
+    float direct;
+    if (t64 <= 512) {
+        direct = t64 <= 128 ? 3.0f + 0.0021f * k : t64 <= 256 ? 3.0f + 0.0028f * k : 4.0f + 0.0050f * k;
+    } else if (t256 >= 512) {
+        direct = (float)((t256 + cus - 1) / cus) * (4.0f + 0.0097f * k);
+    } else {
+        const int64_t last = t128 % (2 * cus);
+        direct = (float)(t128 / (2 * cus) + (last > cus)) * (4.0f + 0.0112f * k) + (last > 0 && last <= cus ? 4.0f + 0.0058f * k : 0.0f);
+    }
+    const float packing = 5.0f + 1.34f * (float)(M + N) * k / 5.0e6f;
+    return direct > product + packing + 1.5f ? bytes : 0;
+}
+
 hipError_t launch_w4a4_gemm(const GemmArgs &a, hipStream_t stream)
 {
+    if (!a.partials && a.workspace && (reinterpret_cast<uintptr_t>(a.workspace) & 255) == 0) {
+        const size_t need = gemm_scratch_bytes(a.M, a.N, a.K, a.O);
+        if (need && a.workspace_bytes >= need) {
+            uint8_t *const a_pk = static_cast<uint8_t *>(a.workspace), *const w_pk = a_pk + f6_packed_bytes(a.M, a.K, a.O);
+            hipError_t err = launch_f6_pack_both(a, a_pk, w_pk, stream);
+            return err != hipSuccess ? err : launch_f6_gemm(a_pk, a.M, w_pk, a.N, a.K, a.O, a.y, a.ldy, nullptr, stream);
+        }
+    }
     GemmParams p;
     p.a_q4 = a.a_q4; p.a_q8 = a.a_q8; p.a_scale = a.a_scale;
     p.w_q4 = a.w_q4; p.w_q8 = a.w_q8; p.w_scale = a.w_scale;

@@ -86,15 +86,18 @@ __device__ __forceinline__ v6u codes_to_fp6(const v4u &w)
 // 4 NG lanes read the 64 NG bytes that a row has in those groups; the images are put together in LDS and leave as whole kilobytes.  (A
 // workgroup per group whose lanes took a row each read half a line of every row, and the other half was fetched by another XCD.)  Before
 // and now, us: 57344 x 8192 172.2, 114.7; 13824 x 5120 27.3, 22.5; 4096 x 28672 44.7, 34.4; 4096 x 8192 16.1, 12.8; 1024 x 4096 4.5, 4.1.
+// The units of a second operand, if any, follow the first one's (grid.y).
 template <int NG>
 __global__ __launch_bounds__(256)
-void pack_rows_kernel(const PackParams p)
+void pack_rows_kernel(const PackParams first, const PackParams second_op)
 {
+    const bool two = (int)blockIdx.y >= first.units;           // the same decision in every lane
+    const PackParams &p = two ? second_op : first;
     constexpr int LPR = 4 * NG, RPL = 256 / LPR, NL = 64 / RPL;       // lanes per row, rows per load, loads
     __shared__ __align__(16) unsigned char img[NG * IMG4];
     const int     G    = p.G4 + p.G8, parts = (p.G4 + NG - 1) / NG;
     const int64_t K4h  = (int64_t)p.G4 * 64;          // bytes of a canonical q4 row
-    const int     unit = blockIdx.y, t = threadIdx.x;
+    const int     unit = (int)blockIdx.y - (two ? first.units : 0), t = threadIdx.x;
     const int64_t m0   = (int64_t)unit * 64;
     uint8_t *const uout = p.out + (int64_t)unit * p.ustride;
     if ((int)blockIdx.x < parts) {
@@ -605,7 +608,7 @@ namespace atom_internal {
 //     moves the last tile back and fetches three units twice (M = 192, K = 8192, N = 28672: 66.6 us, walking 71.9; N = 57344:
 //     130 / 139).
 // Every tile on 83 sizes, and what the rule takes: profiles/w4a4_gemm_f6_tiles.txt.
-static int pick_tile(int64_t au, int64_t wu, int64_t cus)
+static int pick_tile(int64_t au, int64_t wu, int64_t cus, int64_t *what = nullptr)
 {
     struct { int ua, uw, rounds, first, more; } const tile[5] = {
         {1, 1, 3, 13, 21}, {1, 2, 1, 21, 37}, {2, 2, 1, 37, 60}, {2, 2, 1, 45, 0}, {4, 2, 1, 79, 79}};
@@ -621,6 +624,7 @@ static int pick_tile(int64_t au, int64_t wu, int64_t cus)
                                     : n * tile[i].more;
         if (cost < least) { least = cost; best = i; }
     }
+    if (what) *what = least;
     return best == 3 && au == 3 ? -1 : best;
 }
 
@@ -638,8 +642,7 @@ size_t f6_packed_bytes(int64_t rows, int K, int O)
     return (size_t)(units * ((int64_t)G4 * IMG4 + (int64_t)G8 * IMG8));
 }
 
-hipError_t launch_f6_pack(const void *q4, const void *q8, const void *scale, int64_t rows, int K, int O,
-                          void *out, hipStream_t stream)
+static PackParams pack_params(const void *q4, const void *q8, const void *scale, int64_t rows, int K, int O, void *out)
 {
     PackParams p;
     p.q4 = static_cast<const uint8_t *>(q4); p.q8 = static_cast<const int8_t *>(q8);
@@ -649,13 +652,41 @@ hipError_t launch_f6_pack(const void *q4, const void *q8, const void *scale, int
     p.units = (int)((rows + 63) / 64);
     p.G4 = (K - O) >> 7; p.G8 = O >> 7; p.O = O;
     p.ustride = (int64_t)p.G4 * IMG4 + (int64_t)p.G8 * IMG8;
+    return p;
+}
+
+static hipError_t launch_pack(const PackParams &p, const PackParams &q, hipStream_t stream)
+{
+    const unsigned units = (unsigned)(p.units + q.units);
     // up to eight workgroups of one group per compute unit, one round of them: the time is that of one (1024 x 4096 4.1 us, with four groups
     // 4.8; 1024 x 11008 5.9, 6.8; 4096 x 8192 is 4032 of them)
-    if ((int64_t)p.G4 * p.units <= 2048)
-        hipLaunchKernelGGL(pack_rows_kernel<1>, dim3((unsigned)(p.G4 + p.G8), (unsigned)p.units), dim3(256), 0, stream, p);
+    if ((int64_t)p.G4 * units <= 2048)
+        hipLaunchKernelGGL(pack_rows_kernel<1>, dim3((unsigned)(p.G4 + p.G8), units), dim3(256), 0, stream, p, q);
     else
-        hipLaunchKernelGGL(pack_rows_kernel<4>, dim3((unsigned)((p.G4 + 3) / 4 + p.G8), (unsigned)p.units), dim3(256), 0, stream, p);
+        hipLaunchKernelGGL(pack_rows_kernel<4>, dim3((unsigned)((p.G4 + 3) / 4 + p.G8), units), dim3(256), 0, stream, p, q);
     return hipGetLastError();
+}
+
+hipError_t launch_f6_pack(const void *q4, const void *q8, const void *scale, int64_t rows, int K, int O,
+                          void *out, hipStream_t stream)
+{
+    PackParams none{};
+    return launch_pack(pack_params(q4, q8, scale, rows, K, O, out), none, stream);
+}
+
+hipError_t launch_f6_pack_both(const GemmArgs &a, void *a_out, void *w_out, hipStream_t stream)
+{
+    return launch_pack(pack_params(a.a_q4, a.a_q8, a.a_scale, a.M, a.K, a.O, a_out),
+                       pack_params(a.w_q4, a.w_q8, a.w_scale, a.N, a.K, a.O, w_out), stream);
+}
+
+float f6_product_us(int64_t M, int64_t N, int K, int O, int64_t cus)
+{
+    const int G4 = (K - O) >> 7;
+    if (O != 128 || G4 < 7) return 0.0f;
+    int64_t cost;
+    pick_tile((M + 63) / 64, (N + 63) / 64, cus, &cost);
+    return 5.0f + 0.0093f * (float)cost * (float)(G4 + 2);       // (operands that were just written: out of the last-level cache)
 }
 
 hipError_t launch_f6_gemm(const void *a_pk, int64_t M, const void *w_pk, int64_t N, int K, int O, void *y,

@@ -32,6 +32,8 @@ struct GemmArgs {
 };
 
 size_t     gemm_workspace_bytes(int64_t M, int64_t N, int K, int O);
+// workspace with which launch_w4a4_gemm packs the operands on the way (0: it would not be faster)
+size_t     gemm_scratch_bytes(int64_t M, int64_t N, int K, int O);
 hipError_t launch_w4a4_gemm(const GemmArgs &a, hipStream_t stream);
 // Group sizes 64 and 256 (atom_gemm_gs.hip): one plain kernel, a single ascending chain of groups.
 hipError_t launch_w4a4_gemm_gs(const GemmArgs &a, int group_size, hipStream_t stream);
@@ -48,6 +50,10 @@ hipError_t launch_tile_weight_decode(const void *q4, const void *q8, int64_t N, 
 size_t     f6_packed_bytes(int64_t rows, int K, int O);
 hipError_t launch_f6_pack(const void *q4, const void *q8, const void *scale, int64_t rows, int K, int O,
                           void *out, hipStream_t stream);
+// activations and weights of a in one launch
+hipError_t launch_f6_pack_both(const GemmArgs &a, void *a_out, void *w_out, hipStream_t stream);
+// estimate of launch_f6_gemm's time, us; 0: not one of its common shapes
+float      f6_product_us(int64_t M, int64_t N, int K, int O, int64_t cus);
 hipError_t launch_f6_gemm(const void *a_pk, int64_t M, const void *w_pk, int64_t N, int K, int O, void *y,
                           int64_t ldy, int32_t *partials, hipStream_t stream);
 

@@ -329,6 +329,15 @@ PyObject *w4a4_gemm(Args a)
         own = make({(int64_t)need}, kByte, a4);
         w = &own;
     }
+    // room to pack the operands on the way where that is faster; a call that finds none goes without
+    const size_t room = need || w || partials ? 0 : atom_w4a4_gemm_scratch_bytes(M, N, &d);
+    if (room) {
+        try {
+            own = make({(int64_t)room}, kByte, a4);
+            w = &own;
+        } catch (const c10::OutOfMemoryError &) {
+        }
+    }
     ATOM_CALL(atom_w4a4_gemm, data(a4), data(a8), data(as), M, data(w4), data(w8), data(ws), N, &d, y.data(),
               ld(*y.t, M, N), partials, w ? data(*w) : nullptr, w ? bytes(*w) : 0);
     return y.give();

@@ -1,0 +1,95 @@
+"""atom_w4a4_gemm with room to pack its operands on the way: the bits of the product on packed operands (one ascending run of groups,
+which test_gpu_packed.py and test_gpu_exact.py hold against the oracle), and the kernels for canonical operands where there is no room."""
+import pytest
+import torch
+
+import paper_2310_19102_amd as atom
+
+pytestmark = pytest.mark.gpu
+
+
+def _operands(M, N, K, seed=0):
+    g = torch.Generator(device="cuda").manual_seed(seed + M + N + K)
+    idx = torch.randperm(K, generator=g, device="cuda").to(torch.int32)
+    qa = atom.atom_quantize_act(torch.randn((M, K), generator=g, device="cuda").half(), None, 0.0, idx)
+    qw = atom.atom_quantize_weight(torch.randn((N, K), generator=g, device="cuda").half() * 0.02, idx)
+    return qa, qw
+
+
+def _prepacked(qa, qw, M, N, K):
+    return atom.atom_w4a4_gemm_prepacked(atom.atom_pack_act(*qa), M, atom.atom_pack_weight(*qw), N, K)
+
+
+# one row more than the streaming kernels take, odd sizes; without room 64 x 64 tiles with two sets, 128 x 128 with two sets and with one,
+# 256 x 128
+@pytest.mark.parametrize("M,N,K", [(257, 4096, 4096), (777, 3001, 4224), (1000, 8000, 4096), (2101, 8191, 1024)])
+def test_bits_of_the_packed_product(M, N, K):
+    print(f"[case] packing on the way M={M} N={N} K={K}", flush=True)
+    assert atom.atom_w4a4_gemm_scratch_bytes(M, N, K) > 0
+    qa, qw = _operands(M, N, K)
+    want = _prepacked(qa, qw, M, N, K)
+    assert torch.equal(atom.atom_w4a4_gemm(*qa, *qw), want)
+    ld = N + 5                                                   # rows off the 16-byte grid, nothing written between them
+    wide = torch.full((M, ld), 7.0, dtype=torch.float16, device="cuda")
+    atom.atom_w4a4_gemm(*qa, *qw, out=wide[:, :N])
+    assert torch.equal(wide[:, :N], want) and bool((wide[:, N:] == 7.0).all())
+    # without room: the kernels for canonical operands.  Their sums differ by the rounding of fp32 additions in another order
+    # (up to K / 128 + 1 of them, 2^-24 each) and of one fp16 store on either side (2^-11)
+    need = atom.atom_w4a4_gemm_scratch_bytes(M, N, K)
+    room = torch.full((need + 256,), 0x5A, dtype=torch.uint8, device="cuda")
+    aligned = room[-room.data_ptr() % 256:][:need]
+    for ws in (aligned[:need - 1], room[16:], room[:16]):        # too small, off its grid, tiny
+        y = atom.atom_w4a4_gemm(*qa, *qw, workspace=ws)
+        assert bool((room == 0x5A).all())
+        bound = 2.0 ** -10 * want.double().abs() + (K // 128 + 1) * 2.0 ** -23 * want.double().abs().max()
+        assert bool(((y.double() - want.double()).abs() <= bound).all())
+    assert torch.equal(atom.atom_w4a4_gemm(*qa, *qw, workspace=aligned), want)
+
+
+def test_calls_that_keep_their_kernels():
+    M, N, K = 512, 4096, 4096
+    assert atom.atom_w4a4_gemm_scratch_bytes(M, N, K) > 0
+    for none in (dict(M=256), dict(n_outlier=256), dict(group_size=64), dict(K=1000), dict(K=896), dict(N=0), dict(N=1 << 22)):
+        assert atom.atom_w4a4_gemm_scratch_bytes(**{**dict(M=M, N=N, K=K), **none}) == 0, none
+    qa, qw = _operands(M, N, K)
+    part = torch.empty((M, N, K // 128), dtype=torch.int32, device="cuda")      # the dump of the sums takes no workspace
+    y = atom.atom_w4a4_gemm(*qa, *qw, partials=part)
+    scale = torch.einsum("mg,ng->mng", qa[2].double()[:4], qw[2].double())
+    assert torch.allclose((part[:4].double() * scale).sum(2), y[:4].double(), rtol=2.0 ** -10, atol=1e-3 * float(y.abs().max()))
+
+
+def test_no_memory_for_the_packed_operands():
+    """The call goes without them when the allocator has none to give."""
+    M, N, K = 777, 3001, 4224
+    qa, qw = _operands(M, N, K)
+    y, tiny = torch.empty((M, N), dtype=torch.float16, device="cuda"), torch.empty(16, dtype=torch.uint8, device="cuda")
+    direct = atom.atom_w4a4_gemm(*qa, *qw, workspace=tiny)
+    assert not torch.equal(direct, _prepacked(qa, qw, M, N, K))
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    try:
+        torch.cuda.set_per_process_memory_fraction(1e-6)
+        atom.atom_w4a4_gemm(*qa, *qw, out=y)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(y, direct)
+
+
+def test_captured_and_replayed():
+    M, N, K = 300, 4096, 4096
+    qa, qw = _operands(M, N, K)
+    other, _ = _operands(M, N, K, seed=1)
+    want = [_prepacked(q, qw, M, N, K) for q in (qa, other)]
+    live, y = [t.clone() for t in qa], torch.empty((M, N), dtype=torch.float16, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        atom.atom_w4a4_gemm(*live, *qw, out=y)
+    for turn in range(4):
+        for t, s in zip(live, (qa, other)[turn % 2]):
+            t.copy_(s)
+        y.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want[turn % 2]), turn
+        atom.atom_w4a4_gemm(*other, *qw)                         # the program's own work between the replays
