@@ -30,6 +30,7 @@ EXPORTS = (
     "atom_w4a4_gemm_decode_tiled",
     "atom_permute_rows",
     "atom_decode_linear",
+    "atom_decode_linear_wants_codes",
     "atom_decode_linear_coop",
     "atom_decode_linear_coop_sync_bytes",
     "atom_decode_linear_lds_bytes",
@@ -111,6 +112,8 @@ def load_library():
     L.atom_permute_rows.restype = ctypes.c_int
     L.atom_permute_rows.argtypes = [vp, i64, i64, i64, vp, i64, vp, i64, vp]
     L.atom_decode_linear.restype = ctypes.c_int
+    L.atom_decode_linear_wants_codes.restype = ctypes.c_int
+    L.atom_decode_linear_wants_codes.argtypes = [i64, i64, dp]
     L.atom_decode_linear.argtypes = [vp, i64, i64, vp, f32, vp, dp, f32, vp, vp, vp, i64, vp, i64, vp, vp, vp, vp]
     L.atom_decode_linear_coop_sync_bytes.restype = sz
     L.atom_decode_linear_coop_sync_bytes.argtypes = []
@@ -292,8 +295,9 @@ def atom_decode_linear(x: torch.Tensor, gamma: Optional[torch.Tensor], eps: floa
                        reorder_idx: Optional[torch.Tensor], w_q4: torch.Tensor, w_q8: torch.Tensor,
                        w_scale: torch.Tensor, group_size: int = 128, clip: float = 0.9,
                        out: Optional[torch.Tensor] = None, debug: bool = False, bits: int = 4):
-    """One launch for ``Y = linear(x)`` at M <= 16 rows: front end (RMSNorm when ``gamma`` is given,
-    reorder, group quantisation) and weight-streaming group GEMM.  Returns ``Y`` [M, N] fp16, or
+    """One call for ``Y = linear(x)`` at M <= 16 rows: front end (RMSNorm when ``gamma`` is given,
+    reorder, group quantisation) and weight-streaming group GEMM, in one launch or, where that is faster
+    (``atom_decode_linear_wants_codes`` of the C library), in two.  Returns ``Y`` [M, N] fp16, or
     ``(Y, (q4, q8, scale))`` with ``debug`` (the activation codes the kernel computed)."""
     return _run().decode_linear(x, gamma, eps, reorder_idx, w_q4, w_q8, w_scale, group_size, clip, out, debug, bits)
 

@@ -238,6 +238,12 @@ size_t atom_decode_linear_lds_bytes(int64_t M, const atom_desc *d, int with_norm
     return atom_internal::decode_linear_lds_bytes((int)M, d->K, d->n_outlier, with_norm != 0, with_index == 0);
 }
 
+int atom_decode_linear_wants_codes(int64_t M, int64_t N, const atom_desc *d)
+{
+    if (check_desc(d) != ATOM_OK || M <= 0 || N <= 0) return 0;
+    return atom_internal::decode_linear_splits((int)(M < 17 ? M : 17), N, d->K, d->n_outlier);
+}
+
 atom_status atom_decode_linear(const void *x_f16, int64_t M, int64_t ldx, const void *gamma_f16,
                                float eps, const int32_t *reorder_idx, const atom_desc *d, float clip,
                                const void *w_q4, const void *w_q8, const void *w_scale, int64_t N,
@@ -258,6 +264,22 @@ atom_status atom_decode_linear(const void *x_f16, int64_t M, int64_t ldx, const 
         !aligned(w_q4, 16) || !aligned(w_q8, 16) || !aligned(w_scale, 2) || !aligned(y_f16, 2) ||
         (ndbg && (!aligned(dbg_q4, 4) || !aligned(dbg_q8, 4) || !aligned(dbg_scale, 2))))
         return ATOM_ERR_ALIGN;
+    if (ndbg && aligned(dbg_q4, 16) && aligned(dbg_q8, 16) && atom_internal::decode_linear_splits((int)M, N, d->K, d->n_outlier)) {
+        hipError_t e2 = atom_internal::launch_quantize_rows(x_f16, M, ldx, 0, nullptr, 0, nullptr, 0, gamma_f16, eps, reorder_idx,
+                                                            d->K, d->n_outlier, d->bits_normal, clip, dbg_q4, dbg_q8, dbg_scale,
+                                                            static_cast<hipStream_t>(stream));
+        if (e2 != hipSuccess) return ATOM_ERR_HIP;
+        atom_internal::GemmArgs g;
+        g.a_q4 = static_cast<const uint8_t *>(dbg_q4); g.a_q8 = static_cast<const int8_t *>(dbg_q8);
+        g.a_scale = static_cast<const uint16_t *>(dbg_scale); g.M = M;
+        g.w_q4 = static_cast<const uint8_t *>(w_q4); g.w_q8 = static_cast<const int8_t *>(w_q8);
+        g.w_scale = static_cast<const uint16_t *>(w_scale); g.N = N;
+        g.K = d->K; g.O = d->n_outlier;
+        g.y = static_cast<uint16_t *>(y_f16); g.ldy = ldy;
+        g.partials = nullptr; g.workspace = nullptr; g.workspace_bytes = 0;
+        e2 = atom_internal::launch_w4a4_gemm(g, static_cast<hipStream_t>(stream));
+        return e2 == hipSuccess ? ATOM_OK : ATOM_ERR_HIP;
+    }
     hipError_t err = atom_internal::launch_decode_linear(x_f16, (int)M, ldx, gamma_f16, eps, reorder_idx, d->K,
                                                          d->n_outlier, d->bits_normal, clip, w_q4, w_q8, w_scale,
                                                          N, y_f16, ldy, dbg_q4, dbg_q8, dbg_scale,

@@ -375,9 +375,18 @@ PyObject *decode_linear(Args a)
     Codes q;
     if (debug) q.take(Py_None, M, K, gs, O, x);
     const atom_desc d = desc(K, gs, O, whole(a[11]));
+    void *c4 = nullptr, *c8 = nullptr, *cs = nullptr;
+    Tensor own;
+    if (debug) {
+        c4 = q.q4.data(); c8 = q.q8.data(); cs = q.sc.data();
+    } else if (atom_decode_linear_wants_codes(M, N, &d)) {          // one array for the three, each from a 256-byte boundary
+        const auto up = [](int64_t n) { return (n + 255) / 256 * 256; };
+        const int64_t n4 = up(M * (K - O) / 2), n8 = up(M * O);
+        own = make({n4 + n8 + M * groups(K, gs) * 2}, kByte, x);
+        c4 = data(own); c8 = (char *)c4 + n4; cs = (char *)c8 + n8;
+    }
     ATOM_CALL(atom_decode_linear, data(x), M, ld(x, M, K), gamma, eps, (const int32_t *)idx, &d, clip, data(w4),
-              data(w8), data(ws), N, y.data(), ld(*y.t, M, N), debug ? q.q4.data() : nullptr,
-              debug ? q.q8.data() : nullptr, debug ? q.sc.data() : nullptr);
+              data(w8), data(ws), N, y.data(), ld(*y.t, M, N), c4, c8, cs);
     if (!debug) return y.give();
     PyObject *codes = tuple({&q.q4, &q.q8, &q.sc});
     return Py_BuildValue("(NN)", y.give(), codes);
