@@ -324,6 +324,256 @@ hipError_t launch_tile(const MxParams &p, hipStream_t stream)
     return hipGetLastError();
 }
 
+// The same for launches that wide tiles cover in one round: 256 x 32 TN, eight wavefronts of 32 rows x 32 TN columns, three stages.
+//
+// What bounds the tiles above is how fast a compute unit loads: it has at most 256 lines of 128 bytes in flight, whatever asks for them, and
+// loads return in order across its wavefronts, so a request out of the L2 waits behind one from the last-level cache or the memory (0.4
+// to 0.65 us): 50 to 65 GB/s per compute unit, where L2 hits alone would give 130.  So bytes per multiply-add count, and the power that moving them takes.
+// Only the accumulators (16 TN registers) stay; the fragments of the weights are read from LDS four MFMAs ahead, in one run over both halves of
+// a step, and the barrier of a step stands before its last MFMAs, behind which the first fragments of the next step are read.
+// In turn on one card, us, the best of the tiles above and this kernel (weights from memory / the last-level cache): M = 1024, K = 4096,
+// N = 22016 64.5, 54.3 / 60.0, 51.9 (TN = 12); M = 2048, N = 12288 62.2, 55.1; M = 2048, N = 10000 58.0, 49.4 (TN = 10); M = 1300, K = 5120,
+// N = 16000 68.4, 64.4.  TN = 9 and 11 are within 3 % of 10 and 12.  Clocks fall to about 1.6 GHz with all compute units at it.
+template <int TN>
+struct MxWide {
+    static constexpr int NW    = 8, NT = 512, NST = 3;
+    static constexpr int BM    = 256, BN = 32 * TN;
+    static constexpr int CODES = (BM + BN) * ROWB;
+    static constexpr int NSC   = (BM + BN + 63) / 64;      // requests of 64 scale dwords per stage (the last may be half used)
+    static constexpr int STAGE = CODES + 256 * NSC;
+    static constexpr int NBLK  = (BM + BN) / 16;           // requests of a kilobyte (16 rows) per stage
+    static constexpr int J     = (NBLK + NW - 1) / NW, JS = (NSC + NW - 1) / NW, LOADS = J + JS;
+    static constexpr int SPARE = NST * STAGE;              // 16 bytes that are written and never read
+    static constexpr int LDS   = SPARE + 64;
+    static constexpr int PITCH = 144;                      // output staging: 32 rows of 64 columns per wavefront
+    static constexpr int AHEAD = 4;                        // fragments read ahead of their MFMA
+    static_assert(NW * 32 * PITCH <= NST * STAGE && LDS <= 160 * 1024 && 2 * LOADS <= 63, "LDS, vmcnt");
+};
+
+template <int TN>
+__global__ __launch_bounds__(512, 2)
+void mx_gemm_wide_kernel(MxParams p)
+{
+    using Gm = MxWide<TN>;
+    constexpr int BM = Gm::BM, BN = Gm::BN, NW = Gm::NW, J = Gm::J, JS = Gm::JS, LOADS = Gm::LOADS, STAGE = Gm::STAGE, NST = Gm::NST, AHEAD = Gm::AHEAD;
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lr = lane & 31, g = lane >> 5;
+
+    const int tiles_m = (int)((p.M + BM - 1) / BM);
+    const int bid = atom_gemm::xcd_contiguous_block_id();
+    const int64_t m0 = (int64_t)(bid % tiles_m) * BM, n0 = (int64_t)(bid / tiles_m) * BN;
+
+    const int K4 = p.K - p.O;
+    const int S4 = K4 >> 7, S8 = p.O >> 6, S = S4 + S8;
+
+    // ---- loader, as above
+    uint32_t goff[J], soff[JS];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int b = NW * j + wave, trow = 16 * b + (lane >> 2);
+        const bool act = b < BM / 16;
+        int64_t r = act ? m0 + trow : n0 + (trow - BM);
+        const int64_t last = (act ? p.M : p.N) - 1;
+        r = r < last ? r : last;
+        goff[j] = (uint32_t)r * ROWB + 16u * (((lane & 3) - (lane >> 4)) & 3);
+    }
+#pragma unroll
+    for (int j = 0; j < JS; ++j) {
+        const int b = NW * j + wave;
+        const bool act = b < BM / 64;
+        int64_t r = act ? m0 + 64 * b + lane : n0 + (64 * b - BM) + lane;
+        const int64_t last = (act ? p.M : p.N) - 1;
+        soff[j] = (uint32_t)(r < last ? r : last) * 4u;
+    }
+    const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(smem), spare = lds0 + Gm::SPARE;
+    struct Src { const uint8_t *a, *w, *ae, *we; };
+    auto src_of = [&](int u) __attribute__((always_inline)) -> Src {
+        const bool    f8 = u < S8;
+        const int64_t sl = f8 ? u : u - S8;
+        const int64_t d  = f8 ? S4 + (u >> 1) : u - S8;
+        return {(f8 ? p.a_q8 : p.a_q4) + sl * p.M * ROWB, (f8 ? p.w_q8 : p.w_q4) + sl * p.N * ROWB,
+                p.a_e8 + d * p.M * 4, p.w_e8 + d * p.N * 4};
+    };
+    auto request = [&](int k, const Src &s, int buf) __attribute__((always_inline)) {
+        const uint32_t st = lds0 + buf * STAGE;
+        if (k < J) {
+            const int b = NW * k + wave;
+            const uint8_t *base = NW * (k + 1) <= BM / 16 ? s.a : s.w;                 // (BM / 16 is whole rounds of the wavefronts)
+            if (NW * (k + 1) <= Gm::NBLK) dma16(st + 1024 * b, goff[k], base);
+            else dma16_masked(b < Gm::NBLK ? st + 1024 * b : spare, goff[k], base, b < Gm::NBLK ? ~0ull : 1ull);
+        } else {
+            const int b = NW * (k - J) + wave;
+            const uint8_t *base = NW * (k - J) >= BM / 64 ? s.we : b < BM / 64 ? s.ae : s.we;
+            if (NW * (k - J + 1) <= Gm::NSC || b < Gm::NSC) dma4(st + Gm::CODES + 256 * b, soff[k < J ? 0 : k - J], base);
+            else dma16_masked(spare, 0u, s.a, 1ull);
+        }
+    };
+    static_assert(BM / 16 % NW == 0, "a request's operand is known at compile time");
+    auto request_all = [&](int u, int buf) __attribute__((always_inline)) {
+        const Src s = src_of(u);
+#pragma unroll
+        for (int k = 0; k < LOADS; ++k) request(k, s, buf);
+    };
+
+    v16f acc[TN];
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[t][v] = 0.0f;
+
+    const int a_base = mx_lds_off(32 * wave + lr, g), b_base = mx_lds_off(BM + lr, g);
+    const int sa_off = Gm::CODES + 4 * (32 * wave + lr), sb_off = Gm::CODES + 4 * (BM + lr);
+    struct Frag { v4i b; int s; };
+    auto read_frag = [&](const uint8_t *buf, int i) __attribute__((always_inline)) -> Frag {       // i = TN * half + block of columns
+        const int half = i / TN, t = i % TN;
+        return {*reinterpret_cast<const v4i *>(buf + ((half ? b_base ^ 32 : b_base) + 2048 * t)),
+                (int)(*reinterpret_cast<const uint32_t *>(buf + sb_off + 128 * t) >> (8 * g))};
+    };
+    auto read_sa = [&](const uint8_t *buf) __attribute__((always_inline)) -> int {
+        return (int)(*reinterpret_cast<const uint32_t *>(buf + sa_off) >> (8 * g));
+    };
+
+    // Step u: tile u is in stage u % 3.  At its start stage (u - 1) % 3 has been read by everyone and is refilled with tile u + 2; before its
+    // end tile u + 1 has landed.
+    int cur = 0;
+#pragma unroll
+    for (int v = 0; v < NST; ++v) request_all(min(v, S - 1), v);
+    __builtin_amdgcn_s_waitcnt(wait_imm(2 * LOADS));
+    __syncthreads();
+    int u = 0;
+    auto next_stage = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_s_waitcnt(wait_imm(LOADS));
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        cur = cur + 1 == NST ? 0 : cur + 1;
+        ++u;
+    };
+    auto refill = [&](int k, const Src &s) __attribute__((always_inline)) { request(k, s, cur == 0 ? NST - 1 : cur - 1); };
+    bool started = false;                                  // (the first step has nothing to refill)
+
+    // ---- FP8 steps, in pairs that share their scales
+    auto fp8_step = [&](auto opsel) __attribute__((always_inline)) {
+        if (started) {
+            const Src s = src_of(min(u + 2, S - 1));
+#pragma unroll
+            for (int k = 0; k < LOADS; ++k) refill(k, s);
+        }
+        started = true;
+        const uint8_t *buf = smem + cur * STAGE;
+        const v8i a = join(*reinterpret_cast<const v4i *>(buf + a_base), *reinterpret_cast<const v4i *>(buf + (a_base ^ 32)));
+        const int sa = read_sa(buf);
+#pragma unroll
+        for (int t = 0; t < TN; ++t) {
+            const Frag lo = read_frag(buf, t);
+            const v8i b = join(lo.b, *reinterpret_cast<const v4i *>(buf + ((b_base ^ 32) + 2048 * t)));
+            acc[t] = mfma_mx<0, decltype(opsel)::value>(b, a, acc[t], lo.s, sa);
+            ATOM_F6_PIN(acc[t]);
+            if (t % 2 == 1) ATOM_F6_SLOT_END();            // (not all fragments of the step in registers at once)
+        }
+        next_stage();
+    };
+    while (u < S8) {
+        fp8_step(std::integral_constant<int, 0>{});
+        fp8_step(std::integral_constant<int, 2>{});
+    }
+
+    // ---- FP4 steps
+    constexpr int NF = 2 * TN, RING = AHEAD + 1, LASTREAD = NF - AHEAD - 1;      // MFMA behind which the step's last fragment is read
+    constexpr int SLOTS = LASTREAD + 1;                                          // the requests stand behind these
+    Frag f[RING];
+    v4i a0, a1;
+    int sa;
+    {
+        const uint8_t *buf = smem + cur * STAGE;
+        a0 = *reinterpret_cast<const v4i *>(buf + a_base);
+        sa = read_sa(buf);
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) f[i] = read_frag(buf, i);
+    }
+    Src ahead = src_of(min(u + 2, S - 1));
+    // (the ring of fragments turns by NF per step: its start is a template argument, and RING steps bring it back)
+    auto fp4_step = [&](auto start) __attribute__((always_inline)) {
+        constexpr int ST = decltype(start)::value;
+        const uint8_t *buf = smem + cur * STAGE;
+        a1 = *reinterpret_cast<const v4i *>(buf + (a_base ^ 32));
+        int sa_next = sa;
+#pragma unroll
+        for (int i = 0; i < NF; ++i) {
+            const Frag &x = f[(ST + i) % RING];
+            if (i < TN) acc[i]      = mfma_mx<4, 0>(widen(x.b), widen(a0), acc[i], x.s, sa);
+            else        acc[i - TN] = mfma_mx<4, 2>(widen(x.b), widen(a1), acc[i - TN], x.s, sa);
+            ATOM_F6_PIN(acc[i % TN]);
+            if (i + AHEAD < NF) f[(ST + i + AHEAD) % RING] = read_frag(buf, i + AHEAD);
+#pragma unroll
+            for (int k = 0; k < LOADS; ++k)
+                if (k * SLOTS / LOADS == i) refill(k, ahead);
+            if (i == LASTREAD + 1) {
+                next_stage();
+                const uint8_t *nbuf = smem + cur * STAGE;
+                a0 = *reinterpret_cast<const v4i *>(nbuf + a_base);
+                sa_next = read_sa(nbuf);
+            }
+            if (i > LASTREAD) {                            // AHEAD - 1 MFMAs are left: a fragment of the next step behind each, two behind the first
+                const uint8_t *nbuf = smem + cur * STAGE;
+                const int n = i - LASTREAD - 1;
+                if (i == LASTREAD + 1) f[(ST + NF) % RING] = read_frag(nbuf, 0);
+                else f[(ST + NF + n) % RING] = read_frag(nbuf, n);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        sa = sa_next;
+        if (u + 2 < S) { ahead.a += p.M * ROWB; ahead.w += p.N * ROWB; ahead.ae += p.M * 4; ahead.we += p.N * 4; }
+    };
+    static_assert(RING == 5, "five steps bring the ring back");
+    for (;;) {
+        if (u >= S) break;
+        fp4_step(std::integral_constant<int, 0>{});
+        if (u >= S) break;
+        fp4_step(std::integral_constant<int, NF % 5>{});
+        if (u >= S) break;
+        fp4_step(std::integral_constant<int, 2 * NF % 5>{});
+        if (u >= S) break;
+        fp4_step(std::integral_constant<int, 3 * NF % 5>{});
+        if (u >= S) break;
+        fp4_step(std::integral_constant<int, 4 * NF % 5>{});
+    }
+
+    // ---- store, 64 columns at a time through LDS.  The last (repeated) requests must have landed before the stages are reused.
+    __builtin_amdgcn_s_waitcnt(wait_imm(0));
+    __syncthreads();
+    uint8_t *reg = smem + wave * (32 * Gm::PITCH);
+#pragma unroll
+    for (int t0 = 0; t0 < TN; t0 += 2) {
+#pragma unroll
+        for (int t = t0; t < t0 + 2 && t < TN; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const v2h lo = __builtin_convertvector((v2f{acc[t][4 * q], acc[t][4 * q + 1]}), v2h);
+                const v2h hi = __builtin_convertvector((v2f{acc[t][4 * q + 2], acc[t][4 * q + 3]}), v2h);
+                *reinterpret_cast<v2u *>(reg + lr * Gm::PITCH + (32 * (t - t0) + 8 * q + 4 * g) * 2) =
+                    v2u{__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi)};
+            }
+        // (LDS only, and the wavefront reads what it wrote itself)
+        if (t0 + 2 <= TN) atom_gemm::store_block<32, 64>(reg, Gm::PITCH, p.y, p.ldy, m0 + 32 * wave, n0 + 32 * t0, p.M, p.N, lane);
+        else              atom_gemm::store_block<32, 32>(reg, Gm::PITCH, p.y, p.ldy, m0 + 32 * wave, n0 + 32 * t0, p.M, p.N, lane);
+    }
+}
+
+template <int TN>
+hipError_t launch_wide(const MxParams &p, hipStream_t stream)
+{
+    using Gm = MxWide<TN>;
+    auto kern = &mx_gemm_wide_kernel<TN>;
+    static atom_launch::LdsOptIn opt_in;
+    hipError_t err = atom_launch::ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(kern), Gm::LDS);
+    if (err != hipSuccess) return err;
+    const int64_t tiles = ((p.M + Gm::BM - 1) / Gm::BM) * ((p.N + Gm::BN - 1) / Gm::BN);
+    hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(Gm::NT), Gm::LDS, stream, p);
+    return hipGetLastError();
+}
+
 // Which tile.  The cost of a launch, in microseconds per K step, with f tiles per compute unit: `full` for each whole tile
 // every compute unit has, and for a last part r of them what they add when few compute units have one (`alone` where it is
 // all there is, `more` beside other workgroups), growing to `full` as the chip fills and the power limit sets in.  Measured
@@ -336,20 +586,22 @@ hipError_t launch_tile(const MxParams &p, hipStream_t stream)
 //   M = 1024, N = 22016, K = 4096:   64 x 64 103.4, 64 x 128 85.5, 128 x 128 62.4, 128 x 256 55.9, 256 x 256 61.1
 //   M = 4096, N = 22016, K = 4096:   64 x 64 436.6, 64 x 128 331.6, 128 x 128 251.2, 128 x 256 207.0, 256 x 256 203.1
 // (The kernel before, 256 x 256 and 128 x 128 with four wavefronts: 15.0, 16.4, 15.7, 49.1, 73.5 and 242.3.)
-enum Tile { k64x64, k64x128, k128x128, k128x256, k256x256, kTiles };
+enum Tile { k64x64, k64x128, k128x128, k128x256, k256x256, k256x320, k256x384, kTiles };
 struct TileCost { int bm, bn; float alone, more, full; };
 constexpr TileCost kCost[kTiles] = {{64, 64, 0.150f, 0.080f, 0.125f}, {64, 128, 0.190f, 0.110f, 0.205f}, {128, 128, 0.235f, 0.110f, 0.300f},
-                                    {128, 256, 0.380f, 0.280f, 0.590f}, {256, 256, 0.600f, 0.600f, 1.050f}};
+                                    {128, 256, 0.380f, 0.280f, 0.590f}, {256, 256, 0.600f, 0.600f, 1.050f},
+                                    {256, 320, 0.950f, 0.950f, 1.280f}, {256, 384, 1.060f, 1.060f, 1.460f}};
 
 int64_t tiles_of(const TileCost &t, int64_t M, int64_t N) { return ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn); }
 
-Tile pick_tile(int64_t M, int64_t N, int cus)
+Tile pick_tile(int64_t M, int64_t N, int K, int cus)
 {
     Tile best = k256x256;
     float least = 0.0f;
     for (int i = kTiles - 1; i >= 0; --i) {
         const int64_t tiles = tiles_of(kCost[i], M, N);
         if (tiles > 0x7fffff) continue;                    // (the grid's limit in threads; the 256 x 256 tile takes what is left)
+        if (i > k256x256 && (tiles > cus || K < 2048)) continue;         // (the wide kernel: one round, and steps enough for its prologue and store)
         const TileCost &t = kCost[i];
         const float r = (float)(tiles % cus) / (float)cus, few = tiles < cus ? t.alone : t.more;
         const float cost = t.full * (float)(tiles / cus) + (r > 0.0f ? few + (t.full - few) * r * r * r : 0.0f);
@@ -363,7 +615,14 @@ Tile pick_tile(int64_t M, int64_t N, int cus)
 // Which tile a launch takes, as the test of the tiles asks it (rows and columns of the tile in one number).
 extern "C" int atom_internal_mx_tile(int64_t M, int64_t N, int64_t cus)
 {
-    const TileCost &t = kCost[pick_tile(M, N, (int)cus)];
+    const TileCost &t = kCost[pick_tile(M, N, 0, (int)cus)];
+    return 1000 * t.bm + t.bn;
+}
+
+// The same for a call of K channels (above: of few).
+extern "C" int atom_internal_mx_tile_k(int64_t M, int64_t N, int32_t K, int64_t cus)
+{
+    const TileCost &t = kCost[pick_tile(M, N, K, (int)cus)];
     return 1000 * t.bm + t.bn;
 }
 
@@ -378,12 +637,14 @@ hipError_t launch_mx_gemm(const void *a_q4, const void *a_q8, const void *a_e8, 
     p.w_q4 = (const uint8_t *)w_q4; p.w_q8 = (const uint8_t *)w_q8; p.w_e8 = (const uint8_t *)w_e8;
     p.y = (uint16_t *)y; p.M = M; p.N = N; p.ldy = ldy; p.K = K; p.O = O;
     const int cus = atom_launch::compute_units();
-    switch (pick_tile(M, N, cus)) {
+    switch (pick_tile(M, N, K, cus)) {
     case k64x64:   return launch_tile<2, 2, 1, 1, 4>(p, stream);
     case k64x128:  return launch_tile<2, 2, 1, 2, 6>(p, stream);
     case k128x128:                                         // up to one per compute unit with four stages, else three workgroups per compute unit
         return tiles_of(kCost[k128x128], M, N) <= cus ? launch_tile<2, 2, 2, 2, 4>(p, stream) : launch_tile<2, 2, 2, 2, 3>(p, stream);
     case k128x256: return launch_tile<2, 4, 2, 2, 3>(p, stream);
+    case k256x320: return launch_wide<10>(p, stream);
+    case k256x384: return launch_wide<12>(p, stream);
     default:       return launch_tile<4, 2, 2, 4, 4>(p, stream);
     }
 }

@@ -39,11 +39,28 @@ def tile(M, N):
 ])
 def test_mx_tiles(name, M, K, N):
     assert tile(M, N) == name
+    check(name, M, K, N)
+
+
+@pytest.mark.parametrize("name,M,K,N", [
+    ("256x320", 1024, 2048, 17000),      # the fewest channels of the wide kernel; a last column tile of 40
+    ("256x320", 1793, 2176, 9601),       # a last row tile of one row, an odd row length
+    ("256x384", 900, 2304, 22015),       # ragged both ways
+    ("256x384", 2048, 2048, 12288),      # whole tiles, one per compute unit
+])
+def test_mx_wide_tiles(name, M, K, N):
+    pick = ctypes.CDLL(atom.binding._LIB_PATH).atom_internal_mx_tile_k
+    t = pick(ctypes.c_int64(M), ctypes.c_int64(N), ctypes.c_int32(K), ctypes.c_int64(torch.cuda.get_device_properties(0).multi_processor_count))
+    assert f"{t // 1000}x{t % 1000}" == name
+    check(name, M, K, N)
+
+
+def check(name, M, K, N, O=128):
     print(f"[case] mx tile {name} M={M} K={K} N={N}", flush=True)
-    lin = _rand_linear(M, K, N, 128, seed=M + N, norm=False)
+    lin = _rand_linear(M, K, N, O, seed=M + N, norm=False)
     idx = lin.idx.cuda()
-    ga = atom.atom_mx_quantize_act(lin.x.cuda(), None, 0.0, idx, 128, 0.9)
-    gw = atom.atom_mx_quantize_weight(lin.w.cuda(), idx, 128, 0.85)
+    ga = atom.atom_mx_quantize_act(lin.x.cuda(), None, 0.0, idx, O, 0.9)
+    gw = atom.atom_mx_quantize_weight(lin.w.cuda(), idx, O, 0.85)
     y = atom.atom_mx_gemm(*ga, *gw)
     rows = np.unique(np.concatenate([np.arange(min(M, 20)), np.arange(max(0, M - 20), M),
                                      np.random.default_rng(M).choice(M, min(M, 24), replace=False)]))
