@@ -44,9 +44,10 @@ def test_mx_tiles(name, M, K, N):
 
 @pytest.mark.parametrize("name,M,K,N", [
     ("256x320", 1024, 2048, 17000),      # the fewest channels of the wide kernel; a last column tile of 40
-    ("256x320", 1793, 2176, 9601),       # a last row tile of one row, an odd row length
+    ("256x320", 1793, 2176, 10001),      # a last row tile of one row, an odd row length
     ("256x384", 900, 2304, 22015),       # ragged both ways
     ("256x384", 2048, 2048, 12288),      # whole tiles, one per compute unit
+    ("256x384", 2999, 2048, 13823),      # more than one per compute unit
 ])
 def test_mx_wide_tiles(name, M, K, N):
     pick = ctypes.CDLL(atom.binding._LIB_PATH).atom_internal_mx_tile_k
