@@ -180,7 +180,7 @@ void quantize_rows_kernel(const __half *x, int64_t rows, int64_t ld,
 
 
 template <bool NORM, int NS, int NT, int PRE, bool IDENT, bool MX>
-__global__ __launch_bounds__(NT, NS == 4 && NT == 512 && !NORM ? 4 : 1)     // (at most 128 registers where that needs no spill: two workgroups per CU)
+__global__ __launch_bounds__(NT, min_waves(NORM, NS, NT, PRE, IDENT, false, MX))
 void quantize_rows_fast_kernel(const __half *x, int64_t rows, int64_t ld,
                                const __half *res, int64_t ldr, __half *sum_out, int64_t ldo,
                                const __half *__restrict__ gamma, float eps,
@@ -272,6 +272,7 @@ hipError_t launch_gather(const QuantArgs &a, bool few, hipStream_t stream)
     const size_t lds = quantize_lds_bytes(a.K, NORM);
     if (a.K <= 2048)  return launch_fast<NORM, 1, 256, PRE, false, MX>(a, lds, stream);
     if (few && a.K <= 4096)  return launch_fast<NORM, 1, 512, PRE, false, MX>(a, lds, stream);
+    if (few && a.K <= 5120)  return launch_fast<NORM, 1, 640, PRE, false, MX>(a, lds, stream);
     if (few && a.K <= 8192)  return launch_fast<NORM, 1, 1024, PRE, false, MX>(a, lds, stream);
     if (few && a.K <= 16384) return launch_fast<NORM, 2, 1024, PRE, false, MX>(a, lds, stream);
     if (a.K <= 4096)  return launch_fast<NORM, 2, 256, PRE, false, MX>(a, lds, stream);

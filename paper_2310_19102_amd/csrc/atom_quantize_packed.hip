@@ -19,21 +19,20 @@ namespace {
 using namespace atom_quantize_rows;
 
 template <bool NORM, int NS, int NT, int PRE, bool IDENT>
-__global__ __launch_bounds__(NT, NS == 4 && NT == 512 && !NORM ? 4 : 1)
+__global__ __launch_bounds__(NT, min_waves(NORM, NS, NT, PRE, IDENT, true, false))
 void quantize_rows_packed_kernel(const __half *x, int64_t rows, int64_t ld, const __half *res, int64_t ldr,
                                  __half *sum_out, int64_t ldo, const __half *__restrict__ gamma, float eps,
                                  const int32_t *__restrict__ idx, int K, int O, int nbits, float clip,
-                                 uint8_t *__restrict__ pk_out, unsigned pk_lds_off)
+                                 uint8_t *__restrict__ pk_out, unsigned pk_lds_off, int rpw)
 {
     extern __shared__ __align__(16) float lds[];
     uint8_t *pk_lds = reinterpret_cast<uint8_t *>(lds) + pk_lds_off;
     // A workgroup takes a run of consecutive rows, and consecutive runs go to workgroups of the same
     // XCD (the hardware deals workgroup ids round-robin to the 8 XCDs): the 16-byte pieces that the
     // rows r .. r+7 of a unit put into one 128-byte line then meet in one L2 instead of eight.
-    const int64_t nb = gridDim.x, b = blockIdx.x;
-    const int64_t per = nb >> 3, rem = nb & 7, xcd = b & 7;
+    const int nb = gridDim.x, b = blockIdx.x;
+    const int per = nb >> 3, rem = nb & 7, xcd = b & 7;
     const int64_t logical = xcd * per + (xcd < rem ? xcd : rem) + (b >> 3);
-    const int64_t rpw = (rows + nb - 1) / nb;
     const int64_t first = logical * rpw, last = first + rpw < rows ? first + rpw : rows;
     quantize_rows_fast_body<NORM, NS, NT, PRE, IDENT, true>(lds, first, 1, x, last, ld, res, ldr, sum_out,
                                                             ldo, gamma, eps, idx, K, O, nbits, clip, nullptr, nullptr,
@@ -93,7 +92,7 @@ hipError_t launch_cfg(const PackedArgs &a, hipStream_t stream)
     const int64_t grid = (a.rows + rows_per_wg - 1) / rows_per_wg;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), lds, stream, (const __half *)a.x, a.rows, a.ld,
                        (const __half *)a.res, a.ldr, (__half *)a.sum_out, a.ldo, (const __half *)a.gamma, a.eps, a.idx,
-                       a.K, a.O, a.nbits, a.clip, (uint8_t *)a.out, (unsigned)front);
+                       a.K, a.O, a.nbits, a.clip, (uint8_t *)a.out, (unsigned)front, (int)((a.rows + grid - 1) / grid));
     return hipGetLastError();
 }
 
@@ -106,6 +105,7 @@ hipError_t dispatch_k(const PackedArgs &a, hipStream_t stream)
     // 10.0; 4096 rows, SwiGLU: 35.4 and 29.5).
     const bool few = a.rows <= atom_launch::compute_units();
     if (few && a.K <= 4096)  return launch_cfg<NORM, 1, 512, PRE, IDENT>(a, stream);
+    if (few && a.K <= 5120)  return launch_cfg<NORM, 1, 640, PRE, IDENT>(a, stream);
     if (few && a.K <= 8192 && !(IDENT && NORM)) return launch_cfg<NORM, 1, 1024, PRE, IDENT>(a, stream);
     if (few && a.K <= 16384 && a.K > 8192) return launch_cfg<NORM, 2, 1024, PRE, IDENT>(a, stream);
     if (a.K <= 4096)  return launch_cfg<NORM, 2, 256, PRE, IDENT>(a, stream);

@@ -45,11 +45,14 @@ __device__ __forceinline__ uint4 add_halves(const uint4 &a, const uint4 &b)
 // exp(x) on [-87, 87] from IEEE operations only (one value on every machine, the CPU
 // oracle's included): n = round(x*log2(e)); r = x - n*ln2 with ln2 split in two, the first
 // part short enough for n*ln2_hi to be exact; e^r by its Taylor polynomial of degree 7 in
-// Horner form; 2^n through the exponent field.
+// Horner form; 2^n through the exponent field.  The rounding is one fused multiply-add onto 1.5 * 2^23, which leaves n in
+// the low bits as well: a shift and an add put it into the exponent of e^r (between 0.7 and 1.5, and |n| <= 126).  Both are
+// exact, and for every fp16 x the fused product rounds to the same n as a rounded one.
 __device__ __forceinline__ float exp_ieee(float x)
 {
     x = __builtin_amdgcn_fmed3f(x, -87.0f, 87.0f);
-    const float n = rintf(x * 1.44269502162933349609375f);
+    const float biased = fmaf(x, 1.44269502162933349609375f, 12582912.0f);
+    const float n = biased - 12582912.0f;
     float r = fmaf(n, -0.693145751953125f, x);
     r = fmaf(n, -1.428606765330187045037746429443359375e-06f, r);
     float p = 1.0f / 5040.0f;
@@ -60,7 +63,7 @@ __device__ __forceinline__ float exp_ieee(float x)
     p = fmaf(p, r, 0.5f);
     p = fmaf(p, r, 1.0f);
     p = fmaf(p, r, 1.0f);
-    return __builtin_amdgcn_ldexpf(p, (int)n);     // (normal numbers both: the same as the product with 2^n)
+    return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, p) + (__builtin_bit_cast(uint32_t, biased) << 23));
 }
 
 // silu(g) * u in fp32: sigma = the correctly rounded 1/(1 + exp(-g)), then (g*sigma)*u.  g is an fp16 number, so
@@ -116,22 +119,37 @@ __device__ __forceinline__ float row16_max(float v)
     return v;
 }
 
-// max over the 16 lanes of a DPP row by rotations (max is exact in any order); one
-// v_max_f32 with a DPP operand per step, no LDS crossbar traffic
-__device__ __forceinline__ float row16_max_dpp(float v)
+// max over the 16 lanes of a DPP row by rotations (max is exact in any order), no LDS crossbar traffic.  Of values that are
+// not negative and not NaN, whose bits are in the order of the numbers: one v_max_u32 with a DPP operand per step (as floats a move,
+// a canonicalising maximum and the maximum itself).
+__device__ __forceinline__ float row16_max_dpp(float f)
 {
+    uint32_t v = __builtin_bit_cast(uint32_t, f);
 #define ATOM_ROW_ROR(n)                                                                          \
-    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(                          \
-                     0, __builtin_bit_cast(int, v), 0x120 | (n), 0xF, 0xF, false)))
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 | (n), 0xF, 0xF, false))
     ATOM_ROW_ROR(8);
     ATOM_ROW_ROR(4);
     ATOM_ROW_ROR(2);
     ATOM_ROW_ROR(1);
 #undef ATOM_ROW_ROR
-    return v;
+    return __builtin_bit_cast(float, v);
 }
 
-// Scale of a group from its maximum (Section 2 symmetric equations, fp32, stored as fp16) and the
+// Scale of a group from its maximum (Section 2 symmetric equations, fp32, stored as fp16).  The division by 15 (7, 255) is a
+// product with the rounded reciprocal and one correction, a = amax * 2 clip cut to the finite numbers: the same fp16 for
+// every fp32 a >= 0 and each of the three (all of them were compared).
+__device__ __forceinline__ __half group_scale(float amax, bool is4, int nbits, float clip)
+{
+    const float denom = is4 ? (nbits == 3 ? 7.0f : 15.0f) : 255.0f;
+    const float recip = is4 ? (nbits == 3 ? 1.0f / 7.0f : 1.0f / 15.0f) : 1.0f / 255.0f;
+    const float a     = fminf((2.0f * amax) * clip, 3.40282346638528859812e38f);
+    const float q     = a * recip;
+    float s32         = fmaf(fmaf(-q, denom, a), recip, q);
+    asm volatile("" : "+v"(s32));      // (rounded to fp32 and then to fp16: left to itself the compiler makes one rounding of the two)
+    return (s32 > 65504.0f) ? __ushort_as_half((unsigned short)0x7bffu) : __float2half_rn(s32);
+}
+
+// The scale of a group from its maximum and the
 // codes of this lane's eight values: the IEEE quotient by the stored scale, round-half-to-even, clamp.
 // The quotient takes three instructions per element.  s is an fp16 number, and r = rcp(s) with one Newton step is
 // the correctly rounded 1/s for every one of them (every scale is tested, at its ties and beside them).  q = y r is within two
@@ -143,12 +161,9 @@ __device__ __forceinline__ __half quantise_lane8(const float (&y)[8], float amax
                                                  float (&q)[8], float &s)
 {
     // normal channels: n = nbits (4, or 3 with the codes still in nibbles), outliers n = 8
-    const float denom = is4 ? (nbits == 3 ? 7.0f : 15.0f) : 255.0f;
     const float qmin  = is4 ? (nbits == 3 ? -4.0f : -8.0f) : -128.0f;
     const float qmax  = is4 ? (nbits == 3 ? 3.0f : 7.0f) : 127.0f;
-    const float s32   = ((2.0f * amax) * clip) / denom;
-    const __half sh   = (s32 > 65504.0f) ? __ushort_as_half((unsigned short)0x7bffu)
-                                         : __float2half_rn(s32);
+    const __half sh   = group_scale(amax, is4, nbits, clip);
     s = __half2float(sh);
     const float r0    = __builtin_amdgcn_rcpf(s);
     const float e0    = fmaf(-s, r0, 1.0f);
@@ -209,6 +224,23 @@ struct NoHook { __device__ __forceinline__ void operator()() const {} };
 // half, chunk), then copied out as whole 16-byte chunks.
 typedef _Float16 pk_v32h __attribute__((ext_vector_type(32)));
 typedef unsigned pk_v6u  __attribute__((ext_vector_type(6)));
+// Wavefronts per SIMD that a kernel's registers have to leave room for, where the compiler would take a few more than that without being
+// told: two workgroups of 512 threads per CU instead of one, five of 256 or four of 320 instead of four and three.
+constexpr int min_waves(bool norm, int ns, int nt, int pre, bool ident, bool packed, bool mx)
+{
+    if (nt == 512 && ns == 4) return norm ? 1 : 4;
+    if (nt == 512 && ns == 3) return norm && !ident && (pre == kAdd || packed || mx) ? 1 : 4;
+    return nt <= 320 && ns == 2 && pre != kAdd ? 5 : 1;
+}
+// A lane's place behind a pointer that is the same for the workgroup, as 32 bits beside it in the memory instruction.  (The offset is
+// made opaque where it is used: as 64-bit addresses in front of the loop over rows they took up to 20 registers.)
+template <class T>
+__device__ __forceinline__ char *at(T *base, unsigned offset)
+{
+    asm volatile("" : "+v"(offset));
+    return const_cast<char *>(reinterpret_cast<const char *>(base)) + offset;
+}
+
 constexpr int kImg4 = 6656, kImg8 = 8704, kSc4 = 6144, kSc8 = 8192;
 
 // MX: codes and scale bytes of the MX variant (FP4 E2M1 / FP8 E4M3, one E8M0 byte per 32 channels = 4 lanes) in their
@@ -238,22 +270,25 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
 
     uint4 raw[NS];
     uint4 rres[PRE != kPlain ? NS : 1];
+    // Threads past the end of the row load its last vector again (and use nothing of it): with a branch around each load the
+    // compiler waits for every one of them inside its branch, one memory latency after the other.
+    auto load_vector = [&](const __half *p, int i) -> uint4 {
+        return *reinterpret_cast<const uint4 *>(at(p, 16u * (unsigned)min(tid + NT * i, V - 1)));
+    };
     auto fetch_row = [&](int64_t row) {
-        const __half *xr = x + row * ld;
+        const __half *xr = x + row * ld, *rr = PRE != kPlain ? res + row * ldr : nullptr;
 #pragma unroll
         for (int i = 0; i < NS; ++i) {
-            const int v = tid + NT * i;
-            raw[i] = v < V ? *reinterpret_cast<const uint4 *>(xr + 8 * v) : make_uint4(0, 0, 0, 0);
-            if (PRE != kPlain)
-                rres[i] = v < V ? *reinterpret_cast<const uint4 *>(res + row * ldr + 8 * v)
-                                : make_uint4(0, 0, 0, 0);
+            raw[i] = load_vector(xr, i);
+            if (PRE != kPlain) rres[i] = load_vector(rr, i);
         }
     };
     int64_t row = row_first;
     if (row < rows) fetch_row(row);       // (first: the longest way of all the loads before the loop)
     // gather offsets (bytes into ybuf) of this lane's 8 channels in each of its groups
-    // (with 1024 threads two 16-bit channel numbers share a register)
-    constexpr bool OPACK = NT >= 1024;
+    // (with 1024 threads or four sweeps two of them share a register: as 16-bit offsets up to 16384 channels, as channel numbers beyond)
+    constexpr bool OPACK = NT >= 1024 || NS >= 4;
+    constexpr int OSHIFT = !OPACK || NS * NT <= 2048 ? 2 : 0;
     uint32_t off[IDENT ? 1 : NS][OPACK ? 4 : 8];
 #pragma unroll
     for (int j = 0; j < (IDENT ? 0 : NS); ++j) {
@@ -266,9 +301,9 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const uint32_t c = min((unsigned)id[e], (unsigned)(K - 1));
-            if (!OPACK)          off[j][e] = 4u * c;
-            else if (e % 2 == 0) off[j][e / 2] = c;
-            else                 off[j][e / 2] |= c << 16;
+            if (!OPACK)          off[j][e] = c << OSHIFT;
+            else if (e % 2 == 0) off[j][e / 2] = c << OSHIFT;
+            else                 off[j][e / 2] |= c << (16 + OSHIFT);
         }
     }
     // gamma stays in registers too, except with 1024 threads (128 registers per lane):
@@ -277,10 +312,7 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
     uint4 graw[NORM && GREG ? NS : 1];
     if (NORM && GREG) {
 #pragma unroll
-        for (int i = 0; i < NS; ++i) {
-            const int v = tid + NT * i;
-            graw[i] = v < V ? *reinterpret_cast<const uint4 *>(gamma + 8 * v) : make_uint4(0, 0, 0, 0);
-        }
+        for (int i = 0; i < NS; ++i) graw[i] = load_vector(gamma, i);
     }
 
     after_first_fetch();
@@ -294,7 +326,7 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
                 const int v = tid + NT * i;
                 if (v < V) {
                     raw[i] = add_halves(raw[i], rres[i]);
-                    *reinterpret_cast<uint4 *>(sum_out + row * ldo + 8 * v) = raw[i];
+                    *reinterpret_cast<uint4 *>(at(sum_out + row * ldo, 16u * (unsigned)v)) = raw[i];
                 }
             }
         }
@@ -381,7 +413,7 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
                         // unpacked here, per row: hoisted out of the row loop the unpacked
                         // offsets would take the registers the packing saves
                         asm volatile("" : "+v"(o));
-                        o = e % 2 ? (o >> 16) << 2 : (o & 0xffffu) << 2;
+                        o = (e % 2 ? o >> 16 : o & 0xffffu) << (2 - OSHIFT);
                     }
                     y[e] = *reinterpret_cast<const float *>(reinterpret_cast<const unsigned char *>(ybuf) + o);
                 }
@@ -448,6 +480,10 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
             const __half sh = quantise_lane8(y, amax, is4, nbits, clip, q, s);
             const bool nz = s != 0.0f;
             if constexpr (PACKED) {
+                if (__builtin_expect(__ballot(!nz) != 0, 0)) {      // (a group of zeros: rare, and one branch for the wavefront)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) q[e] = nz ? q[e] : 0.0f;
+                }
                 if (live) {
                     const int pos = lane & 15;                      // 8 channels at 8 * pos of the group
                     const int64_t unit = row >> 6;
@@ -455,11 +491,18 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
                     uint8_t *ubase = pk_out + unit * ((int64_t)G4 * kImg4 + (int64_t)(G - G4) * kImg8);
                     if (is4) {
                         // the E3M2 number of each code (a plain conversion: every code is representable);
-                        // eight codes = 48 bits, at byte 6 (pos % 4) of the 24 bytes of their 32-channel block
+                        // eight codes = 48 bits, at byte 6 (pos % 4) of the 24 bytes of their 32-channel block.
+                        // (+ 0: a code that was rounded up to zero is -0, and FP6 has a sign bit.  The other 24 numbers are
+                        // converted too and not used: whatever the registers hold.)
+                        typedef _Float16 v2h __attribute__((ext_vector_type(2)));
                         pk_v32h h;
+                        asm volatile("" : "=v"(h));
 #pragma unroll
-                        // (+ 0.0f: a code that was rounded up to zero is -0.0f, and FP6 has a sign bit)
-                        for (int e = 0; e < 32; ++e) h[e] = e < 8 ? (_Float16)((nz ? q[e & 7] : 0.0f) + 0.0f) : (_Float16)0.0f;
+                        for (int e = 0; e < 8; e += 2) {
+                            const v2h two = __builtin_bit_cast(v2h, __builtin_amdgcn_cvt_pkrtz(q[e], q[e + 1])) + (v2h)(_Float16)0.0f;
+                            h[e] = two[0];
+                            h[e + 1] = two[1];
+                        }
                         const pk_v6u f6 = __builtin_amdgcn_cvt_scalef32_pk32_bf6_f16(h, 1.0f);
                         const int blk = pos >> 2;                   // block b: half b % 2, first or second MFMA b / 2
                         uint16_t *dst = reinterpret_cast<uint16_t *>(pk_lds + 96 * gg + 48 * (blk & 1) + 24 * (blk >> 1) + 6 * (pos & 3));
@@ -467,7 +510,7 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
                         dst[1] = (uint16_t)(f6[0] >> 16);
                         dst[2] = (uint16_t)f6[1];
                         if (pos == 0)
-                            *reinterpret_cast<uint2 *>(ubase + (int64_t)gg * kImg4 + kSc4 + 8 * r) = make_uint2(__half_as_ushort(sh), 0u);
+                            *reinterpret_cast<uint2 *>(at(ubase + kSc4 + 8 * r, (unsigned)gg * kImg4)) = make_uint2(__half_as_ushort(sh), 0u);
                     } else {
                         uint32_t w0 = 0, w1 = 0;
 #pragma unroll
@@ -475,16 +518,16 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
                             w0 |= (uint32_t)((int)q[e] & 0xFF) << (8 * e);
                             w1 |= (uint32_t)((int)q[e + 4] & 0xFF) << (8 * e);
                         }
-                        *reinterpret_cast<uint2 *>(pk_lds + 3 * (K4 >> 2) + (j0 - K4)) = make_uint2(nz ? w0 : 0u, nz ? w1 : 0u);
+                        *reinterpret_cast<uint2 *>(pk_lds + 3 * (K4 >> 2) + (j0 - K4)) = make_uint2(w0, w1);
                         if (pos == 0)
-                            *reinterpret_cast<uint2 *>(ubase + (int64_t)G4 * kImg4 + (int64_t)(gg - G4) * kImg8 + kSc8 + 8 * r) =
+                            *reinterpret_cast<uint2 *>(at(ubase + (int64_t)G4 * kImg4 + kSc8 + 8 * r, (unsigned)(gg - G4) * kImg8)) =
                                 make_uint2(__half_as_ushort(sh), 0u);
                     }
                 }
             } else if (live) {
                 if (is4) {
                     const uint32_t w = pack_nibbles8(q);
-                    *reinterpret_cast<uint32_t *>(q4 + row * (int64_t)(K4 >> 1) + (j0 >> 1)) = nz ? w : 0u;
+                    *reinterpret_cast<uint32_t *>(at(q4 + row * (int64_t)(K4 >> 1), (unsigned)j0 >> 1)) = nz ? w : 0u;
                 } else {
                     uint32_t w0 = 0, w1 = 0;
 #pragma unroll
@@ -492,10 +535,10 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
                         w0 |= (uint32_t)((int)q[e] & 0xFF) << (8 * e);
                         w1 |= (uint32_t)((int)q[e + 4] & 0xFF) << (8 * e);
                     }
-                    *reinterpret_cast<uint2 *>(q8 + row * (int64_t)O + (j0 - K4)) =
+                    *reinterpret_cast<uint2 *>(at(q8 + row * (int64_t)O, (unsigned)(j0 - K4))) =
                         make_uint2(nz ? w0 : 0u, nz ? w1 : 0u);
                 }
-                if ((lane & 15) == 0) scale[row * (int64_t)G + gg] = sh;
+                if ((lane & 15) == 0) *reinterpret_cast<__half *>(at(scale + row * (int64_t)G, 2u * (unsigned)gg)) = sh;
             }
         }
         if (!IDENT || NORM || PACKED) __syncthreads();   // ybuf and qbuf are rewritten by the next row
@@ -508,15 +551,15 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
             const int n4 = 6 * G4, n8 = O >> 4;
             for (int j = tid; j < n4 + n8; j += NT) {
                 const uint4 v = *reinterpret_cast<const uint4 *>(pk_lds + 16 * j);
-                uint8_t *dst;
+                unsigned dst;
                 if (j < n4) {
-                    const int gq = j / 6, hc = j - 6 * gq, hh = hc >= 3 ? 1 : 0, c = hc - 3 * hh;
-                    dst = ubase + (int64_t)gq * kImg4 + 2048 * c + 1024 * hh + 16 * r;
+                    const unsigned gq = (unsigned)j / 6, hc = j - 6 * gq, hh = hc >= 3 ? 1 : 0, c = hc - 3 * hh;
+                    dst = gq * kImg4 + 2048 * c + 1024 * hh + 16 * r;
                 } else {
-                    const int j8 = j - n4, g8 = j8 >> 3, c = j8 & 7;
-                    dst = ubase + (int64_t)G4 * kImg4 + (int64_t)g8 * kImg8 + 128 * r + 16 * ((c ^ r ^ ((r >> 3) & 1)) & 7);
+                    const unsigned j8 = j - n4, g8 = j8 >> 3, c = j8 & 7;
+                    dst = G4 * kImg4 + g8 * kImg8 + 128 * r + 16 * ((c ^ r ^ ((r >> 3) & 1)) & 7);
                 }
-                *reinterpret_cast<uint4 *>(dst) = v;
+                *reinterpret_cast<uint4 *>(at(ubase, dst)) = v;
             }
             if (IDENT && !NORM) __syncthreads();     // (no other barrier stands before the next row's writes to pk_lds)
         }
