@@ -113,7 +113,7 @@ def load_library():
     L.atom_permute_rows.argtypes = [vp, i64, i64, i64, vp, i64, vp, i64, vp]
     L.atom_decode_linear.restype = ctypes.c_int
     L.atom_decode_linear_wants_codes.restype = ctypes.c_int
-    L.atom_decode_linear_wants_codes.argtypes = [i64, i64, dp]
+    L.atom_decode_linear_wants_codes.argtypes = [i64, i64, dp, ctypes.c_int]
     L.atom_decode_linear.argtypes = [vp, i64, i64, vp, f32, vp, dp, f32, vp, vp, vp, i64, vp, i64, vp, vp, vp, vp]
     L.atom_decode_linear_coop_sync_bytes.restype = sz
     L.atom_decode_linear_coop_sync_bytes.argtypes = []

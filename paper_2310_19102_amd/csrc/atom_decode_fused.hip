@@ -384,13 +384,18 @@ size_t decode_linear_lds_bytes(int M, int K, int O, bool norm, bool ident)
 // Two launches cost 7.5 to 9.3 us, most of it the host's, whatever the rows up to the time of the weight stream; the kernel above repeats
 // the front end of every row in every workgroup.  us, one launch and two: K = N = 4096: 1 row 6.1, 9.3; 2 7.6, 9.2; 3 9.1, 9.0; 8 15.8, 9.2;
 // 16 26.3, 9.3; N = 11008: 1 11.7, 9.3; 8 31.5, 9.4; K = 11008, N = 4096: 1 13.9, 11.5; 8 35.6, 12.0; K = 1024, N = 1000: 4 8.1, 9.4; 8
-// 11.8, 9.3; K = 8192, N = 28672: 1 61.2, 27.5; 16 274, 37.9.  The line is a product of rows, channels and (from 5120 on, where a second
-// round of workgroups begins to count) outputs.
-bool decode_linear_splits(int M, int64_t N, int K, int O)
+// 11.8, 9.3; K = 8192, N = 28672: 1 61.2, 27.5; 16 274, 37.9.  The line is a product of rows, channels and (beyond 8192, where the
+// workgroups come in a second round: K = 2048, 2 rows, N = 8192: 7.8 and 9.3, 1 row, N = 22016: 15.1 and 9.2) outputs.  Without a norm a row costs little more than half as much (K = N = 4096: 3 rows 7.4, 4 8.2,
+// 5 9.1, 8 11.5; K = 2048: 6 8.3), which counts where the rows are what is long.  More than 4096 channels and more than 4096 outputs: the
+// workgroups of two register sets come one to a CU and in two rounds (K = N = 5120, 1 row: 15.4 with a norm, 13.3 without; two launches 7.6
+// to 9.1; with K or N 4096 7.2 to 8.4).
+bool decode_linear_splits(int M, int64_t N, int K, int O, bool norm)
 {
     // (the two launches address the weights with 32-bit offsets)
     if (M > 16 || (uint64_t)N * (uint64_t)(K - O) / 2 >= 1ull << 32 || (uint64_t)N * (uint64_t)O >= 1ull << 32) return false;
-    return (double)M * (double)(K + 2048) * (double)(N > 5120 ? N : 5120) > 66.5e6;
+    if (K > 4096 && N > 4096) return true;
+    const double row = !norm && K <= 5120 && N <= 5120 ? 0.5 : 1.0;
+    return row * (double)M * (double)(K + 2048) * (double)(N > 8192 ? N : 5120) > 66.5e6;
 }
 
 hipError_t launch_decode_linear(const void *x, int M, int64_t ldx, const void *gamma, float eps,

@@ -379,7 +379,7 @@ PyObject *decode_linear(Args a)
     Tensor own;
     if (debug) {
         c4 = q.q4.data(); c8 = q.q8.data(); cs = q.sc.data();
-    } else if (atom_decode_linear_wants_codes(M, N, &d)) {          // one array for the three, each from a 256-byte boundary
+    } else if (atom_decode_linear_wants_codes(M, N, &d, gamma != nullptr)) {   // one array for the three, each from a 256-byte boundary
         const auto up = [](int64_t n) { return (n + 255) / 256 * 256; };
         const int64_t n4 = up(M * (K - O) / 2), n8 = up(M * O);
         own = make({n4 + n8 + M * groups(K, gs) * 2}, kByte, x);

@@ -20,17 +20,19 @@ def _case(M, K, N, norm, seed=0):
     return x, gamma, idx, w, qa, atom.atom_w4a4_gemm(*qa, *w)
 
 
-def _wants(M, N, K):
+def _wants(M, N, K, norm=True):
     from paper_2310_19102_amd.binding import _desc
-    return atom.load_library().atom_decode_linear_wants_codes(M, N, ctypes.byref(_desc(K, 128, 128)))
+    return atom.load_library().atom_decode_linear_wants_codes(M, N, ctypes.byref(_desc(K, 128, 128)), int(norm))
 
 
 @pytest.mark.parametrize("M,K,N,norm,two", [
     (1, 4096, 8192, True, False), (1, 4096, 11008, True, True), (1, 11008, 512, False, True), (2, 4096, 4096, True, False),
-    (3, 4096, 4096, True, True), (4, 1024, 1000, False, False), (16, 1024, 40, True, True), (9, 5120, 1300, False, True)])
+    (3, 4096, 4096, True, True), (4, 1024, 1000, False, False), (16, 1024, 40, True, True), (9, 5120, 1300, False, True),
+    (4, 4096, 4096, False, False), (5, 4096, 4096, False, True), (1, 5120, 4096, True, False), (1, 5120, 5120, True, True),
+    (2, 2048, 8192, True, False)])
 def test_both_sides_of_the_line(M, K, N, norm, two):
     print(f"[case] decode linear, {'two launches' if two else 'one launch'} M={M} K={K} N={N} norm={norm}", flush=True)
-    assert bool(_wants(M, N, K)) == two
+    assert bool(_wants(M, N, K, norm)) == two
     x, gamma, idx, w, qa, want = _case(M, K, N, norm)
     wide = torch.full((M, N + 3), 7.0, dtype=torch.float16, device="cuda")
     atom.atom_decode_linear(x, gamma, 1e-5, idx, *w, out=wide[:, :N])
