@@ -59,12 +59,16 @@ struct FusedParams {
 // NORM: RMSNorm in the front end.  NS: register sets of the front end (K <= 4096 * NS).
 // DEPTH: groups whose weight loads are in flight together per wavefront.
 // IDENT: no reorder index (x already is in reordered order): the row routine without its gather.
-template <bool NORM, int NS, int DEPTH, bool IDENT>
+// ONE: one row.  Its kernel has no loop over rows, where the first wait is one for the weights, too (K = N = 4096, us: 5.1
+// with a norm and 4.5 without, in the loop 6.1 and 5.4);
+// the first row by itself and then the others was faster and slower by turns (a second copy of the routine: 2 rows of 2048 channels on 8192
+// outputs 8.6 -> 9.1 us).
+template <bool NORM, int NS, int DEPTH, bool IDENT, bool ONE>
 __global__ __launch_bounds__(NT)
 void decode_linear_kernel(const FusedParams p)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int K = p.K, O = p.O, K4 = K - O, G = K >> 7, G4 = K4 >> 7, M = p.M;
+    const int K = p.K, O = p.O, K4 = K - O, G = K >> 7, G4 = K4 >> 7, M = ONE ? 1 : p.M;
     // LDS: [front-end staging | a4 [M][K4/2] | a8 [M][O] | a_scale [M][G]]; the staging area
     // (at least 8 KB) holds the slices' partial tiles at the end
     float    *front = reinterpret_cast<float *>(smem);
@@ -111,10 +115,10 @@ void decode_linear_kernel(const FusedParams p)
     // ---- the front end, all rows, into LDS ---------------------------------------------------
     // The first weight loads are issued from inside the routine, right after the loads of its
     // first row: loads return in order, and the routine must not wait for the weights.
-    quantize_rows_fast_body<NORM, NS, NT, kPlain, IDENT>(front, 0, 1, p.x, M, p.ldx, nullptr, 0, nullptr, 0,
-                                                         p.gamma, p.eps, p.idx, K, O, p.nbits, p.clip, a4, a8,
-                                                         reinterpret_cast<__half *>(as),
-                                                         [&]() { load_weights(g_begin); });
+    const auto load_first = [&]() { load_weights(g_begin); };
+    quantize_rows_fast_body<NORM, NS, NT, kPlain, IDENT, false, decltype(load_first), false, ONE>(
+        front, 0, 1, p.x, M, p.ldx, nullptr, 0, nullptr, 0, p.gamma, p.eps, p.idx, K, O, p.nbits, p.clip, a4, a8,
+        reinterpret_cast<__half *>(as), load_first);
     if (IDENT && !NORM) __syncthreads();       // (that variant of the routine has no barrier of its own)
     // every code and scale is in LDS
     if (p.dbg_q4 && blockIdx.x == 0) {
@@ -188,15 +192,22 @@ unsigned front_bytes(int K, bool norm, bool ident)
     return ((need > red ? need : red) + 15u) & ~15u;
 }
 
-template <bool NORM, int NS, int DEPTH, bool IDENT>
+template <bool NORM, int NS, int DEPTH, bool IDENT, bool ONE>
 hipError_t launch_cfg(const FusedParams &p, size_t lds, hipStream_t stream)
 {
-    auto kern = &decode_linear_kernel<NORM, NS, DEPTH, IDENT>;
+    auto kern = &decode_linear_kernel<NORM, NS, DEPTH, IDENT, ONE>;
     static atom_launch::LdsOptIn opt_in;
     hipError_t err = atom_launch::ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(kern), lds);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(kern, dim3((unsigned)((p.N + TN - 1) / TN)), dim3(NT), lds, stream, p);
     return hipGetLastError();
+}
+
+template <bool NORM, int NS, int DEPTH>
+hipError_t launch_rows(const FusedParams &p, size_t lds, hipStream_t stream)
+{
+    if (p.idx) return p.M == 1 ? launch_cfg<NORM, NS, DEPTH, false, true>(p, lds, stream) : launch_cfg<NORM, NS, DEPTH, false, false>(p, lds, stream);
+    return p.M == 1 ? launch_cfg<NORM, NS, DEPTH, true, true>(p, lds, stream) : launch_cfg<NORM, NS, DEPTH, true, false>(p, lds, stream);
 }
 
 template <bool NORM, int NS>
@@ -207,8 +218,7 @@ hipError_t launch_depth(const FusedParams &p, size_t lds, hipStream_t stream)
     const bool blocks4 = G % 2 == 0 && G >= 4;
     const int nblk = blocks4 ? (G + 3) >> 2 : G;
     const int run = (blocks4 ? 4 : 1) * ((nblk + NW - 1) / NW);
-    if (p.idx) return run <= 4 ? launch_cfg<NORM, NS, 4, false>(p, lds, stream) : launch_cfg<NORM, NS, 8, false>(p, lds, stream);
-    return run <= 4 ? launch_cfg<NORM, NS, 4, true>(p, lds, stream) : launch_cfg<NORM, NS, 8, true>(p, lds, stream);
+    return run <= 4 ? launch_rows<NORM, NS, 4>(p, lds, stream) : launch_rows<NORM, NS, 8>(p, lds, stream);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -382,10 +392,11 @@ size_t decode_linear_lds_bytes(int M, int K, int O, bool norm, bool ident)
 }
 
 // Two launches cost 7.5 to 9.3 us, most of it the host's, whatever the rows up to the time of the weight stream; the kernel above repeats
-// the front end of every row in every workgroup.  us, one launch and two: K = N = 4096: 1 row 6.1, 9.3; 2 7.6, 9.2; 3 9.1, 9.0; 8 15.8, 9.2;
+// the front end of every row in every workgroup.  us, one launch and two: K = N = 4096: 1 row 5.1, 9.3; 2 7.4, 9.2; 3 9.1, 9.0; 8 15.8, 9.2;
 // 16 26.3, 9.3; N = 11008: 1 11.7, 9.3; 8 31.5, 9.4; K = 11008, N = 4096: 1 13.9, 11.5; 8 35.6, 12.0; K = 1024, N = 1000: 4 8.1, 9.4; 8
-// 11.8, 9.3; K = 8192, N = 28672: 1 61.2, 27.5; 16 274, 37.9.  The line is a product of rows, channels and (beyond 8192, where the
-// workgroups come in a second round: K = 2048, 2 rows, N = 8192: 7.8 and 9.3, 1 row, N = 22016: 15.1 and 9.2) outputs.  Without a norm a row costs little more than half as much (K = N = 4096: 3 rows 7.4, 4 8.2,
+// 11.8, 9.3; K = 8192, N = 28672: 1 61.2, 27.5; 16 274, 37.9.  The line is a product of rows, channels and outputs: up to 4096 and 8192
+// of them (one and two workgroups on a CU; K = 4096, 2 rows, N = 8192: 10.4 and 9.2; K = 2048: 8.6 and 9.2) by the step, beyond, where the
+// workgroups come in a second round, by their number (K = 2048, 1 row, N = 22016: 15.1 and 9.2).  Without a norm a row costs little more than half as much (K = N = 4096: 3 rows 7.4, 4 8.2,
 // 5 9.1, 8 11.5; K = 2048: 6 8.3), which counts where the rows are what is long.  More than 4096 channels and more than 4096 outputs: the
 // workgroups of two register sets come one to a CU and in two rounds (K = N = 5120, 1 row: 15.4 with a norm, 13.3 without; two launches 7.6
 // to 9.1; with K or N 4096 7.2 to 8.4).
@@ -394,8 +405,8 @@ bool decode_linear_splits(int M, int64_t N, int K, int O, bool norm)
     // (the two launches address the weights with 32-bit offsets)
     if (M > 16 || (uint64_t)N * (uint64_t)(K - O) / 2 >= 1ull << 32 || (uint64_t)N * (uint64_t)O >= 1ull << 32) return false;
     if (K > 4096 && N > 4096) return true;
-    const double row = !norm && K <= 5120 && N <= 5120 ? 0.5 : 1.0;
-    return row * (double)M * (double)(K + 2048) * (double)(N > 8192 ? N : 5120) > 66.5e6;
+    const double row = !norm && K <= 5120 && N <= 8192 ? 0.5 : 1.0;
+    return row * (double)M * (double)(K + 2048) * (double)(N > 8192 ? N : N > 4096 ? 7400 : 5120) > 66.5e6;
 }
 
 hipError_t launch_decode_linear(const void *x, int M, int64_t ldx, const void *gamma, float eps,

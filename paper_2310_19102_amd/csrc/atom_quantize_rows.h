@@ -216,6 +216,9 @@ struct NoHook { __device__ __forceinline__ void operator()() const {} };
 
 // after_first_fetch is called once, right after the global loads of the first row are issued (a
 // caller with loads of its own that may take longer to return issues them there).
+// ONE: the row row_first only, without a loop.  In a loop the wait for a row's values is the same
+// instruction for every row, and behind the fetch of a next row it is a wait for all loads: a
+// caller's own, too, which are meant to fly while the row is quantised.
 // PACKED: the codes and scales do not go to the canonical arrays but straight into the unit images
 // the packed GEMM reads (units of 64 rows; per unit one image per group: INT4 codes as FP6 E3M2 in
 // three 16-byte chunks per row and half at 2048 c + 1024 h + 16 r, scales as 8-byte entries at
@@ -247,7 +250,8 @@ constexpr int kImg4 = 6656, kImg8 = 8704, kSc4 = 6144, kSc8 = 8192;
 // step-major arrays instead: q4 [K4/128][rows][64], q8 [O/64][rows][64], scale as bytes [K/128][rows][4].  The hardware
 // converts two values at a time, divided by the block's power of two, to the nearest, ties to even (13 vector
 // instructions per lane and group, where comparing with every boundary took 120: 4096 x 8192 with RMSNorm 48 -> 26.5 us).
-template <bool NORM, int NS, int NT, int PRE, bool IDENT = false, bool PACKED = false, class Hook = NoHook, bool MX = false>
+template <bool NORM, int NS, int NT, int PRE, bool IDENT = false, bool PACKED = false, class Hook = NoHook, bool MX = false,
+          bool ONE = false>
 __device__ __forceinline__
 void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
                              const __half *x, int64_t rows, int64_t ld,
@@ -391,7 +395,7 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
             }
         }
         // the next row's loads fly while this one is quantised
-        if (row + row_step < rows) fetch_row(row + row_step);
+        if (!ONE && row + row_step < rows) fetch_row(row + row_step);
         if (!IDENT) __syncthreads();
 
         // ---- 3./4. reorder, group amax, scale, quantise, pack ----------------
@@ -563,6 +567,7 @@ void quantize_rows_fast_body(float *lds, int64_t row_first, int64_t row_step,
             }
             if (IDENT && !NORM) __syncthreads();     // (no other barrier stands before the next row's writes to pk_lds)
         }
+        if constexpr (ONE) break;
     }
 }
 
