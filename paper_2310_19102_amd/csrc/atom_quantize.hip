@@ -179,7 +179,7 @@ void quantize_rows_kernel(const __half *x, int64_t rows, int64_t ld,
 }
 
 
-template <bool NORM, int NS, int NT, int PRE, bool IDENT, bool MX>
+template <bool NORM, int NS, int NT, int PRE, bool IDENT, bool MX, bool ONE>
 __global__ __launch_bounds__(NT, min_waves(NORM, NS, NT, PRE, IDENT, false, MX))
 void quantize_rows_fast_kernel(const __half *x, int64_t rows, int64_t ld,
                                const __half *res, int64_t ldr, __half *sum_out, int64_t ldo,
@@ -189,7 +189,7 @@ void quantize_rows_fast_kernel(const __half *x, int64_t rows, int64_t ld,
                                __half *__restrict__ scale)
 {
     extern __shared__ __align__(16) float lds[];
-    quantize_rows_fast_body<NORM, NS, NT, PRE, IDENT, false, NoHook, MX>(lds, blockIdx.x, gridDim.x, x, rows, ld, res, ldr, sum_out, ldo,
+    quantize_rows_fast_body<NORM, NS, NT, PRE, IDENT, false, NoHook, MX, ONE>(lds, blockIdx.x, gridDim.x, x, rows, ld, res, ldr, sum_out, ldo,
                                                gamma, eps, idx, K, O, nbits, clip, q4, q8, scale);
 }
 
@@ -226,10 +226,6 @@ struct QuantArgs {
 template <bool NORM, int NS, int NT, int PRE, bool IDENT = false, bool MX = false>
 hipError_t launch_fast(const QuantArgs &a, size_t lds, hipStream_t stream)
 {
-    auto kern = &quantize_rows_fast_kernel<NORM, NS, NT, PRE, IDENT, MX>;
-    static atom_launch::LdsOptIn opt_in;   // the opt-in for more than 64 KB of dynamic LDS
-    hipError_t err = atom_launch::ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(kern), lds);
-    if (err != hipSuccess) return err;
     // workgroups resident per CU (LDS- and wave-limited), then rows dealt evenly over one
     // wave of them
     const int cus = atom_launch::compute_units();
@@ -239,6 +235,12 @@ hipError_t launch_fast(const QuantArgs &a, size_t lds, hipStream_t stream)
     const int64_t slots = (int64_t)cus * per_cu;
     const int64_t rows_per_wg = (a.rows + slots - 1) / slots;
     const int64_t grid = (a.rows + rows_per_wg - 1) / rows_per_wg;
+    const bool one = one_row_pays(NORM, NS, NT, IDENT) && rows_per_wg == 1;
+    auto kern = one ? &quantize_rows_fast_kernel<NORM, NS, NT, PRE, IDENT, MX, one_row_pays(NORM, NS, NT, IDENT)>
+                    : &quantize_rows_fast_kernel<NORM, NS, NT, PRE, IDENT, MX, false>;
+    static atom_launch::LdsOptIn opt_in[2];   // the opt-in for more than 64 KB of dynamic LDS
+    hipError_t err = atom_launch::ensure_dynamic_lds(opt_in[one], reinterpret_cast<const void *>(kern), lds);
+    if (err != hipSuccess) return err;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), lds, stream, (const __half *)a.x,
                        a.rows, a.ld, (const __half *)a.res, a.ldr, (__half *)a.sum_out, a.ldo,
                        (const __half *)a.gamma, a.eps, a.idx, a.K, a.O, a.nbits, a.clip, (uint8_t *)a.q4,

@@ -18,7 +18,7 @@ namespace {
 
 using namespace atom_quantize_rows;
 
-template <bool NORM, int NS, int NT, int PRE, bool IDENT>
+template <bool NORM, int NS, int NT, int PRE, bool IDENT, bool ONE>
 __global__ __launch_bounds__(NT, min_waves(NORM, NS, NT, PRE, IDENT, true, false))
 void quantize_rows_packed_kernel(const __half *x, int64_t rows, int64_t ld, const __half *res, int64_t ldr,
                                  __half *sum_out, int64_t ldo, const __half *__restrict__ gamma, float eps,
@@ -34,7 +34,7 @@ void quantize_rows_packed_kernel(const __half *x, int64_t rows, int64_t ld, cons
     const int per = nb >> 3, rem = nb & 7, xcd = b & 7;
     const int64_t logical = xcd * per + (xcd < rem ? xcd : rem) + (b >> 3);
     const int64_t first = logical * rpw, last = first + rpw < rows ? first + rpw : rows;
-    quantize_rows_fast_body<NORM, NS, NT, PRE, IDENT, true>(lds, first, 1, x, last, ld, res, ldr, sum_out,
+    quantize_rows_fast_body<NORM, NS, NT, PRE, IDENT, true, NoHook, false, ONE>(lds, first, 1, x, last, ld, res, ldr, sum_out,
                                                             ldo, gamma, eps, idx, K, O, nbits, clip, nullptr, nullptr,
                                                             nullptr, NoHook(), pk_out, pk_lds);
     // rows past the end of the matrix, up to the end of the last unit: zero codes, zero scales; dealt over all
@@ -77,12 +77,8 @@ struct PackedArgs {
 template <bool NORM, int NS, int NT, int PRE, bool IDENT>
 hipError_t launch_cfg(const PackedArgs &a, hipStream_t stream)
 {
-    auto kern = &quantize_rows_packed_kernel<NORM, NS, NT, PRE, IDENT>;
     const size_t front = sizeof(float) * (size_t)((IDENT ? 0 : a.K) + (NORM ? a.K / 8 : 0));
     const size_t lds = front + 3 * (size_t)((a.K - a.O) / 4) + (size_t)a.O;
-    static atom_launch::LdsOptIn opt_in;
-    hipError_t err = atom_launch::ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(kern), lds);
-    if (err != hipSuccess) return err;
     const int cus = atom_launch::compute_units();
     int64_t per_cu = (int64_t)(160 * 1024) / (int64_t)(lds > 0 ? lds : 1);
     const int64_t by_waves = 2048 / NT;
@@ -90,6 +86,12 @@ hipError_t launch_cfg(const PackedArgs &a, hipStream_t stream)
     const int64_t slots = (int64_t)cus * per_cu;
     const int64_t rows_per_wg = (a.rows + slots - 1) / slots;
     const int64_t grid = (a.rows + rows_per_wg - 1) / rows_per_wg;
+    const bool one = one_row_pays(NORM, NS, NT, IDENT) && rows_per_wg == 1;
+    auto kern = one ? &quantize_rows_packed_kernel<NORM, NS, NT, PRE, IDENT, one_row_pays(NORM, NS, NT, IDENT)>
+                    : &quantize_rows_packed_kernel<NORM, NS, NT, PRE, IDENT, false>;
+    static atom_launch::LdsOptIn opt_in[2];
+    hipError_t err = atom_launch::ensure_dynamic_lds(opt_in[one], reinterpret_cast<const void *>(kern), lds);
+    if (err != hipSuccess) return err;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), lds, stream, (const __half *)a.x, a.rows, a.ld,
                        (const __half *)a.res, a.ldr, (__half *)a.sum_out, a.ldo, (const __half *)a.gamma, a.eps, a.idx,
                        a.K, a.O, a.nbits, a.clip, (uint8_t *)a.out, (unsigned)front, (int)((a.rows + grid - 1) / grid));
