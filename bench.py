@@ -69,6 +69,7 @@ class DeviceLinear:
         self.name, self.M, self.K, self.N = lin.name, lin.M, lin.K, lin.N
         self.G = lin.K // lin.group_size
         self.lin = lin
+        self.workspace = None              # of atom_w4a4_gemm: the caller's own, or what the call takes
         self.packed = (lin.M > 64 and not streams_weights(lin)) if packed is None else packed
         # packed path: the front end can write the tiled activations itself (one launch less, no
         # canonical arrays).  As kernel time it is 5-10 % behind front end + re-tiling pass (its 16-byte
@@ -123,7 +124,7 @@ class DeviceLinear:
             return
         qw = self.qw_ring[self.turn % len(self.qw_ring)]
         self.turn += 1
-        atom.atom_w4a4_gemm(*self.qa, *qw, self.lin.group_size, out=self.y)
+        atom.atom_w4a4_gemm(*self.qa, *qw, self.lin.group_size, out=self.y, workspace=self.workspace)
 
     def gemm_tiled(self):
         """Decode-sized GEMM on weight codes re-tiled into whole lines per load (M <= 64)."""
@@ -413,8 +414,10 @@ def extra_measurements(headline_config):
                     "gemm_us_in_graph_warm_weights": tgemm * 1e6})
         del L
         torch.cuda.empty_cache()
-    # the canonical INT8-MFMA kernel on the Llama-7B gate/up shape, for comparison with the packed one
+    # the canonical INT8-MFMA kernel on the Llama-7B gate/up shape, for comparison with the packed one (a workspace too small to
+    # pack the operands into: without one of the caller's they are packed on the way)
     L = DeviceLinear(synth.make(4, 0), packed=False)
+    L.workspace = torch.empty(16, dtype=torch.uint8, device="cuda")
     t, ge, fe, pk, _ = run_steps([L], 50, 10, 0.1)
     out.append({"workload": "config4 mlp_gate_up M=1024 K=4096 N=22016, canonical weights (INT8 MFMA kernel)",
                 "gemm_us": ge * 1e6, "gemm_tops": L.ops / ge / 1e12,
