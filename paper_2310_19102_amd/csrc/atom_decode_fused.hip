@@ -246,7 +246,9 @@ hipError_t launch_depth(const FusedParams &p, size_t lds, hipStream_t stream)
 // about as long as the gap between two launches in a stream, so inside a HIP graph the kernel
 // ties with the two launches (and loses where N / 16 workgroups need a second round, which can
 // only start when the first, waiting, round is through); called eagerly, where the host's launch
-// cost sets the pace, one launch is what counts.
+// cost sets the pace, one launch is what counts.  Producers done earlier are not always a gain: with all loads of their row in flight
+// N = 4096 is 4 to 6 % faster (K = 5120, 8 rows: 9.6 -> 9.2 us), but 5120 and 8192 channels on 11008 outputs and more, three consumers to
+// a CU, 3 to 4 % slower (12 rows: 13.2 -> 13.7): the codes are fetched in the middle of the weights.
 // ------------------------------------------------------------------------------------------
 constexpr uint32_t kSpinLimit = 1u << 18;
 constexpr int kBuckets = 32;

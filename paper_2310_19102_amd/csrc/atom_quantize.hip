@@ -293,6 +293,7 @@ hipError_t dispatch_quantize(const QuantArgs &a, hipStream_t stream)
     // to bring to a barrier.  8 rows, times with the threads of many rows and with twice as many: RMSNorm 3.6 / 3.4 us
     // (K = 4096), 4.3 / 4.2 (8192), 5.3 / 5.4 (11008), 6.6 / 6.0 (16384); without a norm 2.9 / 2.7, 3.4 / 3.3, 4.1 / 4.1, 4.7 / 4.5;
     // SwiGLU 3.6 / 3.2, 4.4 / 4.0, 5.6 / 5.2, 7.0 / 6.1; MX 3.4 / 3.2, 4.1 / 3.9, 5.1 / 5.0, 6.1 / 5.4.  At 512 rows and more it is up to a third slower.
+    // 4097 to 5120 channels: 640 threads, one vector each at 5120 (8 rows, RMSNorm: 1024 threads 3.9, 640 3.4).
     const bool few = a.rows <= atom_launch::compute_units();
     const bool sane_clip = a.clip >= 9.5367431640625e-07f && a.clip <= 1.0f && a.gs == 128;   // what the fast kernels take
     if (!a.idx && a.K <= 32768 && sane_clip) {
