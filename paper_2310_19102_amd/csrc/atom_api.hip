@@ -241,7 +241,7 @@ size_t atom_decode_linear_lds_bytes(int64_t M, const atom_desc *d, int with_norm
 int atom_decode_linear_wants_codes(int64_t M, int64_t N, const atom_desc *d, int with_norm)
 {
     if (check_desc(d) != ATOM_OK || M <= 0 || N <= 0) return 0;
-    return atom_internal::decode_linear_splits((int)(M < 17 ? M : 17), N, d->K, d->n_outlier, with_norm != 0);
+    return atom_internal::decode_linear_splits((int)(M < 17 ? M : 17), N, d->K, d->n_outlier, with_norm != 0, 0);
 }
 
 atom_status atom_decode_linear(const void *x_f16, int64_t M, int64_t ldx, const void *gamma_f16,
@@ -264,8 +264,9 @@ atom_status atom_decode_linear(const void *x_f16, int64_t M, int64_t ldx, const 
         !aligned(w_q4, 16) || !aligned(w_q8, 16) || !aligned(w_scale, 2) || !aligned(y_f16, 2) ||
         (ndbg && (!aligned(dbg_q4, 4) || !aligned(dbg_q8, 4) || !aligned(dbg_scale, 2))))
         return ATOM_ERR_ALIGN;
+    const uintptr_t scales = reinterpret_cast<uintptr_t>(w_scale) | reinterpret_cast<uintptr_t>(dbg_scale);
     if (ndbg && aligned(dbg_q4, 16) && aligned(dbg_q8, 16) &&
-        atom_internal::decode_linear_splits((int)M, N, d->K, d->n_outlier, gamma_f16 != nullptr)) {
+        atom_internal::decode_linear_splits((int)M, N, d->K, d->n_outlier, gamma_f16 != nullptr, scales)) {
         hipError_t e2 = atom_internal::launch_quantize_rows(x_f16, M, ldx, 0, nullptr, 0, nullptr, 0, gamma_f16, eps, reorder_idx,
                                                             d->K, d->n_outlier, d->bits_normal, clip, dbg_q4, dbg_q8, dbg_scale,
                                                             static_cast<hipStream_t>(stream));

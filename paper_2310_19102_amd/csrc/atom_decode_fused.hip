@@ -402,8 +402,12 @@ size_t decode_linear_lds_bytes(int M, int K, int O, bool norm, bool ident)
 // 5 9.1, 8 11.5; K = 2048: 6 8.3), which counts where the rows are what is long.  More than 4096 channels and more than 4096 outputs: the
 // workgroups of two register sets come one to a CU and in two rounds (K = N = 5120, 1 row: 15.4 with a norm, 13.3 without; two launches 7.6
 // to 9.1; with K or N 4096 7.2 to 8.4).
-bool decode_linear_splits(int M, int64_t N, int K, int O, bool norm)
+bool decode_linear_splits(int M, int64_t N, int K, int O, bool norm, uintptr_t scales)
 {
+    // Y has the same bits either way only where both sum the groups in the same runs.  The kernel above takes blocks of four groups for
+    // an even number of them from 4 on, the GEMM also asks for both scale arrays on 4-byte boundaries.
+    const int G = K >> 7;
+    if (G % 2 == 0 && G >= 4 && (scales & 3)) return false;
     // (the two launches address the weights with 32-bit offsets)
     if (M > 16 || (uint64_t)N * (uint64_t)(K - O) / 2 >= 1ull << 32 || (uint64_t)N * (uint64_t)O >= 1ull << 32) return false;
     if (K > 4096 && N > 4096) return true;

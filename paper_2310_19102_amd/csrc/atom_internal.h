@@ -77,8 +77,9 @@ hipError_t launch_permute_rows(const void *in, int64_t rows_in, int64_t rows_out
 // One-launch decode linear (atom_decode_fused.hip): front end in the prologue of the
 // weight-streaming GEMM, M <= 16.
 size_t decode_linear_lds_bytes(int M, int K, int O, bool norm, bool ident);
-// whether front end and GEMM as two launches through arrays of codes are faster
-bool   decode_linear_splits(int M, int64_t N, int K, int O, bool norm);
+// whether front end and GEMM as two launches through arrays of codes are faster and give the same bits; scales: the addresses of both
+// scale arrays or'ed (their alignment counts)
+bool   decode_linear_splits(int M, int64_t N, int K, int O, bool norm, uintptr_t scales);
 hipError_t launch_decode_linear(const void *x, int M, int64_t ldx, const void *gamma, float eps,
                                 const int32_t *idx, int K, int O, int nbits, float clip,
                                 const void *w_q4, const void *w_q8, const void *w_scale, int64_t N,

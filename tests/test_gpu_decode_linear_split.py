@@ -64,3 +64,42 @@ def test_refused_as_before():
             atom.atom_decode_linear(x, gamma, 1e-5, idx, *w, **bad)
     with pytest.raises(atom.AtomError):
         atom.atom_decode_linear(torch.cat([x, x]), gamma, 1e-5, idx, *w)
+
+
+@pytest.mark.parametrize("M,K,N,O,bits", [
+    (8, 4096, 11008, 128, 4), (8, 5376, 8200, 128, 4),       # a multiple of four groups, two groups left over
+    (12, 4224, 5000, 128, 4), (12, 4096, 8192, 256, 4),      # an odd number of groups, two INT8 groups
+    (16, 512, 16400, 128, 4), (16, 384, 16400, 128, 4),      # fewer than eight groups
+    (16, 256, 30000, 128, 4), (9, 4096, 8192, 128, 3)])      # one INT4 group, W3A3
+def test_scales_off_the_grid_keep_the_bits(M, K, N, O, bits):
+    """Y of a call that gives arrays for the codes is Y of the one launch, also where one of the scale arrays stands on an odd half-word."""
+    from paper_2310_19102_amd.binding import _desc
+    print(f"[case] decode linear, scales off the grid M={M} K={K} N={N} O={O} bits={bits}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + K + N)
+    idx = torch.randperm(K, generator=g, device="cuda").to(torch.int32)
+    x = torch.randn((M, K), generator=g, device="cuda").half()
+    gamma = (1 + 0.1 * torch.randn(K, generator=g, device="cuda")).half()
+    w = list(atom.atom_quantize_weight(torch.randn((N, K), generator=g, device="cuda").half() * 0.02, idx, 128, O, bits=bits))
+    L, d, P = atom.load_library(), _desc(K, 128, O, bits), lambda t: ctypes.c_void_p(t.data_ptr())
+
+    def off(t, by):                                          # the same numbers `by` bytes past a 256-byte boundary
+        b = torch.empty(t.numel() + 4, dtype=t.dtype, device="cuda")[by // t.element_size():][:t.numel()].view(t.shape)
+        return b.copy_(t)
+
+    def call(scale, codes):
+        y = torch.zeros((M, N), dtype=torch.float16, device="cuda")
+        rc = L.atom_decode_linear(P(x), M, K, P(gamma), ctypes.c_float(1e-5), P(idx), ctypes.byref(d), ctypes.c_float(0.9), P(w[0]), P(w[1]),
+                                  P(scale), N, P(y), N, *(map(P, codes) if codes else (None, None, None)),
+                                  ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rc == 0
+        return y
+
+    want = call(w[2], None)
+    for by in (0, 2, 4):
+        scale = off(w[2], by)
+        assert torch.equal(call(scale, None), want)
+        codes = [torch.empty((M, n), dtype=t, device="cuda") for n, t in (((K - O) // 2, torch.uint8), (O, torch.int8), (K // 128, torch.half))]
+        assert torch.equal(call(scale, codes), want), f"weight scales {by} bytes off"
+        codes[2] = off(codes[2], by)
+        assert torch.equal(call(w[2], codes), want), f"activation scales {by} bytes off"
+    assert torch.equal(atom.atom_decode_linear(x, gamma, 1e-5, idx, *w, bits=bits), want)
