@@ -401,7 +401,13 @@ size_t decode_linear_lds_bytes(int M, int K, int O, bool norm, bool ident)
 // workgroups come in a second round, by their number (K = 2048, 1 row, N = 22016: 15.1 and 9.2).  Without a norm a row costs little more than half as much (K = N = 4096: 3 rows 7.4, 4 8.2,
 // 5 9.1, 8 11.5; K = 2048: 6 8.3), which counts where the rows are what is long.  More than 4096 channels and more than 4096 outputs: the
 // workgroups of two register sets come one to a CU and in two rounds (K = N = 5120, 1 row: 15.4 with a norm, 13.3 without; two launches 7.6
-// to 9.1; with K or N 4096 7.2 to 8.4).
+// to 9.1; with K or N 4096 7.2 to 8.4).  (Those two are eager; inside a graph, where the second launch is cheap, two are ahead by more: K = N = 4096, 3
+// rows 9.7 in one and 7.2 in two; 1 row on 11008 outputs 10.5 and 9.7.)
+// Outside the common case (odd K / 128, fewer than 8 groups, more than one INT8 group, scales off their boundaries) the second launch is the
+// general decode GEMM, 1.3 to 1.9 times as slow as those of the common case, and only rows count.  In a graph, one launch and two: K = 1152, N = 8192,
+// with a norm: 4 rows 10.2, 12.0; 5 11.4, 12.2; 6 12.6, 12.3; 8 14.9, 12.5; without: 8 11.1, 12.4; 10 12.3, 12.4; 12 13.6, 12.5; K = 8320, N = 11008, 1 row: 28.6,
+// 34.3; K = 4096, two INT8 groups, N = 11008, 1 row 11.4, 16.6.  Two launches are ahead at all of 98 sizes (K 256 to 11264, N 512 to 28672) from 6 rows on with
+// a norm and from 11 without.
 bool decode_linear_splits(int M, int64_t N, int K, int O, bool norm, uintptr_t scales)
 {
     // Y has the same bits either way only where both sum the groups in the same runs.  The kernel above takes blocks of four groups for
@@ -410,9 +416,14 @@ bool decode_linear_splits(int M, int64_t N, int K, int O, bool norm, uintptr_t s
     if (G % 2 == 0 && G >= 4 && (scales & 3)) return false;
     // (the two launches address the weights with 32-bit offsets)
     if (M > 16 || (uint64_t)N * (uint64_t)(K - O) / 2 >= 1ull << 32 || (uint64_t)N * (uint64_t)O >= 1ull << 32) return false;
-    if (K > 4096 && N > 4096) return true;
-    const double row = !norm && K <= 5120 && N <= 8192 ? 0.5 : 1.0;
-    return row * (double)M * (double)(K + 2048) * (double)(N > 8192 ? N : N > 4096 ? 7400 : 5120) > 66.5e6;
+    GemmParams g{};
+    g.a_scale = g.w_scale = reinterpret_cast<const uint16_t *>(scales);
+    g.M = M; g.N = N; g.K = K; g.O = O;
+    const bool common = common_tail(g) != 0;
+    if (!common && M < (norm ? 6 : 11)) return false;
+    if (common && K > 4096 && N > 4096) return true;
+    const double work = (double)M * (double)(K + 2048) * (double)(N > 8192 ? N : N > 4096 ? 7400 : 5120);
+    return (!norm && K <= 5120 && N <= 8192 ? 0.5 : 1.0) * work > 66.5e6;
 }
 
 hipError_t launch_decode_linear(const void *x, int M, int64_t ldx, const void *gamma, float eps,

@@ -235,3 +235,13 @@ def test_cooperative_decode_linear_argument_validation():
     assert call(d=D(4096, 128, 256, 4, 8)) == 3                  # two INT8 groups
     assert call(d=D(16384, 128, 128, 4, 8), ldx=16384) == 3      # K beyond the front end of one workgroup
     assert call(d=D(4096, 64, 128, 4, 8)) == 3                   # group size
+
+
+@pytest.mark.parametrize("K,O,N", [(4224, 128, 8192), (8320, 128, 11008), (4096, 256, 11008), (640, 128, 8192), (384, 128, 28672)])
+def test_decode_linear_wants_codes_beyond_the_common_case(K, O, N):
+    """An odd number of groups, fewer than eight, two INT8 groups: the second launch would be the general decode GEMM, which pays from 6 rows
+    on with a norm and from 11 without."""
+    d = binding._desc(K, 128, O)
+    wants = lambda M, norm: bool(atom.load_library().atom_decode_linear_wants_codes(M, N, ctypes.byref(d), norm))
+    assert [wants(M, 1) for M in range(1, 18)] == [6 <= M <= 16 for M in range(1, 18)]
+    assert [wants(M, 0) for M in range(1, 18)] == [11 <= M <= 16 for M in range(1, 18)]
