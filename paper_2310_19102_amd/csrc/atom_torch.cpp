@@ -338,8 +338,11 @@ PyObject *w4a4_gemm(Args a)
         } catch (const c10::OutOfMemoryError &) {
         }
     }
+    // packed operands go only where all the bytes that the tensor counts are its own and the device's (a workspace is never required, and
+    // any tensor is taken for one)
+    const bool usable = w && w->device() == a4.device() && w->is_contiguous();
     ATOM_CALL(atom_w4a4_gemm, data(a4), data(a8), data(as), M, data(w4), data(w8), data(ws), N, &d, y.data(),
-              ld(*y.t, M, N), partials, w ? data(*w) : nullptr, w ? bytes(*w) : 0);
+              ld(*y.t, M, N), partials, usable ? data(*w) : nullptr, usable ? bytes(*w) : 0);
     return y.give();
 }
 

@@ -46,6 +46,21 @@ def test_bits_of_the_packed_product(M, N, K):
     assert torch.equal(atom.atom_w4a4_gemm(*qa, *qw, workspace=aligned), want)
 
 
+def test_workspaces_that_cannot_be_written():
+    """A tensor on the host, or one that counts more bytes than it has, is no room: the call goes without, as if it were too small."""
+    M, N, K = 777, 3001, 4224
+    qa, qw = _operands(M, N, K)
+    need = atom.atom_w4a4_gemm_scratch_bytes(M, N, K)
+    direct = atom.atom_w4a4_gemm(*qa, *qw, workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
+    host = torch.full((need + 256,), 0x5A, dtype=torch.uint8)
+    host = host[-host.data_ptr() % 256:]
+    for ws in (host, torch.empty(1, dtype=torch.uint8, device="cuda").expand(need), torch.empty(2 * need, dtype=torch.uint8, device="cuda")[::2]):
+        assert ws.numel() >= need and ws.data_ptr() % 256 == 0
+        assert torch.equal(atom.atom_w4a4_gemm(*qa, *qw, workspace=ws), direct)
+    torch.cuda.synchronize()
+    assert bool((host == 0x5A).all())
+
+
 def test_calls_that_keep_their_kernels():
     M, N, K = 512, 4096, 4096
     assert atom.atom_w4a4_gemm_scratch_bytes(M, N, K) > 0
