@@ -385,8 +385,11 @@ PyObject *decode_linear(Args a)
     } else if (atom_decode_linear_wants_codes(M, N, &d, gamma != nullptr)) {   // one array for the three, each from a 256-byte boundary
         const auto up = [](int64_t n) { return (n + 255) / 256 * 256; };
         const int64_t n4 = up(M * (K - O) / 2), n8 = up(M * O);
-        own = make({n4 + n8 + M * groups(K, gs) * 2}, kByte, x);
-        c4 = data(own); c8 = (char *)c4 + n4; cs = (char *)c8 + n8;
+        try {
+            own = make({n4 + n8 + M * groups(K, gs) * 2}, kByte, x);
+            c4 = data(own); c8 = (char *)c4 + n4; cs = (char *)c8 + n8;
+        } catch (const c10::OutOfMemoryError &) {       // one launch then, the same bits
+        }
     }
     ATOM_CALL(atom_decode_linear, data(x), M, ld(x, M, K), gamma, eps, (const int32_t *)idx, &d, clip, data(w4),
               data(w8), data(ws), N, y.data(), ld(*y.t, M, N), c4, c8, cs);

@@ -103,3 +103,23 @@ def test_scales_off_the_grid_keep_the_bits(M, K, N, O, bits):
         codes[2] = off(codes[2], by)
         assert torch.equal(call(w[2], codes), want), f"activation scales {by} bytes off"
     assert torch.equal(atom.atom_decode_linear(x, gamma, 1e-5, idx, *w, bits=bits), want)
+
+
+def test_no_memory_for_the_codes():
+    """A call with an output of the caller's needs no memory: where the allocator has none for the codes it is one launch, the same bits."""
+    M, K, N = 8, 4096, 4096
+    assert _wants(M, N, K)
+    x, gamma, idx, w, _, want = _case(M, K, N, True)
+    y = torch.zeros((M, N), dtype=torch.float16, device="cuda")
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    try:
+        torch.cuda.set_per_process_memory_fraction(1e-6)
+        with pytest.raises(torch.OutOfMemoryError):
+            while True:                                      # what the allocator still has of its small blocks
+                held.append(torch.empty(16384, dtype=torch.uint8, device="cuda"))
+        atom.atom_decode_linear(x, gamma, 1e-5, idx, *w, out=y)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(y, want)
