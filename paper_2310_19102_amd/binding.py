@@ -386,8 +386,18 @@ def atom_w4a4_gemm(a_q4, a_q8, a_scale, w_q4, w_q8, w_scale, group_size: int = 1
                    workspace: Optional[torch.Tensor] = None):
     """Y[M, N] fp16 = group-dequantised product of quantised activations and
     weights.  ``partials`` (int32 [M, N, G]) also receives every per-group
-    integer sum.  Without a ``workspace`` of the caller's, sizes that gain from it
-    take ``atom_w4a4_gemm_scratch_bytes`` of scratch for the call."""
+    integer sum.
+
+    Sizes that gain from it pack both operands on the way, into
+    ``atom_w4a4_gemm_scratch_bytes`` (up to 1 GiB): the caller's ``workspace``,
+    or memory taken for the call where PyTorch's allocator has it without giving
+    back other blocks (under capture it stays in the graph's pool).  A
+    ``workspace`` smaller than that, an empty one included, is left alone and
+    keeps the call to the kernels for canonical operands, as does
+    ``partials``.  The packed product adds all groups in one ascending run, the
+    other kernels may split K: ``Y`` differs by fp32 rounding.  A caller who
+    needs the same bits whatever memory is free gives a workspace, of full size
+    or an empty one."""
     return _run().w4a4_gemm(a_q4, a_q8, a_scale, w_q4, w_q8, w_scale, group_size, out, partials, workspace)
 
 

@@ -11,6 +11,9 @@
 #include <Python.h>
 
 #include <ATen/hip/EmptyTensor.h>
+#include <ATen/hip/HIPContext.h>
+#include <c10/hip/HIPCachingAllocator.h>
+#include <c10/hip/HIPGraphsC10Utils.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -107,6 +110,28 @@ Tensor make(at::IntArrayRef shape, Kind k, const Tensor &like)
 }
 
 Tensor make(std::initializer_list<int64_t> shape, Kind k, const Tensor &like) { return make(at::IntArrayRef(shape), k, like); }
+
+// Whether the allocator is likely to have n bytes without giving back what it keeps.  A request that neither its free blocks nor the device
+// can serve makes it return every free block to the device, behind a synchronisation, before it raises: too much for memory that a call can do
+// without, and that asks again with every call.  (Under capture it returns nothing, and the device is not asked.)
+bool has_room(int64_t n, c10::DeviceIndex device)
+{
+    namespace allocator = c10::hip::HIPCachingAllocator;
+    if (c10::hip::currentStreamCaptureStatusMayInitCtx() != c10::hip::CaptureStatus::None) return true;
+    size_t largest = 1;                                                // (0: the device's free memory counts as well)
+    allocator::cacheInfo(device, &largest);
+    if (largest >= (size_t)n) return true;
+    const double with = (double)n + (double)(20 << 20);               // (what it takes from the device is rounded up, to 20 MB at least)
+    const double fraction = allocator::getMemoryFraction(device);
+    if (fraction < 1.0) {
+        const auto stats = allocator::getDeviceStats(device);
+        const auto &reserved = stats.reserved_bytes[static_cast<size_t>(c10::CachingAllocator::StatType::AGGREGATE)];
+        if ((double)reserved.current + with > fraction * (double)at::cuda::getDeviceProperties(device)->totalGlobalMem) return false;
+    }
+    largest = 0;
+    allocator::cacheInfo(device, &largest);
+    return (double)largest >= with;
+}
 
 // Row stride of a matrix with `cols` columns (a single row may report any stride).
 int64_t ld(const Tensor &t, int64_t rows, int64_t cols)
@@ -331,7 +356,7 @@ PyObject *w4a4_gemm(Args a)
     }
     // room to pack the operands on the way where that is faster; a call that finds none goes without
     const size_t room = need || w || partials ? 0 : atom_w4a4_gemm_scratch_bytes(M, N, &d);
-    if (room) {
+    if (room && has_room((int64_t)room, a4.device().index())) {
         try {
             own = make({(int64_t)room}, kByte, a4);
             w = &own;

@@ -90,6 +90,44 @@ def test_no_memory_for_the_packed_operands():
     assert torch.equal(y, direct)
 
 
+def test_scratch_is_not_taken_from_what_the_allocator_keeps():
+    """Near the limit of the memory the call goes without, before the allocator gives its free blocks back to look for more; where a free
+    block is large enough it is used."""
+    M, N, K = 777, 13824, 5120
+    need = atom.atom_w4a4_gemm_scratch_bytes(M, N, K)
+    assert need > 48 << 20
+    qa, qw = _operands(M, N, K)
+    y, tiny = torch.empty((M, N), dtype=torch.float16, device="cuda"), torch.empty(16, dtype=torch.uint8, device="cuda")
+    direct, packed = atom.atom_w4a4_gemm(*qa, *qw, workspace=tiny), _prepacked(qa, qw, M, N, K)
+    assert not torch.equal(direct, packed)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    torch.cuda.set_per_process_memory_fraction(1e-6)
+    with pytest.raises(torch.OutOfMemoryError):
+        while True:                                              # what is free in segments that are in use
+            held.append(torch.empty(need // 2, dtype=torch.uint8, device="cuda"))
+    torch.cuda.set_per_process_memory_fraction(1.0)
+    kept = [torch.empty(24 << 20, dtype=torch.uint8, device="cuda") for _ in range(8)]
+    del kept
+    total = torch.cuda.get_device_properties(0).total_memory
+
+    def call(spare):
+        before = torch.cuda.memory_stats()
+        try:
+            torch.cuda.set_per_process_memory_fraction((before["reserved_bytes.all.current"] + spare) / total)
+            atom.atom_w4a4_gemm(*qa, *qw, out=y)
+        finally:
+            torch.cuda.set_per_process_memory_fraction(1.0)
+        after = torch.cuda.memory_stats()
+        assert after["num_alloc_retries"] == before["num_alloc_retries"]
+        return after["reserved_bytes.all.current"] - before["reserved_bytes.all.current"]
+
+    assert call(16 << 20) == 0 and torch.equal(y, direct)
+    assert call(256 << 20) >= need and torch.equal(y, packed)
+    assert call(16 << 20) == 0 and torch.equal(y, packed)        # (the block of the call before)
+
+
 def test_captured_and_replayed():
     M, N, K = 300, 4096, 4096
     qa, qw = _operands(M, N, K)
