@@ -379,12 +379,15 @@ size_t gemm_workspace_bytes(int64_t, int64_t, int, int) { return 0; }
 
 // Beyond 256 rows the kernels above are bound by what they do to every code and every integer sum on the vector ALU; the product on packed
 // operands takes about 0.6 of their time, and packing both is one pass at the memory's rate.  So where a caller has room for the
-// packed operands, they are packed on the way whenever that is estimated to pay.  Estimates in us, fitted to 120 sizes; a round of
+// packed operands, they are packed on the way whenever that is estimated to pay.  Estimates in us; a round of
 // workgroups of the kernels above costs a constant and a time per channel of K:
 //   tiles of 64 rows in up to 128, 256 and 512 workgroups   3 + 0.0021 K, 3 + 0.0028 K, 4 + 0.0050 K (K split four, four and two ways)
-//   tiles of 256 x 128, from 512 on, one per compute unit   4 + 0.0097 K
+//   tiles of 256 x 128, from 512 on, one per compute unit   6.7 + 0.01047 K
 //   tiles of 128 x 128, two per compute unit                4 + 0.0112 K; at most one of them (the last round) 4 + 0.0058 K
 // and against them stand the product as its tiles are chosen (f6_product_us), 5 for one more launch, 5 TB/s for the codes read and written.
+// They are within 5 to 9 % of what is measured, so packing has to be ahead by 2.5 us: of 1445 sizes that
+// then pack (profiles/w4a4_gemm_packing_on_the_way.txt) 7 to 9 are slower, by up to 3 %.  With 1.5 us M = 900, K = 3072, N = 2048 was 18.7 -> 20.4 us, M = 3000,
+// K = N = 2048 29.0 -> 30.1.
 // Measured (GEMM alone, weights from memory; rows: kernels above, packed on the way): K = 5120, N = 13824: 257 62.6, 57.7; 777 103, 81.3;
 // 4096 406, 267; K = 11008, N = 4096: 257 55.9, 36.7; 1024 69.8, 59.0; 4096 247, 169; K = 4096, N = 4096: 1024 34.7, 29.8; 4096 103,
 // 76.3; K = 8192, N = 22016: 450 146, 132; 4096 993, 642.  Where the kernels above stay: K = 2048, N = 8192: 640 28.5, 29; K = 6400,
@@ -403,13 +406,13 @@ size_t gemm_scratch_bytes(int64_t M, int64_t N, int K, int O)
     if (t64 <= 512) {
         direct = t64 <= 128 ? 3.0f + 0.0021f * k : t64 <= 256 ? 3.0f + 0.0028f * k : 4.0f + 0.0050f * k;
     } else if (t256 >= 512) {
-        direct = (float)((t256 + cus - 1) / cus) * (4.0f + 0.0097f * k);
+        direct = (float)((t256 + cus - 1) / cus) * (6.7f + 0.01047f * k);
     } else {
         const int64_t last = t128 % (2 * cus);
         direct = (float)(t128 / (2 * cus) + (last > cus)) * (4.0f + 0.0112f * k) + (last > 0 && last <= cus ? 4.0f + 0.0058f * k : 0.0f);
     }
     const float packing = 5.0f + 1.34f * (float)(M + N) * k / 5.0e6f;
-    return direct > product + packing + 1.5f ? bytes : 0;
+    return direct > product + packing + 2.5f ? bytes : 0;
 }
 
 hipError_t launch_w4a4_gemm(const GemmArgs &a, hipStream_t stream)

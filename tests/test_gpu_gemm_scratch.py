@@ -66,6 +66,8 @@ def test_calls_that_keep_their_kernels():
     assert atom.atom_w4a4_gemm_scratch_bytes(M, N, K) > 0
     for none in (dict(M=256), dict(n_outlier=256), dict(group_size=64), dict(K=1000), dict(K=896), dict(N=0), dict(N=1 << 22)):
         assert atom.atom_w4a4_gemm_scratch_bytes(**{**dict(M=M, N=N, K=K), **none}) == 0, none
+    for size in ((900, 2048, 3072), (1024, 2048, 3072), (3000, 2048, 2048), (1200, 3072, 4096), (777, 1024, 6400)):   # packing costs what it gains
+        assert atom.atom_w4a4_gemm_scratch_bytes(*size) == 0, size
     qa, qw = _operands(M, N, K)
     part = torch.empty((M, N, K // 128), dtype=torch.int32, device="cuda")      # the dump of the sums takes no workspace
     y = atom.atom_w4a4_gemm(*qa, *qw, partials=part)
