@@ -128,7 +128,7 @@ __device__ __forceinline__ float half_of(const uint4 (&raw)[4], int i)
     return __half2float(__ushort_as_half((unsigned short)((i & 1) ? w >> 16 : w & 0xFFFFu)));
 }
 
-// 16 bytes of the cache.  ONCE: with the hint that nothing reads them again (launches of a large cache, see launch_decode_attention_kv4).
+// 16 bytes of the cache.  ONCE: with the hint that nothing reads them again (see attention_reads_once).
 template <bool ONCE>
 __device__ __forceinline__ uint4 load_row(const uint8_t *p)
 {
@@ -887,6 +887,27 @@ size_t decode_attention_workspace_bytes(int B, int H, int Hkv, int64_t Tmax)
     return S > 1 ? (size_t)B * H * S * (128 + 2) * sizeof(float) : 0;
 }
 
+// A cache that the last-level cache (256 MB) does not keep until the next step is read with the hint that nothing reads it
+// again: the memory then delivers 7.1 instead of 6.3 TB/s (a plain read of 400 MB and more).  Append and attention, lengths from T / 4 to
+// T, us, without and with the hint; in MB the codes of all Tmax rows: 32 heads, 64 x 2048 (537 MB) 77.8, 68.7; 128 x 2048 139.2,
+// 130.0; 90 x 1024 (377) 56.6, 54.1; 60 x 1024 (252) 42.1, 40.3; 40 x 1024 (168) 32.7, 31.9; 28 x 1024 (117) 28.6, 28.5;
+// 20 x 1024 (84) 23.1, 23.3; 40 heads, 8 x 10000 (410) 64.1, 60.6; 85 x 161 (70) 24.7, 25.3; 64 heads on 8, 128 x 2048 (268) 56.3, 54.2.
+// The line goes by capacity: how full the cache is, only the device knows.  Little filled (attention alone, 128 x 2048, 32 heads, 100 to 300
+// tokens, 105 MB): with four such caches in turn, as layers of a model, 34.8, 33.8; one and the same cache again and again, out of the
+// last-level cache, 32.2, 33.1.
+// Query heads that share a cache head outside the grouped-query kernel (more than 16 of them) read the same rows one after the other: no
+// hint (64 heads on 2, 64 x 8192: 435, with the hint 513; 32 on 1, 128 x 8192 373, 426).
+static bool attention_reads_once(int B, int H, int Hkv, int64_t Tmax, bool gqa)
+{
+    return (gqa || H == Hkv) && (int64_t)B * Hkv * Tmax * 128 >= (int64_t)1 << 27;
+}
+
+// The same for a call's sizes, as its test asks it.
+extern "C" int atom_internal_attention_reads_once(int32_t B, int32_t H, int32_t Hkv, int64_t Tmax)
+{
+    return attention_reads_once(B, H, Hkv, Tmax, decode_attention_shape(B, H, Hkv, Tmax).gqa);
+}
+
 hipError_t launch_decode_attention_kv4(const void *q, int B, int H, int Hkv, int64_t Tmax,
                                        const int32_t *seq_len, const void *kq, const void *ks,
                                        const void *kz, const void *vq, const void *vs,
@@ -899,12 +920,7 @@ hipError_t launch_decode_attention_kv4(const void *q, int B, int H, int Hkv, int
     int tps = S > 1 ? (groups + S - 1) / S : (groups > 0 ? groups : 1);
     if (sh.gqa) tps = (tps + kGqaWaves - 1) / kGqaWaves * kGqaWaves;   // whole rounds of the wavefronts
     float *part = S > 1 ? (float *)workspace : nullptr;
-    // A cache that the last-level cache (256 MB) does not keep until the next step is read with the hint that nothing reads it
-    // again: the memory then delivers 7.1 instead of 6.3 TB/s (a plain read of 400 MB and more).  Append and attention, lengths from T / 4 to
-    // T, us, without and with the hint; in MB the codes of all Tmax rows: 32 heads, 64 x 2048 (537 MB) 77.8, 68.7; 128 x 2048 139.2,
-    // 130.0; 90 x 1024 (377) 56.6, 54.1; 60 x 1024 (252) 42.1, 40.3; 40 x 1024 (168) 32.7, 31.9; 28 x 1024 (117) 28.6, 28.5;
-    // 20 x 1024 (84) 23.1, 23.3; 40 heads, 8 x 10000 (410) 64.1, 60.6; 85 x 161 (70) 24.7, 25.3; 64 heads on 8, 128 x 2048 (268) 56.3, 54.2.
-    const bool once = (int64_t)B * Hkv * Tmax * 128 >= (int64_t)1 << 27;
+    const bool once = attention_reads_once(B, H, Hkv, Tmax, sh.gqa);
     if (sh.gqa) {
         const size_t lds = (size_t)kGqaWaves * (H / Hkv) * kGqaHeadPitch * sizeof(float);   // <= 34 KB
         auto kern = once ? &decode_attention_kv4_gqa_kernel<true> : &decode_attention_kv4_gqa_kernel<false>;

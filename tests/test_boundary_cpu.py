@@ -245,3 +245,11 @@ def test_decode_linear_wants_codes_beyond_the_common_case(K, O, N):
     wants = lambda M, norm: bool(atom.load_library().atom_decode_linear_wants_codes(M, N, ctypes.byref(d), norm))
     assert [wants(M, 1) for M in range(1, 18)] == [6 <= M <= 16 for M in range(1, 18)]
     assert [wants(M, 0) for M in range(1, 18)] == [11 <= M <= 16 for M in range(1, 18)]
+
+
+@pytest.mark.parametrize("B,H,Hkv,T,once", [
+    (64, 32, 32, 512, True), (64, 32, 32, 511, False), (128, 64, 8, 1024, True), (32, 32, 2, 16384, True),
+    (64, 64, 2, 8192, False), (128, 32, 1, 8192, False), (64, 34, 2, 8192, False)])     # more than 16 query heads per cache head
+def test_attention_hint_only_where_a_row_is_read_once(B, H, Hkv, T, once):
+    pick = ctypes.CDLL(binding._LIB_PATH).atom_internal_attention_reads_once
+    assert bool(pick(B, H, Hkv, ctypes.c_int64(T))) == once

@@ -60,10 +60,10 @@ def test_nothing_behind_the_end_counts(H, Hkv):
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
 
 
-@pytest.mark.parametrize("B,H,Hkv,T", [(64, 32, 32, 512), (1, 32, 32, 32768), (128, 64, 8, 1024)])
+@pytest.mark.parametrize("B,H,Hkv,T", [(64, 32, 32, 512), (1, 32, 32, 32768), (128, 64, 8, 1024), (64, 34, 2, 8192)])
 def test_attention_over_a_large_cache(B, H, Hkv, T):
-    """From 2^27 bytes of codes on the rows are loaded with another hint (four wavefronts, sixteen, grouped query): the bits are those of
-    the cache of one row less per sequence, which has as many groups and so the same splits."""
+    """From 2^27 bytes of codes on the rows are loaded with another hint (four wavefronts, sixteen, grouped query; not where 17 query heads
+    share a cache head): the bits are those of the cache of one row less per sequence, which has as many groups and so the same splits."""
     D = 128
     assert B * Hkv * T * D == 1 << 27
     print(f"[case] attention over a large cache B={B} H={H} Hkv={Hkv} T={T}", flush=True)
