@@ -105,9 +105,11 @@ hipError_t dispatch_k(const PackedArgs &a, hipStream_t stream)
     // Threads as in the canonical front end, for the same reasons (8 rows with the threads of many rows and with twice as many: RMSNorm
     // 5.6 / 5.1 us at K = 4096, 7.3 / 7.5 at 8192, 12.1 / 11.4 at 16384; 1024 rows of 5120 in order: RMSNorm with 320 threads 9.6, with 512
     // 10.0; 4096 rows, SwiGLU: 35.4 and 29.5).
+    // One row of 4097 to 5120 channels keeps 1024 threads, in order with a norm 512: its only workgroup also writes the zeros of 63 rows, and that is
+    // what takes the time (5120 channels with 640: RMSNorm 14.8 us, SwiGLU 14.6; with 1024 13.7, 13.2; two rows 9.4, 9.1 with 640).
     const bool few = a.rows <= atom_launch::compute_units();
     if (few && a.K <= 4096)  return launch_cfg<NORM, 1, 512, PRE, IDENT>(a, stream);
-    if (few && a.K <= 5120)  return launch_cfg<NORM, 1, 640, PRE, IDENT>(a, stream);
+    if (few && a.K <= 5120 && a.rows > 1)  return launch_cfg<NORM, 1, 640, PRE, IDENT>(a, stream);
     if (few && a.K <= 8192 && !(IDENT && NORM)) return launch_cfg<NORM, 1, 1024, PRE, IDENT>(a, stream);
     if (few && a.K <= 16384 && a.K > 8192) return launch_cfg<NORM, 2, 1024, PRE, IDENT>(a, stream);
     if (a.K <= 4096)  return launch_cfg<NORM, 2, 256, PRE, IDENT>(a, stream);

@@ -58,6 +58,19 @@ def test_rows(M, K):
     assert torch.equal(atom.atom_swiglu_quantize_act_packed(dx, up, di), atom.atom_pack_act(*glu))
 
 
+@pytest.mark.parametrize("M", [1, 2])                    # 1024 (in order with a norm 512) and 640 threads
+@pytest.mark.parametrize("K", [4224, 5120])
+def test_packed_rows_of_a_few(M, K):
+    print(f"[case] packed front end M={M} K={K}", flush=True)
+    x, idx = _rows(3, K, M + K)
+    dx, up, gamma = torch.from_numpy(x[:M]).cuda(), torch.from_numpy(x[3 - M:]).cuda(), torch.linspace(0.5, 2.0, K, device="cuda").half()
+    for di in (torch.from_numpy(idx).cuda(), None):
+        for g in (None, gamma):
+            assert torch.equal(atom.atom_quantize_act_packed(dx, g, 1e-6, di), atom.atom_pack_act(*atom.atom_quantize_act(dx, g, 1e-6, di)))
+        assert torch.equal(atom.atom_add_quantize_act_packed(dx, up, gamma, 1e-6, di)[1], atom.atom_pack_act(*atom.atom_add_quantize_act(dx, up, gamma, 1e-6, di)[1:]))
+        assert torch.equal(atom.atom_swiglu_quantize_act_packed(dx, up, di), atom.atom_pack_act(*atom.atom_swiglu_quantize_act(dx, up, di)))
+
+
 def _halves_of(denom):
     """Pairs of fp16 factors (the first in [32, 64), where silu is the identity) whose product is denom * t / 2 by a power of two, t odd
     and of twelve bits: with clip 1 the scale lies in the middle between two fp16 numbers."""
