@@ -290,3 +290,18 @@ def test_mx_instruction_model():
     lost = ref - y
     assert (lost >= 0).all() and (lost <= 7 * 2.0 ** -13 * 448).all(), "an octet lost more than 7 * 2^-13 of its largest product"
     assert np.array_equal(y[4:], ref[4:]), "a product within 13 bits of its octet's largest was lost"
+
+
+@pytest.mark.parametrize("norm", [False, True])
+@pytest.mark.parametrize("M,K", [(300, 12416), (1100, 14336), (600, 16384), (600, 20480)])
+def test_mx_front_end_many_rows(M, K, norm):
+    """Four sweeps of 512 threads (a register to each reorder offset), three of 1024 (two to a register), several rows to a workgroup."""
+    print(f"[case] mx front end M={M} K={K} norm={norm}", flush=True)
+    rng = np.random.default_rng(M + K)
+    x = (rng.standard_normal((M, K)) * np.exp(1.5 * rng.standard_normal(K))).astype(np.float16)
+    idx, gamma = rng.permutation(K).astype(np.int32), np.linspace(0.5, 2.0, K).astype(np.float16) if norm else None
+    x[0, idx[:32]] = 0.0
+    rows = np.array([0, 1, M // 2, M - 1])
+    got = atom.atom_mx_quantize_act(torch.from_numpy(x).cuda(), None if gamma is None else torch.from_numpy(gamma).cuda(), 1e-6,
+                                    torch.from_numpy(idx).cuda(), 128, 0.9)
+    _equal(tuple(t[rows] for t in _row_major(got)), oracle.mx_quantize_act(x[rows], gamma, 1e-6, idx, 128, 0.9), "act rows")
