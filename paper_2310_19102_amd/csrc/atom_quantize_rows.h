@@ -228,11 +228,14 @@ struct NoHook { __device__ __forceinline__ void operator()() const {} };
 typedef _Float16 pk_v32h __attribute__((ext_vector_type(32)));
 typedef unsigned pk_v6u  __attribute__((ext_vector_type(6)));
 // Wavefronts per SIMD that a kernel's registers have to leave room for, where the compiler would take a few more than that without being
-// told: two workgroups of 512 threads per CU instead of one, five of 256 or four of 320 instead of four and three.
+// told: two workgroups of 512 threads per CU instead of one, five of 256 or four of 320 instead of four and three.  Two kernels with the loop over rows
+// spill for it and are the faster ones: RMSNorm of three sweeps (2 registers; 1100 rows of 11008 16.8 us, without the bound 21.8; 4096 43.1, 55.4) and its
+// tiled form of two sweeps of 256 (1 register; 2500 rows of 4096 12.0, 13.0; 4096 19.8, 19.6; 8192 35.5, 33.1).  Not the residual add with RMSNorm in order,
+// tiled, three sweeps (6 registers: 1100 rows of 9216 24.2, 25.0, but 3000 of 10240 52.3, 48.5, and 4096 of 9216 75.5, 61.0).
 constexpr int min_waves(bool norm, int ns, int nt, int pre, bool ident, bool packed, bool mx)
 {
     if (nt == 512 && ns == 4) return norm ? 1 : 4;
-    if (nt == 512 && ns == 3) return norm && !ident && (pre == kAdd || packed || mx) ? 1 : 4;
+    if (nt == 512 && ns == 3) return norm && (ident ? packed && pre == kAdd : pre == kAdd || packed || mx) ? 1 : 4;
     return nt <= 320 && ns == 2 && pre != kAdd ? 5 : 1;
 }
 // Where a workgroup has one row, a kernel without the loop over rows (ONE) has 20 to 40 registers less, room for another workgroup on the CU,

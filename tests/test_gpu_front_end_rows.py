@@ -24,7 +24,8 @@ def _rows(M, K, seed):
 
 @pytest.mark.parametrize("M,K", [(5, 4224), (5, 4992), (70, 5120), (5, 8064),       # 640 and 1024 threads, most, all and some of them
                                  (1100, 4992), (1100, 7168), (2100, 3968),         # 320, 512 and 256 threads, several rows each
-                                 (800, 11008), (800, 12416), (800, 16384)])        # three and four sweeps
+                                 (800, 11008), (800, 12416), (800, 16384),         # three and four sweeps
+                                 (1100, 9216), (1100, 13824)])                     # the same, several rows each also in order
 def test_rows(M, K):
     print(f"[case] front end rows M={M} K={K}", flush=True)
     x, idx = _rows(M, K, M + K)
@@ -52,6 +53,17 @@ def test_rows(M, K):
     same(added, oracle.quantize_act(npy(h[some]), npy(gamma), 1e-6, idx, 128, 128, 0.9), "add")
     h2, packed = atom.atom_add_quantize_act_packed(dx, up, gamma, 1e-6, di)
     assert torch.equal(h, h2) and torch.equal(packed, atom.atom_pack_act(*added))
+
+    ordered = [t[..., di.long()].contiguous() for t in (dx, up, gamma, h)]
+    norm_order = atom.atom_quantize_act(ordered[0], ordered[2], 1e-6, None)
+    ho, *added_order = atom.atom_add_quantize_act(*ordered[:3], 1e-6, None)
+    assert torch.equal(ho, ordered[3])
+    ho, packed = atom.atom_add_quantize_act_packed(*ordered[:3], 1e-6, None)
+    assert torch.equal(ho, ordered[3]) and torch.equal(packed, atom.atom_pack_act(*added_order))
+    assert torch.equal(atom.atom_quantize_act_packed(ordered[0], ordered[2], 1e-6, None), atom.atom_pack_act(*norm_order))
+    identity = np.arange(K, dtype=np.int32)                  # (the sum of squares of a row in another order is another sum)
+    same(norm_order, oracle.quantize_act(npy(ordered[0][some]), npy(ordered[2]), 1e-6, identity, 128, 128, 0.9), "norm, in order")
+    same(added_order, oracle.quantize_act(npy(ho[some]), npy(ordered[2]), 1e-6, identity, 128, 128, 0.9), "add, in order")
 
     glu = atom.atom_swiglu_quantize_act(dx, up, di)
     same(glu, oracle.swiglu_quantize_act(x[some], x[::-1][some], idx, 128, 128, 0.9), "SwiGLU")
