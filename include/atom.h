@@ -289,7 +289,9 @@ atom_status atom_decode_linear(const void *x_f16, int64_t M, int64_t ldx,
  * atom_w4a4_gemm at this size: they request their weights, wait until M rows
  * are counted, and fetch the codes, so the front end runs while the weights
  * travel from HBM.  Y is bit-identical to atom_quantize_act followed by
- * atom_w4a4_gemm (the same kernel routine, the same sum over groups).
+ * atom_w4a4_gemm (the same kernel routine, the same sum over groups).  Where
+ * those two launches are faster (up to 8192 channels with more than eight rows
+ * or many outputs) the call is made of them and leaves sync_words alone.
  *
  *   a_q4 [M, (K-O)/2], a_q8 [M, O], a_scale [M, K/Gs]   outputs (device), also
  *                 the kernel's own channel between its workgroups: each

@@ -314,7 +314,8 @@ def atom_decode_linear_coop(x: torch.Tensor, gamma: Optional[torch.Tensor], eps:
                             clip: float = 0.9, out: Optional[torch.Tensor] = None,
                             codes: Optional[Tuple[torch.Tensor, ...]] = None, bits: int = 4):
     """One launch for ``Y = linear(x)`` at M <= 16 rows with the front end done once: the first M
-    workgroups quantise the rows, the others stream the weights meanwhile.  ``sync_words``:
+    workgroups quantise the rows, the others stream the weights meanwhile (two launches, the same bits, where those are
+    faster).  ``sync_words``:
     ``atom_decode_linear_coop_sync()`` (int32 zeros on the device), zero before the first call, left
     zero by every call (word 1 set = a wait ran out).  Returns ``(Y, (q4, q8, scale))``: the codes are outputs as in atom_quantize_act."""
     return _run().decode_linear_coop(x, gamma, eps, reorder_idx, w_q4, w_q8, w_scale, sync_words, group_size, clip,

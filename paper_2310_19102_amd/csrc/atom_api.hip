@@ -244,6 +244,28 @@ int atom_decode_linear_wants_codes(int64_t M, int64_t N, const atom_desc *d, int
     return atom_internal::decode_linear_splits((int)(M < 17 ? M : 17), N, d->K, d->n_outlier, with_norm != 0, 0);
 }
 
+// Front end and GEMM that meet in the caller's arrays of codes.
+static atom_status decode_linear_two_launches(const void *x, int64_t M, int64_t ldx, const void *gamma, float eps,
+                                              const int32_t *idx, const atom_desc *d, float clip, const void *w_q4,
+                                              const void *w_q8, const void *w_scale, int64_t N, void *y, int64_t ldy, void *a_q4,
+                                              void *a_q8, void *a_scale, void *stream)
+{
+    hipError_t err = atom_internal::launch_quantize_rows(x, M, ldx, 0, nullptr, 0, nullptr, 0, gamma, eps, idx, d->K, d->n_outlier,
+                                                         d->bits_normal, clip, a_q4, a_q8, a_scale,
+                                                         static_cast<hipStream_t>(stream));
+    if (err != hipSuccess) return ATOM_ERR_HIP;
+    atom_internal::GemmArgs g;
+    g.a_q4 = static_cast<const uint8_t *>(a_q4); g.a_q8 = static_cast<const int8_t *>(a_q8);
+    g.a_scale = static_cast<const uint16_t *>(a_scale); g.M = M;
+    g.w_q4 = static_cast<const uint8_t *>(w_q4); g.w_q8 = static_cast<const int8_t *>(w_q8);
+    g.w_scale = static_cast<const uint16_t *>(w_scale); g.N = N;
+    g.K = d->K; g.O = d->n_outlier;
+    g.y = static_cast<uint16_t *>(y); g.ldy = ldy;
+    g.partials = nullptr; g.workspace = nullptr; g.workspace_bytes = 0;
+    err = atom_internal::launch_w4a4_gemm(g, static_cast<hipStream_t>(stream));
+    return err == hipSuccess ? ATOM_OK : ATOM_ERR_HIP;
+}
+
 atom_status atom_decode_linear(const void *x_f16, int64_t M, int64_t ldx, const void *gamma_f16,
                                float eps, const int32_t *reorder_idx, const atom_desc *d, float clip,
                                const void *w_q4, const void *w_q8, const void *w_scale, int64_t N,
@@ -267,20 +289,8 @@ atom_status atom_decode_linear(const void *x_f16, int64_t M, int64_t ldx, const 
     const uintptr_t scales = reinterpret_cast<uintptr_t>(w_scale) | reinterpret_cast<uintptr_t>(dbg_scale);
     if (ndbg && aligned(dbg_q4, 16) && aligned(dbg_q8, 16) &&
         atom_internal::decode_linear_splits((int)M, N, d->K, d->n_outlier, gamma_f16 != nullptr, scales)) {
-        hipError_t e2 = atom_internal::launch_quantize_rows(x_f16, M, ldx, 0, nullptr, 0, nullptr, 0, gamma_f16, eps, reorder_idx,
-                                                            d->K, d->n_outlier, d->bits_normal, clip, dbg_q4, dbg_q8, dbg_scale,
-                                                            static_cast<hipStream_t>(stream));
-        if (e2 != hipSuccess) return ATOM_ERR_HIP;
-        atom_internal::GemmArgs g;
-        g.a_q4 = static_cast<const uint8_t *>(dbg_q4); g.a_q8 = static_cast<const int8_t *>(dbg_q8);
-        g.a_scale = static_cast<const uint16_t *>(dbg_scale); g.M = M;
-        g.w_q4 = static_cast<const uint8_t *>(w_q4); g.w_q8 = static_cast<const int8_t *>(w_q8);
-        g.w_scale = static_cast<const uint16_t *>(w_scale); g.N = N;
-        g.K = d->K; g.O = d->n_outlier;
-        g.y = static_cast<uint16_t *>(y_f16); g.ldy = ldy;
-        g.partials = nullptr; g.workspace = nullptr; g.workspace_bytes = 0;
-        e2 = atom_internal::launch_w4a4_gemm(g, static_cast<hipStream_t>(stream));
-        return e2 == hipSuccess ? ATOM_OK : ATOM_ERR_HIP;
+        return decode_linear_two_launches(x_f16, M, ldx, gamma_f16, eps, reorder_idx, d, clip, w_q4, w_q8, w_scale, N, y_f16, ldy, dbg_q4,
+                                          dbg_q8, dbg_scale, stream);
     }
     hipError_t err = atom_internal::launch_decode_linear(x_f16, (int)M, ldx, gamma_f16, eps, reorder_idx, d->K,
                                                          d->n_outlier, d->bits_normal, clip, w_q4, w_q8, w_scale,
@@ -310,6 +320,9 @@ atom_status atom_decode_linear_coop(const void *x_f16, int64_t M, int64_t ldx, c
     if (M > 16 || !(clip >= 9.5367431640625e-07f && clip <= 1.0f) ||
         !atom_internal::decode_linear_coop_supported((int)M, d->K, d->n_outlier, a_scale, w_scale, N))
         return ATOM_ERR_UNSUPPORTED;
+    if (atom_internal::decode_linear_coop_splits((int)M, N, d->K))
+        return decode_linear_two_launches(x_f16, M, ldx, gamma_f16, eps, reorder_idx, d, clip, w_q4, w_q8, w_scale, N, y_f16, ldy, a_q4,
+                                          a_q8, a_scale, stream);
     hipError_t err = atom_internal::launch_decode_linear_coop(x_f16, (int)M, ldx, gamma_f16, eps, reorder_idx, d->K,
                                                               d->n_outlier, d->bits_normal, clip, w_q4, w_q8,
                                                               w_scale, N, y_f16, ldy, a_q4, a_q8, a_scale,

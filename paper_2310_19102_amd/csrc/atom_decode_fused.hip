@@ -244,11 +244,9 @@ hipError_t launch_depth(const FusedParams &p, size_t lds, hipStream_t stream)
 //
 // What it costs: the chain front end -> release -> poll -> fetch of the codes from memory is
 // about as long as the gap between two launches in a stream, so inside a HIP graph the kernel
-// ties with the two launches (and loses where N / 16 workgroups need a second round, which can
-// only start when the first, waiting, round is through); called eagerly, where the host's launch
-// cost sets the pace, one launch is what counts.  Producers done earlier are not always a gain: with all loads of their row in flight
-// N = 4096 is 4 to 6 % faster (K = 5120, 8 rows: 9.6 -> 9.2 us), but 5120 and 8192 channels on 11008 outputs and more, three consumers to
-// a CU, 3 to 4 % slower (12 rows: 13.2 -> 13.7): the codes are fetched in the middle of the weights.
+// ties with the two launches at best (and loses where N / 16 workgroups need a second round, which can
+// only start when the first, waiting, round is through, and from nine rows on); called eagerly, it saves the second launch.
+// decode_linear_coop_splits says where the entry point takes the two launches instead.
 // ------------------------------------------------------------------------------------------
 constexpr uint32_t kSpinLimit = 1u << 18;
 constexpr int kBuckets = 32;
@@ -451,6 +449,17 @@ hipError_t launch_decode_linear(const void *x, int M, int64_t ldx, const void *g
 
 size_t decode_linear_coop_sync_bytes() { return 4 * (size_t)kSyncWords; }
 
+// Where two launches through the caller's arrays are faster, in a graph and called eagerly.  us, the kernel above and two launches, graph: 12 rows: K = N = 4096
+// 9.8, 7.7; K = 5120, N = 11008 15.8, 12.5; K = 8192, N = 5120 15.3, 14.4; 8 rows: K = 4096, N = 11008 13.0, 10.6; K = 5120, N = 22016 22.3, 19.4; 1 row:
+// K = 8192, N = 22016 26.6, 23.6; eagerly: 9 rows: K = 1024, N = 2048 7.7, 7.5; K = 4096, N = 512 8.4, 6.3 to 7.3.  The kernel stays for K = 4096, N = 8192, 8 rows,
+// eagerly 10.9 and 11.1 to 11.4, and for more than 8192 channels (K = N = 11008, 8 rows: 23.0, 24.7).  More than 5120 channels, 8193 to 12288 outputs and up to 8
+// rows: both are 1 to 5 % behind the same kernel with slower producers (their loads one sweep after the other; called eagerly K = 8192, N = 11008: 1 row 14.8 with
+// those, 15.3 in the kernel, 15.2 in two launches; 8 rows 16.6, 17.0, 17.3; K = 6144: 12.5, 13.1, 12.7; N = 9216: 12.2, 12.5, 12.4).
+bool decode_linear_coop_splits(int M, int64_t N, int K)
+{
+    return K <= 8192 && (M > 8 || N > 10240 || (N > 8192 && K <= 5120));
+}
+
 bool decode_linear_coop_supported(int M, int K, int O, const void *a_scale, const void *w_scale, int64_t N)
 {
     GemmParams g{};
@@ -485,3 +494,6 @@ hipError_t launch_decode_linear_coop(const void *x, int M, int64_t ldx, const vo
 }
 
 }  // namespace atom_internal
+
+// Whether a call of these sizes that the cooperative kernel takes goes to two launches instead, as its test asks it.
+extern "C" int atom_internal_decode_linear_coop_splits(int32_t M, int64_t N, int32_t K) { return atom_internal::decode_linear_coop_splits(M, N, K); }

@@ -91,6 +91,8 @@ hipError_t launch_decode_linear(const void *x, int M, int64_t ldx, const void *g
 // zeroed bytes.
 size_t     decode_linear_coop_sync_bytes();
 bool       decode_linear_coop_supported(int M, int K, int O, const void *a_scale, const void *w_scale, int64_t N);
+// whether front end and GEMM as two launches are faster (the same bits)
+bool       decode_linear_coop_splits(int M, int64_t N, int K);
 hipError_t launch_decode_linear_coop(const void *x, int M, int64_t ldx, const void *gamma, float eps,
                                      const int32_t *idx, int K, int O, int nbits, float clip,
                                      const void *w_q4, const void *w_q8, const void *w_scale, int64_t N,

@@ -253,3 +253,11 @@ def test_decode_linear_wants_codes_beyond_the_common_case(K, O, N):
 def test_attention_hint_only_where_a_row_is_read_once(B, H, Hkv, T, once):
     pick = ctypes.CDLL(binding._LIB_PATH).atom_internal_attention_reads_once
     assert bool(pick(B, H, Hkv, ctypes.c_int64(T))) == once
+
+
+@pytest.mark.parametrize("M,K,N,two", [
+    (8, 4096, 8192, False), (9, 4096, 8192, True), (16, 8192, 16, True), (16, 8448, 5000, False),
+    (1, 4096, 8193, True), (8, 5120, 11008, True), (8, 5376, 10240, False), (1, 8192, 10241, True), (4, 8448, 22016, False)])
+def test_cooperative_decode_linear_in_two_launches_where_they_are_faster(M, K, N, two):
+    pick = ctypes.CDLL(binding._LIB_PATH).atom_internal_decode_linear_coop_splits
+    assert bool(pick(M, ctypes.c_int64(N), K)) == two

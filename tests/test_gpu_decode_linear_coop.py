@@ -38,6 +38,8 @@ def _rand_linear(M, K, N, seed, norm=True):
     (3, 1024, 16, True, True),         # eight groups: one consumer, most wavefronts without a group
     (4, 4096, 22016, True, False),     # no index; 1376 consumers: more than are resident at one time
     (9, 11008, 4096, False, False),
+    (16, 8448, 1000, True, True),      # sixteen rows in one launch
+    (5, 8448, 22016, False, False),    # one launch of 1376 consumers
 ])
 def test_coop_decode_linear(M, K, N, norm, index):
     print(f"[case] cooperative decode linear M={M} K={K} N={N} norm={norm} index={index}", flush=True)
