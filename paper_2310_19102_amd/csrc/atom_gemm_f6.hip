@@ -658,9 +658,10 @@ static PackParams pack_params(const void *q4, const void *q8, const void *scale,
 static hipError_t launch_pack(const PackParams &p, const PackParams &q, hipStream_t stream)
 {
     const unsigned units = (unsigned)(p.units + q.units);
-    // up to eight workgroups of one group per compute unit, one round of them: the time is that of one (1024 x 4096 4.1 us, with four groups
-    // 4.8; 1024 x 11008 5.9, 6.8; 4096 x 8192 is 4032 of them)
-    if ((int64_t)p.G4 * units <= 2048)
+    // One group to a workgroup up to eleven of them per compute unit, where the time is that of a round (1024 x 4096 4.1 us, with four groups
+    // 4.8; 1024 x 11008 5.9, 6.8; 13824 x 1664, 2592 of them, 7.4, 8.2; 8192 x 3072, 2944 of them, 8.3, 8.4; 4096 x 8192, 4032 of them, 11.1, 10.4), and where
+    // four would leave most of a row's last workgroup idle (152064 rows of 256: 11.3, 17.9; 16384 of 1280: 6.4, 8.8)
+    if ((int64_t)p.G4 * units <= 2816 || p.G4 < 4 || (p.G4 % 4 == 1 && p.G4 < 12))
         hipLaunchKernelGGL(pack_rows_kernel<1>, dim3((unsigned)(p.G4 + p.G8), units), dim3(256), 0, stream, p, q);
     else
         hipLaunchKernelGGL(pack_rows_kernel<4>, dim3((unsigned)((p.G4 + 3) / 4 + p.G8), units), dim3(256), 0, stream, p, q);

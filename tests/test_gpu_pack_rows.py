@@ -13,6 +13,17 @@ pytestmark = pytest.mark.gpu
 def test_many_rows_are_the_ranges(G4, O):
     rows, step = 64 * 150 - 37, 64 * 25                       # 150 units: more than 2048 images; 25: fewer; the last unit is cut
     assert 150 * G4 > 2048 >= 25 * G4
+    check(rows, step, G4, O)
+
+
+@pytest.mark.parametrize("G4,units", [(15, 200), (16, 200), (17, 200), (18, 200), (12, 236), (4, 720), (6, 500),      # four groups to a workgroup
+                                      (1, 2900), (3, 1000), (5, 600), (9, 320)])      # one, as in the ranges
+def test_many_images_are_the_ranges(G4, units):
+    assert G4 * units > 2816
+    check(64 * units - 37, 64 * max(1, 2000 // G4), G4, 128)
+
+
+def check(rows, step, G4, O):
     print(f"[case] pack {rows} rows, {G4} INT4 groups, {O} outliers", flush=True)
     K = 128 * G4 + O
     g = torch.Generator(device="cuda").manual_seed(G4 + O)
