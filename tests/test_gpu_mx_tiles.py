@@ -50,10 +50,22 @@ def test_mx_tiles(name, M, K, N):
     ("256x384", 2999, 2048, 13823),      # more than one per compute unit
 ])
 def test_mx_wide_tiles(name, M, K, N):
+    assert tile_k(M, N, K) == name
+    check(name, M, K, N)
+
+
+# the wide kernel's loop over FP8 steps beyond its first pair: four, six and thirty of them, the last with one FP4 step behind them
+@pytest.mark.parametrize("O", [256, 384, 1920])
+@pytest.mark.parametrize("name,M,K,N", [("256x320", 1024, 2048, 17000), ("256x384", 2048, 2048, 12280)])
+def test_mx_wide_tiles_and_outliers(name, M, K, N, O):
+    assert tile_k(M, N, K) == name
+    check(name, M, K, N, O)
+
+
+def tile_k(M, N, K):
     pick = ctypes.CDLL(atom.binding._LIB_PATH).atom_internal_mx_tile_k
     t = pick(ctypes.c_int64(M), ctypes.c_int64(N), ctypes.c_int32(K), ctypes.c_int64(torch.cuda.get_device_properties(0).multi_processor_count))
-    assert f"{t // 1000}x{t % 1000}" == name
-    check(name, M, K, N)
+    return f"{t // 1000}x{t % 1000}"
 
 
 def check(name, M, K, N, O=128):
