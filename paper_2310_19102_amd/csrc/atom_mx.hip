@@ -603,7 +603,10 @@ hipError_t launch_wide(const MxParams &p, hipStream_t stream)
 //   M = 777,  N = 13824, K = 5120:   64 x 64 64.3, 64 x 128 54.7, 128 x 128 38.5, 128 x 256 43.3, 256 x 256 40.2
 //   M = 1024, N = 22016, K = 4096:   64 x 64 103.4, 64 x 128 85.5, 128 x 128 62.4, 128 x 256 55.9, 256 x 256 61.1
 //   M = 4096, N = 22016, K = 4096:   64 x 64 436.6, 64 x 128 331.6, 128 x 128 251.2, 128 x 256 207.0, 256 x 256 203.1
-// The wide tiles, fitted to 29 sizes of K = 2048 to 14336 on another card (256 x 256, 256 x 320, 256 x 384):
+// The wide tiles come out of it too well, since nothing stands for their prologue and store, one workgroup to a compute unit: they also have to be ahead
+// in microseconds (kOther, kWide: with K / 128 + 1 steps, fitted to 361 sizes of K = 2048 to 14336 where the cost takes them, within 3 to 5 %:
+// profiles/mx_gemm_wide_tiles.txt).  Without that 32 of the 361 were slower than the tile they replaced, by up to 6 % (K = 2048, M = 3000, N = 12288 128 x 256 50.7,
+// 256 x 320 53.1; K = 5120, M = 1300, N = 28672 128 x 256 112.3, 256 x 384 116.4), with it 10, by up to 5 %.  256 x 256, 256 x 320, 256 x 384 on another card:
 //   M = 1024, N = 22016, K = 4096:   64.6, 72.7, 52.1          M = 2048, N = 10000, K = 4096:    63.0, 48.0, 50.3
 //   M = 1200, N = 12288, K = 11008:  81.9, 95.4, 92.5          M = 1300, N = 16000, K = 5120:    73.2, 85.3, 61.9
 //   M = 4096, N = 22016, K = 4096:   206.0, -, 199.4           M = 1500, N = 8192,  K = 8192:    60.8, -, 68.4
@@ -616,20 +619,36 @@ constexpr TileCost kCost[kTiles] = {{64, 64, 0.150f, 0.080f, 0.125f}, {64, 128, 
 
 int64_t tiles_of(const TileCost &t, int64_t M, int64_t N) { return ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn); }
 
+struct OtherTime { float launch, round, cost, mb; };        // us: once, per round of tiles, per K step and unit of cost, per MB of operands
+constexpr OtherTime kOther[k256x256 + 1] = {{5.0f, 0.0f, 1.0f, 0.0f}, {5.0f, 0.0f, 1.0f, 0.0f}, {1.8f, 0.91f, 0.945f, 0.082f}, {7.4f, 0.18f, 0.89f, 0.090f},
+                                            {4.3f, 4.4f, 0.89f, 0.028f}};
+struct WideTime { float round, step, last; };               // us: per round of tiles, per K step of a round, what the last round's fill adds to a step
+constexpr WideTime kWide[2] = {{7.1f, 1.117f, 0.124f}, {8.45f, 1.27f, 0.083f}};
+
 Tile pick_tile(int64_t M, int64_t N, int K, int cus)
 {
-    Tile best = k256x256;
-    float least = 0.0f;
-    for (int i = kTiles - 1; i >= 0; --i) {
+    Tile other = k256x256, best = k256x256;
+    float least = 0.0f, least_other = 0.0f;
+    for (int i = 0; i < kTiles; ++i) {
         const int64_t tiles = tiles_of(kCost[i], M, N);
         if (tiles > 0x7fffff) continue;                    // (the grid's limit in threads; the 256 x 256 tile takes what is left)
         if (i > k256x256 && K < 2048) continue;            // (the wide kernel: steps enough for its prologue and store)
         const TileCost &t = kCost[i];
         const float r = (float)(tiles % cus) / (float)cus, few = tiles < cus ? t.alone : t.more;
         const float cost = t.full * (float)(tiles / cus) + (r > 0.0f ? few + (t.full - few) * r * r * r : 0.0f);
-        if (least == 0.0f || cost < least) { least = cost; best = (Tile)i; }
+        if (i <= k256x256 && (least_other == 0.0f || cost <= least_other)) { least_other = cost; other = (Tile)i; }
+        if (least == 0.0f || cost <= least) { least = cost; best = (Tile)i; }
     }
-    return best;
+    if (best <= k256x256) return best;
+    const float     steps = (float)(K / 128 + 1);
+    const int64_t   tiles = tiles_of(kCost[best], M, N), tiles_other = tiles_of(kCost[other], M, N);
+    const WideTime  &w = kWide[best - k256x320];
+    const OtherTime &o = kOther[other];
+    const float r    = (float)(tiles % cus) / (float)cus;
+    const float wide = (float)((tiles + cus - 1) / cus) * (w.round + w.step * steps) + w.last * r * r * r * steps;
+    const float us   = o.launch + o.round * (float)((tiles_other + cus - 1) / cus) + o.cost * least_other * steps +
+                       o.mb * (float)(M + N) * (float)K * 0.56e-6f;
+    return wide < 1.02f * us ? best : other;
 }
 
 }  // namespace

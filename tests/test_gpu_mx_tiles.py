@@ -54,6 +54,13 @@ def test_mx_wide_tiles(name, M, K, N):
     check(name, M, K, N)
 
 
+@pytest.mark.parametrize("name,M,K,N", [
+    ("128x128", 3000, 2048, 11008), ("128x128", 1300, 2048, 13824), ("128x256", 3000, 2048, 12288), ("128x256", 1300, 5120, 28672)])
+def test_mx_wide_tiles_have_to_be_ahead(name, M, K, N):
+    """Cheaper per step, but behind with a prologue and a store to every round."""
+    assert tile_k(M, N, K) == name
+
+
 # the wide kernel's loop over FP8 steps beyond its first pair: four, six and thirty of them, the last with one FP4 step behind them
 @pytest.mark.parametrize("O", [256, 384, 1920])
 @pytest.mark.parametrize("name,M,K,N", [("256x320", 1024, 2048, 17000), ("256x384", 2048, 2048, 12280)])
