@@ -326,10 +326,11 @@ hipError_t launch_tile(const MxParams &p, hipStream_t stream)
 
 // The same on wide tiles, 256 x 32 TN: eight wavefronts of 64 rows x 16 TN columns, three stages.
 //
-// What bounds the tiles above is how fast a compute unit loads: it has at most 256 lines of 128 bytes in flight, whatever asks for them, and
-// loads return in order across its wavefronts, so a request out of the L2 waits behind one from the last-level cache or the memory (0.4
-// to 0.65 us): 50 to 65 GB/s per compute unit, where L2 hits alone would give 130.  So bytes per multiply-add count, and the power that moving
-// them takes: clocks fall to about 1.6 GHz with all compute units at it.  Only the accumulators stay (16 TN registers); the fragments of the
+// The tiles above load 41 to 45 GB/s per compute unit, which has about 256 lines of 128 bytes in flight at most (alone 54 GB/s out of the memory, 96 to 110 out of the
+// last-level cache, 115 to 148 out of the L2, with all of them at it 25, 29 and 115: profiles/loads_per_compute_unit.txt); loads return in order across its wavefronts, so a
+// request out of the L2 waits behind one from farther away.  So this kernel loads fewer bytes per multiply-add: 28 GB/s at M = 1024, K = 4096, N = 22016, which
+// no longer bounds it.  A step of 256 x 384 takes 1.27 us, its MFMAs alone 0.74 at their full rate (clocks fall to about 1.6 GHz with all compute units at it), and a round 8.5 us for
+// prologue and store, which nothing overlaps (fitted to 185 sizes).  Only the accumulators stay (16 TN registers); the fragments of the
 // weights are read from LDS four MFMAs ahead, in one run over both halves of a step, and the barrier of a step stands before its last MFMAs, behind
 // which the first fragments of the next step are read.  (With 32 rows x 32 TN columns per wavefront LDS gives 1.6 times as much and the kernel is 3 to 9 %
 // slower; TN = 9 and 11 were within 3 % of 10 and 12.)
@@ -341,7 +342,7 @@ struct MxWide {
     static constexpr int NW    = 8, NT = 512, NST = 3;
     static constexpr int BM    = 256, BN = 32 * TN;
     static constexpr int CODES = (BM + BN) * ROWB;
-    static constexpr int NSC   = (BM + BN + 63) / 64;      // requests of 64 scale dwords per stage (the last may be half used)
+    static constexpr int NSC   = (BM + BN) / 64;          // requests of 64 scale dwords per stage
     static constexpr int STAGE = CODES + 256 * NSC;
     static constexpr int NBLK  = (BM + BN) / 16;           // requests of a kilobyte (16 rows) per stage
     static constexpr int J     = (NBLK + NW - 1) / NW, JS = (NSC + NW - 1) / NW, LOADS = J + JS;
@@ -350,6 +351,7 @@ struct MxWide {
     static constexpr int PITCH = 144;                      // output staging: 32 rows of 64 columns per wavefront
     static constexpr int AHEAD = 2;                        // fragments read ahead of their MFMAs
     static_assert(NW * 32 * PITCH <= NST * STAGE && LDS <= 160 * 1024 && 2 * LOADS <= 63, "LDS, vmcnt");
+    static_assert(TN % 2 == 0, "two wavefronts side by side in N, whole requests of scales");
 };
 
 template <int TN>
@@ -595,7 +597,7 @@ hipError_t launch_wide(const MxParams &p, hipStream_t stream)
 // Which tile.  The cost of a launch, in microseconds per K step, with f tiles per compute unit: `full` for each whole tile
 // every compute unit has, and for a last part r of them what they add when few compute units have one (`alone` where it is
 // all there is, `more` beside other workgroups), growing to `full` as the chip fills and the power limit sets in.  Measured
-// at 43 sizes, K = 1024 to 14336 (profiles/mx_gemm_tiles.txt has all of them; us, weights from memory; the choice is within 5 % of the
+// at 43 sizes, K = 1024 to 14336 (profiles/mx_gemm_tiles.txt has all of them; us, weights from memory; the choice among these five is within 5 % of the
 // best tile but at M = 256, N = 22016 and M = 2048, N = 12288, K = 4096, where 128 x 256 would be 8 and 10 % faster):
 //   M = 65,   N = 4096,  K = 4096:   64 x 64 9.2, 64 x 128 10.7, 128 x 128 11.3, 128 x 256 16.9, 256 x 256 23.7
 //   M = 256,  N = 12288, K = 4096:   64 x 64 18.2, 64 x 128 18.0, 128 x 128 14.2, 128 x 256 20.7, 256 x 256 25.5
