@@ -111,26 +111,47 @@ Tensor make(at::IntArrayRef shape, Kind k, const Tensor &like)
 
 Tensor make(std::initializer_list<int64_t> shape, Kind k, const Tensor &like) { return make(at::IntArrayRef(shape), k, like); }
 
+bool capturing() { return c10::hip::currentStreamCaptureStatusMayInitCtx() != c10::hip::CaptureStatus::None; }
+
+// Memory for the length of a call only may be part of a captured graph where it comes from a pool that the graph keeps (torch.cuda.graph).  In a
+// capture that the allocator does not know of the block would be free again when the call returns, and a replay would write into
+// whatever has it by then.
+bool safe_to_capture(const Tensor &t)
+{
+    if (!capturing()) return true;
+    const size_t at = (size_t)t.data_ptr();
+    try {
+        for (const auto &s : c10::hip::HIPCachingAllocator::snapshot().segments)
+            if (s.device == t.device().index() && at - s.address < s.total_size) return s.owner_private_pool_id != c10::MempoolId_t{0, 0};
+    } catch (const c10::Error &) {                                     // (an allocator of the program's own that does not say)
+    }
+    return false;
+}
+
 // Whether the allocator is likely to have n bytes without giving back what it keeps.  A request that neither its free blocks nor the device
 // can serve makes it return every free block to the device, behind a synchronisation, before it raises: too much for memory that a call can do
 // without, and that asks again with every call.  (Under capture it returns nothing, and the device is not asked.)
 bool has_room(int64_t n, c10::DeviceIndex device)
 {
     namespace allocator = c10::hip::HIPCachingAllocator;
-    if (c10::hip::currentStreamCaptureStatusMayInitCtx() != c10::hip::CaptureStatus::None) return true;
-    size_t largest = 1;                                                // (0: the device's free memory counts as well)
-    allocator::cacheInfo(device, &largest);
-    if (largest >= (size_t)n) return true;
-    const double with = (double)n + (double)(20 << 20);               // (what it takes from the device is rounded up, to 20 MB at least)
-    const double fraction = allocator::getMemoryFraction(device);
-    if (fraction < 1.0) {
-        const auto stats = allocator::getDeviceStats(device);
-        const auto &reserved = stats.reserved_bytes[static_cast<size_t>(c10::CachingAllocator::StatType::AGGREGATE)];
-        if ((double)reserved.current + with > fraction * (double)at::cuda::getDeviceProperties(device)->totalGlobalMem) return false;
+    if (capturing()) return true;
+    try {
+        size_t largest = 1;                                            // (0: the device's free memory counts as well)
+        allocator::cacheInfo(device, &largest);
+        if (largest >= (size_t)n) return true;
+        const double with = (double)n + (double)(20 << 20);           // (what it takes from the device is rounded up, to 20 MB at least)
+        const double fraction = allocator::getMemoryFraction(device);
+        if (fraction < 1.0) {
+            const auto stats = allocator::getDeviceStats(device);
+            const auto &reserved = stats.reserved_bytes[static_cast<size_t>(c10::CachingAllocator::StatType::AGGREGATE)];
+            if ((double)reserved.current + with > fraction * (double)at::cuda::getDeviceProperties(device)->totalGlobalMem) return false;
+        }
+        largest = 0;
+        allocator::cacheInfo(device, &largest);
+        return (double)largest >= with;
+    } catch (const c10::Error &) {                                     // (an allocator of the program's own that does not say)
+        return true;
     }
-    largest = 0;
-    allocator::cacheInfo(device, &largest);
-    return (double)largest >= with;
 }
 
 // Row stride of a matrix with `cols` columns (a single row may report any stride).
@@ -359,7 +380,7 @@ PyObject *w4a4_gemm(Args a)
     if (room && has_room((int64_t)room, a4.device().index())) {
         try {
             own = make({(int64_t)room}, kByte, a4);
-            w = &own;
+            if (safe_to_capture(own)) w = &own;
         } catch (const c10::OutOfMemoryError &) {
         }
     }
@@ -412,7 +433,7 @@ PyObject *decode_linear(Args a)
         const int64_t n4 = up(M * (K - O) / 2), n8 = up(M * O);
         try {
             own = make({n4 + n8 + M * groups(K, gs) * 2}, kByte, x);
-            c4 = data(own); c8 = (char *)c4 + n4; cs = (char *)c8 + n8;
+            if (safe_to_capture(own)) { c4 = data(own); c8 = (char *)c4 + n4; cs = (char *)c8 + n8; }
         } catch (const c10::OutOfMemoryError &) {       // one launch then, the same bits
         }
     }
