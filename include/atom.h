@@ -269,8 +269,9 @@ atom_status atom_permute_rows(const void *in_f16, int64_t rows_in, int64_t cols,
  * Alignment as atom_quantize_act and atom_w4a4_gemm; debug arrays 4-byte.
  * Where atom_decode_linear_wants_codes(M, N, d, norm) is not 0, a call that gets the three arrays, the
  * two code arrays on 16-byte boundaries, is faster: front end and GEMM are then two launches that
- * meet in them.  Y has the same bits in one launch and in two; where other alignments of dbg_scale or
- * w_scale would change the order of its sums, the call stays one launch.
+ * meet in them (so that no other call may have them at the same time).  Y has the same bits in one
+ * launch and in two; where other alignments of dbg_scale or w_scale would change the order of its sums,
+ * the call stays one launch.
  */
 int atom_decode_linear_wants_codes(int64_t M, int64_t N, const atom_desc *d, int with_norm);
 atom_status atom_decode_linear(const void *x_f16, int64_t M, int64_t ldx,

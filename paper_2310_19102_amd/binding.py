@@ -297,7 +297,8 @@ def atom_decode_linear(x: torch.Tensor, gamma: Optional[torch.Tensor], eps: floa
                        out: Optional[torch.Tensor] = None, debug: bool = False, bits: int = 4):
     """One call for ``Y = linear(x)`` at M <= 16 rows: front end (RMSNorm when ``gamma`` is given,
     reorder, group quantisation) and weight-streaming group GEMM, in one launch or, where that is faster
-    (``atom_decode_linear_wants_codes`` of the C library), in two.  Returns ``Y`` [M, N] fp16, or
+    (``atom_decode_linear_wants_codes`` of the C library) and memory for the codes can be had, in two: the
+    same bits.  Returns ``Y`` [M, N] fp16, or
     ``(Y, (q4, q8, scale))`` with ``debug`` (the activation codes the kernel computed)."""
     return _run().decode_linear(x, gamma, eps, reorder_idx, w_q4, w_q8, w_scale, group_size, clip, out, debug, bits)
 
@@ -392,7 +393,8 @@ def atom_w4a4_gemm(a_q4, a_q8, a_scale, w_q4, w_q8, w_scale, group_size: int = 1
     Sizes that gain from it pack both operands on the way, into
     ``atom_w4a4_gemm_scratch_bytes`` (up to 1 GiB): the caller's ``workspace``,
     or memory taken for the call where PyTorch's allocator has it without giving
-    back other blocks (under capture it stays in the graph's pool).  A
+    back other blocks (under torch.cuda.graph it stays in the graph's pool, in a
+    capture begun otherwise none is taken).  A
     ``workspace`` smaller than that, an empty one included, is left alone and
     keeps the call to the kernels for canonical operands, as does
     ``partials``.  The packed product adds all groups in one ascending run, the
