@@ -48,10 +48,10 @@ __host__ __device__ constexpr int wait_imm(int n) { return (n & 15) | (7 << 4) |
 template <int S>
 __device__ __forceinline__ v16f mfma_f6(const v12i &a, const v12i &b, v16f c)
 {
-    // cbsz = blgp = 3: both operands E3M2 (six registers each); scale bytes 127 = 2^0
+    // cbsz = blgp = 3: both operands E3M2 (six registers each); no scales: the form of the instruction without them
     const v8i a8 = __builtin_shufflevector(a, a, 6 * S, 6 * S + 1, 6 * S + 2, 6 * S + 3, 6 * S + 4, 6 * S + 5, -1, -1);
     const v8i b8 = __builtin_shufflevector(b, b, 6 * S, 6 * S + 1, 6 * S + 2, 6 * S + 3, 6 * S + 4, 6 * S + 5, -1, -1);
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, c, 3, 3, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, c, 3, 3, 0, 0, 0, 0);
 }
 
 // Order control.  MFMAs and fused multiply-adds have no side effects, so instruction selection
@@ -70,7 +70,7 @@ __device__ __forceinline__ v16f mfma_f6(const v12i &a, const v12i &b, v16f c)
 __device__ __forceinline__ void dma16(uint32_t lds, uint32_t voff, const uint8_t *base)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(lds), "v"(voff), "s"(base) : "memory", "m0");
+                 :: "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(voff), "s"(base) : "memory", "m0");
 }
 
 // The same for the lanes of a (uniform) mask only; every lane of the wavefront is active around it.
@@ -79,12 +79,12 @@ __device__ __forceinline__ void dma16_masked(uint32_t lds, uint32_t voff, const 
     const uint64_t m = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(mask >> 32)) << 32 |
                        (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)mask);
     asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1"
-                 :: "s"(lds), "v"(voff), "s"(base), "s"(m) : "memory", "m0");
+                 :: "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(voff), "s"(base), "s"(m) : "memory", "m0");
 }
 
 // The kernels for one INT8 group and at least seven INT4 groups, with at least a tile's units of either operand:
 // few tiles (atom_gemm_f6_thin.hip; tile 0: 64 x 64, 1: 64 x 128, 2: 128 x 128) and many (atom_gemm_f6_walk.hip; tile 0:
-// 128 x 128, 1: 256 x 128).
+// 128 x 128, 1: 256 x 128, 2: 256 x 192, 3: 128 x 384, 4: 256 x 256).
 hipError_t launch_thin(const F6Params &p, int tile, hipStream_t stream);
 hipError_t launch_walk(const F6Params &p, int tile, hipStream_t stream);
 

@@ -595,9 +595,11 @@ hipError_t launch_f6_cfg(const F6Params &p, hipStream_t stream)
 
 namespace atom_internal {
 
-// Tile of a launch: 0, 1, 2 = thin 64 x 64, 64 x 128, 128 x 128; 3, 4 = walking 128 x 128, 256 x 128; -1: the general
-// kernel.  The estimate is the time per INT4 group in units of 10 ns: rounds of tiles over the compute units times what a
-// tile's step takes.  Thin tiles win where large ones leave compute units without work; beyond the first round (64 x 64: the
+// Tile of a launch: 0, 1, 2 = thin 64 x 64, 64 x 128, 128 x 128; 3 to 7 = walking 128 x 128, 256 x 128, 256 x 192, 128 x 384,
+// 256 x 256; -1: the general kernel.
+//
+// Among the first five the estimate is the time per INT4 group in units of 10 ns: rounds of tiles over the compute units times
+// what a tile's step takes.  Thin tiles win where large ones leave compute units without work; beyond the first round (64 x 64: the
 // third) they pay prologue and store in the open and fetch more bytes per multiply-add than the walking ones.  Two lines
 // beside that, both at K = 4096 / 11008, weights from HBM:
 //   * 128 x 128 with hardly more tiles than compute units: the few that share one cost less than a full second round (M = 384,
@@ -607,8 +609,33 @@ namespace atom_internal {
 //   * three units of rows: the general kernel leaves the fourth unit of its two rows of tiles out of its requests, the walking one
 //     moves the last tile back and fetches three units twice (M = 192, K = 8192, N = 28672: 66.6 us, walking 71.9; N = 57344:
 //     130 / 139).
-// Every tile on 83 sizes, and what the rule takes: profiles/w4a4_gemm_f6_tiles.txt.
-static int pick_tile(int64_t au, int64_t wu, int64_t cus, int64_t *what = nullptr)
+//
+// Against that tile stand the three wide ones, which fetch fewer bytes per multiply-add and cover the output in fewer
+// rounds, by an estimate of the whole time (fit_us): a launch, prologue, INT8 group and store of each round, and the steps of the
+// full rounds and of the last one, which is faster the fewer of its compute units have a tile.  Fitted to 544 sizes (M = 65 to 4096,
+// K = 2688 to 14336, N = 1000 to 28672): taken at 158 of them, where the time is 0.73 to 1.04 of the other tile's (at 4 above 1.01); over
+// all of M > 256 the geometric mean is 0.95, and 0.1 % behind the best of the two sides.  With fewer than twenty groups the
+// wide tiles' prologues and stores take what their steps gain (16 groups, M = 2304, N = 8200: 47.7 us on 128 x 128, 50.2 at best on
+// a wide one; seven, M = 1100, N = 16300: 32.4, 33.8; M = 1700, N = 2870: 15.3, 17.7).
+// Every tile on these sizes and what the rule takes: profiles/w4a4_gemm_f6_tiles.txt.
+struct TileTime { int ua, uw, round, full, part, share; };        // ns of a round, and per group of a full one, of a part of one, and by its share
+
+// Estimated time of a launch in ns.  128 x 128 tiles walk two to a compute unit, so a full round is two of them to each, and
+// there is a line for a last round of up to one and one of more.
+static int64_t fit_ns(int tile, int64_t au, int64_t wu, int64_t G4, int64_t cus)
+{
+    static const TileTime time[8] = {
+        {1, 1, 0, 180, 130, 80}, {1, 2, 0, 340, 220, 140}, {2, 2, 1000, 510, 360, 110}, {2, 2, 3400, 770, 440, 50},
+        {4, 2, 4700, 700, 510, 240}, {4, 3, 6700, 1080, 650, 340}, {2, 6, 6500, 1060, 780, 220}, {4, 4, 6100, 1330, 860, 300}};
+    const TileTime &t = time[tile];
+    const int64_t tiles = ((au + t.ua - 1) / t.ua) * ((wu + t.uw - 1) / t.uw), slots = tile == 3 ? 2 * cus : cus;
+    const int64_t full = tiles / slots, rest = tiles % slots;
+    const int64_t last = rest == 0 ? 0 : rest > cus ? 710 + 250 * (rest - cus) / cus : t.part + t.share * rest / cus;
+    return 4000 + (full + (rest != 0)) * t.round + G4 * (full * t.full + last);
+}
+
+// `us`: the estimate of the tile taken, operands out of the last-level cache.
+static int pick_tile(int64_t au, int64_t wu, int64_t G4, int64_t cus, float *us = nullptr)
 {
     struct { int ua, uw, rounds, first, more; } const tile[5] = {
         {1, 1, 3, 13, 21}, {1, 2, 1, 21, 37}, {2, 2, 1, 37, 60}, {2, 2, 1, 45, 0}, {4, 2, 1, 79, 79}};
@@ -624,15 +651,29 @@ static int pick_tile(int64_t au, int64_t wu, int64_t cus, int64_t *what = nullpt
                                     : n * tile[i].more;
         if (cost < least) { least = cost; best = i; }
     }
-    if (what) *what = least;
-    return best == 3 && au == 3 ? -1 : best;
+    if (us) *us = 5.0f + 0.0093f * (float)least * (float)(G4 + 2);
+    const bool general = best == 3 && au == 3;
+    if (G4 >= 20 && best >= 0) {
+        int64_t ns = fit_ns(best, au, wu, G4, cus);
+        for (int i = 5; i < 8; ++i) {
+            static const int ua[3] = {4, 2, 4}, uw[3] = {3, 6, 4};
+            if (au < ua[i - 5] || wu < uw[i - 5]) continue;
+            const int64_t wide = fit_ns(i, au, wu, G4, cus);
+            if (wide < ns) { ns = wide; best = i; }
+        }
+        if (best >= 5) {
+            if (us) *us = 1.0f + 0.001f * (float)ns;
+            return best;
+        }
+    }
+    return general ? -1 : best;
 }
 
 // The same for the sizes of a call without a dump; -1: the general kernel.
 static int tile_of_launch(int64_t M, int64_t N, int K, int O, int64_t cus)
 {
     const int G4 = (K - O) >> 7, G8 = O >> 7;
-    return G8 == 1 && G4 >= 7 ? pick_tile((M + 63) / 64, (N + 63) / 64, cus) : -1;
+    return G8 == 1 && G4 >= 7 ? pick_tile((M + 63) / 64, (N + 63) / 64, G4, cus) : -1;
 }
 
 size_t f6_packed_bytes(int64_t rows, int K, int O)
@@ -685,9 +726,9 @@ float f6_product_us(int64_t M, int64_t N, int K, int O, int64_t cus)
 {
     const int G4 = (K - O) >> 7;
     if (O != 128 || G4 < 7) return 0.0f;
-    int64_t cost;
-    pick_tile((M + 63) / 64, (N + 63) / 64, cus, &cost);
-    return 5.0f + 0.0093f * (float)cost * (float)(G4 + 2);       // (operands that were just written: out of the last-level cache)
+    float us;
+    pick_tile((M + 63) / 64, (N + 63) / 64, G4, cus, &us);
+    return us;                                                   // (operands that were just written: out of the last-level cache)
 }
 
 hipError_t launch_f6_gemm(const void *a_pk, int64_t M, const void *w_pk, int64_t N, int K, int O, void *y,
