@@ -483,25 +483,30 @@ void w4a4_gemm_decode16_kernel(const GemmParams p)
 
 constexpr int kResidentRows = 32;           // rows of a workgroup of the next kernel
 
-// Many blocks of channels per compute unit, 17 to 64 rows, K from 3840 to 8192 (30 to 64 groups): a workgroup takes 32 rows and a
+// Many blocks of channels per compute unit, 17 to 64 rows, K from 3840 to 8192 (30 to 64 groups): a workgroup takes 16 RB rows and a
 // run of channel blocks, and every wavefront keeps the activation operand of its K-slice (NBK blocks of four groups, or one less) in
 // registers for all of them.  w4a4_gemm_decode16_kernel reads the activations again for each block or two, more bytes from the L2 than
 // the weights are, and every workgroup pays its own start and its own meeting of slices; here only weights stream, those of
 // the next two blocks in flight while one is multiplied.  Same sums in the same order: the same bits.
-// Canonical weights from memory, us, that kernel and this one: K = 4096: M = 32, N = 22016 17.1 / 14.5; M = 64, N = 8999
-// 14.9 / 11.1, 22016 22.8 / 20.4; K = 5120, N = 27648: M = 32 27.8 / 24.8, M = 64 42.7 / 38.3; K = 8192: M = 20, N = 57344
-// 71.7 / 55.5, M = 64, N = 9000 27.2 / 20.9.  What bounds it now: the weights (9.0 us for 22016 x 4096 when only read) behind a
-// start of 4 us in which the activations arrive, and at 64 rows the two passes over the weights.  64 rows per workgroup read
-// them once, but the widening for twice the rows stands in the way (N = 22016 21.1); weights three blocks ahead: no faster.
+// With one block of groups per wavefront (K up to 4096) the operand is kept widened to bytes: the widening is 24 of the 60 vector
+// instructions of a group and 32 rows, and paid for each block of channels it kept 64 rows from one pass over the weights.  Canonical weights
+// from memory, K = 4096, us, widened for every block (two sets of 32 rows beyond 32) and kept: N = 22016: M = 17 15.2 / 14.3, 32 15.8 / 15.0,
+// 40 20.4 / 16.6, 64 21.0 / 19.0; N = 28672: M = 40 25.0 / 19.2, 64 25.6 / 21.3; N = 11008: M = 33 12.2 / 10.5.  K = 3840 (TAIL = 1) with 32 rows
+// is as fast either way with few rows and 3 % slower with all 32 (N = 28672 18.1 / 18.6): not kept there.
+// K = 8192 has no registers for it (two row blocks spill 44): widened for every block.  w4a4_gemm_decode16_kernel and this one: M = 20,
+// N = 57344 71.7 / 55.5, M = 64, N = 9000 27.2 / 20.9.
+// What bounds it now: the weights (9.0 us for 22016 x 4096 when only read; 4.4 TB/s by the slope over N) behind a start of 5 us with 32 rows
+// and 7 with 64 in which the activations arrive.  The first block's weights requested ahead of the activations: 1 us slower.  Weights
+// three blocks ahead: no faster.
 // A wavefront with one block where others have two (K from 4352 to 7680) is code of its own and requests only what it uses.  (With a
 // second request of its first block in the missing one's place six of eight wavefronts read their weights twice at K = 5120:
 // M = 33, N = 13824 22.8 us, 20.3 so, w4a4_gemm_decode16_kernel 22.6; M = 32, N = 16400 19.5, 17.7, 18.3; K = 4352, M = 33, N = 13824
 // 22.1, 16.6, 19.3.)
-template <int NBK, int TAIL>
+template <int RB, int NBK, int TAIL>
 __global__ __launch_bounds__(NT, 2)
 void w4a4_gemm_decode_resident_kernel(const GemmParams p)
 {
-    constexpr int RB = kResidentRows / 16;
+    constexpr bool KEEP = NBK == 1 && (RB > 2 || TAIL == 3);   // the widened activations stay
     // [parity of the pair of channel blocks][which of the pair][K-slice][row block, lane, register]
     constexpr int RED = RB * 256;
     __shared__ __align__(16) float red[4 * NW * RED];
@@ -581,12 +586,23 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
         __builtin_amdgcn_sched_barrier(0);
         fetch(wb, first + 1);
         __builtin_amdgcn_sched_barrier(0);
-        if (kc != 0) {                                    // k-slots 4 .. 15 of the scale MFMA stay empty
+        // (KEEP: widened once, for all channel blocks)
+        v4i xa[NB][RB][4][KEEP ? 2 : 1];
+        auto widened = [&](int j, int rb, int d, int half) __attribute__((always_inline)) -> v4i {
+            if (HAS8 && j == NB - 1 && d == TAIL) return __builtin_bit_cast(v4i, half ? ax[rb] : aq[j][rb][d]);
+            return half ? widen_hi(aq[j][rb][d]) : widen_lo(aq[j][rb][d]);
+        };
 #pragma unroll
-            for (int j = 0; j < NB; ++j)
+        for (int j = 0; j < NB; ++j)
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb) avs[j][rb] = make_uint2(0, 0);
-        }
+            for (int rb = 0; rb < RB; ++rb) {
+                if (kc != 0) avs[j][rb] = make_uint2(0, 0);       // k-slots 4 .. 15 of the scale MFMA stay empty
+                if constexpr (KEEP)
+#pragma unroll
+                    for (int d = 0; d < ng4(j) + (HAS8 && j == NB - 1 ? 1 : 0); ++d)
+#pragma unroll
+                        for (int half = 0; half < 2; ++half) xa[j][rb][d][half] = widened(j, rb, d, half);
+            }
 
         auto step = [&](Weights &w, int blk, int slot_of) __attribute__((always_inline)) {
             float acc[RB][4];
@@ -594,16 +610,17 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
             for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[rb][e] = 0.0f;
-            // (the widened codes are made again for every block: hoisted out of the loop they would take twice the registers)
+            if constexpr (!KEEP) {                        // (hoisted out of the loop the widened codes would take twice the registers)
 #pragma unroll
-            for (int j = 0; j < NB; ++j)
+                for (int j = 0; j < NB; ++j)
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb) {
+                    for (int rb = 0; rb < RB; ++rb) {
 #pragma unroll
-                    for (int d = 0; d < ng4(j); ++d)
-                        asm volatile("" : "+v"(aq[j][rb][d].x), "+v"(aq[j][rb][d].y), "+v"(aq[j][rb][d].z), "+v"(aq[j][rb][d].w));
-                    asm volatile("" : "+v"(avs[j][rb].x), "+v"(avs[j][rb].y));
-                }
+                        for (int d = 0; d < ng4(j); ++d)
+                            asm volatile("" : "+v"(aq[j][rb][d].x), "+v"(aq[j][rb][d].y), "+v"(aq[j][rb][d].z), "+v"(aq[j][rb][d].w));
+                        asm volatile("" : "+v"(avs[j][rb].x), "+v"(avs[j][rb].y));
+                    }
+            }
             auto group = [&](auto jc, auto dc) __attribute__((always_inline)) {
                 constexpr int J = decltype(jc)::value, D = decltype(dc)::value;
                 constexpr bool INT8 = HAS8 && J == NB - 1 && D == TAIL;
@@ -612,8 +629,7 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
                 const uint2 ws = kc != 0 ? make_uint2(0, 0) : w.s[J];
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) {
-                    const v4i x0 = INT8 ? __builtin_bit_cast(v4i, aq[J][rb][D]) : widen_lo(aq[J][rb][D]);
-                    const v4i x1 = INT8 ? __builtin_bit_cast(v4i, ax[rb]) : widen_hi(aq[J][rb][D]);
+                    const v4i x0 = KEEP ? xa[J][rb][D][0] : widened(J, rb, D, 0), x1 = KEEP ? xa[J][rb][D][KEEP ? 1 : 0] : widened(J, rb, D, 1);
                     v4i c = __builtin_amdgcn_mfma_i32_16x16x64_i8(x0, b0, zi, 0, 0, 0);
                     c = __builtin_amdgcn_mfma_i32_16x16x64_i8(x1, b1, c, 0, 0, 0);
                     const v4f32 sc = __builtin_amdgcn_mfma_f32_16x16x16f16(scale_operand<D>(avs[J][rb]), scale_operand<D>(ws), zf, 0, 0, 0);
@@ -701,12 +717,23 @@ bool resident(int64_t M, int64_t N, int K, int64_t cus)
     return M > 16 && M <= 64 && nblk >= NW && nblk <= 2 * NW && blocks * sets > 4 * cus;
 }
 
+// Beyond 32 rows a workgroup takes all of them (K up to 4096), or there are two sets of workgroups of 32 rows each.  A lone set reads the
+// weights once but starts later (three or four blocks of rows to fetch and widen), and the blocks of channels of a compute unit
+// are whole numbers, one and two of them to the same N: fitted, K = 4096, us, 4.2 + 2.2 n for 33 to 48 rows and 4.5 + 2.45 n
+// beyond, n the most blocks that a workgroup has, and 1.6 + 1.78 n for two sets.  Measured at M = 64, one set and two: N = 8208 11.4 / 10.1,
+// 10000 12.2 / 10.9, 12288 12.3 / 11.9, 14000 14.2 / 13.5, 16384 14.4 / 15.9; at M = 33: 10.1 / 9.7, 10.5 / 10.2, 10.7 / 11.2, 12.0 / 12.6, 12.9 / 15.2.
 template <int TAIL>
 void launch_resident(const GemmParams &p, hipStream_t stream)
 {
-    const unsigned sets = (unsigned)((p.M + kResidentRows - 1) / kResidentRows);
-    auto kern = p.K <= 512 * NW ? &w4a4_gemm_decode_resident_kernel<1, TAIL> : &w4a4_gemm_decode_resident_kernel<2, TAIL>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)atom_launch::compute_units() / sets, sets), dim3(NT), 0, stream, p);   // (fewer workgroups than blocks: every one has some)
+    const int64_t cus = atom_launch::compute_units(), blocks = (p.N + TN - 1) / TN;
+    const int64_t one = (blocks + cus - 1) / cus, two = (blocks + cus / 2 - 1) / (cus / 2);
+    const bool    split = p.M > 32 && (p.K > 512 * NW || 160 + 178 * two < (p.M <= 48 ? 420 + 220 * one : 450 + 245 * one));
+    const unsigned sets = split ? 2 : 1;
+    auto kern = p.K > 512 * NW        ? &w4a4_gemm_decode_resident_kernel<2, 2, TAIL>
+              : p.M <= 32 || split    ? &w4a4_gemm_decode_resident_kernel<2, 1, TAIL>
+              : p.M <= 48             ? &w4a4_gemm_decode_resident_kernel<3, 1, TAIL>
+                                      : &w4a4_gemm_decode_resident_kernel<4, 1, TAIL>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)cus / sets, sets), dim3(NT), 0, stream, p);                // (fewer workgroups than blocks: every one has some)
 }
 
 // The kernels of the common case: M <= 16 staged, else blocks of 16 rows.

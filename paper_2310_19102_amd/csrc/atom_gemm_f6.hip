@@ -614,7 +614,7 @@ namespace atom_internal {
 // rounds, by an estimate of the whole time (fit_us): a launch, prologue, INT8 group and store of each round, and the steps of the
 // full rounds and of the last one, which is faster the fewer of its compute units have a tile.  Fitted to 544 sizes (M = 65 to 4096,
 // K = 2688 to 14336, N = 1000 to 28672): taken at 158 of them, where the time is 0.73 to 1.04 of the other tile's (at 4 above 1.01); over
-// all of M > 256 the geometric mean is 0.95, and 0.1 % behind the best of the two sides.  With fewer than twenty groups the
+// all of M > 256 the geometric mean is 0.95, and 0.1 % behind the best of the two sides.  With up to sixteen groups the
 // wide tiles' prologues and stores take what their steps gain (16 groups, M = 2304, N = 8200: 47.7 us on 128 x 128, 50.2 at best on
 // a wide one; seven, M = 1100, N = 16300: 32.4, 33.8; M = 1700, N = 2870: 15.3, 17.7).
 // Every tile on these sizes and what the rule takes: profiles/w4a4_gemm_f6_tiles.txt.
@@ -653,7 +653,7 @@ static int pick_tile(int64_t au, int64_t wu, int64_t G4, int64_t cus, float *us 
     }
     if (us) *us = 5.0f + 0.0093f * (float)least * (float)(G4 + 2);
     const bool general = best == 3 && au == 3;
-    if (G4 >= 20 && best >= 0) {
+    if (G4 >= 17 && best >= 0) {
         int64_t ns = fit_ns(best, au, wu, G4, cus);
         for (int i = 5; i < 8; ++i) {
             static const int ua[3] = {4, 2, 4}, uw[3] = {3, 6, 4};
