@@ -336,6 +336,8 @@ hipError_t launch_tile(const MxParams &p, hipStream_t stream)
 // slower; TN = 9 and 11 were within 3 % of 10 and 12.)
 // In turn on one card, us, the best of the tiles above and this kernel, weights from memory: M = 1024, K = 4096, N = 22016 64.5, 52.1 (TN = 12);
 // M = 1300, N = 13824 52.4, 47.4; M = 2048, N = 10000 58.0, 48.0 (TN = 10); M = 1700, K = 14336, N = 11264 158.7, 134.1; M = 4096, N = 12288 110.6, 104.8.
+// (16 x 16 x 128 MFMAs instead take a tenth less power and turn as fast, operands in registers; here, 0.97 to 1.03 of the time: half as long, they leave half
+// the room for what stands between them.)
 template <int TN>
 struct MxWide {
     static constexpr int TM    = 2, CN = TN / 2, WM = 4;   // blocks of rows and of columns of a wavefront, wavefronts side by side in M
@@ -432,28 +434,26 @@ void mx_gemm_wide_kernel(MxParams p)
 
     const int wm = wave % WM, wn = wave / WM;
     const int a_base = mx_lds_off(32 * TM * wm + lr, g), b_base = mx_lds_off(BM + 32 * CN * wn + lr, g);
-    const int sa_off = Gm::CODES + 4 * (32 * TM * wm + lr), sb_off = Gm::CODES + 4 * (BM + 32 * CN * wn + lr);
+    // A scale is read as a byte alone, the block's of its half: shifted out of its dword it would be waited for behind every fragment's
+    // read, not where its MFMA stands (M = 1024, K = 4096, N = 22016
+    // 52.2 us, so 50.8; M = 3000 147.8, 141.9; M = 1700, K = 14336, N = 11264 134.2, 132.3)
+    const int sa_off = Gm::CODES + 4 * (32 * TM * wm + lr) + g, sb_off = Gm::CODES + 4 * (BM + 32 * CN * wn + lr) + g;
     struct Frag { v4i b; int s; };
     auto read_frag = [&](const uint8_t *buf, int i) __attribute__((always_inline)) -> Frag {       // i = CN * half + block of columns
         const int half = i / CN, t = i % CN;
         return {*reinterpret_cast<const v4i *>(buf + ((half ? b_base ^ 32 : b_base) + 2048 * t)),
-                (int)(*reinterpret_cast<const uint32_t *>(buf + sb_off + 128 * t) >> (8 * g))};
+                (int)buf[sb_off + 128 * t + 2 * half]};
     };
-    struct Rows { v4i a[TM]; };
+    struct Rows { v4i a[TM]; int s[TM]; };
     auto read_rows = [&](const uint8_t *buf, int half) __attribute__((always_inline)) -> Rows {
         Rows x;
 #pragma unroll
-        for (int r = 0; r < TM; ++r) x.a[r] = *reinterpret_cast<const v4i *>(buf + ((half ? a_base ^ 32 : a_base) + 2048 * r));
+        for (int r = 0; r < TM; ++r) {
+            x.a[r] = *reinterpret_cast<const v4i *>(buf + ((half ? a_base ^ 32 : a_base) + 2048 * r));
+            x.s[r] = (int)buf[sa_off + 128 * r + 2 * half];
+        }
         return x;
     };
-    struct RowScales { int s[TM]; };
-    auto read_sa = [&](const uint8_t *buf) __attribute__((always_inline)) -> RowScales {
-        RowScales x;
-#pragma unroll
-        for (int r = 0; r < TM; ++r) x.s[r] = (int)(*reinterpret_cast<const uint32_t *>(buf + sa_off + 128 * r) >> (8 * g));
-        return x;
-    };
-
     // Step u: tile u is in stage u % 3.  At its start stage (u - 1) % 3 has been read by everyone and is refilled with tile u + 2; before its
     // end tile u + 1 has landed.
     int cur = 0;
@@ -473,7 +473,8 @@ void mx_gemm_wide_kernel(MxParams p)
     bool started = false;                                  // (the first step has nothing to refill)
 
     // ---- FP8 steps, in pairs that share their scales
-    auto fp8_step = [&](auto opsel) __attribute__((always_inline)) {
+    auto fp8_step = [&](auto second) __attribute__((always_inline)) {            // (of a pair: its scales are the second half of the dword)
+        constexpr int HALF = decltype(second)::value;
         if (started) {
             const Src s = src_of(min(u + 2, S - 1));
 #pragma unroll
@@ -482,14 +483,13 @@ void mx_gemm_wide_kernel(MxParams p)
         started = true;
         const uint8_t *buf = smem + cur * STAGE;
         const Rows lo = read_rows(buf, 0), hi = read_rows(buf, 1);
-        const RowScales sa = read_sa(buf);
 #pragma unroll
         for (int t = 0; t < CN; ++t) {
-            const Frag x = read_frag(buf, t);
-            const v8i b = join(x.b, *reinterpret_cast<const v4i *>(buf + ((b_base ^ 32) + 2048 * t)));
+            const Frag x = read_frag(buf, t), y = read_frag(buf, CN + t);
+            const v8i b = join(x.b, y.b);
 #pragma unroll
             for (int r = 0; r < TM; ++r) {
-                acc[r][t] = mfma_mx<0, decltype(opsel)::value>(b, join(lo.a[r], hi.a[r]), acc[r][t], x.s, sa.s[r]);
+                acc[r][t] = mfma_mx<0, 0>(b, join(lo.a[r], hi.a[r]), acc[r][t], HALF ? y.s : x.s, HALF ? hi.s[r] : lo.s[r]);
                 ATOM_F6_PIN(acc[r][t]);
             }
             if (t % 2 == 1) ATOM_F6_SLOT_END();            // (not all fragments of the step in registers at once)
@@ -498,7 +498,7 @@ void mx_gemm_wide_kernel(MxParams p)
     };
     while (u < S8) {
         fp8_step(std::integral_constant<int, 0>{});
-        fp8_step(std::integral_constant<int, 2>{});
+        fp8_step(std::integral_constant<int, 1>{});
     }
 
     // ---- FP4 steps
@@ -506,11 +506,9 @@ void mx_gemm_wide_kernel(MxParams p)
     constexpr int SLOTS = TM * (LASTREAD + 1);                                   // the requests stand behind these MFMAs
     Frag f[RING];
     Rows a0, a1;
-    RowScales sa;
     {
         const uint8_t *buf = smem + cur * STAGE;
         a0 = read_rows(buf, 0);
-        sa = read_sa(buf);
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) f[i] = read_frag(buf, i);
     }
@@ -520,14 +518,13 @@ void mx_gemm_wide_kernel(MxParams p)
         constexpr int ST = decltype(start)::value;
         const uint8_t *buf = smem + cur * STAGE;
         a1 = read_rows(buf, 1);
-        RowScales sa_next = sa;
 #pragma unroll
         for (int i = 0; i < NF; ++i) {
             const Frag &x = f[(ST + i) % RING];
 #pragma unroll
             for (int r = 0; r < TM; ++r) {
-                if (i < CN) acc[r][i % CN] = mfma_mx<4, 0>(widen(x.b), widen(a0.a[r]), acc[r][i % CN], x.s, sa.s[r]);
-                else        acc[r][i % CN] = mfma_mx<4, 2>(widen(x.b), widen(a1.a[r]), acc[r][i % CN], x.s, sa.s[r]);
+                if (i < CN) acc[r][i % CN] = mfma_mx<4, 0>(widen(x.b), widen(a0.a[r]), acc[r][i % CN], x.s, a0.s[r]);
+                else        acc[r][i % CN] = mfma_mx<4, 0>(widen(x.b), widen(a1.a[r]), acc[r][i % CN], x.s, a1.s[r]);
                 ATOM_F6_PIN(acc[r][i % CN]);
                 if (r == 0 && i + AHEAD < NF) f[(ST + i + AHEAD) % RING] = read_frag(buf, i + AHEAD);
 #pragma unroll
@@ -538,12 +535,10 @@ void mx_gemm_wide_kernel(MxParams p)
             if (i == LASTREAD + 1) {
                 next_stage();
                 a0 = read_rows(smem + cur * STAGE, 0);
-                sa_next = read_sa(smem + cur * STAGE);
             }
             if (i > LASTREAD) f[(ST + NF + i - LASTREAD - 1) % RING] = read_frag(smem + cur * STAGE, i - LASTREAD - 1);    // of the next step
             __builtin_amdgcn_sched_barrier(0);
         }
-        sa = sa_next;
         if (u + 2 < S) { ahead.a += p.M * ROWB; ahead.w += p.N * ROWB; ahead.ae += p.M * 4; ahead.we += p.N * 4; }
     };
     auto steps = [&](auto self, auto k) __attribute__((always_inline)) -> bool {       // RING steps, or to the end
