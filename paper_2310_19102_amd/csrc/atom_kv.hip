@@ -104,20 +104,45 @@ __device__ __forceinline__ float max_across_chunks(float v, unsigned zero)
     return fmaxf(__builtin_bit_cast(float, r[0]), __builtin_bit_cast(float, other));
 }
 
-// the same exchange for a sum: v(l) + v(l ^ 16), then that + its l ^ 32 partner (the order of
-// the two ds_bpermute exchanges it replaces: float addition commutes, the result is bit-identical)
-__device__ __forceinline__ float sum_across_chunks(float v, unsigned zero)
+// One step of a reduction of four values over the lanes l, l ^ 16, l ^ 32, l ^ 48, each result in one chunk of lanes: a's own and
+// its partner row's (half's) value in the rows (the half) that keep a, likewise b's in the others, to be added or compared.
+struct Two { float mine, other; };
+template <int WIDTH>
+__device__ __forceinline__ Two swap_two(float a, float b)
 {
     typedef unsigned v2ui __attribute__((ext_vector_type(2)));
-    unsigned u = __builtin_bit_cast(unsigned, v);
-    v2ui r = __builtin_amdgcn_permlane16_swap(u, u | zero, false, false);
-    unsigned other = r[1];
-    asm volatile("" : "+v"(other));
-    u = __builtin_bit_cast(unsigned, __builtin_bit_cast(float, r[0]) + __builtin_bit_cast(float, other));
-    r = __builtin_amdgcn_permlane32_swap(u, u | zero, false, false);
-    other = r[1];
-    asm volatile("" : "+v"(other));
-    return __builtin_bit_cast(float, r[0]) + __builtin_bit_cast(float, other);
+    const unsigned ua = __builtin_bit_cast(unsigned, a), ub = __builtin_bit_cast(unsigned, b);
+    v2ui r;
+    if constexpr (WIDTH == 16) r = __builtin_bit_cast(v2ui, __builtin_amdgcn_permlane16_swap(ua, ub, false, false));
+    else                       r = __builtin_bit_cast(v2ui, __builtin_amdgcn_permlane32_swap(ua, ub, false, false));
+    unsigned second = r[1];
+    asm volatile("" : "+v"(second));      // (as in max_across_chunks)
+    return {__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, second)};
+}
+template <int WIDTH>
+__device__ __forceinline__ float swap_max(float a, float b) { const Two t = swap_two<WIDTH>(a, b); return fmaxf(t.mine, t.other); }
+template <int WIDTH>
+__device__ __forceinline__ float swap_add(float a, float b) { const Two t = swap_two<WIDTH>(a, b); return t.mine + t.other; }
+
+// The way back: o[i] = the value of lane 16 i + (l & 15) in every lane l.
+__device__ __forceinline__ void spread(float v, float (&o)[4])
+{
+    typedef unsigned v2ui __attribute__((ext_vector_type(2)));
+    unsigned u = __builtin_bit_cast(unsigned, v), w = u;
+    asm volatile("" : "+v"(w));           // (two registers: a swap exchanges parts of them)
+    const v2ui r = __builtin_bit_cast(v2ui, __builtin_amdgcn_permlane32_swap(u, w, false, false));
+    unsigned a = r[0], b = r[1];
+    asm volatile("" : "+v"(b));           // (as in max_across_chunks)
+    unsigned a2 = a, b2 = b;
+    asm volatile("" : "+v"(a2), "+v"(b2));
+    const v2ui x = __builtin_bit_cast(v2ui, __builtin_amdgcn_permlane16_swap(a, a2, false, false));
+    const v2ui y = __builtin_bit_cast(v2ui, __builtin_amdgcn_permlane16_swap(b, b2, false, false));
+    unsigned x1 = x[1], y1 = y[1];
+    asm volatile("" : "+v"(x1), "+v"(y1));
+    o[0] = __builtin_bit_cast(float, (unsigned)x[0]);
+    o[1] = __builtin_bit_cast(float, x1);
+    o[2] = __builtin_bit_cast(float, (unsigned)y[0]);
+    o[3] = __builtin_bit_cast(float, y1);
 }
 
 // value i (0..31) of the 32 fp16 numbers held by four 16-byte registers (i known at compile time)
@@ -151,18 +176,25 @@ constexpr int kTokens = 64;                // tokens per wavefront group: four s
 //   scores  : the codes become fp16 offset + c, two at a time (unpack8), and meet the
 //             matching pairs of q in v_dot2_f32_f16 (fp32 accumulate); the offsets and the
 //             zero point leave as sum(offset * q) + z * sum(q) per chunk (offsets of 16 and
-//             256 keep the cancellation in fp32 harmless); the four chunks of a token are
-//             added across lanes; then * scale * sm_scale.
-//   softmax : online, per wavefront (running max m and sum l); the accumulators are rescaled
+//             256 keep the cancellation in fp32 harmless); all four steps first, then the four chunks of a
+//             token are added across lanes such that lane l ends with token l of the group, where its scales are;
+//             then * scale * sm_scale.
+//   softmax : online, per wavefront (running max m and sum l), in the order of the steps, but the maxima, weights and sums of the
+//             four steps are found together and spread to the lanes afterwards; the accumulators are rescaled
 //             only when the maximum moves.
 //   values  : acc[d] += w * (16 + code[d]) with w = p * v_scale (unpack8_16), the fp16 codes
 //             read by mixed-precision fmas; the 16 and the zero points leave once per group
 //             of 64 tokens through the sums of w and w * z; the 16 tokens of the lanes meet
-//             once, at the end; the wavefronts merge through LDS.
+//             once, at the end, each half of them keeping half of the values; the wavefronts merge through LDS.
+//   What bounds it besides the memory: the vector instructions of a group, at four cycles each (two for fp32 additions and fused
+//             multiply-adds): of 2200 cycles 640 for the scores' codes and products and 1024 for the values'.  Against one step after the
+//             other with its own cross-lane work (32 heads, lengths from T / 4 to T, us): 64 x 1024 40.9 -> 39.8, 64 x 200 17.0 -> 16.2,
+//             128 x 512 42.8 -> 41.6, 64 x 2048 67.0 -> 66.3, 16 x 1024 19.5 -> 18.9, 8 x 1024 12.2 either way.  Same sums in the same
+//             order, the same bits.  (Codes as subnormal numbers, one shift and four ands for eight of them, and no offsets to take out:
+//             12 to 19 % faster and no less exact, but other roundings, which a decoder's next quantisation turns into other codes.)
 //   loads   : the codes of the next group (four steps ahead) are in flight while a step is
 //             computed.  Scales and zero points are read once per group, lane l taking
-//             token l of the 64, one full cache line per array, and reach the lane that
-//             needs them through ds_bpermute: 2-byte loads per step would have several
+//             token l of the 64, one full cache line per array: 2-byte loads per step would have several
 //             wavefronts wait on the same line, which stalls the vector cache.
 //             q is asked for before everything else: loads return in order, and a conversion of q that waits for the first
 //             rows as well delays every wavefront's first scores.  Lengths from T / 4 to T, us, q behind the rows and in
@@ -204,15 +236,12 @@ void decode_attention_kv4_kernel(const __half *__restrict__ q, int H, int Hkv, i
     const bool alive = G < g_end;                        // then T >= 1: clamped addresses are valid
     const int  t_last = min(T, g_end * kTokens) - 1;     // loads never leave this split's tokens
 
-    struct Stage { uint4 k, v; };
-    Stage st[4];
+    uint4 kst[4], vst[4];
     uint32_t kmeta = 0, vmeta = 0;        // scale bits | zero << 16 of token `lane` of the group
-    auto fetch = [&](Stage &s_, int tile) {
+    auto row_of = [&](int tile) -> uint32_t {
         int t = tile * kTile + tl;
         t = t <= t_last ? t : t_last;     // masked tokens and steps past the end repeat the last token
-        const uint32_t off = (uint32_t)t * (D / 2) + 16u * c;
-        s_.k = load_row<ONCE>(kb + off);
-        s_.v = load_row<ONCE>(vb + off);
+        return (uint32_t)t * (D / 2) + 16u * c;
     };
     auto fetch_meta = [&](int g, uint32_t &km, uint32_t &vm) {
         int t = g * kTokens + lane;
@@ -220,14 +249,15 @@ void decode_attention_kv4_kernel(const __half *__restrict__ q, int H, int Hkv, i
         km = (uint32_t)__half_as_ushort(ksb[(uint32_t)t]) | ((uint32_t)(uint16_t)kzb[(uint32_t)t] << 16);
         vm = (uint32_t)__half_as_ushort(vsb[(uint32_t)t]) | ((uint32_t)(uint16_t)vzb[(uint32_t)t] << 16);
     };
-    float acc[32];                        // acc[8j + 2k + half] <-> d = 32c + 8j + k + 4 half
-#pragma unroll
-    for (int i = 0; i < 32; ++i) acc[i] = 0.0f;
     float m_run = -INFINITY, l_run = 0.0f;
     if (alive) {                          // every first load leaves before any is waited for, q first: loads return in order
         fetch_meta(G, kmeta, vmeta);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) fetch(st[i], 4 * G + i);
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t off = row_of(4 * G + i);
+            kst[i] = load_row<ONCE>(kb + off);
+            vst[i] = load_row<ONCE>(vb + off);
+        }
         __builtin_amdgcn_sched_barrier(0);
         // this lane's 32 query values as 16 pairs in the order unpack8 delivers the codes of a
         // dword (dword j holds d = 32c + 8j + 0..7), and the sums that take the offsets back out
@@ -244,77 +274,98 @@ void decode_attention_kv4_kernel(const __half *__restrict__ q, int H, int Hkv, i
                     qoff += kOff[k] * (lo + hi);
                 }
         }
-
-        unsigned c_zero = 0u;                 // a zero the compiler cannot see (sum_across_chunks)
-        asm volatile("" : "+s"(c_zero));
-        float wsum = 0.0f, zacc = 0.0f;       // sums of w = p * v_scale and of w * v_zero since the last flush
-
-        auto consume = [&](const Stage &s_, int tile, int slot) {
-            // this token's scale and zero point sit in lane 16 * slot + tl
-            const int src = (16 * slot + tl) << 2;
-            const uint32_t km = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)kmeta);
-            const uint32_t vm = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)vmeta);
-
-            // ---- scores
-            const uint32_t kw[4] = {s_.k.x, s_.k.y, s_.k.z, s_.k.w};
-            float dot = 0.0f;
+        float acc[32];                    // acc[8j + 2k + half] <-> d = 32c + 8j + k + 4 half
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                uint32_t pr[4];
-                unpack8(kw[j], pr);
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    dot = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, pr[k]), qp[4 * j + k], dot, false);
-            }
-            const float k_s = __half2float(__ushort_as_half((unsigned short)(km & 0xFFFFu)));
-            const float k_z = (float)(int16_t)(km >> 16);
-            const float part_ = sum_across_chunks(dot - fmaf(k_z, qsum, qoff), c_zero);
-            const bool valid = tile * kTile + tl < T;
-            const float score = valid ? part_ * (k_s * sm_scale) : -INFINITY;
-
-            // ---- online softmax (every lane of the wavefront ends up with the same m and l)
-            const float m_new = fmaxf(m_run, row16_max(score));
-            if (m_new > m_run) {                              // rare after the first few steps
-                const float alpha = __expf(m_run - m_new);    // 0 on the first step
-                l_run *= alpha;
-                wsum *= alpha;
-                zacc *= alpha;
-#pragma unroll
-                for (int i = 0; i < 32; ++i) acc[i] *= alpha;
-                m_run = m_new;
-            }
-            const float p = __expf(score - m_run);
-            l_run += row16_sum(p);
-
-            // ---- values: the fp16 halves go straight into mixed-precision fmas
-            const float v_s = __half2float(__ushort_as_half((unsigned short)(vm & 0xFFFFu)));
-            const float v_z = (float)(int16_t)(vm >> 16);
-            const float wgt = p * v_s;
-            wsum += wgt;
-            zacc = fmaf(wgt, v_z, zacc);
-            const uint32_t vw[4] = {s_.v.x, s_.v.y, s_.v.z, s_.v.w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                uint32_t pr[4];
-                unpack8_16(vw[j], pr);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const h2 cv = __builtin_bit_cast(h2, pr[k]);
-                    acc[8 * j + 2 * k]     = fmaf(wgt, (float)cv[0], acc[8 * j + 2 * k]);
-                    acc[8 * j + 2 * k + 1] = fmaf(wgt, (float)cv[1], acc[8 * j + 2 * k + 1]);
-                }
-            }
-        };
+        for (int i = 0; i < 32; ++i) acc[i] = 0.0f;
 
         while (G < g_end) {
             const int Gn = G + kWaves;                    // past the end: clamped, unused loads
             uint32_t nk, nv;
             fetch_meta(Gn, nk, nv);
+            const int steps = (T - G * kTokens + kTile - 1) / kTile;      // those that hold tokens: four and more but for a sequence's last group
+            // ---- scores: every lane its chunk of head dimensions of token tl of each step ...
+            float dot[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            auto product = [&](int i) __attribute__((always_inline)) {
+                const uint32_t kw[4] = {kst[i].x, kst[i].y, kst[i].z, kst[i].w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    uint32_t pr[4];
+                    unpack8(kw[j], pr);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        dot[i] = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, pr[k]), qp[4 * j + k], dot[i], false);
+                }
+            };
+            product(0);
+            if (steps > 1) {
+                product(1);
+                product(2);
+                product(3);
+            }
+            uint32_t row[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {                 // the slot's next use is a group away (on every path: the compiler counts the loads in flight)
+                row[i] = row_of(4 * Gn + i);
+                kst[i] = load_row<ONCE>(kb + row[i]);
+            }
+            float kz[4];
+            spread((float)(int16_t)(kmeta >> 16), kz);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) dot[i] -= fmaf(kz[i], qsum, qoff);
+            // ... and the four chunks meet in lane 16 i + tl: lane l has token l of the group, as it has its scales
+            const float sum = swap_add<32>(swap_add<16>(dot[0], dot[1]), swap_add<16>(dot[2], dot[3]));
+            const float k_s = __half2float(__ushort_as_half((unsigned short)(kmeta & 0xFFFFu)));
+            const float score = G * kTokens + lane < T ? sum * (k_s * sm_scale) : -INFINITY;
+
+            // ---- online softmax, step by step (every lane of the wavefront has the same m and l)
+            float mx[4], m[5];
+            spread(row16_max(score), mx);
+            m[0] = m_run;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) m[i + 1] = fmaxf(m[i], mx[i]);
+            const bool  moved = m[4] > m_run;             // rare after the first groups; the same decision in every lane
+            const float m_lo = c & 1 ? m[2] : m[1], m_hi = c & 1 ? m[4] : m[3];
+            const float p = __expf(score - (c & 2 ? m_hi : m_lo));
+            float ps[4], alpha[4];
+            spread(row16_sum(p), ps);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int tile = 4 * G + i;
-                if (tile * kTile < T) consume(st[i], tile, i);
-                fetch(st[i], 4 * Gn + i);                 // the slot's next use is four steps away
+                alpha[i] = 1.0f;
+                if (moved) alpha[i] = m[i + 1] > m[i] ? __expf(m[i] - m[i + 1]) : 1.0f;   // 0 on the first step
+                l_run = l_run * alpha[i] + ps[i];
+            }
+            m_run = m[4];
+
+            // ---- values: the fp16 halves go straight into mixed-precision fmas
+            float w[4], vz[4];
+            spread(p * __half2float(__ushort_as_half((unsigned short)(vmeta & 0xFFFFu))), w);
+            spread((float)(int16_t)(vmeta >> 16), vz);
+            float wsum = 0.0f, zacc = 0.0f;               // sums of w = p * v_scale and of w * v_zero of this group
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (i == 0 || i < steps) {
+                    if (moved) {
+                        wsum *= alpha[i];
+                        zacc *= alpha[i];
+#pragma unroll
+                        for (int e = 0; e < 32; ++e) acc[e] *= alpha[i];
+                    }
+                    wsum += w[i];
+                    zacc = fmaf(w[i], vz[i], zacc);
+                    const uint32_t vw[4] = {vst[i].x, vst[i].y, vst[i].z, vst[i].w};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        uint32_t pr[4];
+                        unpack8_16(vw[j], pr);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const h2 cv = __builtin_bit_cast(h2, pr[k]);
+                            acc[8 * j + 2 * k]     = fmaf(w[i], (float)cv[0], acc[8 * j + 2 * k]);
+                            acc[8 * j + 2 * k + 1] = fmaf(w[i], (float)cv[1], acc[8 * j + 2 * k + 1]);
+                        }
+                    }
+                }
+                vst[i] = load_row<ONCE>(vb + row[i]);
             }
             // the offsets of this group's four steps leave the accumulators now, not at the end:
             // left in, their sum grows with the sequence and its rounding would show in
@@ -322,25 +373,31 @@ void decode_attention_kv4_kernel(const __half *__restrict__ q, int H, int Hkv, i
             const float off = fmaf(16.0f, wsum, zacc);
 #pragma unroll
             for (int i = 0; i < 32; ++i) acc[i] -= off;
-            wsum = 0.0f;
-            zacc = 0.0f;
             kmeta = nk;
             vmeta = nv;
             G = Gn;
         }
-    }
 
-    // ---- the 16 tokens of the lanes meet; lane (0, c) then holds chunk c of this wavefront
+        // ---- the 16 tokens of the lanes meet, half of the values at a time in each half of them: lanes that differ in bits 3, 2, 1, 0
+        // keep the upper or the lower half of what both have; lane l ends with acc[2 (l & 15)] and the next
+        auto meet = [&](auto n_c, auto from_other) __attribute__((always_inline)) {
+            constexpr int n = decltype(n_c)::value;                 // values kept; the lanes differ in bit n / 2
+            const bool up = (lane & (n / 2)) != 0;
 #pragma unroll
-    for (int i = 0; i < 32; ++i) acc[i] = row16_sum(acc[i]);
-    if (tl == 0) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-#pragma unroll
-                for (int hf = 0; hf < 2; ++hf)
-                    s_acc[wave][32 * c + 8 * j + k + 4 * hf] = acc[8 * j + 2 * k + hf];
+            for (int i = 0; i < n; ++i) {
+                const float keep = up ? acc[i + n] : acc[i], give = up ? acc[i] : acc[i + n];
+                acc[i] = keep + __builtin_bit_cast(float, from_other(__builtin_bit_cast(int, give)));
+            }
+        };
+        meet(std::integral_constant<int, 16>(), [](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, false); });   // row_ror:8
+        meet(std::integral_constant<int, 8>(), [](int v) {          // from four lanes on and from four lanes back
+            return __builtin_amdgcn_update_dpp(__builtin_amdgcn_update_dpp(0, v, 0x12C, 0xF, 0xF, false), v, 0x124, 0xF, 0xA, false);
+        });
+        meet(std::integral_constant<int, 4>(), [](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false); });     // quad_perm
+        meet(std::integral_constant<int, 2>(), [](int v) { return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false); });
+        float *dst = &s_acc[wave][32 * c + 8 * (tl >> 2) + (tl & 3)];
+        dst[0] = acc[0];
+        dst[4] = acc[1];
     }
     if (lane == 0) {
         s_m[wave] = m_run;
@@ -348,7 +405,7 @@ void decode_attention_kv4_kernel(const __half *__restrict__ q, int H, int Hkv, i
     }
     __syncthreads();
 
-    // ---- merge the wavefronts: out = sum_w e^(m_w - M) acc_w / sum_w e^(m_w - M) l_w
+    // ---- merge the wavefronts: out = sum_w e^(m_w - M) acc_w / sum_w e^(m_w - M) l_w (a wavefront without tokens has left no acc_w)
     if (tid < D) {
         float M = s_m[0];
 #pragma unroll
@@ -356,8 +413,9 @@ void decode_attention_kv4_kernel(const __half *__restrict__ q, int H, int Hkv, i
         float num = 0.0f, den = 0.0f;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
-            const float e = s_m[w] == -INFINITY ? 0.0f : __expf(s_m[w] - M);
-            num += e * s_acc[w][tid];
+            const bool  none = s_m[w] == -INFINITY;
+            const float e = none ? 0.0f : __expf(s_m[w] - M);
+            num += none ? 0.0f : e * s_acc[w][tid];
             den += e * s_l[w];
         }
         if (part == nullptr) {
@@ -397,40 +455,6 @@ __device__ __forceinline__ void unpack8_16_mfma(uint32_t w, uint32_t mask, uint3
     pr[1] = ((w << 2) & mask) | magic;
     pr[2] = ((w >> 2) & mask) | magic;
     pr[3] = ((w >> 6) & mask) | magic;
-}
-
-// One step of a maximum of four values over the lanes l, l ^ 16, l ^ 32, l ^ 48, each result in one chunk of lanes: that of
-// a's own and its partner row's (half's) value in the rows (the half) that keep a, likewise of b in the others.
-template <int WIDTH>
-__device__ __forceinline__ float swap_max(float a, float b)
-{
-    const unsigned ua = __builtin_bit_cast(unsigned, a), ub = __builtin_bit_cast(unsigned, b);
-    v2u r;
-    if constexpr (WIDTH == 16) r = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane16_swap(ua, ub, false, false));
-    else                       r = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane32_swap(ua, ub, false, false));
-    unsigned second = r[1];
-    asm volatile("" : "+v"(second));      // (as in max_across_chunks)
-    return fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, second));
-}
-
-// The way back: o[i] = the value of lane 16 i + (l & 15) in every lane l.
-__device__ __forceinline__ void spread(float v, float (&o)[4])
-{
-    unsigned u = __builtin_bit_cast(unsigned, v), w = u;
-    asm volatile("" : "+v"(w));           // (two registers: a swap exchanges parts of them)
-    const v2u r = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane32_swap(u, w, false, false));
-    unsigned a = r[0], b = r[1];
-    asm volatile("" : "+v"(b));           // (as in max_across_chunks)
-    unsigned a2 = a, b2 = b;
-    asm volatile("" : "+v"(a2), "+v"(b2));
-    const v2u x = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane16_swap(a, a2, false, false));
-    const v2u y = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane16_swap(b, b2, false, false));
-    unsigned x1 = x[1], y1 = y[1];
-    asm volatile("" : "+v"(x1), "+v"(y1));
-    o[0] = __builtin_bit_cast(float, (unsigned)x[0]);
-    o[1] = __builtin_bit_cast(float, x1);
-    o[2] = __builtin_bit_cast(float, (unsigned)y[0]);
-    o[3] = __builtin_bit_cast(float, y1);
 }
 
 constexpr int kGqaWaves    = 4;
