@@ -596,7 +596,7 @@ hipError_t launch_f6_cfg(const F6Params &p, hipStream_t stream)
 namespace atom_internal {
 
 // Tile of a launch: 0, 1, 2 = thin 64 x 64, 64 x 128, 128 x 128; 3 to 7 = walking 128 x 128, 256 x 128, 256 x 192, 128 x 384,
-// 256 x 256; -1: the general kernel.
+// 256 x 256, 192 x 128; -1: the general kernel.
 //
 // Among the first five the estimate is the time per INT4 group in units of 10 ns: rounds of tiles over the compute units times
 // what a tile's step takes.  Thin tiles win where large ones leave compute units without work; beyond the first round (64 x 64: the
@@ -608,7 +608,7 @@ namespace atom_internal {
 //     M = 512, N = 8576, 268 tiles: 32.9 / 73.8 us, 256 x 128 30.1 / 64.1); with two rows 258 tiles are slow already;
 //   * three units of rows: the general kernel leaves the fourth unit of its two rows of tiles out of its requests, the walking one
 //     moves the last tile back and fetches three units twice (M = 192, K = 8192, N = 28672: 66.6 us, walking 71.9; N = 57344:
-//     130 / 139).
+//     130 / 139).  From 17 groups on both yield to tiles of 192 rows (below).
 //
 // Against that tile stand the three wide ones, which fetch fewer bytes per multiply-add and cover the output in fewer
 // rounds, by an estimate of the whole time (fit_us): a launch, prologue, INT8 group and store of each round, and the steps of the
@@ -617,6 +617,12 @@ namespace atom_internal {
 // all of M > 256 the geometric mean is 0.95, and 0.1 % behind the best of the two sides.  With up to sixteen groups the
 // wide tiles' prologues and stores take what their steps gain (16 groups, M = 2304, N = 8200: 47.7 us on 128 x 128, 50.2 at best on
 // a wide one; seven, M = 1100, N = 16300: 32.4, 33.8; M = 1700, N = 2870: 15.3, 17.7).
+//
+// Where 256 x 128 (or, of three units, the general kernel) comes out and as many rows of tiles of 192 cover M, those are taken: the same
+// number of tiles with three quarters of the work each.  On six wavefronts, two SIMDs with two and two with one, that is not worth
+// three quarters of the time, so nowhere else.  Weights from HBM, us: M = 192, K = 4096, N = 22016 36.0 -> 30.7 (general), K = 5120, N = 27648
+// 47.3 -> 41.2, K = 8192, N = 57344 131 -> 117; M = 320, K = 5120, N = 13824 39.1 -> 36.5 (256 x 128), M = 384, K = 4096, N = 12288 31.7 -> 29.2,
+// M = 576, K = N = 8192 51.3 -> 51.7 (from the cache 49.9 -> 45.7).
 // Every tile on these sizes and what the rule takes: profiles/w4a4_gemm_f6_tiles.txt.
 struct TileTime { int ua, uw, round, full, part, share; };        // ns of a round, and per group of a full one, of a part of one, and by its share
 
@@ -653,6 +659,7 @@ static int pick_tile(int64_t au, int64_t wu, int64_t G4, int64_t cus, float *us 
     }
     if (us) *us = 5.0f + 0.0093f * (float)least * (float)(G4 + 2);
     const bool general = best == 3 && au == 3;
+    const bool rows192 = G4 >= 17 && (general || (best == 4 && (au + 2) / 3 == (au + 3) / 4));
     if (G4 >= 17 && best >= 0) {
         int64_t ns = fit_ns(best, au, wu, G4, cus);
         for (int i = 5; i < 8; ++i) {
@@ -666,7 +673,7 @@ static int pick_tile(int64_t au, int64_t wu, int64_t G4, int64_t cus, float *us 
             return best;
         }
     }
-    return general ? -1 : best;
+    return rows192 ? 8 : general ? -1 : best;
 }
 
 // The same for the sizes of a call without a dump; -1: the general kernel.

@@ -3,7 +3,8 @@
 // WM x WN wavefronts, each with a block of 64 rows and 32 JW columns of its own = 2 JW sub-tiles of 32 x 32; per sub-tile and INT4
 // group two FP6 MFMAs, the fp16 MFMA of the scale products between them, and then 16 fused multiply-adds.  Tiles (WM, WN, JW):
 // 128 x 128 (2, 2, 2), two workgroups per compute unit with three LDS stages each; one workgroup of eight wavefronts per compute unit
-// for 256 x 128 (4, 2, 2), four stages, and 256 x 192 (4, 2, 3), 128 x 384 (2, 4, 3) and 256 x 256 (4, 2, 4), three.
+// for 256 x 128 (4, 2, 2), four stages, and 256 x 192 (4, 2, 3), 128 x 384 (2, 4, 3) and 256 x 256 (4, 2, 4), three; 192 x 128 (3, 2, 2) has six
+// wavefronts and four stages.
 //
 // What bounds it: the power limit, and behind it no single pipe.  With operands of zeros the same instructions run at 2.39 GHz,
 // with real ones at 1.7 to 2.1, so what a step moves counts as much as what it issues.  M = 4096, K = 8192, N = 16384, 256 x 128: 434 us;
@@ -59,7 +60,7 @@ struct Walk {
     static constexpr int APART = round_kb(WM * IMG4);         // activation part of a stage, in whole requests
     static constexpr int WPART = round_kb(NJ * IMG4);
     static constexpr int STAGE = APART + WPART;
-    static constexpr int NST   = NW == 8 && JW == 2 ? 4 : 3; // LDS stages
+    static constexpr int NST   = NW >= 6 && JW == 2 ? 4 : 3; // LDS stages
     static constexpr int NA    = APART / 1024, NB = WPART / 1024;
     static constexpr int NR    = NA + NB;                     // requests of a stage: those of the activations, then the weights'
     static constexpr int LPW   = (NR + NW - 1) / NW;
@@ -467,7 +468,8 @@ hipError_t launch_walk(const F6Params &p, int tile, hipStream_t stream)
     case 1:  return launch_cfg<4, 2, 2>(p, stream);
     case 2:  return launch_cfg<4, 2, 3>(p, stream);
     case 3:  return launch_cfg<2, 4, 3>(p, stream);
-    default: return launch_cfg<4, 2, 4>(p, stream);
+    case 4:  return launch_cfg<4, 2, 4>(p, stream);
+    default: return launch_cfg<3, 2, 2>(p, stream);
     }
 }
 

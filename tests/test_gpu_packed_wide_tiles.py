@@ -1,4 +1,4 @@
-"""The wide tiles of the packed GEMM (256 x 192, 128 x 384, 256 x 256) at the edges of their ranges: Y bit-identical to the kernel
+"""The wide tiles of the packed GEMM (256 x 192, 128 x 384, 256 x 256) and those of 192 rows at the edges of their ranges: Y bit-identical to the kernel
 that dumps the integer sums (which tests/test_gpu_packed.py holds against the oracle), and nothing written around the output."""
 import ctypes
 
@@ -11,7 +11,7 @@ from test_gpu_parity import _rand_linear
 
 pytestmark = pytest.mark.gpu
 
-TILES = {5: "256x192", 6: "128x384", 7: "256x256"}
+TILES = {5: "256x192", 6: "128x384", 7: "256x256", 8: "192x128"}
 BORDER = 3                 # guard rows above and below Y, and guard columns left and right of it (an odd number: off the 16-byte grid)
 
 
@@ -28,6 +28,12 @@ BORDER = 3                 # guard rows above and below Y, and guard columns lef
     ("256x256", 515, 20, 19595),         # moved back both ways
     ("256x256", 1218, 21, 19666),        # two rounds
     ("256x256", 1028, 20, 21706),        # two rounds, moved back by three units of rows
+    ("192x128", 150, 17, 22001),         # one tile of rows, ragged; the fewest groups
+    ("192x128", 192, 19, 22050),         # whole rows; an odd number of column units
+    ("192x128", 290, 21, 13851),         # moved back both ways
+    ("192x128", 321, 20, 12300),
+    ("192x128", 190, 18, 57000),         # two rounds
+    ("192x128", 515, 22, 8200),          # 129 column units, moved back both ways
 ])
 def test_wide_tiles(name, M, G4, N):
     K = 128 * (G4 + 1)
