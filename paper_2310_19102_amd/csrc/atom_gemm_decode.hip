@@ -249,7 +249,7 @@ void w4a4_gemm_decode_kernel(const GemmParams p)
 }
 
 // The cases decoding runs in, written out on their own: RB blocks of 16 activation rows per
-// workgroup (blockIdx.y says which 16 RB rows: up to four sets of workgroups, 256 rows), O = 128 (one INT8 group, the last group of K), 32-bit offsets, and either G a
+// workgroup (blockIdx.y says which 16 RB rows of up to 256), O = 128 (one INT8 group, the last group of K), 32-bit offsets, and either G a
 // multiple of four with 8-byte aligned scale rows (TAIL = 3: the last block of four is three INT4
 // groups and the INT8 group; the four scales of a batch are one 8-byte load) or G = 4 j + 2 with
 // 4-byte aligned scale rows (TAIL = 1: the last block is one INT4 group and the INT8 group; two
@@ -289,7 +289,7 @@ void w4a4_gemm_decode16_kernel(const GemmParams p)
     const int col = lane & 15, kc = lane >> 4;
 
     const int K4 = p.K - 128, G = p.K >> 7;
-    // blockIdx.y: which 16 RB rows of the activations (one block for M <= 64, up to four for 256 rows)
+    // blockIdx.y: which 16 RB rows of the activations
     const int row0 = (int)blockIdx.y * (16 * RB);
     const int M = min((int)p.M - row0, 16 * RB);          // rows of this workgroup
     const int64_t n0 = (int64_t)blockIdx.x * (TN * CB);
@@ -358,7 +358,7 @@ void w4a4_gemm_decode16_kernel(const GemmParams p)
             return *reinterpret_cast<const uint4 *>(p.a_q4 + (srow[rb][i] + (uint32_t)gb * 64u - back));
         };
         s00 = stage_load(0, 0); s01 = stage_load(0, 1); s02 = stage_load(0, 2); s03 = stage_load(0, 3);
-        s10 = stage_load(1, 0); s11 = stage_load(1, 1); s12 = stage_load(1, 2); s13 = stage_load(1, 3);
+        if constexpr (RB > 1) { s10 = stage_load(1, 0); s11 = stage_load(1, 1); s12 = stage_load(1, 2); s13 = stage_load(1, 3); }
         if constexpr (RB > 2) {
             s20 = stage_load(2, 0); s21 = stage_load(2, 1); s22 = stage_load(2, 2); s23 = stage_load(2, 3);
             s30 = stage_load(3, 0); s31 = stage_load(3, 1); s32 = stage_load(3, 2); s33 = stage_load(3, 3);
@@ -404,7 +404,7 @@ void w4a4_gemm_decode16_kernel(const GemmParams p)
             for (int d = 0; d < NG4; ++d) aq[rb][d] = *reinterpret_cast<const uint4 *>(st_r + 64 * d);
         };
         through_lds(std::integral_constant<int, 0>(), s00, s01, s02, s03);
-        through_lds(std::integral_constant<int, 1>(), s10, s11, s12, s13);
+        if constexpr (RB > 1) through_lds(std::integral_constant<int, 1>(), s10, s11, s12, s13);
         if constexpr (RB > 2) {
             through_lds(std::integral_constant<int, 2>(), s20, s21, s22, s23);
             through_lds(std::integral_constant<int, 3>(), s30, s31, s32, s33);
@@ -743,6 +743,13 @@ void launch_common(const GemmParams &p, unsigned blocks, hipStream_t stream)
     if (p.M <= 4)       hipLaunchKernelGGL((w4a4_gemm_decode_staged_kernel<1, TILED, TAIL>), dim3(blocks), dim3(NT), 0, stream, p);
     else if (p.M <= 8)  hipLaunchKernelGGL((w4a4_gemm_decode_staged_kernel<2, TILED, TAIL>), dim3(blocks), dim3(NT), 0, stream, p);
     else if (p.M <= 16) hipLaunchKernelGGL((w4a4_gemm_decode_staged_kernel<4, TILED, TAIL>), dim3(blocks), dim3(NT), 0, stream, p);
+    // As many sets of workgroups as give every one of them a compute unit of its own, of 16 or of 32 rows: fewer rows in the chain of a
+    // wavefront.  Sets of 64 (up to 32 rows: 32), 32 and 16 rows, weights from HBM, us: M = 64: K = 4096, N = 1000 5.6, 4.2, 4.0, N = 2048 5.7, 4.3,
+    // 4.7; K = 8192, N = 1000 8.6, 6.2, 5.8, N = 2048 11.5, 7.8, 8.4; M = 32: K = 4096, N = 2048 -, 4.2, 3.6, N = 4096 -, 5.3, 5.6; K = 11008, N =
+    // 2048 -, 10.8, 8.5, N = 4096 -, 11.6, 13.0; M = 128: K = 8192, N = 500 8.5, 6.1, 4.9.  (At both N = 2048 with 64 rows and N = 4096 with
+    // 32 sets of 16 are two to a compute unit.)
+    else if ((int64_t)blocks * ((p.M + 15) / 16) <= atom_launch::compute_units())
+        hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<1, 1, TILED, TAIL>), dim3(blocks, (unsigned)((p.M + 15) / 16)), dim3(NT), 0, stream, p);
     else if (!TILED && resident(p.M, p.N, p.K, atom_launch::compute_units())) launch_resident<TAIL>(p, stream);
     else if (p.M <= 32) hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<2, 1, TILED, TAIL>), dim3(blocks), dim3(NT), 0, stream, p);
     // Four row blocks (and with more than 64 rows further sets of workgroups for rows 64 and up: the
@@ -751,8 +758,10 @@ void launch_common(const GemmParams &p, unsigned blocks, hipStream_t stream)
     // weights from HBM: N = 4096 6.6 us with one, 8.2 us with two; N = 5120 10.9 / 8.3; N = 8192 11.5 /
     // 9.1; N = 11008 16.2 / 15.3; N = 22016 30.8 / 23.7.
     else {
-        const unsigned yb = (unsigned)((p.M + 63) / 64);
-        if ((int64_t)blocks * yb <= atom_launch::compute_units())
+        const unsigned yb = (unsigned)((p.M + 63) / 64), y32 = (unsigned)((p.M + 31) / 32);
+        if ((int64_t)blocks * y32 <= atom_launch::compute_units())
+            hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<2, 1, TILED, TAIL>), dim3(blocks, y32), dim3(NT), 0, stream, p);
+        else if ((int64_t)blocks * yb <= atom_launch::compute_units())
             hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<4, 1, TILED, TAIL>), dim3(blocks, yb), dim3(NT), 0, stream, p);
         else
             hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<4, 2, TILED, TAIL>), dim3((blocks + 1) / 2, yb), dim3(NT), 0, stream, p);

@@ -1,5 +1,5 @@
 """Decode GEMM where the blocks of four groups don't divide by the eight K-slices (8 n + 2 and 8 n + 4 of them: the slices are dealt to the wavefronts
-out of order): each kernel of up to 64 rows against the float64 sum of the integer sums of the groups, which the dumping kernel gives."""
+out of order): each kernel, and its sets of workgroups, against the float64 sum of the integer sums of the groups, which the dumping kernel gives."""
 import pytest
 import torch
 
@@ -8,8 +8,9 @@ import paper_2310_19102_amd as atom
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("K", [4864, 5120, 5888, 6144, 9216, 10240])          # 10, 10, 12, 12, 18, 20 blocks; one or three INT4 groups beside the INT8 group
-@pytest.mark.parametrize("M,N", [(1, 300), (16, 4096), (8, 4112), (17, 300), (32, 8400), (33, 4200), (64, 8300)])
+@pytest.mark.parametrize("K", [1280, 4864, 5120, 5888, 6144, 9216, 10240])          # 3, 10, 10, 12, 12, 18, 20 blocks; one or three INT4 groups beside the INT8 group
+@pytest.mark.parametrize("M,N", [(1, 300), (16, 4096), (8, 4112), (17, 300), (32, 8400), (33, 4200), (64, 8300),
+                                 (40, 1000), (50, 2040), (200, 300)])         # sets of 16 and of 32 rows
 def test_slices(M, N, K):
     print(f"[case] decode slices M={M} N={N} K={K}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(M + N + K)
