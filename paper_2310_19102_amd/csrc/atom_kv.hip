@@ -899,7 +899,14 @@ AttentionShape decode_attention_shape(int B, int H, int Hkv, int64_t Tmax)
         if (want > 64) want = 64;
         return {4, want < 1 ? 1 : (int)want, false};
     }
-    int64_t want = (256 + bh - 1) / bh, cap = groups / 16;     // 256 x 16 wavefronts = four per SIMD
+    // 256 x 16 wavefronts = four per SIMD.  A few workgroups more than that are a second round.  Of several sequences the shorter ones leave their last
+    // workgroups empty, and one more split than fits is the better side (40 heads, T / 4 to T: 2 x 16000 tokens 30.1 us in four, 33.9 in three; 3 x
+    // 8000 26.3 in three, 28.9 in two); a lone sequence has no shorter ones (1 x 40 heads in seven and six: 8192 tokens 25.7, 18.7, 16000 37.8, 25.3),
+    // and with more than 192 heads in all two splits are two rounds anyway (in two and one: 7 x 32 heads: 2200 tokens 23.6, 18.8, 4096 31.4, 27.0, 8192
+    // 45.3, 43.6; 6 x 40 heads, 4096 34.5, 26.8; 5 x 40 heads: 5500 35.6, 32.8, but 7000 35.8, 39.6, 9500 42.9, 49.6).  Up to 2048 tokens the splits, and with
+    // them the order of the sums, are what they were (7 x 32 heads, 2048: 22.7, in one 17.4).
+    int64_t want = (256 + bh - 1) / bh, cap = groups / 16;
+    if (groups > 32 && (B == 1 || (bh > 192 && (groups <= 96 || bh > 200)))) want = bh <= 256 ? 256 / bh : 1;
     if (want > cap) want = cap;
     if (want > 64) want = 64;
     return {16, want < 1 ? 1 : (int)want, false};
