@@ -493,8 +493,9 @@ constexpr int kResidentRows = 32;           // rows of a workgroup of the next k
 // from memory, K = 4096, us, widened for every block (two sets of 32 rows beyond 32) and kept: N = 22016: M = 17 15.2 / 14.3, 32 15.8 / 15.0,
 // 40 20.4 / 16.6, 64 21.0 / 19.0; N = 28672: M = 40 25.0 / 19.2, 64 25.6 / 21.3; N = 11008: M = 33 12.2 / 10.5.  K = 3840 (TAIL = 1) with 32 rows
 // is as fast either way with few rows and 3 % slower with all 32 (N = 28672 18.1 / 18.6): not kept there.
-// K = 8192 has no registers for it (two row blocks spill 44): widened for every block.  w4a4_gemm_decode16_kernel and this one: M = 20,
-// N = 57344 71.7 / 55.5, M = 64, N = 9000 27.2 / 20.9.
+// With two blocks there are registers to keep the first one's (236; both spill 44).  None kept and the first: K = 8192, N = 22016: M = 32 30.2 / 29.0, 64
+// 40.8 / 38.1; N = 57344, M = 64 91.0 / 82.2; K = 5120: N = 13824, M = 40 19.2 / 17.0, 64 19.3 / 17.7, N = 28672 33.2 / 31.4, M = 20 23.0 / 22.3.
+// w4a4_gemm_decode16_kernel and this one without: M = 20, N = 57344 71.7 / 55.5, M = 64, N = 9000 27.2 / 20.9.
 // What bounds it now: the weights (9.0 us for 22016 x 4096 when only read; 4.4 TB/s by the slope over N) behind a start of 5 us with 32 rows
 // and 7 with 64 in which the activations arrive.  The first block's weights requested ahead of the activations: 1 us slower.  Weights
 // three blocks ahead: no faster.
@@ -506,7 +507,8 @@ template <int RB, int NBK, int TAIL>
 __global__ __launch_bounds__(NT, 2)
 void w4a4_gemm_decode_resident_kernel(const GemmParams p)
 {
-    constexpr bool KEEP = NBK == 1 && (RB > 2 || TAIL == 3);   // the widened activations stay
+    // whether the widened activations of block j stay
+    constexpr auto keep = [](int j) constexpr { return NBK == 1 ? RB > 2 || TAIL == 3 : j == 0; };
     // [parity of the pair of channel blocks][which of the pair][K-slice][row block, lane, register]
     constexpr int RED = RB * 256;
     __shared__ __align__(16) float red[4 * NW * RED];
@@ -587,7 +589,7 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
         fetch(wb, first + 1);
         __builtin_amdgcn_sched_barrier(0);
         // (KEEP: widened once, for all channel blocks)
-        v4i xa[NB][RB][4][KEEP ? 2 : 1];
+        v4i xa[NB][RB][4][2];
         auto widened = [&](int j, int rb, int d, int half) __attribute__((always_inline)) -> v4i {
             if (HAS8 && j == NB - 1 && d == TAIL) return __builtin_bit_cast(v4i, half ? ax[rb] : aq[j][rb][d]);
             return half ? widen_hi(aq[j][rb][d]) : widen_lo(aq[j][rb][d]);
@@ -597,7 +599,7 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
                 if (kc != 0) avs[j][rb] = make_uint2(0, 0);       // k-slots 4 .. 15 of the scale MFMA stay empty
-                if constexpr (KEEP)
+                if (keep(j))
 #pragma unroll
                     for (int d = 0; d < ng4(j) + (HAS8 && j == NB - 1 ? 1 : 0); ++d)
 #pragma unroll
@@ -610,9 +612,10 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
             for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[rb][e] = 0.0f;
-            if constexpr (!KEEP) {                        // (hoisted out of the loop the widened codes would take twice the registers)
+            // (hoisted out of the loop the widened codes would take twice the registers)
 #pragma unroll
-                for (int j = 0; j < NB; ++j)
+            for (int j = 0; j < NB; ++j)
+                if (!keep(j))
 #pragma unroll
                     for (int rb = 0; rb < RB; ++rb) {
 #pragma unroll
@@ -620,7 +623,6 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
                             asm volatile("" : "+v"(aq[j][rb][d].x), "+v"(aq[j][rb][d].y), "+v"(aq[j][rb][d].z), "+v"(aq[j][rb][d].w));
                         asm volatile("" : "+v"(avs[j][rb].x), "+v"(avs[j][rb].y));
                     }
-            }
             auto group = [&](auto jc, auto dc) __attribute__((always_inline)) {
                 constexpr int J = decltype(jc)::value, D = decltype(dc)::value;
                 constexpr bool INT8 = HAS8 && J == NB - 1 && D == TAIL;
@@ -629,7 +631,7 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
                 const uint2 ws = kc != 0 ? make_uint2(0, 0) : w.s[J];
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) {
-                    const v4i x0 = KEEP ? xa[J][rb][D][0] : widened(J, rb, D, 0), x1 = KEEP ? xa[J][rb][D][KEEP ? 1 : 0] : widened(J, rb, D, 1);
+                    const v4i x0 = keep(J) ? xa[J][rb][D][0] : widened(J, rb, D, 0), x1 = keep(J) ? xa[J][rb][D][1] : widened(J, rb, D, 1);
                     v4i c = __builtin_amdgcn_mfma_i32_16x16x64_i8(x0, b0, zi, 0, 0, 0);
                     c = __builtin_amdgcn_mfma_i32_16x16x64_i8(x1, b1, c, 0, 0, 0);
                     const v4f32 sc = __builtin_amdgcn_mfma_f32_16x16x16f16(scale_operand<D>(avs[J][rb]), scale_operand<D>(ws), zf, 0, 0, 0);
