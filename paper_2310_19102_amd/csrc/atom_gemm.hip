@@ -355,8 +355,9 @@ hipError_t dispatch(const GemmParams &p, hipStream_t stream)
     // their workgroups pass in at most three rounds (weights from HBM, K = 4096, against the tiled
     // kernels below: M = 128: N = 4096 8.1 / 14.2 us, N = 8192 15.1 / 18.3, N = 12288 21.6 / 26.3, but
     // N = 16384 29.0 / 27.6; M = 192: N = 8192 21.0 / 24.2; M = 256: N = 4096 14.0 / 17.2, but N = 8192
-    // 27.3 / 25.3; K = 11008, N = 4096: M = 128 19.8 / 34.3, M = 256 35.6 / 46.7)
-    if (!DBG && p.M <= 256 && decode_tiled_supported(p) && decode_rounds(p) <= 3) return launch_decode(p, stream);
+    // 27.3 / 25.3; K = 11008, N = 4096: M = 128 19.8 / 34.3, M = 256 35.6 / 46.7), or the one that keeps the activations where that is
+    // estimated to be the faster (resident_sets)
+    if (!DBG && p.M <= 256 && decode_tiled_supported(p) && decode_many_rows(p)) return launch_decode(p, stream);
     // Launches of few tiles are bound by the latency of one tile's chain of K-steps: 64 x 64
     // tiles put every compute unit to work and four (or two) wavefront sets per workgroup split
     // that chain (M = 256, N = K = 4096: 25.7 us on 128 x 128 tiles with two sets).
@@ -373,7 +374,28 @@ hipError_t dispatch(const GemmParams &p, hipStream_t stream)
 
 }  // namespace
 
+namespace atom_gemm {
+
+// Estimated time of the kernels above in us (the constants: gemm_scratch_bytes).
+float tiles_us(int64_t M, int64_t N, int K, int64_t cus)
+{
+    const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64), t128 = ((M + 127) / 128) * ((N + 127) / 128), t256 = ((M + 255) / 256) * ((N + 127) / 128);
+    const float   k = (float)K;
+    if (t64 <= 512) {
+        return t64 <= 128 ? 3.0f + 0.0021f * k : t64 <= 256 ? 3.0f + 0.0028f * k : 4.0f + 0.0050f * k;
+    } else if (t256 >= 512) {
+        return (float)((t256 + cus - 1) / cus) * (6.7f + 0.01047f * k);
+    } else {
+        const int64_t last = t128 % (2 * cus);
+        return (float)(t128 / (2 * cus) + (last > cus)) * (4.0f + 0.0112f * k) + (last > 0 && last <= cus ? 4.0f + 0.0058f * k : 0.0f);
+    }
+}
+
+}  // namespace atom_gemm
+
 namespace atom_internal {
+
+using atom_gemm::tiles_us;
 
 size_t gemm_workspace_bytes(int64_t, int64_t, int, int) { return 0; }
 
@@ -400,17 +422,7 @@ size_t gemm_scratch_bytes(int64_t M, int64_t N, int K, int O)
     const int64_t cus = atom_launch::compute_units();
     const float product = f6_product_us(M, N, K, O, cus);
     if (product == 0.0f) return 0;
-    const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64), t128 = ((M + 127) / 128) * ((N + 127) / 128), t256 = ((M + 255) / 256) * ((N + 127) / 128);
-    const float   k = (float)K;
-    float direct;
-    if (t64 <= 512) {
-        direct = t64 <= 128 ? 3.0f + 0.0021f * k : t64 <= 256 ? 3.0f + 0.0028f * k : 4.0f + 0.0050f * k;
-    } else if (t256 >= 512) {
-        direct = (float)((t256 + cus - 1) / cus) * (6.7f + 0.01047f * k);
-    } else {
-        const int64_t last = t128 % (2 * cus);
-        direct = (float)(t128 / (2 * cus) + (last > cus)) * (4.0f + 0.0112f * k) + (last > 0 && last <= cus ? 4.0f + 0.0058f * k : 0.0f);
-    }
+    const float k = (float)K, direct = tiles_us(M, N, K, cus);
     const float packing = 5.0f + 1.34f * (float)(M + N) * k / 5.0e6f;
     return direct > product + packing + 2.5f ? bytes : 0;
 }

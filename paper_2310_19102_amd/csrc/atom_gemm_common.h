@@ -198,8 +198,10 @@ hipError_t launch_decode(const GemmParams &p, hipStream_t stream);
 hipError_t launch_tile_weight(const void *q4, const void *q8, int64_t N, int K, int O, void *t4, void *t8,
                               hipStream_t stream);
 bool decode_tiled_supported(const GemmParams &p);
-// rounds of workgroups (one per CU) the streaming kernels take for more than 64 rows
-int decode_rounds(const GemmParams &p);
+// whether a problem of the common case with 65 to 256 rows goes to the streaming kernels
+bool decode_many_rows(const GemmParams &p);
+// estimated time of the tiled kernels in us (atom_gemm.hip)
+float tiles_us(int64_t M, int64_t N, int K, int64_t cus);
 hipError_t launch_decode_tiled(const GemmParams &p, hipStream_t stream);
 
 }  // namespace atom_gemm

@@ -719,6 +719,47 @@ bool resident(int64_t M, int64_t N, int K, int64_t cus)
     return M > 16 && M <= 64 && nblk >= NW && nblk <= 2 * NW && blocks * sets > 4 * cus;
 }
 
+// Rounds of workgroups over the compute units of w4a4_gemm_decode16_kernel on more than 64 rows, as launch_common picks them.
+int64_t decode_rounds(int64_t M, int64_t N, int64_t cus)
+{
+    const int64_t blocks = (N + TN - 1) / TN, yb = (M + 63) / 64;
+    const int64_t wgs = blocks * yb <= cus ? blocks * yb : (blocks + 1) / 2 * yb;
+    return (wgs + cus - 1) / cus;
+}
+
+// Workgroups of a set: a multiple of eight, where that leaves nine tenths of them, so that those with the same channels run on the same XCD and read the weights
+// through one L2.  As many as there are room for and a multiple of eight: three sets (85, 80), M = 96, K = 8192, N = 11008 33.4 / 29.3 us, five (51, 48), M =
+// 160, K = 5120, N = 8192 24.9 / 22.5, six (42, 40), M = 192, K = 8192, N = 22016 85.3 / 86.2, N = 8192 38.0 / 37.0; but seven (36, 32), M = 224, K = 5120, N = 8192 28.9 / 29.8.
+int64_t set_width(int64_t cus, int64_t sets)
+{
+    const int64_t w = cus / sets, even = w & ~(int64_t)7;
+    return 10 * even >= 9 * w ? even : w;
+}
+
+// Rows of a set of workgroups beyond 64 rows: K up to 4096 64, or 48 where these are as many sets.
+int64_t set_rows(int64_t M, int K)
+{
+    return K > 512 * NW ? 32 : (M + 47) / 48 <= (M + 63) / 64 ? 48 : 64;
+}
+
+// 65 to 256 rows, the same K: sets of workgroups share the compute units, and a compute unit has n blocks of 16 channels.  Against
+// w4a4_gemm_decode16_kernel (up to three rounds of its workgroups) it is ahead wherever it may run at all; against the tiled kernels it is by the estimates
+// of both: fitted, us, 5.0 + 1.75 n with sets of 48 rows, 5.5 + 2.1 n of 64, and with K beyond 4096 4 + 0.0006 K + (0.3 + 0.000244 K) n; the
+// tiled kernels' is a tenth low with one round of tiles and weights from HBM.  Tiled or w4a4_gemm_decode16_kernel, and this: K = 4096: N = 8192: M = 96
+// 15.9, 12.0, 256 26.5, 21.3; N = 13824: M = 65 25.7, 16.4, 128 27.9, 20.5, but 256 31.1, 32.3; N = 22016: M = 128 32.5, 28.9, 192 52.6, 40.5; K = 5120, N =
+// 13824: M = 128 34.3, 27.6, but 192 35.4, 40.9; K = 8192: N = 13824: M = 128 61.2, 40.6, but 192 53.9, 58.9; N = 22016: M = 192 96.8, 86.3.
+bool resident_sets(int64_t M, int64_t N, int K, int64_t cus)
+{
+    const int     nblk = ((K >> 7) + 3) >> 2;
+    const int64_t blocks = (N + TN - 1) / TN, rows = set_rows(M, K), sets = (M + rows - 1) / rows;
+    if (M <= 64 || M > 256 || nblk < NW || nblk > 2 * NW || blocks * ((M + kResidentRows - 1) / kResidentRows) <= 4 * cus || sets > cus) return false;
+    if (decode_rounds(M, N, cus) <= 3) return true;
+    const float n = (float)((blocks + set_width(cus, sets) - 1) / set_width(cus, sets)), k = (float)K;
+    const float us = rows == 48 ? 5.0f + 1.75f * n : rows == 64 ? 5.5f + 2.1f * n : 4.0f + 0.0006f * k + (0.3f + 0.000244f * k) * n;
+    const bool  one = ((M + 127) / 128) * ((N + 127) / 128) <= cus;
+    return us < (one ? 1.1f : 1.0f) * tiles_us(M, N, K, cus);
+}
+
 // Beyond 32 rows a workgroup takes all of them (K up to 4096), or there are two sets of workgroups of 32 rows each.  A lone set reads the
 // weights once but starts later (three or four blocks of rows to fetch and widen), and the blocks of channels of a compute unit
 // are whole numbers, one and two of them to the same N: fitted, K = 4096, us, 4.2 + 2.2 n for 33 to 48 rows and 4.5 + 2.45 n
@@ -729,13 +770,14 @@ void launch_resident(const GemmParams &p, hipStream_t stream)
 {
     const int64_t cus = atom_launch::compute_units(), blocks = (p.N + TN - 1) / TN;
     const int64_t one = (blocks + cus - 1) / cus, two = (blocks + cus / 2 - 1) / (cus / 2);
-    const bool    split = p.M > 32 && (p.K > 512 * NW || 160 + 178 * two < (p.M <= 48 ? 420 + 220 * one : 450 + 245 * one));
-    const unsigned sets = split ? 2 : 1;
-    auto kern = p.K > 512 * NW        ? &w4a4_gemm_decode_resident_kernel<2, 2, TAIL>
-              : p.M <= 32 || split    ? &w4a4_gemm_decode_resident_kernel<2, 1, TAIL>
-              : p.M <= 48             ? &w4a4_gemm_decode_resident_kernel<3, 1, TAIL>
-                                      : &w4a4_gemm_decode_resident_kernel<4, 1, TAIL>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)cus / sets, sets), dim3(NT), 0, stream, p);                // (fewer workgroups than blocks: every one has some)
+    const bool    split = p.M > 32 && p.M <= 64 && (p.K > 512 * NW || 160 + 178 * two < (p.M <= 48 ? 420 + 220 * one : 450 + 245 * one));
+    const int64_t rows = p.M <= 32 || split ? kResidentRows : p.M > 64 ? set_rows(p.M, p.K) : p.M <= 48 ? 48 : 64;
+    const unsigned sets = (unsigned)((p.M + rows - 1) / rows);
+    auto kern = p.K > 512 * NW ? &w4a4_gemm_decode_resident_kernel<2, 2, TAIL>
+              : rows == 32     ? &w4a4_gemm_decode_resident_kernel<2, 1, TAIL>
+              : rows == 48     ? &w4a4_gemm_decode_resident_kernel<3, 1, TAIL>
+                               : &w4a4_gemm_decode_resident_kernel<4, 1, TAIL>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)set_width(cus, sets), sets), dim3(NT), 0, stream, p);                // (fewer workgroups than blocks: every one has some)
 }
 
 // The kernels of the common case: M <= 16 staged, else blocks of 16 rows.
@@ -752,7 +794,7 @@ void launch_common(const GemmParams &p, unsigned blocks, hipStream_t stream)
     // 32 sets of 16 are two to a compute unit.)
     else if ((int64_t)blocks * ((p.M + 15) / 16) <= atom_launch::compute_units())
         hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<1, 1, TILED, TAIL>), dim3(blocks, (unsigned)((p.M + 15) / 16)), dim3(NT), 0, stream, p);
-    else if (!TILED && resident(p.M, p.N, p.K, atom_launch::compute_units())) launch_resident<TAIL>(p, stream);
+    else if (!TILED && (resident(p.M, p.N, p.K, atom_launch::compute_units()) || resident_sets(p.M, p.N, p.K, atom_launch::compute_units()))) launch_resident<TAIL>(p, stream);
     else if (p.M <= 32) hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<2, 1, TILED, TAIL>), dim3(blocks), dim3(NT), 0, stream, p);
     // Four row blocks (and with more than 64 rows further sets of workgroups for rows 64 and up: the
     // weights of a channel block are then read again, out of the caches): two channel
@@ -800,6 +842,7 @@ void tile_weight_kernel(const uint8_t *__restrict__ q4, const int8_t *__restrict
 
 // Whether a decode GEMM of the common case on canonical weights takes the kernel that keeps the activations, as its test asks it.
 extern "C" int atom_internal_decode_resident(int64_t M, int64_t N, int K, int64_t cus) { return resident(M, N, K, cus); }
+extern "C" int atom_internal_decode_resident_sets(int64_t M, int64_t N, int K, int64_t cus) { return resident_sets(M, N, K, cus); }
 
 namespace atom_gemm {
 
@@ -814,12 +857,10 @@ hipError_t launch_tile_weight(const void *q4, const void *q8, int64_t N, int K, 
 // What the kernels that read tiled weights need: the common case (see common_tail).
 bool decode_tiled_supported(const GemmParams &p) { return common_tail(p) != 0; }
 
-int decode_rounds(const GemmParams &p)
+bool decode_many_rows(const GemmParams &p)
 {
     const int64_t cus = atom_launch::compute_units();
-    const int64_t blocks = (p.N + TN - 1) / TN, yb = (p.M + 63) / 64;
-    const int64_t wgs = blocks * yb <= cus ? blocks * yb : (blocks + 1) / 2 * yb;     // as launch_common picks them
-    return (int)((wgs + cus - 1) / cus);
+    return decode_rounds(p.M, p.N, cus) <= 3 || resident_sets(p.M, p.N, p.K, cus);
 }
 
 hipError_t launch_decode_tiled(const GemmParams &p, hipStream_t stream)
