@@ -780,6 +780,15 @@ void launch_resident(const GemmParams &p, hipStream_t stream)
     hipLaunchKernelGGL(kern, dim3((unsigned)set_width(cus, sets), sets), dim3(NT), 0, stream, p);                // (fewer workgroups than blocks: every one has some)
 }
 
+// Workgroups along the channels of w4a4_gemm_decode16_kernel in `sets` sets of rows: a multiple of eight, the last ones without channels of their own, where
+// all of them keep a compute unit or are in rounds anyway: those with the same channels then run on the same XCD and read the weights through one L2.  As
+// they come and so: K = 8192, N = 1000: M = 64 5.9 / 5.2 us, 128 7.6 / 6.6; K = 11008, M = 33: N = 1000 7.2 / 6.5, N = 2000 9.7 / 9.2.
+unsigned channel_groups(int64_t groups, int64_t sets, int64_t cus)
+{
+    const int64_t even = (groups + 7) & ~(int64_t)7;
+    return (unsigned)(sets > 1 && (even * sets <= cus || groups * sets > cus) ? even : groups);
+}
+
 // The kernels of the common case: M <= 16 staged, else blocks of 16 rows.
 template <bool TILED, int TAIL>
 void launch_common(const GemmParams &p, unsigned blocks, hipStream_t stream)
@@ -793,7 +802,7 @@ void launch_common(const GemmParams &p, unsigned blocks, hipStream_t stream)
     // 2048 -, 10.8, 8.5, N = 4096 -, 11.6, 13.0; M = 128: K = 8192, N = 500 8.5, 6.1, 4.9.  (At both N = 2048 with 64 rows and N = 4096 with
     // 32 sets of 16 are two to a compute unit.)
     else if ((int64_t)blocks * ((p.M + 15) / 16) <= atom_launch::compute_units())
-        hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<1, 1, TILED, TAIL>), dim3(blocks, (unsigned)((p.M + 15) / 16)), dim3(NT), 0, stream, p);
+        hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<1, 1, TILED, TAIL>), dim3(channel_groups(blocks, (p.M + 15) / 16, atom_launch::compute_units()), (unsigned)((p.M + 15) / 16)), dim3(NT), 0, stream, p);
     else if (!TILED && (resident(p.M, p.N, p.K, atom_launch::compute_units()) || resident_sets(p.M, p.N, p.K, atom_launch::compute_units()))) launch_resident<TAIL>(p, stream);
     else if (p.M <= 32) hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<2, 1, TILED, TAIL>), dim3(blocks), dim3(NT), 0, stream, p);
     // Four row blocks (and with more than 64 rows further sets of workgroups for rows 64 and up: the
@@ -804,11 +813,11 @@ void launch_common(const GemmParams &p, unsigned blocks, hipStream_t stream)
     else {
         const unsigned yb = (unsigned)((p.M + 63) / 64), y32 = (unsigned)((p.M + 31) / 32);
         if ((int64_t)blocks * y32 <= atom_launch::compute_units())
-            hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<2, 1, TILED, TAIL>), dim3(blocks, y32), dim3(NT), 0, stream, p);
+            hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<2, 1, TILED, TAIL>), dim3(channel_groups(blocks, y32, atom_launch::compute_units()), y32), dim3(NT), 0, stream, p);
         else if ((int64_t)blocks * yb <= atom_launch::compute_units())
-            hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<4, 1, TILED, TAIL>), dim3(blocks, yb), dim3(NT), 0, stream, p);
+            hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<4, 1, TILED, TAIL>), dim3(channel_groups(blocks, yb, atom_launch::compute_units()), yb), dim3(NT), 0, stream, p);
         else
-            hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<4, 2, TILED, TAIL>), dim3((blocks + 1) / 2, yb), dim3(NT), 0, stream, p);
+            hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<4, 2, TILED, TAIL>), dim3(channel_groups((blocks + 1) / 2, yb, atom_launch::compute_units()), yb), dim3(NT), 0, stream, p);
     }
 }
 
