@@ -483,7 +483,7 @@ void w4a4_gemm_decode16_kernel(const GemmParams p)
 
 constexpr int kResidentRows = 32;           // rows of a workgroup of the next kernel
 
-// Many blocks of channels per compute unit, 17 to 64 rows, K from 3840 to 8192 (30 to 64 groups): a workgroup takes 16 RB rows and a
+// Many blocks of channels per compute unit, 17 to 256 rows, K from 3840 to 12288 (30 to 96 groups): a workgroup takes 16 RB rows and a
 // run of channel blocks, and every wavefront keeps the activation operand of its K-slice (NBK blocks of four groups, or one less) in
 // registers for all of them.  w4a4_gemm_decode16_kernel reads the activations again for each block or two, more bytes from the L2 than
 // the weights are, and every workgroup pays its own start and its own meeting of slices; here only weights stream, those of
@@ -493,9 +493,11 @@ constexpr int kResidentRows = 32;           // rows of a workgroup of the next k
 // from memory, K = 4096, us, widened for every block (two sets of 32 rows beyond 32) and kept: N = 22016: M = 17 15.2 / 14.3, 32 15.8 / 15.0,
 // 40 20.4 / 16.6, 64 21.0 / 19.0; N = 28672: M = 40 25.0 / 19.2, 64 25.6 / 21.3; N = 11008: M = 33 12.2 / 10.5.  K = 3840 (TAIL = 1) with 32 rows
 // is as fast either way with few rows and 3 % slower with all 32 (N = 28672 18.1 / 18.6): not kept there.
-// With two blocks there are registers to keep the first one's (236; both spill 44).  None kept and the first: K = 8192, N = 22016: M = 32 30.2 / 29.0, 64
-// 40.8 / 38.1; N = 57344, M = 64 91.0 / 82.2; K = 5120: N = 13824, M = 40 19.2 / 17.0, 64 19.3 / 17.7, N = 28672 33.2 / 31.4, M = 20 23.0 / 22.3.
-// w4a4_gemm_decode16_kernel and this one without: M = 20, N = 57344 71.7 / 55.5, M = 64, N = 9000 27.2 / 20.9.
+// With two blocks of groups (K up to 8192) and TAIL = 3 the weights of one block of channels are in registers instead of two, every piece requested for
+// the next where it has been used, and all activations are kept widened (254 registers); TAIL = 1, whose last block has fewer of them in flight, is 1 to 2 %
+// slower so and has two sets of weights and the first block of groups kept.  None kept, the first, and all: K = 8192: N = 22016: M = 32 30.2 / 29.0 / 28.5, 64
+// 40.8 / 38.3 / 37.5; N = 11008, M = 64 25.9 / 24.3 / 22.8; K = 5120, N = 13824, M = 40 19.2 / 18.3 / 16.9.  Three blocks (K up to 12288): widened every time,
+// one set of weights (two spill 28 registers with TAIL = 3, and without spills K = 11008, N = 11008, M = 64 takes 35.1, 31.6 so).
 // What bounds it now: the weights (9.0 us for 22016 x 4096 when only read; 4.4 TB/s by the slope over N) behind a start of 5 us with 32 rows
 // and 7 with 64 in which the activations arrive.  The first block's weights requested ahead of the activations: 1 us slower.  Weights
 // three blocks ahead: no faster.
@@ -508,7 +510,9 @@ __global__ __launch_bounds__(NT, 2)
 void w4a4_gemm_decode_resident_kernel(const GemmParams p)
 {
     // whether the widened activations of block j stay
-    constexpr auto keep = [](int j) constexpr { return NBK == 1 ? RB > 2 || TAIL == 3 : j == 0; };
+    // three blocks: the weights of one block of channels in registers, refilled piece by piece for the next where they have been used
+    constexpr bool SINGLE = NBK == 3 || (NBK == 2 && TAIL == 3);
+    constexpr auto keep = [](int j) constexpr { return NBK == 1 ? RB > 2 || TAIL == 3 : NBK == 2 ? TAIL == 3 || j == 0 : false; };
     // [parity of the pair of channel blocks][which of the pair][K-slice][row block, lane, register]
     constexpr int RED = RB * 256;
     __shared__ __align__(16) float red[4 * NW * RED];
@@ -543,20 +547,28 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
         auto ng4 = [](int j) constexpr { return HAS8 && j == NB - 1 ? TAIL : 4; };       // INT4 groups of block j
 
         struct Weights { uint4 q[NB][4], x; uint2 s[NB]; };
-        auto fetch = [&](Weights &w, int blk) __attribute__((always_inline)) {
+        struct Place { uint32_t w4o, w8o, so; };                // of a block of channels' weights
+        auto place = [&](int blk) __attribute__((always_inline)) -> Place {
             blk = blk < last ? blk : last - 1;            // past the end: the last block once more, not used
             int64_t wr = (int64_t)blk * TN + col;         // clamped: columns >= N are computed and never stored
             wr = wr < p.N ? wr : p.N - 1;
-            const uint32_t w4o = (uint32_t)(wr * (K4 >> 1)) + kc * 16, w8o = (uint32_t)(wr * 128) + kc * 16;
+            return {(uint32_t)(wr * (K4 >> 1)) + kc * 16, (uint32_t)(wr * 128) + kc * 16, (uint32_t)wr * (uint32_t)G};
+        };
+        auto fetch_piece = [&](Weights &w, const Place &at, int j, int d) __attribute__((always_inline)) {
+            if (HAS8 && j == NB - 1 && d == TAIL) {
+                w.q[j][d] = *reinterpret_cast<const uint4 *>(w8b + at.w8o);
+                w.x       = *reinterpret_cast<const uint4 *>(w8b + (at.w8o + 64u));
+            } else if (d < ng4(j)) {
+                w.q[j][d] = *reinterpret_cast<const uint4 *>(p.w_q4 + (at.w4o + (uint32_t)(gb[j] + d) * 64u));
+            }
+        };
+        auto fetch = [&](Weights &w, int blk) __attribute__((always_inline)) {
+            const Place at = place(blk);
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
-                w.s[j] = load_scales<A8>(p.w_scale, (uint32_t)wr * (uint32_t)G, gb[j], G);
+                w.s[j] = load_scales<A8>(p.w_scale, at.so, gb[j], G);
 #pragma unroll
-                for (int d = 0; d < ng4(j); ++d) w.q[j][d] = *reinterpret_cast<const uint4 *>(p.w_q4 + (w4o + (uint32_t)(gb[j] + d) * 64u));
-            }
-            if constexpr (HAS8) {
-                w.q[NB - 1][TAIL] = *reinterpret_cast<const uint4 *>(w8b + w8o);
-                w.x               = *reinterpret_cast<const uint4 *>(w8b + (w8o + 64u));
+                for (int d = 0; d < 4; ++d) fetch_piece(w, at, j, d);
             }
         };
         Weights wa, wb;
@@ -586,7 +598,7 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
         __builtin_amdgcn_sched_barrier(0);
         fetch(wa, first);
         __builtin_amdgcn_sched_barrier(0);
-        fetch(wb, first + 1);
+        if constexpr (!SINGLE) fetch(wb, first + 1);
         __builtin_amdgcn_sched_barrier(0);
         // (KEEP: widened once, for all channel blocks)
         v4i xa[NB][RB][4][2];
@@ -607,6 +619,7 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
             }
 
         auto step = [&](Weights &w, int blk, int slot_of) __attribute__((always_inline)) {
+            const Place next = place(SINGLE ? blk + 1 : blk);
             float acc[RB][4];
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb)
@@ -629,6 +642,11 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
                 const v4i b0 = INT8 ? __builtin_bit_cast(v4i, w.q[J][D]) : widen_lo(w.q[J][D]);
                 const v4i b1 = INT8 ? __builtin_bit_cast(v4i, w.x) : widen_hi(w.q[J][D]);
                 const uint2 ws = kc != 0 ? make_uint2(0, 0) : w.s[J];
+                if constexpr (SINGLE) {
+                    fetch_piece(w, next, J, D);
+                    if constexpr (D == 3 || (HAS8 && J == NB - 1 && D == TAIL)) w.s[J] = load_scales<A8>(p.w_scale, next.so, gb[J], G);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) {
                     const v4i x0 = keep(J) ? xa[J][rb][D][0] : widened(J, rb, D, 0), x1 = keep(J) ? xa[J][rb][D][1] : widened(J, rb, D, 1);
@@ -650,9 +668,10 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
             };
             slot(std::integral_constant<int, 0>());
             if constexpr (NB > 1) slot(std::integral_constant<int, 1>());
+            if constexpr (NB > 2) slot(std::integral_constant<int, 2>());
             // the requests for the block after the next, as soon as these registers are free
             __builtin_amdgcn_sched_barrier(0);
-            fetch(w, blk + 2);
+            if constexpr (!SINGLE) fetch(w, blk + 2);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb)
@@ -664,7 +683,7 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
         int parity = 0;
         for (int blk = first; blk < last; blk += 2, parity ^= 2) {
             step(wa, blk, parity);
-            if (blk + 1 < last) step(wb, blk + 1, parity + 1);
+            if (blk + 1 < last) step(SINGLE ? wa : wb, blk + 1, parity + 1);
             __syncthreads();
             for (int idx = tid; idx < RB * 256; idx += NT) {      // two outputs each: rows m and m + 1 of a column
                 const int one = idx >= RB * 128 ? 1 : 0, t = idx - one * RB * 128;
@@ -705,18 +724,28 @@ void w4a4_gemm_decode_staged_kernel(const GemmParams p)
 }
 
 // Canonical weights, 17 to 64 rows and K such that every wavefront has one or two blocks of four groups (registers for the
-// activations): the kernel that keeps the activations, where a compute unit has more than four blocks of 16 channels and 32
+// activations): the kernel that keeps the activations, with one block where a compute unit has more than four blocks of 16 channels and 32
 // rows to do.  Up to there the other kernels' workgroups are resident together or nearly so, and the start counts: K = 4096, that
 // kernel and the others, M = 32: N = 8192 8.5 / 7.8 us, 11008 9.7 / 10.0, 22016 15.0 / 17.2; M = 64: N = 8192 10.2 / 9.0, 9999 11.7 / 14.9.
-// Just past the line, where the others' last round is one workgroup, they are as fast with 17 rows (K = 5120, N = 16400 17.1 / 16.3,
-// 17408 17.9 / 17.9, 18432 18.2 / 18.3); everywhere else of 539 sizes around the line this kernel is ahead.
+// With two, as soon as a compute unit has more than one block of channels: K = 8192: N = 4300: M = 20 11.3 / 12.1, 64 13.5 / 16.0, N = 13824, M = 32 20.5 / 25.6;
+// K = 4864: N = 6000: M = 20 8.7 / 9.2, 64 10.3 / 11.1; N = 16384, M = 32 14.4 / 18.0; with fewer blocks: N = 3000: M = 32 6.3 / 6.2.
 // Re-tiled weights stay with w4a4_gemm_decode16_kernel.  Canonical and re-tiled, us: K = 4096, N = 22016: M = 32 15.4 / 16.7, M = 64 20.8 /
 // 22.8; K = 5120, N = 28672, M = 64 37.5 / 41.8; K = 8192: M = 32, N = 28672 33.2 / 39.2, M = 64, N = 13824 28.7 / 25.6.
 bool resident(int64_t M, int64_t N, int K, int64_t cus)
 {
     const int     nblk = ((K >> 7) + 3) >> 2;
     const int64_t blocks = (N + TN - 1) / TN, sets = (M + kResidentRows - 1) / kResidentRows;
-    return M > 16 && M <= 64 && nblk >= NW && nblk <= 2 * NW && blocks * sets > 4 * cus;
+    return M > 16 && M <= 64 && nblk >= NW && nblk <= 2 * NW && (nblk > NW ? blocks > cus : blocks * sets > 4 * cus);
+}
+
+// The same with K from 8448 to 12288, three blocks of groups to a wavefront.  This kernel and w4a4_gemm_decode16_kernel, us: K = 11008: N = 22016: M = 20 36.7 / 44.5,
+// 64 51.5 / 60.0; N = 8400: M = 32 22.3 / 26.1, 64 27.5 / 38.8; N = 4300, M = 64 20.2 / 20.9; on the other side N = 6000, M = 32 18.4 / 19.2, but K = 9216:
+// N = 6000, M = 20 14.7 / 13.8, and N = 3000, M = 64 13.9 / 13.3.
+bool resident_three(int64_t M, int64_t N, int K, int64_t cus)
+{
+    const int     nblk = ((K >> 7) + 3) >> 2;
+    const int64_t blocks = (N + TN - 1) / TN;
+    return M > 16 && M <= 64 && nblk > 2 * NW && nblk <= 3 * NW && blocks > (M <= 32 ? 2 : 1) * cus;
 }
 
 // Rounds of workgroups over the compute units of w4a4_gemm_decode16_kernel on more than 64 rows, as launch_common picks them.
@@ -742,22 +771,28 @@ int64_t set_rows(int64_t M, int K)
     return K > 512 * NW ? 32 : (M + 47) / 48 <= (M + 63) / 64 ? 48 : 64;
 }
 
-// 65 to 256 rows, the same K: sets of workgroups share the compute units, and a compute unit has n blocks of 16 channels.  Against
-// w4a4_gemm_decode16_kernel (up to three rounds of its workgroups) it is ahead wherever it may run at all; against the tiled kernels it is by the estimates
-// of both: fitted, us, 5.0 + 1.75 n with sets of 48 rows, 5.5 + 2.1 n of 64, and with K beyond 4096 4 + 0.0006 K + (0.3 + 0.000244 K) n; the
-// tiled kernels' is a tenth low with one round of tiles and weights from HBM.  Tiled or w4a4_gemm_decode16_kernel, and this: K = 4096: N = 8192: M = 96
+// 65 to 256 rows, the same K: sets of workgroups share the compute units, and a compute unit has n blocks of 16 channels.  With K up to 8192 it is ahead of
+// w4a4_gemm_decode16_kernel (up to three rounds of its workgroups) wherever it may run; against the tiled kernels, and with three blocks of groups
+// against both, it is by the estimates of both: fitted, us, 5.0 + 1.75 n with sets of 48 rows, 5.5 + 2.1 n of 64; with K beyond 4096 4 + 0.0006 K + (0.3 +
+// 0.000244 K) n, beyond 8192 9.5 + (0.95 + 0.000217 K) n; a round of w4a4_gemm_decode16_kernel 0.00145 K, and 3; the tiled kernels' is a tenth low with one
+// round of tiles and weights from HBM, beyond 8192 channels only with tiles of 64 x 64.  Tiled or w4a4_gemm_decode16_kernel, and this: K = 4096: N = 8192: M = 96
 // 15.9, 12.0, 256 26.5, 21.3; N = 13824: M = 65 25.7, 16.4, 128 27.9, 20.5, but 256 31.1, 32.3; N = 22016: M = 128 32.5, 28.9, 192 52.6, 40.5; K = 5120, N =
-// 13824: M = 128 34.3, 27.6, but 192 35.4, 40.9; K = 8192: N = 13824: M = 128 61.2, 40.6, but 192 53.9, 58.9; N = 22016: M = 192 96.8, 86.3.
+// 13824: M = 128 34.3, 27.6, but 192 35.4, 40.9; K = 8192: N = 13824: M = 128 61.2, 40.6, but 192 53.9, 58.9; N = 22016: M = 192 96.8, 86.3; K = 11008: N =
+// 11008: M = 96 52.9, 40.5, but 192 66.2, 68.2; N = 4096: M = 160 33.3, 29.2, but 96 19.3, 23.1; N = 13824, M = 128 79.7, 57.2.
 bool resident_sets(int64_t M, int64_t N, int K, int64_t cus)
 {
     const int     nblk = ((K >> 7) + 3) >> 2;
     const int64_t blocks = (N + TN - 1) / TN, rows = set_rows(M, K), sets = (M + rows - 1) / rows;
-    if (M <= 64 || M > 256 || nblk < NW || nblk > 2 * NW || blocks * ((M + kResidentRows - 1) / kResidentRows) <= 4 * cus || sets > cus) return false;
-    if (decode_rounds(M, N, cus) <= 3) return true;
+    if (M <= 64 || M > 256 || nblk < NW || nblk > 3 * NW || blocks * ((M + kResidentRows - 1) / kResidentRows) <= 4 * cus || sets > cus) return false;
+    const int64_t rounds = decode_rounds(M, N, cus);
     const float n = (float)((blocks + set_width(cus, sets) - 1) / set_width(cus, sets)), k = (float)K;
+    if (nblk > 2 * NW) {
+        const float us = 9.5f + (0.95f + 0.000217f * k) * n;
+        return us < (rounds <= 3 ? 3.0f + 0.00145f * k * (float)rounds : (((M + 63) / 64) * ((N + 63) / 64) <= 2 * cus ? 1.1f : 1.0f) * tiles_us(M, N, K, cus));
+    }
+    if (rounds <= 3) return true;
     const float us = rows == 48 ? 5.0f + 1.75f * n : rows == 64 ? 5.5f + 2.1f * n : 4.0f + 0.0006f * k + (0.3f + 0.000244f * k) * n;
-    const bool  one = ((M + 127) / 128) * ((N + 127) / 128) <= cus;
-    return us < (one ? 1.1f : 1.0f) * tiles_us(M, N, K, cus);
+    return us < (((M + 127) / 128) * ((N + 127) / 128) <= cus ? 1.1f : 1.0f) * tiles_us(M, N, K, cus);
 }
 
 // Beyond 32 rows a workgroup takes all of them (K up to 4096), or there are two sets of workgroups of 32 rows each.  A lone set reads the
@@ -773,7 +808,8 @@ void launch_resident(const GemmParams &p, hipStream_t stream)
     const bool    split = p.M > 32 && p.M <= 64 && (p.K > 512 * NW || 160 + 178 * two < (p.M <= 48 ? 420 + 220 * one : 450 + 245 * one));
     const int64_t rows = p.M <= 32 || split ? kResidentRows : p.M > 64 ? set_rows(p.M, p.K) : p.M <= 48 ? 48 : 64;
     const unsigned sets = (unsigned)((p.M + rows - 1) / rows);
-    auto kern = p.K > 512 * NW ? &w4a4_gemm_decode_resident_kernel<2, 2, TAIL>
+    auto kern = p.K > 1024 * NW ? &w4a4_gemm_decode_resident_kernel<2, 3, TAIL>
+              : p.K > 512 * NW ? &w4a4_gemm_decode_resident_kernel<2, 2, TAIL>
               : rows == 32     ? &w4a4_gemm_decode_resident_kernel<2, 1, TAIL>
               : rows == 48     ? &w4a4_gemm_decode_resident_kernel<3, 1, TAIL>
                                : &w4a4_gemm_decode_resident_kernel<4, 1, TAIL>;
@@ -803,7 +839,7 @@ void launch_common(const GemmParams &p, unsigned blocks, hipStream_t stream)
     // 32 sets of 16 are two to a compute unit.)
     else if ((int64_t)blocks * ((p.M + 15) / 16) <= atom_launch::compute_units())
         hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<1, 1, TILED, TAIL>), dim3(channel_groups(blocks, (p.M + 15) / 16, atom_launch::compute_units()), (unsigned)((p.M + 15) / 16)), dim3(NT), 0, stream, p);
-    else if (!TILED && (resident(p.M, p.N, p.K, atom_launch::compute_units()) || resident_sets(p.M, p.N, p.K, atom_launch::compute_units()))) launch_resident<TAIL>(p, stream);
+    else if (!TILED && (resident(p.M, p.N, p.K, atom_launch::compute_units()) || resident_three(p.M, p.N, p.K, atom_launch::compute_units()) || resident_sets(p.M, p.N, p.K, atom_launch::compute_units()))) launch_resident<TAIL>(p, stream);
     else if (p.M <= 32) hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<2, 1, TILED, TAIL>), dim3(blocks), dim3(NT), 0, stream, p);
     // Four row blocks (and with more than 64 rows further sets of workgroups for rows 64 and up: the
     // weights of a channel block are then read again, out of the caches): two channel
