@@ -511,8 +511,8 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
 {
     // whether the widened activations of block j stay
     // three blocks: the weights of one block of channels in registers, refilled piece by piece for the next where they have been used
-    constexpr bool SINGLE = NBK == 3 || (NBK == 2 && TAIL == 3);
-    constexpr auto keep = [](int j) constexpr { return NBK == 1 ? RB > 2 || TAIL == 3 : NBK == 2 ? TAIL == 3 || j == 0 : false; };
+    constexpr bool SINGLE = NBK == 3 || (NBK == 2 && (TAIL == 3 || RB > 2));
+    constexpr auto keep = [](int j) constexpr { return NBK == 1 ? RB > 2 || TAIL == 3 : NBK == 2 && RB == 2 ? TAIL == 3 || j == 0 : false; };
     // [parity of the pair of channel blocks][which of the pair][K-slice][row block, lane, register]
     constexpr int RED = RB * 256;
     __shared__ __align__(16) float red[4 * NW * RED];
@@ -765,16 +765,19 @@ int64_t set_width(int64_t cus, int64_t sets)
     return 10 * even >= 9 * w ? even : w;
 }
 
-// Rows of a set of workgroups beyond 64 rows: K up to 4096 64, or 48 where these are as many sets.
+// Rows of a set of workgroups beyond 64 rows: K up to 4096 64, or 48 where these are as many sets; beyond 32, or 48 where these are two sets instead of three or
+// three instead of five and every wavefront has two blocks of groups, K over 7680 (sets of 32 and 48, us: K = 8192: M = 96, N = 22016 51.1 / 45.1, M = 140, N =
+// 13824 46.9 / 42.4; but K = 7168: M = 80, N = 11008 24.4 / 26.1, M = 136, N = 8192 27.0 / 28.8; K = 5120: M = 96, N = 11008 19.9 / 21.2).
 int64_t set_rows(int64_t M, int K)
 {
+    if (K > 960 * NW && K <= 1024 * NW && (M <= 96 || (M > 128 && M <= 144))) return 48;
     return K > 512 * NW ? 32 : (M + 47) / 48 <= (M + 63) / 64 ? 48 : 64;
 }
 
 // 65 to 256 rows, the same K: sets of workgroups share the compute units, and a compute unit has n blocks of 16 channels.  With K up to 8192 it is ahead of
 // w4a4_gemm_decode16_kernel (up to three rounds of its workgroups) wherever it may run; against the tiled kernels, and with three blocks of groups
 // against both, it is by the estimates of both: fitted, us, 5.0 + 1.75 n with sets of 48 rows, 5.5 + 2.1 n of 64; with K beyond 4096 4 + 0.0006 K + (0.3 +
-// 0.000244 K) n, beyond 8192 9.5 + (0.95 + 0.000217 K) n; a round of w4a4_gemm_decode16_kernel 0.00145 K, and 3; the tiled kernels' is a tenth low with one
+// 0.000244 K) n (1.4 times that by n with sets of 48), beyond 8192 9.5 + (0.95 + 0.000217 K) n; a round of w4a4_gemm_decode16_kernel 0.00145 K, and 3; the tiled kernels' is a tenth low with one
 // round of tiles and weights from HBM, beyond 8192 channels only with tiles of 64 x 64.  Tiled or w4a4_gemm_decode16_kernel, and this: K = 4096: N = 8192: M = 96
 // 15.9, 12.0, 256 26.5, 21.3; N = 13824: M = 65 25.7, 16.4, 128 27.9, 20.5, but 256 31.1, 32.3; N = 22016: M = 128 32.5, 28.9, 192 52.6, 40.5; K = 5120, N =
 // 13824: M = 128 34.3, 27.6, but 192 35.4, 40.9; K = 8192: N = 13824: M = 128 61.2, 40.6, but 192 53.9, 58.9; N = 22016: M = 192 96.8, 86.3; K = 11008: N =
@@ -791,7 +794,8 @@ bool resident_sets(int64_t M, int64_t N, int K, int64_t cus)
         return us < (rounds <= 3 ? 3.0f + 0.00145f * k * (float)rounds : (((M + 63) / 64) * ((N + 63) / 64) <= 2 * cus ? 1.1f : 1.0f) * tiles_us(M, N, K, cus));
     }
     if (rounds <= 3) return true;
-    const float us = rows == 48 ? 5.0f + 1.75f * n : rows == 64 ? 5.5f + 2.1f * n : 4.0f + 0.0006f * k + (0.3f + 0.000244f * k) * n;
+    const float us = nblk > NW  ? 4.0f + 0.0006f * k + (rows == 48 ? 1.4f : 1.0f) * (0.3f + 0.000244f * k) * n
+                   : rows == 48 ? 5.0f + 1.75f * n : 5.5f + 2.1f * n;
     return us < (((M + 127) / 128) * ((N + 127) / 128) <= cus ? 1.1f : 1.0f) * tiles_us(M, N, K, cus);
 }
 
@@ -800,16 +804,18 @@ bool resident_sets(int64_t M, int64_t N, int K, int64_t cus)
 // are whole numbers, one and two of them to the same N: fitted, K = 4096, us, 4.2 + 2.2 n for 33 to 48 rows and 4.5 + 2.45 n
 // beyond, n the most blocks that a workgroup has, and 1.6 + 1.78 n for two sets.  Measured at M = 64, one set and two: N = 8208 11.4 / 10.1,
 // 10000 12.2 / 10.9, 12288 12.3 / 11.9, 14000 14.2 / 13.5, 16384 14.4 / 15.9; at M = 33: 10.1 / 9.7, 10.5 / 10.2, 10.7 / 11.2, 12.0 / 12.6, 12.9 / 15.2.
+// With K from 4352 to 8192 33 to 48 rows are one set as soon as a workgroup of two has six blocks; two sets and one, M = 40: K = 8192: N = 8192 16.2 / 16.2, 11008
+// 22.0 / 20.0, 22016 35.6 / 31.8; K = 5120: N = 8192 11.3 / 11.8, 11008 15.0 / 14.7, 28672 31.2 / 27.3.  (64 rows in one: K = 8192, N = 22016 37.6 / 38.7.)
 template <int TAIL>
 void launch_resident(const GemmParams &p, hipStream_t stream)
 {
     const int64_t cus = atom_launch::compute_units(), blocks = (p.N + TN - 1) / TN;
     const int64_t one = (blocks + cus - 1) / cus, two = (blocks + cus / 2 - 1) / (cus / 2);
-    const bool    split = p.M > 32 && p.M <= 64 && (p.K > 512 * NW || 160 + 178 * two < (p.M <= 48 ? 420 + 220 * one : 450 + 245 * one));
+    const bool    split = p.M > 32 && p.M <= 64 && (p.K > 512 * NW ? p.M > 48 || p.K > 1024 * NW || two < 6 : 160 + 178 * two < (p.M <= 48 ? 420 + 220 * one : 450 + 245 * one));
     const int64_t rows = p.M <= 32 || split ? kResidentRows : p.M > 64 ? set_rows(p.M, p.K) : p.M <= 48 ? 48 : 64;
     const unsigned sets = (unsigned)((p.M + rows - 1) / rows);
     auto kern = p.K > 1024 * NW ? &w4a4_gemm_decode_resident_kernel<2, 3, TAIL>
-              : p.K > 512 * NW ? &w4a4_gemm_decode_resident_kernel<2, 2, TAIL>
+              : p.K > 512 * NW ? (rows == 48 ? &w4a4_gemm_decode_resident_kernel<3, 2, TAIL> : &w4a4_gemm_decode_resident_kernel<2, 2, TAIL>)
               : rows == 32     ? &w4a4_gemm_decode_resident_kernel<2, 1, TAIL>
               : rows == 48     ? &w4a4_gemm_decode_resident_kernel<3, 1, TAIL>
                                : &w4a4_gemm_decode_resident_kernel<4, 1, TAIL>;

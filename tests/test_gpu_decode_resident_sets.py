@@ -48,6 +48,12 @@ def test_three_blocks_of_groups(M, N, K):
     _check(M, N, K)
 
 
+@pytest.mark.parametrize("K", [4352, 4864, 5120, 8192])
+@pytest.mark.parametrize("M,N", [(33, 10300), (48, 11001), (40, 28672)])              # 33 to 48 rows in one set
+def test_one_set_of_48_rows(M, N, K):
+    _check(M, N, K)
+
+
 @pytest.mark.parametrize("M,N,K", [(64, 22016, 4096), (257, 8192, 4096), (65, 4096, 4096), (256, 13824, 4096), (192, 13824, 5120), (128, 13824, 12544),
                                    (128, 13824, 3584)])
 def test_other_side_of_the_rule(M, N, K):
