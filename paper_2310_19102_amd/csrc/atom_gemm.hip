@@ -410,7 +410,7 @@ size_t gemm_workspace_bytes(int64_t, int64_t, int, int) { return 0; }
 // They are within 5 to 9 % of what is measured, so packing has to be ahead by 2.5 us: of 1445 sizes that
 // then pack (profiles/w4a4_gemm_packing_on_the_way.txt) 7 to 9 are slower, by up to 3 %.  With 1.5 us M = 900, K = 3072, N = 2048 was 18.7 -> 20.4 us, M = 3000,
 // K = N = 2048 29.0 -> 30.1.
-// Measured (GEMM alone, weights from memory; rows: kernels above, packed on the way): K = 5120, N = 13824: 257 62.6, 57.7; 777 103, 81.3;
+// Measured (GEMM alone, weights from memory; rows: kernels above, packed on the way, the latter before the wide tiles, which take another 5 to 15 % off): K = 5120, N = 13824: 257 62.6, 57.7; 777 103, 81.3;
 // 4096 406, 267; K = 11008, N = 4096: 257 55.9, 36.7; 1024 69.8, 59.0; 4096 247, 169; K = 4096, N = 4096: 1024 34.7, 29.8; 4096 103,
 // 76.3; K = 8192, N = 22016: 450 146, 132; 4096 993, 642.  Where the kernels above stay: K = 2048, N = 8192: 640 28.5, 29; K = 6400,
 // N = 1300: 257 16.4, 20.2.

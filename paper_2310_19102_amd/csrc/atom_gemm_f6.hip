@@ -611,7 +611,7 @@ namespace atom_internal {
 //     130 / 139).  From 17 groups on both yield to tiles of 192 rows (below).
 //
 // Against that tile stand the three wide ones, which fetch fewer bytes per multiply-add and cover the output in fewer
-// rounds, by an estimate of the whole time (fit_us): a launch, prologue, INT8 group and store of each round, and the steps of the
+// rounds, by an estimate of the whole time (fit_ns): a launch, prologue, INT8 group and store of each round, and the steps of the
 // full rounds and of the last one, which is faster the fewer of its compute units have a tile.  Fitted to 544 sizes (M = 65 to 4096,
 // K = 2688 to 14336, N = 1000 to 28672): taken at 158 of them, where the time is 0.73 to 1.04 of the other tile's (at 4 above 1.01); over
 // all of M > 256 the geometric mean is 0.95, and 0.1 % behind the best of the two sides.  With up to sixteen groups the
