@@ -75,18 +75,18 @@ struct MxTile {
     static constexpr int NW    = WM * WN, NT = 64 * NW;
     static constexpr int BM    = 32 * WM * TM, BN = 32 * WN * TN;
     static constexpr int CODES = (BM + BN) * ROWB;         // bytes of codes per stage, the A rows first
-    static constexpr int STAGE = CODES + (BM + BN) * 4;    // + one scale dword per row
+    static constexpr int NSC   = (BM + BN + 63) / 64;      // requests of 64 scale dwords per stage
+    static constexpr int STAGE = CODES + NSC * 256;        // + one scale dword per row
     static constexpr int NST   = ST;                       // LDS stages
     static constexpr int NBLK  = (BM + BN) / 16;           // requests of a kilobyte (16 rows) per stage
     static constexpr int J     = (NBLK + NW - 1) / NW;     // ... per wavefront
-    static constexpr int NSC   = (BM + BN) / 64;           // requests of 64 scale dwords per stage
     static constexpr int JS    = (NSC + NW - 1) / NW;      // ... per wavefront
     static constexpr int LOADS = J + JS;
     static constexpr int SPARE = NST * STAGE;              // 16 bytes that are written and never read
     static constexpr int LDS   = SPARE + 64;
     static constexpr int PITCH = 64 * TN + 16;             // output staging: bytes per row of a wavefront's block
     static constexpr int EPIW  = 32 * TM * PITCH;
-    static_assert(BM % 64 == 0 && BN % 64 == 0, "whole requests");
+    static_assert(BM % 64 == 0 && BN % 32 == 0, "whole requests of codes, and of the activations' scales");
     static_assert(NW * EPIW <= NST * STAGE && LDS <= 160 * 1024, "LDS");
     static constexpr int PER_CU = 2 * LDS <= 160 * 1024 ? 2 : 1;
 };
@@ -111,7 +111,7 @@ struct MxTile {
 //   * the weights are the row operand of the MFMA, so that a lane holds four consecutive columns of a
 //     row of Y and the output staging is a quarter of the LDS writes.
 template <int WM, int WN, int TM, int TN, int ST>
-__global__ __launch_bounds__(64 * WM * WN, (WM * WN / 4 * MxTile<WM, WN, TM, TN, ST>::PER_CU))
+__global__ __launch_bounds__(64 * WM * WN, (WM * WN * MxTile<WM, WN, TM, TN, ST>::PER_CU + 3) / 4)
 void mx_gemm_dma_kernel(MxParams p)
 {
     using Gm = MxTile<WM, WN, TM, TN, ST>;
@@ -675,8 +675,14 @@ hipError_t launch_mx_gemm(const void *a_q4, const void *a_q8, const void *a_e8, 
     p.w_q4 = (const uint8_t *)w_q4; p.w_q8 = (const uint8_t *)w_q8; p.w_e8 = (const uint8_t *)w_e8;
     p.y = (uint16_t *)y; p.M = M; p.N = N; p.ldy = ldy; p.K = K; p.O = O;
     const int cus = atom_launch::compute_units();
+    // Tiles of 64 x 32, with six stages or eight, where there are compute units for twice the tiles of 64 x 64: what a compute unit has in flight bounds its loads, and
+    // a step of them fetches a quarter less.  64 x 64 and so, M = 128, N = 4096, weights from HBM, us: K = 8192 17.5 / 12.6, 2048 6.9 / 5.8, 1024 5.1 / 4.5 (with eight stages
+    // 4.7).  (64 x 64 with more stages than four: from HBM M = 256, K = 11008 22.4 / 20.2, but from the last-level cache K = 5120 3.5 % slower; 64 x 96 on
+    // six wavefronts for 64 x 128: 1.2 times as slow.)
     switch (pick_tile(M, N, K, cus)) {
-    case k64x64:   return launch_tile<2, 2, 1, 1, 4>(p, stream);
+    case k64x64:
+        if (2 * tiles_of(kCost[k64x64], M, N) <= cus) return K > 4096 ? launch_tile<2, 1, 1, 1, 8>(p, stream) : launch_tile<2, 1, 1, 1, 6>(p, stream);
+        return launch_tile<2, 2, 1, 1, 4>(p, stream);
     case k64x128:  return launch_tile<2, 2, 1, 2, 6>(p, stream);
     case k128x128:                                         // up to one per compute unit with four stages, else three workgroups per compute unit
         return tiles_of(kCost[k128x128], M, N) <= cus ? launch_tile<2, 2, 2, 2, 4>(p, stream) : launch_tile<2, 2, 2, 2, 3>(p, stream);
