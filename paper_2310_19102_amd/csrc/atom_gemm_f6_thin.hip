@@ -327,17 +327,20 @@ namespace atom_gemm_f6 {
 // N = 4096 31.3 -> 28.9; M = 128, K = 8192, N = 10000 27.2 -> 25.1.  64 x 64 with six stages for four: M = 256, K = 4096, N = 4096 11.1 -> 10.5; K =
 // 11008 24.6 -> 23.0.  Six stages are also longer code to fetch, 0.4 us, which fewer groups don't repay: from the cache K = 2048, N = 3000 5.6 -> 5.85 (64 x 32)
 // and 5.8 -> 6.4 (64 x 64), K = 1280, N = 4096 4.7 -> 5.0 and 4.9 -> 5.3, K = 2560 6.1 -> 6.1 and 6.3 -> 6.7; from HBM 7.0 -> 6.3 and 7.1 -> 6.9, 5.6 -> 5.3
-// and 5.7 -> 5.7, 8.0 -> 7.0 and 8.1 -> 7.9.  128 x 96 on twelve wavefronts for 128 x 128 spilled and was 1.04 to 1.08 of it at K = 4096, 5120.
+// and 5.7 -> 5.7, 8.0 -> 7.0 and 8.1 -> 7.9.  What HBM gives these two beyond 64 x 32 is little or less than nothing out of the last-level cache, so they stand
+// where neither loses: 64 x 64 with six stages from 47 groups on (front end and GEMM, warm: M = 192, K = 5120, N = 4096 13.7 -> 14.0; K = 6144 16.0 -> 16.0, K = 11008 24.3 -> 24.0), 64
+// x 96 from 31 groups on up to seven eighths of the compute units (M = 320, K = 5120, N = 4096 18.1 -> 17.7, M = 128, K = 4096, N = 9000 14.6 -> 14.4; but K = 3072, M = 300, N =
+// 4500 14.5 -> 14.9, K = 5120, M = 65, N = 12288, 256 tiles, 17.4 -> 17.8).  128 x 96 on twelve wavefronts for 128 x 128 spilled and was 1.04 to 1.08 of it at K = 4096, 5120.
 hipError_t launch_thin(const F6Params &p, int tile, hipStream_t stream)
 {
     const int64_t cus = atom_launch::compute_units(), t64 = (int64_t)p.a_units * p.w_units;
     const int64_t t96 = (int64_t)p.a_units * ((2 * p.w_units + 2) / 3);
     if (tile == 0) {
         if (p.G4 >= 15 && 2 * t64 <= cus) return launch_cfg<2, 1, 1, 6, 2>(p, stream);
-        if (p.G4 >= 20 && t64 <= cus) return launch_cfg<2, 2, 1, 6, 2>(p, stream);
+        if (p.G4 >= 47 && t64 <= cus) return launch_cfg<2, 2, 1, 6, 2>(p, stream);
         return launch_cfg<2, 2, 1, 4, 3>(p, stream);
     }
-    if (tile == 1) return t96 <= cus ? launch_cfg<2, 3, 1, 4, 2>(p, stream) : launch_cfg<2, 4, 1, 4, 2>(p, stream);
+    if (tile == 1) return p.G4 >= 31 && t96 <= cus - cus / 8 ? launch_cfg<2, 3, 1, 4, 2>(p, stream) : launch_cfg<2, 4, 1, 4, 2>(p, stream);
     return launch_cfg<4, 2, 2, 4, 2>(p, stream);
 }
 

@@ -20,19 +20,19 @@ BORDER = 3                 # guard rows above and below Y, and guard columns lef
     (32, 130, 18, 2090),
     (32, 200, 19, 777),
     (32, 128, 20, 4096),
-    (64, 250, 20, 4090),         # six stages: every remainder of the groups
-    (64, 65, 21, 5000),
-    (64, 700, 22, 1403),
-    (64, 64, 23, 16380),
-    (64, 128, 24, 4100),
-    (64, 192, 25, 5120),
+    (64, 250, 48, 4090),         # six stages: every remainder of the groups
+    (64, 65, 49, 5000),
+    (64, 700, 50, 1403),
+    (64, 64, 51, 16380),
+    (64, 128, 52, 4100),
+    (64, 192, 47, 5120),
     (64, 256, 14, 2000),         # four stages
-    (64, 256, 19, 4096),
-    (96, 64, 7, 16512),          # 258 column units: whole tiles
-    (96, 60, 10, 16576),         # 259: the last tile is moved back by a half unit
-    (96, 70, 9, 10900),          # 171, ragged last unit
-    (96, 320, 12, 4100),         # 65: the last tile is moved back by one half unit of three
-    (96, 320, 19, 4096),
+    (64, 256, 46, 4096),
+    (96, 70, 31, 8300),          # 130 column units: the last tile is moved back by a half unit
+    (96, 128, 32, 9000),         # 141: whole tiles
+    (96, 300, 33, 4100),         # 65: moved back by two half units of three
+    (96, 320, 34, 4096),
+    (128, 60, 10, 16576),        # four stages of 64 x 128
 ])
 def test_thin_columns(columns, M, G4, N):
     K = 128 * (G4 + 1)
