@@ -727,25 +727,26 @@ void w4a4_gemm_decode_staged_kernel(const GemmParams p)
 // activations): the kernel that keeps the activations, with one block where a compute unit has more than four blocks of 16 channels and 32
 // rows to do.  Up to there the other kernels' workgroups are resident together or nearly so, and the start counts: K = 4096, that
 // kernel and the others, M = 32: N = 8192 8.5 / 7.8 us, 11008 9.7 / 10.0, 22016 15.0 / 17.2; M = 64: N = 8192 10.2 / 9.0, 9999 11.7 / 14.9.
-// With two, as soon as a compute unit has more than one block of channels: K = 8192: N = 4300: M = 20 11.3 / 12.1, 64 13.5 / 16.0, N = 13824, M = 32 20.5 / 25.6;
-// K = 4864: N = 6000: M = 20 8.7 / 9.2, 64 10.3 / 11.1; N = 16384, M = 32 14.4 / 18.0; with fewer blocks: N = 3000: M = 32 6.3 / 6.2.
+// With two, as soon as a compute unit has more than one block of channels, up to 24 rows two (K = 7680, M = 17, N = 8000, with the front end and weights from the last-level
+// cache 12.8 / 12.4): K = 8192: N = 4300: M = 32 12.0 / 13.5, 64 13.5 / 16.0, N = 13824, M = 32 20.5 / 25.6;
+// K = 4864: N = 6000: M = 32 9.2 / 9.6, 64 10.3 / 11.1; N = 16384, M = 32 14.4 / 18.0; with fewer blocks: N = 3000: M = 32 6.3 / 6.2.
 // Re-tiled weights stay with w4a4_gemm_decode16_kernel.  Canonical and re-tiled, us: K = 4096, N = 22016: M = 32 15.4 / 16.7, M = 64 20.8 /
 // 22.8; K = 5120, N = 28672, M = 64 37.5 / 41.8; K = 8192: M = 32, N = 28672 33.2 / 39.2, M = 64, N = 13824 28.7 / 25.6.
 bool resident(int64_t M, int64_t N, int K, int64_t cus)
 {
     const int     nblk = ((K >> 7) + 3) >> 2;
     const int64_t blocks = (N + TN - 1) / TN, sets = (M + kResidentRows - 1) / kResidentRows;
-    return M > 16 && M <= 64 && nblk >= NW && nblk <= 2 * NW && (nblk > NW ? blocks > cus : blocks * sets > 4 * cus);
+    return M > 16 && M <= 64 && nblk >= NW && nblk <= 2 * NW && (nblk > NW ? blocks > (M > 24 ? 1 : 2) * cus : blocks * sets > 4 * cus);
 }
 
 // The same with K from 8448 to 12288, three blocks of groups to a wavefront.  This kernel and w4a4_gemm_decode16_kernel, us: K = 11008: N = 22016: M = 20 36.7 / 44.5,
-// 64 51.5 / 60.0; N = 8400: M = 32 22.3 / 26.1, 64 27.5 / 38.8; N = 4300, M = 64 20.2 / 20.9; on the other side N = 6000, M = 32 18.4 / 19.2, but K = 9216:
-// N = 6000, M = 20 14.7 / 13.8, and N = 3000, M = 64 13.9 / 13.3.
+// 64 51.5 / 60.0; N = 8400, M = 64 27.5 / 38.8; K = 12288, N = 16384, M = 20 30.0 / 35.5.  On the other side, with the front end and weights from the last-level cache,
+// K = 9216, M = 20: N = 9000 21.0 / 19.4, 13824 23.3 / 21.7; K = 12288, M = 40, N = 4300 21.5 / 20.2.
 bool resident_three(int64_t M, int64_t N, int K, int64_t cus)
 {
     const int     nblk = ((K >> 7) + 3) >> 2;
     const int64_t blocks = (N + TN - 1) / TN;
-    return M > 16 && M <= 64 && nblk > 2 * NW && nblk <= 3 * NW && blocks > (M <= 32 ? 2 : 1) * cus;
+    return M > 16 && M <= 64 && nblk > 2 * NW && nblk <= 3 * NW && blocks > (M > 32 ? 2 : K > 10240 ? 3 : 4) * cus;
 }
 
 // Rounds of workgroups over the compute units of w4a4_gemm_decode16_kernel on more than 64 rows, as launch_common picks them.

@@ -43,7 +43,7 @@ def _check(M, N, K):
 
 
 @pytest.mark.parametrize("K", [8448, 8704, 9216, 11008, 12288])  # 66, 68, 72, 86 and 96 groups: two or three blocks of groups per wavefront, three
-@pytest.mark.parametrize("M,N", [(17, 8213), (32, 9000), (33, 4112), (64, 5001), (96, 11001), (160, 8200)])
+@pytest.mark.parametrize("M,N", [(17, 16400), (32, 16999), (33, 8208), (64, 9001), (96, 11001), (160, 8200)])
 def test_three_blocks_of_groups(M, N, K):
     _check(M, N, K)
 
