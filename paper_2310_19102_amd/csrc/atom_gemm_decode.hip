@@ -295,7 +295,7 @@ void w4a4_gemm_decode16_kernel(const GemmParams p)
     const int64_t n0 = (int64_t)blockIdx.x * (TN * CB);
     constexpr bool A8 = TAIL == 3;
     const int nblk    = (G + 3) >> 2;
-    const int wave    = slice_of_wave(__builtin_amdgcn_readfirstlane(tid >> 6), nblk, true);
+    const int wave    = slice_of_wave(__builtin_amdgcn_readfirstlane(tid >> 6), nblk);
     const int g_begin = 4 * (int)((int64_t)wave * nblk / NW);
     const int g_end   = min(G, 4 * (int)((int64_t)(wave + 1) * nblk / NW));
 
@@ -525,7 +525,7 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
     const int M = min((int)p.M - row0, 16 * RB);          // rows of this workgroup
     constexpr bool A8 = TAIL == 3;
     const int nblk    = (G + 3) >> 2;
-    const int wave    = slice_of_wave(__builtin_amdgcn_readfirstlane(tid >> 6), nblk, true);
+    const int wave    = slice_of_wave(__builtin_amdgcn_readfirstlane(tid >> 6), nblk);
     const int g_begin = 4 * (int)((int64_t)wave * nblk / NW);
     const int g_end   = min(G, 4 * (int)((int64_t)(wave + 1) * nblk / NW));
     const uint8_t *w8b = reinterpret_cast<const uint8_t *>(p.w_q8), *a8b = reinterpret_cast<const uint8_t *>(p.a_q8);

@@ -86,16 +86,16 @@ struct NoWait {
     __device__ __forceinline__ void passed() const {}
 };
 
-// Which of the eight K-slices a wavefront takes.  A SIMD has two wavefronts of a workgroup, the fourth one apart, and where the blocks of four
-// groups don't divide by eight some slices have one more: with 8 n + 2 or 8 n + 4 blocks those would meet on the same SIMD (K = 5120: slices
+// Which of the eight K-slices a wavefront takes, with more than 16 rows.  A SIMD has two wavefronts of a workgroup, the fourth one apart, and where the blocks of
+// four groups don't divide by eight some slices have one more: with 8 n + 2 or 8 n + 4 blocks those would meet on the same SIMD (K = 5120: slices
 // 3 and 7 of two blocks, the others one), so there the last four slices are taken in turn.  The slices and their order are the same.  In order and in
-// turn, us, weights from HBM: K = 5120: M = 64, N = 4096 9.4 / 8.6, N = 22016 31.2 / 27.3; M = 32, N = 11008 14.0 / 13.2; M = 8, N = 4096 5.6 / 5.3.
-// `alone`: up to 16 rows several workgroups share a compute unit as soon as there are more than one for each, and even out among themselves:
-// K = 6144, M = 8: N = 4096 5.65 / 5.59, but N = 6000 7.4 / 7.7, N = 22016 18.0 / 18.3.  Never where the wavefronts wait for the activations (LATE): the
-// caller has the last one poll for all, and only the last slice is sure to have a group.
-__device__ __forceinline__ int slice_of_wave(int wave, int nblk, bool alone)
+// turn, us, weights from HBM: K = 5120: M = 64, N = 4096 9.4 / 8.6, N = 22016 31.2 / 27.3; M = 32, N = 11008 14.0 / 13.2.  Not in the routine below: up to 16
+// rows several workgroups share a compute unit as soon as there are more than one for each, and even out among themselves (K = 6144, M = 8, N = 6000 7.4 / 7.7); where
+// each has its own it gains (K = 5120, M = 8, N = 4096 5.6 / 5.3), but the choice between the two stands in front of the first requests and costs every other size 0.6 %.  (And
+// where the wavefronts wait for the activations the caller has the last one poll for all, and only the last slice is sure to have a group.)
+__device__ __forceinline__ int slice_of_wave(int wave, int nblk)
 {
-    const int turn = alone && nblk > 8 && ((nblk & 7) == 2 || (nblk & 7) == 4) ? 3 : 0;
+    const int turn = nblk > 8 && ((nblk & 7) == 2 || (nblk & 7) == 4) ? 3 : 0;
     return wave < 4 ? wave : 4 + ((wave + turn) & 3);
 }
 
@@ -125,6 +125,7 @@ void decode_staged_body(const GemmParams &p, int block, unsigned char *stage, Wa
 
     const int tid  = threadIdx.x;
     const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, kc = lane >> 4;
 
     const int K4 = p.K - 128, G = p.K >> 7;
@@ -132,7 +133,6 @@ void decode_staged_body(const GemmParams &p, int block, unsigned char *stage, Wa
     const int64_t n0 = (int64_t)block * TN;
     constexpr bool A8 = TAIL == 3;
     const int nblk    = (G + 3) >> 2;
-    const int wave    = slice_of_wave(__builtin_amdgcn_readfirstlane(tid >> 6), nblk, !LATE && gridDim.x <= 256);       // (256 compute units)
     const int g_begin = 4 * (int)((int64_t)wave * nblk / NW);
     const int g_end   = min(G, 4 * (int)((int64_t)(wave + 1) * nblk / NW));
 
