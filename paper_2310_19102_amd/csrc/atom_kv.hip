@@ -899,14 +899,18 @@ AttentionShape decode_attention_shape(int B, int H, int Hkv, int64_t Tmax)
         if (want > 64) want = 64;
         return {4, want < 1 ? 1 : (int)want, false};
     }
-    // 256 x 16 wavefronts = four per SIMD.  A few workgroups more than that are a second round.  Of several sequences the shorter ones leave their last
-    // workgroups empty, and one more split than fits is the better side (40 heads, T / 4 to T: 2 x 16000 tokens 30.1 us in four, 33.9 in three; 3 x
-    // 8000 26.3 in three, 28.9 in two); a lone sequence has no shorter ones (1 x 40 heads in seven and six: 8192 tokens 25.7, 18.7, 16000 37.8, 25.3),
-    // and with more than 192 heads in all two splits are two rounds anyway (in two and one: 7 x 32 heads: 2200 tokens 23.6, 18.8, 4096 31.4, 27.0, 8192
-    // 45.3, 43.6; 6 x 40 heads, 4096 34.5, 26.8; 5 x 40 heads: 5500 35.6, 32.8, but 7000 35.8, 39.6, 9500 42.9, 49.6).  Up to 2048 tokens the splits, and with
-    // them the order of the sums, are what they were (7 x 32 heads, 2048: 22.7, in one 17.4).
+    // 256 x 16 wavefronts = four per SIMD: a round.  Of several sequences the shorter ones leave their last workgroups empty, and one more split than fits is
+    // the better side (40 heads, T / 4 to T: 2 x 16000 tokens 30.1 us in four, 33.9 in three; 3 x 8000 26.3 in three, 28.9 in two); a lone
+    // sequence has no shorter ones (1 x 40 heads in seven and six: 8192 tokens 25.7, 18.9, 16000 38.8, 26.1).
+    // With more than three quarters of a round of heads the second of two splits is mostly a round of its own: its start costs more than it shares out, but the
+    // longer the tokens of a workgroup, the less, and a batch of one long and otherwise short sequences waits for the long one alone.  Two splits over one, with all sequences
+    // equally long / T / 4 to T (mean of eight orders) / one of T and the others T / 16: 7 x 32 heads: 4096 tokens 1.27 / 1.16 / 0.90, 6144 1.24 / 1.10 / 0.85,
+    // 8192 1.24 / 1.08 / 0.76, 12000 1.19 / 1.02 / 0.73, 16000 1.10 / 0.94 / 0.66; 6 x 40: 6144 1.25 / 1.16 / 0.85, 12000 1.17 / 1.08 / 0.75, 16000 1.13 / 1.10 /
+    // 0.72; 51 x 5: 8192 1.23 / 1.15 / 0.78, 12000 1.17 / 1.14 / 0.75, 16000 1.13 / 1.09 / 0.73; 5 x 40: 4096 1.30 / 1.11 / 0.75, 6144 1.29 / 1.03 / 0.84, 8192
+    // 1.24 / 0.99 / 0.78, 12000 1.20 / 0.92 / 0.68.  The line is where the three cancel: 96 groups at 200 heads, 136 at 224, 163 at 240, 188 at
+    // 255.  Up to 2048 tokens the splits, and with them the order of the sums, are what they were (7 x 32 heads, 2048: 22.7, in one 17.4).
     int64_t want = (256 + bh - 1) / bh, cap = groups / 16;
-    if (groups > 32 && (B == 1 || (bh > 192 && (groups <= 96 || bh > 200)))) want = bh <= 256 ? 256 / bh : 1;
+    if (groups > 32 && (B == 1 || (bh > 192 && 3 * groups <= 5 * bh - 712))) want = bh <= 256 ? 256 / bh : 1;
     if (want > cap) want = cap;
     if (want > 64) want = 64;
     return {16, want < 1 ? 1 : (int)want, false};
