@@ -608,35 +608,40 @@ namespace atom_internal {
 //     M = 512, N = 8576, 268 tiles: 32.9 / 73.8 us, 256 x 128 30.1 / 64.1); with two rows 258 tiles are slow already;
 //   * three units of rows: the general kernel leaves the fourth unit of its two rows of tiles out of its requests, the walking one
 //     moves the last tile back and fetches three units twice (M = 192, K = 8192, N = 28672: 66.6 us, walking 71.9; N = 57344:
-//     130 / 139).  From 17 groups on both yield to tiles of 192 rows (below).
+//     130 / 139).  From 17 groups on both yield to tiles of 192 rows.
 //
-// Against that tile stand the three wide ones, which fetch fewer bytes per multiply-add and cover the output in fewer
-// rounds, by an estimate of the whole time (fit_ns): a launch, prologue, INT8 group and store of each round, and the steps of the
-// full rounds and of the last one, which is faster the fewer of its compute units have a tile.  Fitted to 544 sizes (M = 65 to 4096,
-// K = 2688 to 14336, N = 1000 to 28672): taken at 158 of them, where the time is 0.73 to 1.04 of the other tile's (at 4 above 1.01); over
-// all of M > 256 the geometric mean is 0.95, and 0.1 % behind the best of the two sides.  With up to sixteen groups the
-// wide tiles' prologues and stores take what their steps gain (16 groups, M = 2304, N = 8200: 47.7 us on 128 x 128, 50.2 at best on
-// a wide one; seven, M = 1100, N = 16300: 32.4, 33.8; M = 1700, N = 2870: 15.3, 17.7).
-//
-// Where 256 x 128 (or, of three units, the general kernel) comes out and as many rows of tiles of 192 cover M, those are taken: the same
+// Where 256 x 128 (or, of three units, the general kernel) comes out and as many rows of tiles of 192 cover M, those are taken from 17 groups on: the same
 // number of tiles with three quarters of the work each.  On six wavefronts, two SIMDs with two and two with one, that is not worth
 // three quarters of the time, so nowhere else.  Weights from HBM, us: M = 192, K = 4096, N = 22016 36.0 -> 30.7 (general), K = 5120, N = 27648
 // 47.3 -> 41.2, K = 8192, N = 57344 131 -> 117; M = 320, K = 5120, N = 13824 39.1 -> 36.5 (256 x 128), M = 384, K = 4096, N = 12288 31.7 -> 29.2,
 // M = 576, K = N = 8192 51.3 -> 51.7 (from the cache 49.9 -> 45.7).
+//
+// Against the tile that then stands, the three wide ones, which fetch fewer bytes per multiply-add and cover the output in fewer
+// rounds, by an estimate of the whole time (fit_ns), fitted to 969 sizes (M = 65 to 4096, K = 2304 to 14336, N = 1000 to 28672): taken at 357 of them,
+// where the time is 0.77 to 1.016 of the other tile's (0.888 on average, out of the last-level cache 0.885 and at most 1.022); over all of them what is taken is 1.0006
+// of the best of the candidates (at 7 above 1.02: M = 1096, K = 8192, N = 7598 1.078, M = 707, K = 8192, N = 12288 1.044).  With up to sixteen groups the
+// wide tiles' prologues and stores take what their steps gain (16 groups, M = 2304, N = 8200: 47.7 us on 128 x 128, 50.2 at best on
+// a wide one; seven, M = 1100, N = 16300: 32.4, 33.8; M = 1700, N = 2870: 15.3, 17.7).
 // Every tile on these sizes and what the rule takes: profiles/w4a4_gemm_f6_tiles.txt.
-struct TileTime { int ua, uw, round, full, part, share; };        // ns of a round, and per group of a full one, of a part of one, and by its share
+//
+// ns of a round, and per group of a full round, of a part of one that is all there is, and of one behind full rounds (both: with hardly a tile, and what they
+// grow by up to one per compute unit).  A part behind full rounds costs less: workgroups that walk don't wait for each other, so it starts in the gaps
+// that they leave (128 x 128 in two rounds and eight tiles, and 256 x 192, which one cost for both takes: M = 1536, K = 4096, N = 11008 71.4, 73.9; M = 759, N = 22016 77.1, 78.7).
+struct TileTime { int ua, uw, round, full, alone, alone_share, behind, behind_share; };
 
-// Estimated time of a launch in ns.  128 x 128 tiles walk two to a compute unit, so a full round is two of them to each, and
-// there is a line for a last round of up to one and one of more.
+// Estimated time of a launch in ns, weights from HBM.  128 x 128 tiles walk two to a compute unit, so a full round is two of them to each, and
+// a last round of more than one to each approaches it.
 static int64_t fit_ns(int tile, int64_t au, int64_t wu, int64_t G4, int64_t cus)
 {
-    static const TileTime time[8] = {
-        {1, 1, 0, 180, 130, 80}, {1, 2, 0, 340, 220, 140}, {2, 2, 1000, 510, 360, 110}, {2, 2, 3400, 770, 440, 50},
-        {4, 2, 4700, 700, 510, 240}, {4, 3, 6700, 1080, 650, 340}, {2, 6, 6500, 1060, 780, 220}, {4, 4, 6100, 1330, 860, 300}};
+    static const TileTime time[9] = {
+        {1, 1, 0, 200, 200, 40, 160, 100},    {1, 2, 900, 320, 270, 70, 260, 130},  {2, 2, 1900, 470, 390, 60, 340, 160}, {2, 2, 3600, 850, 460, 40, 200, 210},
+        {4, 2, 5600, 760, 540, 170, 460, 280}, {4, 3, 7400, 1080, 640, 310, 580, 420}, {2, 6, 7800, 1080, 790, 140, 580, 410}, {4, 4, 9000, 1370, 870, 310, 730, 510},
+        {3, 2, 4800, 620, 520, 90, 460, 170}};
     const TileTime &t = time[tile];
     const int64_t tiles = ((au + t.ua - 1) / t.ua) * ((wu + t.uw - 1) / t.uw), slots = tile == 3 ? 2 * cus : cus;
     const int64_t full = tiles / slots, rest = tiles % slots;
-    const int64_t last = rest == 0 ? 0 : rest > cus ? 710 + 250 * (rest - cus) / cus : t.part + t.share * rest / cus;
+    const int64_t last = rest == 0 ? 0 : rest > cus ? t.full - 120 * (slots - rest) / cus
+                       : full == 0 ? t.alone + t.alone_share * rest / cus : t.behind + t.behind_share * rest / cus;
     return 4000 + (full + (rest != 0)) * t.round + G4 * (full * t.full + last);
 }
 
@@ -659,21 +664,17 @@ static int pick_tile(int64_t au, int64_t wu, int64_t G4, int64_t cus, float *us 
     }
     if (us) *us = 5.0f + 0.0093f * (float)least * (float)(G4 + 2);
     const bool general = best == 3 && au == 3;
-    const bool rows192 = G4 >= 17 && (general || (best == 4 && (au + 2) / 3 == (au + 3) / 4));
-    if (G4 >= 17 && best >= 0) {
-        int64_t ns = fit_ns(best, au, wu, G4, cus);
-        for (int i = 5; i < 8; ++i) {
-            static const int ua[3] = {4, 2, 4}, uw[3] = {3, 6, 4};
-            if (au < ua[i - 5] || wu < uw[i - 5]) continue;
-            const int64_t wide = fit_ns(i, au, wu, G4, cus);
-            if (wide < ns) { ns = wide; best = i; }
-        }
-        if (best >= 5) {
-            if (us) *us = 1.0f + 0.001f * (float)ns;
-            return best;
-        }
+    if (G4 < 17 || best < 0) return general ? -1 : best;
+    if (general || (best == 4 && (au + 2) / 3 == (au + 3) / 4)) best = 8;
+    int64_t ns = fit_ns(best, au, wu, G4, cus);
+    for (int i = 5; i < 8; ++i) {
+        static const int ua[3] = {4, 2, 4}, uw[3] = {3, 6, 4};
+        if (au < ua[i - 5] || wu < uw[i - 5]) continue;
+        const int64_t wide = fit_ns(i, au, wu, G4, cus);
+        if (wide < ns) { ns = wide; best = i; }
     }
-    return rows192 ? 8 : general ? -1 : best;
+    if (us && best >= 5 && best < 8) *us = 1.0f + 0.001f * (float)ns;
+    return best;
 }
 
 // The same for the sizes of a call without a dump; -1: the general kernel.
