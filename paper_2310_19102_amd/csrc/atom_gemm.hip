@@ -407,13 +407,13 @@ size_t gemm_workspace_bytes(int64_t, int64_t, int, int) { return 0; }
 //   tiles of 256 x 128, from 512 on, one per compute unit   6.7 + 0.01047 K
 //   tiles of 128 x 128, two per compute unit                4 + 0.0112 K; at most one of them (the last round) 4 + 0.0058 K
 // and against them stand the product as its tiles are chosen (f6_product_us), 5 for one more launch, 5 TB/s for the codes read and written.
-// They are within 5 to 9 % of what is measured, so packing has to be ahead by 2.5 us: of 1445 sizes that
-// then pack (profiles/w4a4_gemm_packing_on_the_way.txt) 7 to 9 are slower, by up to 3 %.  With 1.5 us M = 900, K = 3072, N = 2048 was 18.7 -> 20.4 us, M = 3000,
-// K = N = 2048 29.0 -> 30.1.
-// Measured (GEMM alone, weights from memory; rows: kernels above, packed on the way, the latter before the wide tiles, which take another 5 to 15 % off): K = 5120, N = 13824: 257 62.6, 57.7; 777 103, 81.3;
-// 4096 406, 267; K = 11008, N = 4096: 257 55.9, 36.7; 1024 69.8, 59.0; 4096 247, 169; K = 4096, N = 4096: 1024 34.7, 29.8; 4096 103,
-// 76.3; K = 8192, N = 22016: 450 146, 132; 4096 993, 642.  Where the kernels above stay: K = 2048, N = 8192: 640 28.5, 29; K = 6400,
-// N = 1300: 257 16.4, 20.2.
+// They are within 5 to 9 % of what is measured, so packing has to be ahead by 2.5 us: of 1449 sizes that
+// then pack (profiles/w4a4_gemm_packing_on_the_way.txt) 17 are slower by more than 1 %, 8 by more than 3 % (K = 1152, M = 3000, N = 4096 28.1 -> 30.7); with 2.0
+// instead of 2.5 30 and 18 of 52 more.
+// Measured (GEMM alone, weights from memory; rows: kernels above, packed on the way): K = 5120, N = 13824: 257 65.9, 56.5; 777 102, 75.3;
+// 4096 415, 258; K = 11008, N = 4096: 257 58.4, 38.9; 1024 72.6, 62.5; 4096 251, 158; K = 4096, N = 4096: 1024 32.2, 28.4; 4096 112,
+// 68.5; K = 8192, N = 22016: 450 160, 120; 4096 1015, 588; K = 4096, N = 13824: 300 51.9, 47.3.  Where the kernels above stay: K = 2048, N = 8192: 640 29.7, 28.6; K = 6400,
+// N = 1300: 257 16.8, 19.1.
 size_t gemm_scratch_bytes(int64_t M, int64_t N, int K, int O)
 {
     if (M <= 256 || (M + 63) / 64 + (N + 63) / 64 > 65535) return 0;              // (grid rows of the packing launch)
