@@ -481,7 +481,7 @@ void w4a4_gemm_decode16_kernel(const GemmParams p)
     }
 }
 
-constexpr int kResidentRows = 32;           // rows of a workgroup of the next kernel
+constexpr int kLeastSet = 32;               // rows of the smallest set of workgroups of the next kernel, which its rules also count work in
 
 // Many blocks of channels per compute unit, 17 to 256 rows, K from 3840 to 12288 (30 to 96 groups): a workgroup takes 16 RB rows and a
 // run of channel blocks, and every wavefront keeps the activation operand of its K-slice (NBK blocks of four groups, or one less) in
@@ -735,7 +735,7 @@ void w4a4_gemm_decode_staged_kernel(const GemmParams p)
 bool resident(int64_t M, int64_t N, int K, int64_t cus)
 {
     const int     nblk = ((K >> 7) + 3) >> 2;
-    const int64_t blocks = (N + TN - 1) / TN, sets = (M + kResidentRows - 1) / kResidentRows;
+    const int64_t blocks = (N + TN - 1) / TN, sets = (M + kLeastSet - 1) / kLeastSet;
     return M > 16 && M <= 64 && nblk >= NW && nblk <= 2 * NW && (nblk > NW ? blocks > (M > 24 ? 1 : 2) * cus : blocks * sets > 4 * cus);
 }
 
@@ -787,7 +787,7 @@ bool resident_sets(int64_t M, int64_t N, int K, int64_t cus)
 {
     const int     nblk = ((K >> 7) + 3) >> 2;
     const int64_t blocks = (N + TN - 1) / TN, rows = set_rows(M, K), sets = (M + rows - 1) / rows;
-    if (M <= 64 || M > 256 || nblk < NW || nblk > 3 * NW || blocks * ((M + kResidentRows - 1) / kResidentRows) <= 4 * cus || sets > cus) return false;
+    if (M <= 64 || M > 256 || nblk < NW || nblk > 3 * NW || blocks * ((M + kLeastSet - 1) / kLeastSet) <= 4 * cus || sets > cus) return false;
     const int64_t rounds = decode_rounds(M, N, cus);
     const float n = (float)((blocks + set_width(cus, sets) - 1) / set_width(cus, sets)), k = (float)K;
     if (nblk > 2 * NW) {
@@ -800,6 +800,7 @@ bool resident_sets(int64_t M, int64_t N, int K, int64_t cus)
     return us < (((M + 127) / 128) * ((N + 127) / 128) <= cus ? 1.1f : 1.0f) * tiles_us(M, N, K, cus);
 }
 
+// Rows of a set of workgroups of the kernel that keeps the activations; 0: another kernel runs.
 // Beyond 32 rows a workgroup takes all of them (K up to 4096), or there are two sets of workgroups of 32 rows each.  A lone set reads the
 // weights once but starts later (three or four blocks of rows to fetch and widen), and the blocks of channels of a compute unit
 // are whole numbers, one and two of them to the same N: fitted, K = 4096, us, 4.2 + 2.2 n for 33 to 48 rows and 4.5 + 2.45 n
@@ -807,20 +808,27 @@ bool resident_sets(int64_t M, int64_t N, int K, int64_t cus)
 // 10000 12.2 / 10.9, 12288 12.3 / 11.9, 14000 14.2 / 13.5, 16384 14.4 / 15.9; at M = 33: 10.1 / 9.7, 10.5 / 10.2, 10.7 / 11.2, 12.0 / 12.6, 12.9 / 15.2.
 // With K from 4352 to 8192 33 to 48 rows are one set as soon as a workgroup of two has six blocks; two sets and one, M = 40: K = 8192: N = 8192 16.2 / 16.2, 11008
 // 22.0 / 20.0, 22016 35.6 / 31.8; K = 5120: N = 8192 11.3 / 11.8, 11008 15.0 / 14.7, 28672 31.2 / 27.3.  (64 rows in one: K = 8192, N = 22016 37.6 / 38.7.)
-template <int TAIL>
-void launch_resident(const GemmParams &p, hipStream_t stream)
+int64_t resident_rows(int64_t M, int64_t N, int K, int64_t cus)
 {
-    const int64_t cus = atom_launch::compute_units(), blocks = (p.N + TN - 1) / TN;
-    const int64_t one = (blocks + cus - 1) / cus, two = (blocks + cus / 2 - 1) / (cus / 2);
-    const bool    split = p.M > 32 && p.M <= 64 && (p.K > 512 * NW ? p.M > 48 || p.K > 1024 * NW || two < 6 : 160 + 178 * two < (p.M <= 48 ? 420 + 220 * one : 450 + 245 * one));
-    const int64_t rows = p.M <= 32 || split ? kResidentRows : p.M > 64 ? set_rows(p.M, p.K) : p.M <= 48 ? 48 : 64;
+    if (!resident(M, N, K, cus) && !resident_three(M, N, K, cus) && !resident_sets(M, N, K, cus)) return 0;
+    if (M <= 32) return kLeastSet;
+    if (M > 64) return set_rows(M, K);
+    const int64_t blocks = (N + TN - 1) / TN, one = (blocks + cus - 1) / cus, two = (blocks + cus / 2 - 1) / (cus / 2);
+    if (K > 512 * NW) return M > 48 || K > 1024 * NW || two < 6 ? kLeastSet : 48;
+    if (M <= 48) return 160 + 178 * two < 420 + 220 * one ? kLeastSet : 48;
+    return 160 + 178 * two < 450 + 245 * one ? kLeastSet : 64;
+}
+
+template <int TAIL>
+void launch_resident(const GemmParams &p, int64_t rows, hipStream_t stream)
+{
     const unsigned sets = (unsigned)((p.M + rows - 1) / rows);
     auto kern = p.K > 1024 * NW ? &w4a4_gemm_decode_resident_kernel<2, 3, TAIL>
               : p.K > 512 * NW ? (rows == 48 ? &w4a4_gemm_decode_resident_kernel<3, 2, TAIL> : &w4a4_gemm_decode_resident_kernel<2, 2, TAIL>)
               : rows == 32     ? &w4a4_gemm_decode_resident_kernel<2, 1, TAIL>
               : rows == 48     ? &w4a4_gemm_decode_resident_kernel<3, 1, TAIL>
                                : &w4a4_gemm_decode_resident_kernel<4, 1, TAIL>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)set_width(cus, sets), sets), dim3(NT), 0, stream, p);                // (fewer workgroups than blocks: every one has some)
+    hipLaunchKernelGGL(kern, dim3((unsigned)set_width(atom_launch::compute_units(), sets), sets), dim3(NT), 0, stream, p);   // (fewer workgroups than blocks: every one has some)
 }
 
 // Workgroups along the channels of w4a4_gemm_decode16_kernel in `sets` sets of rows: a multiple of eight, the last ones without channels of their own, where
@@ -846,7 +854,7 @@ void launch_common(const GemmParams &p, unsigned blocks, hipStream_t stream)
     // 32 sets of 16 are two to a compute unit.)
     else if ((int64_t)blocks * ((p.M + 15) / 16) <= atom_launch::compute_units())
         hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<1, 1, TILED, TAIL>), dim3(channel_groups(blocks, (p.M + 15) / 16, atom_launch::compute_units()), (unsigned)((p.M + 15) / 16)), dim3(NT), 0, stream, p);
-    else if (!TILED && (resident(p.M, p.N, p.K, atom_launch::compute_units()) || resident_three(p.M, p.N, p.K, atom_launch::compute_units()) || resident_sets(p.M, p.N, p.K, atom_launch::compute_units()))) launch_resident<TAIL>(p, stream);
+    else if (const int64_t rows = TILED ? 0 : resident_rows(p.M, p.N, p.K, atom_launch::compute_units())) launch_resident<TAIL>(p, rows, stream);
     else if (p.M <= 32) hipLaunchKernelGGL((w4a4_gemm_decode16_kernel<2, 1, TILED, TAIL>), dim3(blocks), dim3(NT), 0, stream, p);
     // Four row blocks (and with more than 64 rows further sets of workgroups for rows 64 and up: the
     // weights of a channel block are then read again, out of the caches): two channel
@@ -892,9 +900,11 @@ void tile_weight_kernel(const uint8_t *__restrict__ q4, const int8_t *__restrict
 
 }  // namespace
 
-// Whether a decode GEMM of the common case on canonical weights takes the kernel that keeps the activations, as its test asks it.
+// Whether a decode GEMM of the common case on canonical weights takes the kernel that keeps the activations, and with how many rows to a set (0: another kernel), as
+// its tests ask it.
 extern "C" int atom_internal_decode_resident(int64_t M, int64_t N, int K, int64_t cus) { return resident(M, N, K, cus); }
 extern "C" int atom_internal_decode_resident_sets(int64_t M, int64_t N, int K, int64_t cus) { return resident_sets(M, N, K, cus); }
+extern "C" int atom_internal_decode_resident_rows(int64_t M, int64_t N, int K, int64_t cus) { return (int)resident_rows(M, N, K, cus); }
 
 namespace atom_gemm {
 

@@ -331,17 +331,30 @@ namespace atom_gemm_f6 {
 // where neither loses: 64 x 64 with six stages from 47 groups on (front end and GEMM, warm: M = 192, K = 5120, N = 4096 13.7 -> 14.0; K = 6144 16.0 -> 16.0, K = 11008 24.3 -> 24.0), 64
 // x 96 from 31 groups on up to seven eighths of the compute units (M = 320, K = 5120, N = 4096 18.1 -> 17.7, M = 128, K = 4096, N = 9000 14.6 -> 14.4; but K = 3072, M = 300, N =
 // 4500 14.5 -> 14.9, K = 5120, M = 65, N = 12288, 256 tiles, 17.4 -> 17.8).  128 x 96 on twelve wavefronts for 128 x 128 spilled and was 1.04 to 1.08 of it at K = 4096, 5120.
+static int thin_form(int64_t au, int64_t wu, int64_t G4, int tile, int64_t cus)
+{
+    const int64_t t64 = au * wu, t96 = au * ((2 * wu + 2) / 3);
+    if (tile == 0) return G4 >= 15 && 2 * t64 <= cus ? 326 : G4 >= 47 && t64 <= cus ? 646 : 644;
+    if (tile == 1) return G4 >= 31 && t96 <= cus - cus / 8 ? 964 : 1284;
+    return 0;
+}
+
 hipError_t launch_thin(const F6Params &p, int tile, hipStream_t stream)
 {
-    const int64_t cus = atom_launch::compute_units(), t64 = (int64_t)p.a_units * p.w_units;
-    const int64_t t96 = (int64_t)p.a_units * ((2 * p.w_units + 2) / 3);
-    if (tile == 0) {
-        if (p.G4 >= 15 && 2 * t64 <= cus) return launch_cfg<2, 1, 1, 6, 2>(p, stream);
-        if (p.G4 >= 47 && t64 <= cus) return launch_cfg<2, 2, 1, 6, 2>(p, stream);
-        return launch_cfg<2, 2, 1, 4, 3>(p, stream);
+    switch (thin_form(p.a_units, p.w_units, p.G4, tile, atom_launch::compute_units())) {
+    case 326:  return launch_cfg<2, 1, 1, 6, 2>(p, stream);
+    case 646:  return launch_cfg<2, 2, 1, 6, 2>(p, stream);
+    case 644:  return launch_cfg<2, 2, 1, 4, 3>(p, stream);
+    case 964:  return launch_cfg<2, 3, 1, 4, 2>(p, stream);
+    case 1284: return launch_cfg<2, 4, 1, 4, 2>(p, stream);
+    default:   return launch_cfg<4, 2, 2, 4, 2>(p, stream);
     }
-    if (tile == 1) return p.G4 >= 31 && t96 <= cus - cus / 8 ? launch_cfg<2, 3, 1, 4, 2>(p, stream) : launch_cfg<2, 4, 1, 4, 2>(p, stream);
-    return launch_cfg<4, 2, 2, 4, 2>(p, stream);
 }
 
 }  // namespace atom_gemm_f6
+
+// The columns and stages of a tile of 64 rows (0: 64 x 64, 1: 64 x 128), 10 times the one and the other, as their test asks it.
+extern "C" int atom_internal_packed_thin_form(int64_t M, int64_t N, int32_t K, int32_t tile, int64_t cus)
+{
+    return atom_gemm_f6::thin_form((M + 63) / 64, (N + 63) / 64, (K - 128) >> 7, tile, cus);
+}

@@ -648,6 +648,16 @@ Tile pick_tile(int64_t M, int64_t N, int K, int cus)
     return wide < 1.02f * us ? best : other;
 }
 
+// Tiles of 64 x 32, with six stages or eight, where there are compute units for twice the tiles of 64 x 64: what a compute unit has in flight bounds its loads, and
+// a step of them fetches a quarter less.  64 x 64 and so, M = 128, N = 4096, weights from HBM, us: K = 8192 17.5 / 12.6, 2048 6.9 / 5.8, 1024 5.1 / 4.5 (with eight stages
+// 4.7).  (64 x 64 with more stages than four: from HBM M = 256, K = 11008 22.4 / 20.2, but from the last-level cache K = 5120 3.5 % slower; 64 x 96 on
+// six wavefronts for 64 x 128: 1.2 times as slow.)
+// (The stages; 0: 64 x 64 as it is.)
+int narrow_stages(int64_t M, int64_t N, int K, int cus)
+{
+    return 2 * tiles_of(kCost[k64x64], M, N) > cus ? 0 : K > 4096 ? 8 : 6;
+}
+
 }  // namespace
 
 // Which tile a launch takes, as the test of the tiles asks it (rows and columns of the tile in one number).
@@ -664,6 +674,12 @@ extern "C" int atom_internal_mx_tile_k(int64_t M, int64_t N, int32_t K, int64_t 
     return 1000 * t.bm + t.bn;
 }
 
+// Stages of the 64 x 32 tiles that a call with tiles of 64 x 64 takes in their place; 0: it does not.
+extern "C" int atom_internal_mx_narrow_stages(int64_t M, int64_t N, int32_t K, int64_t cus)
+{
+    return pick_tile(M, N, K, (int)cus) == k64x64 ? narrow_stages(M, N, K, (int)cus) : 0;
+}
+
 namespace atom_internal {
 
 hipError_t launch_mx_gemm(const void *a_q4, const void *a_q8, const void *a_e8, int64_t M,
@@ -675,14 +691,13 @@ hipError_t launch_mx_gemm(const void *a_q4, const void *a_q8, const void *a_e8, 
     p.w_q4 = (const uint8_t *)w_q4; p.w_q8 = (const uint8_t *)w_q8; p.w_e8 = (const uint8_t *)w_e8;
     p.y = (uint16_t *)y; p.M = M; p.N = N; p.ldy = ldy; p.K = K; p.O = O;
     const int cus = atom_launch::compute_units();
-    // Tiles of 64 x 32, with six stages or eight, where there are compute units for twice the tiles of 64 x 64: what a compute unit has in flight bounds its loads, and
-    // a step of them fetches a quarter less.  64 x 64 and so, M = 128, N = 4096, weights from HBM, us: K = 8192 17.5 / 12.6, 2048 6.9 / 5.8, 1024 5.1 / 4.5 (with eight stages
-    // 4.7).  (64 x 64 with more stages than four: from HBM M = 256, K = 11008 22.4 / 20.2, but from the last-level cache K = 5120 3.5 % slower; 64 x 96 on
-    // six wavefronts for 64 x 128: 1.2 times as slow.)
     switch (pick_tile(M, N, K, cus)) {
     case k64x64:
-        if (2 * tiles_of(kCost[k64x64], M, N) <= cus) return K > 4096 ? launch_tile<2, 1, 1, 1, 8>(p, stream) : launch_tile<2, 1, 1, 1, 6>(p, stream);
-        return launch_tile<2, 2, 1, 1, 4>(p, stream);
+        switch (narrow_stages(M, N, K, cus)) {
+        case 6:  return launch_tile<2, 1, 1, 1, 6>(p, stream);
+        case 8:  return launch_tile<2, 1, 1, 1, 8>(p, stream);
+        default: return launch_tile<2, 2, 1, 1, 4>(p, stream);
+        }
     case k64x128:  return launch_tile<2, 2, 1, 2, 6>(p, stream);
     case k128x128:                                         // up to one per compute unit with four stages, else three workgroups per compute unit
         return tiles_of(kCost[k128x128], M, N) <= cus ? launch_tile<2, 2, 2, 2, 4>(p, stream) : launch_tile<2, 2, 2, 2, 3>(p, stream);
