@@ -195,13 +195,21 @@ atom_status atom_w4a4_gemm(const void *a_q4, const void *a_q8,
  * arrays once, offline, into blocks of 16 rows x one group x 64 lanes x 16
  * bytes, so that every load instruction of the kernel reads whole 128-byte
  * lines (the canonical rows, (K - O)/2 bytes long, start in the middle of
- * lines); rows past N are zeros.  Scales stay canonical.  Same arithmetic and
- * the same sum over groups as atom_w4a4_gemm at these sizes: bit-identical Y.
- * With 17 to 64 rows, K from 3840 to 8192 and more than 16384 output channels
- * (8192 above 32 rows) atom_w4a4_gemm on the canonical weights has a kernel of
- * its own and is mostly the faster call: M = 64, K = 4096, N = 22016 20.8 us
- * against 22.8, M = 32, K = 8192, N = 28672 33.2 against 39.2.  Not so around
- * K = 8192 above 32 rows: M = 64, N = 13824 28.7 against 25.6.
+ * lines); rows past N are zeros.  Scales stay canonical.  Same arithmetic as
+ * atom_w4a4_gemm; up to 64 rows the same sum over groups, bit-identical Y, and
+ * beyond wherever that call takes a kernel for decoding too (else its sums are
+ * in another order, fp32 roundings apart).
+ * Which is the faster call (weights from memory): up to 16 rows this one, by up
+ * to 19 %, the more channels the more (M = 8: K = 4096, N = 22016 11.7 us,
+ * atom_w4a4_gemm 12.7; K = 8192, N = 11008 12.4, 14.7).  With more rows
+ * atom_w4a4_gemm has a kernel of its own for canonical weights with K from 3840
+ * to 12288 and many output channels, and is mostly the faster call: from about
+ * N = 11008 on (17 to 32 rows and K = 4096: 16400), beyond 64 rows from 8192 on,
+ * and at any K where N is so large that this call's workgroups take more than
+ * three rounds: M = 32, K = 8192, N = 28672 32.2 us against 40.1, M = 64,
+ * K = 4096, N = 22016 19.7 against 23.9, M = 128, K = 4096, N = 11008 17.2 against
+ * 21.5, M = 96, K = 2048, N = 13824 15.4 against 22.2.  With fewer channels this
+ * one is, by up to a fifth (M = 64, K = 8192, N = 4096 11.1 against 12.5).
  *
  *   atom_tile_weight_decode_bytes(N, d, which)   size of the tiled INT4
  *                 (which = 0) or INT8 (which = 1) array: ceil(N/16)*16 rows

@@ -1,4 +1,4 @@
-// Weight-streaming variant of the group GEMM for decode-sized M (M <= 64).
+// Weight-streaming variants of the group GEMM for decode-sized M (up to 256 rows).
 //
 // Same arithmetic as atom_gemm.hip (Section 4.2 of the paper, steps 1-3), except
 // that the per-group terms of one output are summed in a fixed tree (eight K-slices,
@@ -509,9 +509,9 @@ template <int RB, int NBK, int TAIL>
 __global__ __launch_bounds__(NT, 2)
 void w4a4_gemm_decode_resident_kernel(const GemmParams p)
 {
-    // whether the widened activations of block j stay
-    // three blocks: the weights of one block of channels in registers, refilled piece by piece for the next where they have been used
+    // one set of weights in registers (three blocks, two with TAIL = 3 or 48 rows), refilled piece by piece for the next block of channels where they have been used
     constexpr bool SINGLE = NBK == 3 || (NBK == 2 && (TAIL == 3 || RB > 2));
+    // whether the widened activations of block j stay
     constexpr auto keep = [](int j) constexpr { return NBK == 1 ? RB > 2 || TAIL == 3 : NBK == 2 && RB == 2 ? TAIL == 3 || j == 0 : false; };
     // [parity of the pair of channel blocks][which of the pair][K-slice][row block, lane, register]
     constexpr int RED = RB * 256;
@@ -730,8 +730,8 @@ void w4a4_gemm_decode_staged_kernel(const GemmParams p)
 // With two, as soon as a compute unit has more than one block of channels, up to 24 rows two (K = 7680, M = 17, N = 8000, with the front end and weights from the last-level
 // cache 12.8 / 12.4): K = 8192: N = 4300: M = 32 12.0 / 13.5, 64 13.5 / 16.0, N = 13824, M = 32 20.5 / 25.6;
 // K = 4864: N = 6000: M = 32 9.2 / 9.6, 64 10.3 / 11.1; N = 16384, M = 32 14.4 / 18.0; with fewer blocks: N = 3000: M = 32 6.3 / 6.2.
-// Re-tiled weights stay with w4a4_gemm_decode16_kernel.  Canonical and re-tiled, us: K = 4096, N = 22016: M = 32 15.4 / 16.7, M = 64 20.8 /
-// 22.8; K = 5120, N = 28672, M = 64 37.5 / 41.8; K = 8192: M = 32, N = 28672 33.2 / 39.2, M = 64, N = 13824 28.7 / 25.6.
+// Re-tiled weights stay with w4a4_gemm_decode16_kernel.  Canonical and re-tiled, us: K = 4096, N = 22016: M = 32 14.6 / 17.1, M = 64 19.7 /
+// 23.9; K = 5120, N = 28672, M = 64 31.0 / 38.8; K = 8192: M = 32, N = 28672 32.2 / 40.1, M = 64, N = 13824 25.3 / 26.5, but M = 33, N = 8192 15.6 / 14.4.
 bool resident(int64_t M, int64_t N, int K, int64_t cus)
 {
     const int     nblk = ((K >> 7) + 3) >> 2;

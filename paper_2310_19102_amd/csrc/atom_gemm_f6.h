@@ -84,7 +84,7 @@ __device__ __forceinline__ void dma16_masked(uint32_t lds, uint32_t voff, const 
 
 // The kernels for one INT8 group and at least seven INT4 groups, with at least a tile's units of either operand:
 // few tiles (atom_gemm_f6_thin.hip; tile 0: 64 x 64, 1: 64 x 128, 2: 128 x 128) and many (atom_gemm_f6_walk.hip; tile 0:
-// 128 x 128, 1: 256 x 128, 2: 256 x 192, 3: 128 x 384, 4: 256 x 256).
+// 128 x 128, 1: 256 x 128, 2: 256 x 192, 3: 128 x 384, 4: 256 x 256, 5: 192 x 128).
 hipError_t launch_thin(const F6Params &p, int tile, hipStream_t stream);
 hipError_t launch_walk(const F6Params &p, int tile, hipStream_t stream);
 

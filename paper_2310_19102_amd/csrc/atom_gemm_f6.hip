@@ -595,7 +595,7 @@ hipError_t launch_f6_cfg(const F6Params &p, hipStream_t stream)
 
 namespace atom_internal {
 
-// Tile of a launch: 0, 1, 2 = thin 64 x 64, 64 x 128, 128 x 128; 3 to 7 = walking 128 x 128, 256 x 128, 256 x 192, 128 x 384,
+// Tile of a launch: 0, 1, 2 = thin 64 x 64, 64 x 128, 128 x 128; 3 to 8 = walking 128 x 128, 256 x 128, 256 x 192, 128 x 384,
 // 256 x 256, 192 x 128; -1: the general kernel.
 //
 // Among the first five the estimate is the time per INT4 group in units of 10 ns: rounds of tiles over the compute units times

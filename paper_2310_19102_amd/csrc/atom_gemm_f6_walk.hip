@@ -469,7 +469,8 @@ hipError_t launch_walk(const F6Params &p, int tile, hipStream_t stream)
     case 2:  return launch_cfg<4, 2, 3>(p, stream);
     case 3:  return launch_cfg<2, 4, 3>(p, stream);
     case 4:  return launch_cfg<4, 2, 4>(p, stream);
-    default: return launch_cfg<3, 2, 2>(p, stream);
+    case 5:  return launch_cfg<3, 2, 2>(p, stream);
+    default: return hipErrorInvalidValue;
     }
 }
 

@@ -38,7 +38,7 @@ hipError_t launch_w4a4_gemm(const GemmArgs &a, hipStream_t stream);
 // Group sizes 64 and 256 (atom_gemm_gs.hip): one plain kernel, a single ascending chain of groups.
 hipError_t launch_w4a4_gemm_gs(const GemmArgs &a, int group_size, hipStream_t stream);
 
-// Decode-sized GEMM (M <= 64) on weight codes re-tiled into whole 128-byte lines per load
+// Decode-sized GEMM (M <= 256) on weight codes re-tiled into whole 128-byte lines per load
 // (atom_gemm_decode.hip); w_q4 / w_q8 of the arguments are the tiled arrays, scales canonical.
 bool       decode_tiled_supported(const GemmArgs &a);
 hipError_t launch_w4a4_gemm_decode_tiled(const GemmArgs &a, hipStream_t stream);
