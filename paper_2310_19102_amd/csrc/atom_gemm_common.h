@@ -19,6 +19,7 @@ struct GemmParams {
     uint16_t *y; int32_t *partials;
     int64_t M, N, ldy;
     int K, O;
+    int swap_slices = 0;                  // decode kernels (slice_of_wave)
 };
 
 __device__ __forceinline__ float half_bits_to_float(uint16_t h)

@@ -295,7 +295,7 @@ void w4a4_gemm_decode16_kernel(const GemmParams p)
     const int64_t n0 = (int64_t)blockIdx.x * (TN * CB);
     constexpr bool A8 = TAIL == 3;
     const int nblk    = (G + 3) >> 2;
-    const int wave    = slice_of_wave(__builtin_amdgcn_readfirstlane(tid >> 6), nblk);
+    const int wave    = slice_of_wave(__builtin_amdgcn_readfirstlane(tid >> 6), p.swap_slices);
     const int g_begin = 4 * (int)((int64_t)wave * nblk / NW);
     const int g_end   = min(G, 4 * (int)((int64_t)(wave + 1) * nblk / NW));
 
@@ -525,7 +525,7 @@ void w4a4_gemm_decode_resident_kernel(const GemmParams p)
     const int M = min((int)p.M - row0, 16 * RB);          // rows of this workgroup
     constexpr bool A8 = TAIL == 3;
     const int nblk    = (G + 3) >> 2;
-    const int wave    = slice_of_wave(__builtin_amdgcn_readfirstlane(tid >> 6), nblk);
+    const int wave    = slice_of_wave(__builtin_amdgcn_readfirstlane(tid >> 6), p.swap_slices);
     const int g_begin = 4 * (int)((int64_t)wave * nblk / NW);
     const int g_end   = min(G, 4 * (int)((int64_t)(wave + 1) * nblk / NW));
     const uint8_t *w8b = reinterpret_cast<const uint8_t *>(p.w_q8), *a8b = reinterpret_cast<const uint8_t *>(p.a_q8);
@@ -925,16 +925,20 @@ bool decode_many_rows(const GemmParams &p)
     return decode_rounds(p.M, p.N, cus) <= 3 || resident_sets(p.M, p.N, p.K, cus);
 }
 
-hipError_t launch_decode_tiled(const GemmParams &p, hipStream_t stream)
+hipError_t launch_decode_tiled(const GemmParams &call, hipStream_t stream)
 {
+    GemmParams p = call;
+    p.swap_slices = swapped_slices(p.K);
     const unsigned blocks = (unsigned)((p.N + TN - 1) / TN);
     if (common_tail(p) == 3) launch_common<true, 3>(p, blocks, stream);
     else                     launch_common<true, 1>(p, blocks, stream);
     return hipGetLastError();
 }
 
-hipError_t launch_decode(const GemmParams &p, hipStream_t stream)
+hipError_t launch_decode(const GemmParams &call, hipStream_t stream)
 {
+    GemmParams p = call;
+    p.swap_slices = swapped_slices(p.K);
     const unsigned blocks = (unsigned)((p.N + TN - 1) / TN);
     const int tail = common_tail(p);
     if (tail == 3) { launch_common<false, 3>(p, blocks, stream); return hipGetLastError(); }

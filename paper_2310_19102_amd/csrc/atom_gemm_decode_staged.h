@@ -88,15 +88,17 @@ struct NoWait {
 
 // Which of the eight K-slices a wavefront takes, with more than 16 rows.  A SIMD has two wavefronts of a workgroup, the fourth one apart, and where the blocks of
 // four groups don't divide by eight some slices have one more: with 8 n + 2 or 8 n + 4 blocks those would meet on the same SIMD (K = 5120: slices
-// 3 and 7 of two blocks, the others one), so there the last four slices are taken in turn.  The slices and their order are the same.  In order and in
-// turn, us, weights from HBM: K = 5120: M = 64, N = 4096 9.4 / 8.6, N = 22016 31.2 / 27.3; M = 32, N = 11008 14.0 / 13.2.  Not in the routine below: up to 16
+// 3 and 7 of two blocks, the others one), so there two and two of the last four wavefronts swap.  The slices and their order are the same.  In order and
+// out of it, us, weights from HBM: K = 5120: M = 64, N = 4096 9.4 / 8.6, N = 22016 31.2 / 27.3; M = 32, N = 11008 14.0 / 13.2.  This stands in front of the first requests, so the
+// host says whether (made from K here, eight scalar instructions, it cost the sizes that it does not serve 0.03 to 0.05 us).  Not in the routine below: up to 16
 // rows several workgroups share a compute unit as soon as there are more than one for each, and even out among themselves (K = 6144, M = 8, N = 6000 7.4 / 7.7); where
-// each has its own it gains (K = 5120, M = 8, N = 4096 5.6 / 5.3), but the choice between the two stands in front of the first requests and costs every other size 0.6 %.  (And
+// each has its own it gains (K = 5120, M = 8, N = 4096 5.6 / 5.3).  (And
 // where the wavefronts wait for the activations the caller has the last one poll for all, and only the last slice is sure to have a group.)
-__device__ __forceinline__ int slice_of_wave(int wave, int nblk)
+__device__ __forceinline__ int slice_of_wave(int wave, int swap) { return wave ^ (wave >> 2 & swap); }
+inline int swapped_slices(int K)
 {
-    const int turn = nblk > 8 && ((nblk & 7) == 2 || (nblk & 7) == 4) ? 3 : 0;
-    return wave < 4 ? wave : 4 + ((wave + turn) & 3);
+    const int nblk = ((K >> 7) + 3) >> 2;
+    return nblk > 8 && ((nblk & 7) == 2 || (nblk & 7) == 4) ? 1 : 0;
 }
 
 // The routine.  Cases: M <= 16, O = 128 (one INT8 group, the last group of K), 32-bit offsets, and
