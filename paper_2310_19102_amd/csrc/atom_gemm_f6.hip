@@ -617,9 +617,9 @@ namespace atom_internal {
 // M = 576, K = N = 8192 51.3 -> 51.7 (from the cache 49.9 -> 45.7).
 //
 // Against the tile that then stands, the three wide ones, which fetch fewer bytes per multiply-add and cover the output in fewer
-// rounds, by an estimate of the whole time (fit_ns), fitted to 969 sizes (M = 65 to 4096, K = 2304 to 14336, N = 1000 to 28672): taken at 357 of them,
-// where the time is 0.77 to 1.016 of the other tile's (0.888 on average, out of the last-level cache 0.885 and at most 1.022); over all of them what is taken is 1.0006
-// of the best of the candidates (at 7 above 1.02: M = 1096, K = 8192, N = 7598 1.078, M = 707, K = 8192, N = 12288 1.044).  With up to sixteen groups the
+// rounds, by an estimate of the whole time (fit_ns), fitted to 969 sizes (M = 65 to 4096, K = 2304 to 14336, N = 1000 to 28672): taken at 360 of them,
+// where the time is 0.76 to 1.02 of the other tile's (0.890 on average); over all of them what is taken is 1.0005
+// of the best of the candidates (at 6 above 1.02: M = 707, K = 8192, N = 12288 1.044, M = 2061, K = 4096, N = 8409 1.040).  With up to sixteen groups the
 // wide tiles' prologues and stores take what their steps gain (16 groups, M = 2304, N = 8200: 47.7 us on 128 x 128, 50.2 at best on
 // a wide one; seven, M = 1100, N = 16300: 32.4, 33.8; M = 1700, N = 2870: 15.3, 17.7).
 // Every tile on these sizes and what the rule takes: profiles/w4a4_gemm_f6_tiles.txt.
@@ -634,19 +634,19 @@ struct TileTime { int ua, uw, round, full, alone, alone_share, behind, behind_sh
 static int64_t fit_ns(int tile, int64_t au, int64_t wu, int64_t G4, int64_t cus)
 {
     static const TileTime time[9] = {
-        {1, 1, 0, 200, 200, 40, 160, 100},    {1, 2, 900, 320, 270, 70, 260, 130},  {2, 2, 1900, 470, 390, 60, 340, 160}, {2, 2, 3600, 850, 460, 40, 200, 210},
-        {4, 2, 5600, 760, 540, 170, 460, 280}, {4, 3, 7400, 1080, 640, 310, 580, 420}, {2, 6, 7800, 1080, 790, 140, 580, 410}, {4, 4, 9000, 1370, 870, 310, 730, 510},
+        {1, 1, 0, 200, 200, 40, 160, 100},    {1, 2, 900, 320, 270, 70, 260, 130},  {2, 2, 1900, 470, 390, 60, 340, 160}, {2, 2, 4100, 860, 460, 40, 180, 250},
+        {4, 2, 6400, 740, 540, 170, 340, 430}, {4, 3, 7400, 1070, 650, 340, 630, 440}, {2, 6, 7900, 1070, 760, 210, 630, 430}, {4, 4, 8200, 1370, 910, 260, 860, 190},
         {3, 2, 4800, 620, 520, 90, 460, 170}};
     const TileTime &t = time[tile];
     const int64_t tiles = ((au + t.ua - 1) / t.ua) * ((wu + t.uw - 1) / t.uw), slots = tile == 3 ? 2 * cus : cus;
     const int64_t full = tiles / slots, rest = tiles % slots;
-    const int64_t last = rest == 0 ? 0 : rest > cus ? t.full - 120 * (slots - rest) / cus
+    const int64_t last = rest == 0 ? 0 : rest > cus ? t.full - 250 * (slots - rest) / cus
                        : full == 0 ? t.alone + t.alone_share * rest / cus : t.behind + t.behind_share * rest / cus;
     return 4000 + (full + (rest != 0)) * t.round + G4 * (full * t.full + last);
 }
 
 // `us`: the estimate of the tile taken, operands out of the last-level cache: for the wide tiles and those of 192 rows fit_ns less what the cache gives and, one launch
-// behind the other, the call's own 4 us do not show (median by tile, of those sizes where it is taken, 1.2 to 2.5 us).
+// behind the other, the call's own 4 us do not show (by tile from 1 us above fit_ns to 4 us below it).
 static int pick_tile(int64_t au, int64_t wu, int64_t G4, int64_t cus, float *us = nullptr)
 {
     struct { int ua, uw, rounds, first, more; } const tile[5] = {
