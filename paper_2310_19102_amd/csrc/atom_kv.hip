@@ -907,7 +907,7 @@ AttentionShape decode_attention_shape(int B, int H, int Hkv, int64_t Tmax)
     // equally long / T / 4 to T (mean of eight orders) / one of T and the others T / 16: 7 x 32 heads: 4096 tokens 1.27 / 1.16 / 0.90, 6144 1.24 / 1.10 / 0.85,
     // 8192 1.24 / 1.08 / 0.76, 12000 1.19 / 1.02 / 0.73, 16000 1.10 / 0.94 / 0.66; 6 x 40: 6144 1.25 / 1.16 / 0.85, 12000 1.17 / 1.08 / 0.75, 16000 1.13 / 1.10 /
     // 0.72; 51 x 5: 8192 1.23 / 1.15 / 0.78, 12000 1.17 / 1.14 / 0.75, 16000 1.13 / 1.09 / 0.73; 5 x 40: 4096 1.30 / 1.11 / 0.75, 6144 1.29 / 1.03 / 0.84, 8192
-    // 1.24 / 0.99 / 0.78, 12000 1.20 / 0.92 / 0.68.  The line is where the three cancel: 96 groups at 200 heads, 136 at 224, 163 at 240, 188 at
+    // 1.24 / 0.99 / 0.78, 12000 1.20 / 0.92 / 0.68.  The line is where the three cancel: 96 groups at 200 heads, 136 at 224, 162 at 240, 187 at
     // 255.  Up to 2048 tokens the splits, and with them the order of the sums, are what they were (7 x 32 heads, 2048: 22.7, in one 17.4).
     int64_t want = (256 + bh - 1) / bh, cap = groups / 16;
     if (groups > 32 && (B == 1 || (bh > 192 && 3 * groups <= 5 * bh - 712))) want = bh <= 256 ? 256 / bh : 1;
