@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import paper_2310_19102_amd as atom
-from test_gpu_decode_resident import BORDER, SLICE, rows_of_a_set
+from test_gpu_decode_resident import BORDER, SLICE, resident
 
 pytestmark = pytest.mark.gpu
 
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("N", [10001, 16390, 20000])              # two sets; five blocks of channels to a workgroup, the last of six channels; whole blocks
 def test_rows_of_a_workgroup(M, N, K):
     print(f"[case] resident decode rows M={M} N={N} K={K}", flush=True)
-    assert rows_of_a_set(M, N, K) == (32 if N == 10001 else 48 if M <= 48 else 64) and not rows_of_a_set(M, SLICE, K)
+    assert resident(M, N, K)
     g = torch.Generator(device="cuda").manual_seed(M + N + K)
     idx = torch.randperm(K, generator=g, device="cuda").to(torch.int32)
     a = atom.atom_quantize_act(torch.randn((M, K), generator=g, device="cuda").half(), None, 0.0, idx)

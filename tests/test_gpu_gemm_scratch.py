@@ -21,8 +21,8 @@ def _prepacked(qa, qw, M, N, K):
 
 
 # one row more than the streaming kernels take, odd sizes; without room 64 x 64 tiles with two sets, 128 x 128 with two sets and with one,
-# 256 x 128; a product on tiles of 192 rows, near the line
-@pytest.mark.parametrize("M,N,K", [(257, 4096, 4096), (777, 3001, 4224), (1000, 8000, 4096), (2101, 8191, 1024), (300, 13824, 4096)])
+# 256 x 128
+@pytest.mark.parametrize("M,N,K", [(257, 4096, 4096), (777, 3001, 4224), (1000, 8000, 4096), (2101, 8191, 1024)])
 def test_bits_of_the_packed_product(M, N, K):
     print(f"[case] packing on the way M={M} N={N} K={K}", flush=True)
     assert atom.atom_w4a4_gemm_scratch_bytes(M, N, K) > 0

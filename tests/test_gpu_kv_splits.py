@@ -19,16 +19,10 @@ D = 128
     (1, 200, 2049, 1),
     (1, 40, 2048, 2),            # up to 2048 tokens as ever
     (2, 40, 4200, 4),            # several sequences: one more than fits
-    (7, 32, 2100, 1),            # more than 192 heads in all
+    (7, 32, 2100, 1),            # more than 200 heads in all
     (7, 32, 2048, 2),
     (5, 40, 6144, 1),            # 200 heads: up to 96 groups
     (5, 40, 6145, 2),
-    (7, 32, 8704, 1),            # 224: up to 136
-    (7, 32, 8705, 2),
-    (6, 40, 10368, 1),           # 240: up to 162
-    (6, 40, 10369, 2),
-    (13, 15, 5568, 1),           # 195: up to 87
-    (13, 15, 5569, 2),
     (12, 16, 2500, 2),           # 192 heads
     (19, 16, 2500, 1),           # more heads than compute units
 ])
